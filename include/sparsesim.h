@@ -164,8 +164,9 @@ typedef struct sim_config {
 } sim_config;
 
 /* Branching gates whose outputs are known to fit the capacity run as one
- * pass (evaluation, a chained scan over 2048-entry tiles, and the ordered
- * write in one kernel) on states of up to 2^24 entries; this flag makes them
+ * pass (evaluation, a chained scan over tiles, and the ordered write in one
+ * kernel) on states of up to 2^25 entries, and so do those that may not fit
+ * (found out at the call's next read of the entry count); this flag makes them
  * run as separate count, scan and write passes instead.  The results are
  * identical. */
 #define SIM_FLAG_U2_TWO_PASS 1u

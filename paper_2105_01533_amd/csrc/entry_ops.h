@@ -47,6 +47,28 @@ __device__ __forceinline__ bool pivot_set(const U2Desc& d, uint64_t lo, uint64_t
   return ((w >> (d.target & 63)) & 1ull) != 0;
 }
 
+// One phase/permutation gate on one entry (Sec. 3.2): the amplitude times m0
+// or m1 by the target bit, then the flip, on labels with the controls set.
+__device__ __forceinline__ void mono_step(const MonoDesc& d, bool wide, uint64_t& lo, uint64_t& hi, double2& a) {
+  const uint32_t t = d.target;
+  const bool thi = wide && t >= 64;
+  const uint64_t tbit = 1ull << (t & 63);
+  bool c = (lo & d.ctrl_lo) == d.ctrl_lo;
+  if (wide) c = c && ((hi & d.ctrl_hi) == d.ctrl_hi);
+  const uint64_t w = thi ? hi : lo;
+  if (d.flags & kHasPhase) {
+    const double2 m = sel2((w & tbit) != 0, d.m1, d.m0);
+    a = sel2(c, cmul(a, m), a);
+  }
+  if (d.flags & kFlip) {
+    const uint64_t f = c ? tbit : 0ull;
+    if (thi)
+      hi ^= f;
+    else
+      lo ^= f;
+  }
+}
+
 // Branching gate outputs of one entry (label lo/hi, amplitude a), given the
 // index j of its partner label ^ x in the same buffer (amp) or kNoPartner:
 // Eq. 2 with the pair rule (of two present partners the one with the pivot
@@ -57,8 +79,10 @@ struct U2Out {
   int mode;
   double2 o0, o1;
 };
-__device__ __forceinline__ U2Out u2_eval(const U2Desc& d, bool wide, const double2* __restrict__ amp, uint64_t lo,
-                                         uint64_t hi, double2 a, uint32_t j) {
+// has: the partner is present; aj: its amplitude (used when the entry's own
+// pivot bit is set).
+__device__ __forceinline__ U2Out u2_eval(const U2Desc& d, bool wide, uint64_t lo, uint64_t hi, double2 a, bool has,
+                                         double2 aj) {
   U2Out r;
   r.o0 = a;   // every path writes both outputs (keeps them in registers)
   r.o1 = a;
@@ -67,14 +91,12 @@ __device__ __forceinline__ U2Out u2_eval(const U2Desc& d, bool wide, const doubl
     return r;
   }
   const bool v = pivot_set(d, lo, hi, wide);
-  if (!v && j != kNoPartner) {
+  if (!v && has) {
     r.mode = 2;
     return r;
   }
   const double2 zero = make_double2(0.0, 0.0);
-  double2 aj = zero;
-  if (v && j != kNoPartner) aj = amp[j];
-  const double2 a0 = sel2(v, aj, a);
+  const double2 a0 = sel2(v, sel2(has, aj, zero), a);
   const double2 a1 = sel2(v, a, zero);
   // The off-diagonal sign comes from b0, the pair's label with the pivot clear.
   const uint64_t b0lo = v ? lo ^ d.x_lo : lo, b0hi = v ? hi ^ d.x_hi : hi;
@@ -88,6 +110,12 @@ __device__ __forceinline__ U2Out u2_eval(const U2Desc& d, bool wide, const doubl
   r.o0 = cadd(cmul(d.u[0], a0), p01);
   r.o1 = cadd(p10, cmul(d.u[3], a1));
   return r;
+}
+__device__ __forceinline__ U2Out u2_eval(const U2Desc& d, bool wide, const double2* __restrict__ amp, uint64_t lo,
+                                         uint64_t hi, double2 a, uint32_t j) {
+  double2 aj = make_double2(0.0, 0.0);
+  if (j != kNoPartner && pivot_set(d, lo, hi, wide) && ctrl_ok(d, lo, hi, wide)) aj = amp[j];
+  return u2_eval(d, wide, lo, hi, a, j != kNoPartner, aj);
 }
 
 // |a|^2 of an output that T_eps drops (0 for exact zeros), for the pruned

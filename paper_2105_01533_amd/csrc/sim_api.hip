@@ -11,9 +11,11 @@
 #include <algorithm>
 #include <chrono>
 #include <cmath>
+#include <cstddef>
 #include <cstdint>
 #include <cstdio>
 #include <cstring>
+#include <functional>
 #include <memory>
 #include <mutex>
 #include <new>
@@ -240,16 +242,20 @@ struct sim_t {
   double k_ms[KC_COUNT] = {};
   uint64_t mono_bytes_base = 0, mono_updates = 0;
   uint64_t pass_bytes_base[5] = {};
-  // Single-pass branching kernel: tile status words, the launch epoch and the
-  // tile counter's value at the start of the next launch.
+  // Single-pass branching kernel: tile status words, the launch epoch and
+  // which of the two tile counters the next launch takes.
   uint64_t* status = nullptr;
   uint32_t u2_epoch = 0;
-  uint32_t ticket_base = 0;
-  // Hash index slots [0, table_dirty) may hold entries; the rest are empty
-  // (the whole index is emptied at creation).  The single-pass branching
-  // kernel empties the slots its gate used, so a separate clearing launch is
-  // needed only after the two-pass form.
-  uint64_t table_dirty = 0;
+  uint32_t u2_par = 0;
+  // The index table the next gate uses (0 or 1); the other one is emptied by
+  // that gate (both are emptied at creation).  built: the gate before has
+  // indexed its outputs into it.
+  uint32_t half = 0;
+  bool built = false;
+  // Sequence number of the last gate that might not fit; that of one that did
+  // not, read back with the entry count.
+  uint32_t over_seq = 0;
+  uint64_t over = 0;
   // Sums of a qubit formed by the last measurement's write (see run_measure);
   // valid only until the next operation.
   struct {
@@ -266,7 +272,7 @@ struct sim_t {
   Layout L;
   Buf buf[2];
   int cur;
-  uint64_t* table;
+  uint32_t* table;             // two index tables of L.slots 32-bit slots each
   uint32_t* partner;
   BlockScratch bs;
   Ctl* ctl;
@@ -362,18 +368,15 @@ int chunk_grid(uint64_t n) {
   return (int)std::max<uint64_t>(1, std::min<uint64_t>(g, kMaxBlocks));
 }
 
-int flat_grid(uint64_t n) {
-  const uint64_t g = (n + 255) / 256;
-  return (int)std::max<uint64_t>(1, std::min<uint64_t>(g, 4096));
-}
-
 uint64_t* d_nnz(sim_t* s, int b) { return &s->ctl->nnz[b]; }
 
 int read_nnz(sim_t* s, uint64_t* out) {
-  HIP_TRY(hipMemcpyAsync(s->h_pinned, d_nnz(s, s->cur), 8, hipMemcpyDeviceToHost, s->stream));
+  // nnz[2], over and over_n are consecutive.
+  HIP_TRY(hipMemcpyAsync(s->h_pinned, s->ctl->nnz, 32, hipMemcpyDeviceToHost, s->stream));
   HIP_TRY(timed_sync(s));
   resolve_events(s);
-  *out = s->h_pinned[0];
+  *out = s->h_pinned[s->cur];
+  s->over = s->h_pinned[2];
   s->nnz_known = true;
   s->nnz_exact = s->nnz_ub = *out;
   return SIM_OK;
@@ -394,24 +397,73 @@ int bs_grid(const sim_t* s, uint64_t n) {
   return (int)std::max<uint64_t>(1, std::min<uint64_t>(tiles, 1u << 30));
 }
 
-// Branching op: index, count, scan, (capacity check), write, swap.
-// split: the gate's partner mask touches a qubit that is the same in every
-// entry, so no entry has a partner: no index is filled, built or probed, and
-// the evaluation runs with no partner array.
-int run_u2(sim_t* s, const sim_gate& g, bool* over, bool split) {
+// A short phase/permutation run (per-entry form) held back for the branching
+// gate after it, whose index build applies it on its way over the labels.
+struct HeldRun {
+  sim_t* s;
+  MonoRun m;
+  uint64_t ub = 0;   // bound on the entry count
+  // The run as a launch of its own (a gate that builds no index).
+  int run_now() {
+    if (!m.ng) return SIM_OK;
+    {
+      KTimer t_(s, KC_MONO);
+      launch_mono(s->stream, s->wide, s->buf[s->cur], d_nnz(s, s->cur), m.g, m.ng, m.run_flags, m.bytes_per_entry,
+                  s->ctl, mono_grid(s, ub), block_of(s));
+    }
+    m = MonoRun{};
+    HIP_TRY(hipGetLastError());
+    return SIM_OK;
+  }
+  MonoRun take() {
+    const MonoRun r = m;
+    m = MonoRun{};
+    return r;
+  }
+};
+constexpr uint64_t kSingleMax = (uint64_t)kMaxBlocks * kU2Tile;   // largest state of the single pass
+
+IndexTab index_tab(sim_t* s, uint32_t half) {
+  return IndexTab{s->table + half * s->L.slots, s->table + (half ^ 1u) * s->L.slots, &s->ctl->tab[half],
+                  &s->ctl->tab[half ^ 1u], s->ctl->labels[half], s->ctl->labels[half ^ 1u], 1.0 / lf_of(&s->cfg),
+                  s->L.slots};
+}
+
+// Forget an index built for a gate that did not come.
+int drop_built(sim_t* s) {
+  if (!s->built) return SIM_OK;
+  s->built = false;
+  launch_index_empty(s->stream, index_tab(s, s->half));
+  HIP_TRY(hipGetLastError());
+  return SIM_OK;
+}
+
+// How one branching gate is to run, besides the gate itself.
+struct U2Plan {
+  bool split;                   // the partner mask touches a qubit that is the same in every entry, so no
+                                // entry has a partner: no index is built or probed
+  HeldRun* before;              // the phase/permutation run held back for this gate
+  std::function<bool(uint64_t, MonoRun*, U2Desc*)> next;   // given the bound on the entry count after this gate:
+                                // whether the gate after it can be prepared, its run and descriptor
+  std::function<uint32_t()> may_exceed;   // called for a gate whose outputs may not fit: its sequence number
+};
+
+// Branching op: index, partner look-ups, single pass (or count, scan, write),
+// swap.  A single pass whose outputs may not fit is launched all the same and
+// found out at the next read of the entry count (Ctl::over); the two-pass form
+// waits for the total (*over).
+int run_u2(sim_t* s, const sim_gate& g, bool* over, const U2Plan& plan) {
   *over = false;
   const uint64_t cap = s->cfg.capacity;
+  const bool two_pass = s->cfg.flags & SIM_FLAG_U2_TWO_PASS;
   uint64_t ub = s->nnz_known ? s->nnz_exact : s->nnz_ub;
-  bool check = false;
-  if (2 * ub > cap) {
+  if (2 * ub > cap && !s->nnz_known && (two_pass || ub > kSingleMax)) {
     uint64_t n;
     int rc = read_nnz(s, &n);
-    if (rc) return rc;
+    if (rc || s->over) return rc;
     ub = n;
-    check = 2 * n > cap;
   }
-  const double lf = lf_of(&s->cfg);
-  const uint64_t slots = std::min<uint64_t>(table_slots(ub, lf), s->L.slots);
+  const bool check = 2 * ub > cap;
   const int other = s->cur ^ 1;
   const uint64_t* nnz_in = d_nnz(s, s->cur);
   const U2Desc d = u2_desc(g, s->cfg.eps);
@@ -419,6 +471,7 @@ int run_u2(sim_t* s, const sim_gate& g, bool* over, bool split) {
   if (!check && !(s->cfg.flags & (SIM_FLAG_U2_TWO_PASS | SIM_FLAG_U2_GLOBAL_INDEX)) && ub <= kLdsU2Max) {
     // Small state (2 ub <= capacity): the whole gate in one block, its
     // partner index in LDS; the global index is not touched.
+    if (int rc = plan.before->run_now()) return rc;
     {
       KTimer t_(s, KC_U2_LDS);
       launch_u2_lds(s->stream, s->wide, s->buf[s->cur], s->buf[other], nnz_in, d, s->ctl, d_nnz(s, other));
@@ -429,51 +482,59 @@ int run_u2(sim_t* s, const sim_gate& g, bool* over, bool split) {
     s->nnz_ub = std::min<uint64_t>(2 * ub, cap);
     return SIM_OK;
   }
-  const uint64_t prior = s->table_dirty;
+  const bool counting = s->cfg.flags & SIM_FLAG_COUNT_INDEX;
+  const bool single = !two_pass && ub <= kSingleMax;
+  const bool split = plan.split && !s->built;
   const uint32_t* partner = split ? nullptr : s->partner;
+  const TabCtl* tc = nullptr;
+  if (++s->u2_epoch >= (1u << 30)) {   // epochs are 30 bits: start over on cleared words
+    launch_fill(s->stream, s->status, 0ull, kMaxBlocks);
+    launch_fill(s->stream, reinterpret_cast<uint64_t*>(s->partner), ~0ull, (cap + 1) / 2);
+    s->u2_epoch = 1;
+  }
   if (!split) {
-    if (const uint64_t dirty = std::min<uint64_t>(prior, slots)) {
-      KTimer t_(s, KC_FILL);
-      launch_fill(s->stream, s->table, kEmptySlot, dirty);
-    }
-    s->table_dirty = std::max<uint64_t>(prior, slots);   // the build below writes into [0, slots)
-    {
+    const IndexTab tab = index_tab(s, s->half);
+    tc = tab.tc;
+    s->half ^= 1u;
+    if (!s->built) {
+      const MonoRun m = plan.before->take();
       KTimer t_(s, KC_BUILD);
-      launch_index_build(s->stream, s->wide, s->buf[s->cur], nnz_in, s->table, slots - 1, d, s->partner,
-                         (s->cfg.flags & SIM_FLAG_COUNT_INDEX) ? s->ctl : nullptr,
-                         flat_grid(ub), 256);
+      launch_index_build(s->stream, s->wide, s->buf[s->cur], nnz_in, tab, d, counting, m, s->ctl, ub);
     }
+    s->built = false;
     {
       KTimer t_(s, KC_U2_PROBE);
-      launch_u2_probe(s->stream, s->wide, s->buf[s->cur], nnz_in, s->table, slots - 1, d, s->partner,
-                      (s->cfg.flags & SIM_FLAG_COUNT_INDEX) ? s->ctl : nullptr, flat_grid(ub),
-                      256);
+      launch_u2_probe(s->stream, s->wide, s->buf[s->cur], nnz_in, tab, d, s->partner, s->u2_epoch, counting, s->ctl,
+                      ub);
     }
+  } else if (int rc = plan.before->run_now()) {
+    return rc;
   }
-  if (!check && !(s->cfg.flags & SIM_FLAG_U2_TWO_PASS) && ub <= (uint64_t)kMaxBlocks * kU2Tile) {
-    // Outputs fit (2 ub <= capacity): evaluate, scan and write in one pass.
-    const uint32_t tile = u2_tile_for(ub);
-    const int T = (int)std::max<uint64_t>(1, (ub + tile - 1) / tile);
-    if (++s->u2_epoch >= (1u << 30)) {   // epochs are 30 bits: start over on cleared words
-      launch_fill(s->stream, s->status, 0ull, kMaxBlocks);
-      s->u2_epoch = 1;
+  if (single) {
+    // Evaluate, scan and write in one pass.
+    const uint64_t ub_out = std::min<uint64_t>(2 * ub, cap);
+    NextGate next{};
+    if (!counting && ub_out <= kSingleMax && plan.next(ub_out, &next.run, &next.d)) {
+      next.tab = index_tab(s, s->half);
+      next.labels = split ? nullptr : s->ctl->labels[s->half ^ 1u];
     }
+    const uint32_t seq = check ? plan.may_exceed() : 0u;
     {
       KTimer t_(s, KC_U2_WRITE);
-      launch_u2_fused(s->stream, s->wide, s->buf[s->cur], s->buf[other], nnz_in, partner, d, s->ctl, s->status,
-                      s->ticket_base, s->u2_epoch, d_nnz(s, other), s->table, split ? 0 : slots, T, tile);
+      launch_u2_fused(s->stream, s->wide, s->buf[s->cur], s->buf[other], nnz_in, partner, d, s->ctl, tc, s->status,
+                      s->u2_par, s->u2_epoch, d_nnz(s, other), cap, seq, next, ub);
     }
     HIP_TRY(hipGetLastError());
-    s->ticket_base += (uint32_t)T;   // only a launched kernel advances the device counter
-    if (!split) s->table_dirty = prior > slots ? prior : 0;   // [0, slots) emptied by the kernel
+    s->u2_par ^= 1u;   // only a launched kernel uses its tile counter
+    s->built = next.tab.slots != nullptr;
     s->cur = other;
     s->nnz_known = false;
-    s->nnz_ub = std::min<uint64_t>(2 * ub, cap);
+    s->nnz_ub = ub_out;
     return SIM_OK;
   }
   {
     KTimer t_(s, KC_U2_COUNT);
-    launch_u2_count(s->stream, s->wide, s->buf[s->cur], nnz_in, d, partner, s->bs.tot, s->ctl, G, 256);
+    launch_u2_count(s->stream, s->wide, s->buf[s->cur], nnz_in, d, partner, s->u2_epoch, s->bs.tot, s->ctl, G, 256);
   }
   {
     KTimer t_(s, KC_SCAN);
@@ -490,7 +551,8 @@ int run_u2(sim_t* s, const sim_gate& g, bool* over, bool split) {
   }
   {
     KTimer t_(s, KC_U2_WRITE);
-    launch_u2_write(s->stream, s->wide, s->buf[s->cur], s->buf[other], nnz_in, partner, s->bs.tot, d, s->ctl, G, 256);
+    launch_u2_write(s->stream, s->wide, s->buf[s->cur], s->buf[other], nnz_in, partner, s->u2_epoch, s->bs.tot, d,
+                    s->ctl, G, 256);
   }
   HIP_TRY(hipGetLastError());
   s->cur = other;
@@ -552,7 +614,7 @@ int run_measure(sim_t* s, uint32_t q, double u, int32_t forced, MeasRec* rec, in
 }
 
 int read_ctl(sim_t* s) {
-  HIP_TRY(hipMemcpyAsync(s->h_ctl, s->ctl, sizeof(Ctl), hipMemcpyDeviceToHost, s->stream));
+  HIP_TRY(hipMemcpyAsync(s->h_ctl, s->ctl, offsetof(Ctl, labels), hipMemcpyDeviceToHost, s->stream));
   HIP_TRY(timed_sync(s));
   resolve_events(s);
   return SIM_OK;
@@ -604,7 +666,7 @@ int sim_create(const sim_config* cfg, void* stream, void* workspace, size_t ws_b
     s->buf[b].key_hi = s->wide ? reinterpret_cast<uint64_t*>(s->ws + s->L.buf_hi[b]) : nullptr;
     s->buf[b].amp = reinterpret_cast<double2*>(s->ws + s->L.buf_amp[b]);
   }
-  s->table = reinterpret_cast<uint64_t*>(s->ws + s->L.table);
+  s->table = reinterpret_cast<uint32_t*>(s->ws + s->L.table);
   s->partner = reinterpret_cast<uint32_t*>(s->ws + s->L.partner);
   s->bs.tot = reinterpret_cast<uint32_t*>(s->ws + s->L.tot);
   s->bs.tot2 = reinterpret_cast<uint32_t*>(s->ws + s->L.tot2);
@@ -617,13 +679,16 @@ int sim_create(const sim_config* cfg, void* stream, void* workspace, size_t ws_b
     return fail(SIM_E_NOMEM, "pinned host allocation failed");
   }
   std::memset(s->h_ctl, 0, sizeof(Ctl));
+  for (auto& t : s->h_ctl->labels)
+    for (LabelCell& c : t) c.and_lo = c.and_hi = ~0ull;
   if (hipMemcpyAsync(s->ctl, s->h_ctl, sizeof(Ctl), hipMemcpyHostToDevice, s->stream) != hipSuccess) {
     sim_destroy(s);
     return fail(SIM_E_HIP, "initialising the control block failed");
   }
   s->cur = 0;
   launch_fill(s->stream, s->status, 0ull, kMaxBlocks);   // epoch 0: no launch has published yet
-  launch_fill(s->stream, s->table, kEmptySlot, s->L.slots);
+  launch_fill(s->stream, reinterpret_cast<uint64_t*>(s->table), ~0ull, s->L.slots);   // both tables
+  launch_fill(s->stream, reinterpret_cast<uint64_t*>(s->partner), ~0ull, (s->cfg.capacity + 1) / 2);
   launch_set_basis(s->stream, s->buf[0], d_nnz(s, 0), 0, 0);
   if (hipStreamSynchronize(s->stream) != hipSuccess || hipGetLastError() != hipSuccess) {
     sim_destroy(s);
@@ -834,6 +899,7 @@ struct CallBufs {
 
 int apply_impl(sim_t* s, const sim_gate* gates, size_t n, int32_t* outcomes, sim_stats* stats, CallBufs cb) {
   s->mchain.valid = false;
+  if (int rc = drop_built(s)) return rc;   // (left by a call that failed)
   sim_stats st;
   std::memset(&st, 0, sizeof st);
   size_t n_mono = 0, n_meas = 0;
@@ -954,18 +1020,52 @@ int apply_impl(sim_t* s, const sim_gate* gates, size_t n, int32_t* outcomes, sim
 
   int result = SIM_OK;
   size_t run_begin = 0, run_len = 0, mono_seen = 0, meas_seen = 0;
-  auto flush = [&]() -> int {
-    if (!run_len) return SIM_OK;
-    const uint64_t ub = s->nnz_known ? s->nnz_exact : s->nnz_ub;
-    uint32_t run_flags = 0;
-    for (size_t k = run_begin; k < run_begin + run_len; ++k) {
-      if (s->rc.descs[k].flags & kHasPhase) run_flags |= kRunPhase;
-      if (s->rc.descs[k].flags & kFlip) run_flags |= kRunFlip;
+  HeldRun held{s, {}};
+  bool run_done = false;   // the pending run was applied by the branching gate before it
+  // The descriptors of ops [begin, begin + len) on the device.
+  auto need_descs = [&](size_t begin, size_t len) -> int {
+    if (begin >= desc_lo && begin + len <= desc_hi) return SIM_OK;
+    // These and those after them, up to 1024 descriptors, in one copy
+    // (the allocation-free form copies from the compiled descriptors,
+    // which stay in place until the call returns).
+    desc_lo = begin;
+    desc_hi = std::min(s->rc.descs.size(), begin + std::max<size_t>(len, 1024));
+    const MonoDesc* src = s->rc.descs.data();
+    if (!cb.fixed) {
+      HIP_TRY(h_desc.reserve(s->rc.descs.size()));
+      std::memcpy(h_desc.p + desc_lo, s->rc.descs.data() + desc_lo, (desc_hi - desc_lo) * sizeof(MonoDesc));
+      src = h_desc.p;
     }
-    // Algorithmic bytes per entry: label read (+ write if a gate flips),
-    // amplitude read and write if a gate has a phase.
+    HIP_TRY(hipMemcpyAsync(cb.descs + desc_lo, src + desc_lo, (desc_hi - desc_lo) * sizeof(MonoDesc),
+                           hipMemcpyHostToDevice, s->stream));
+    return SIM_OK;
+  };
+  // Run flags of ops [begin, begin + len) and the algorithmic bytes per entry
+  // of a pass over them: label read (+ write if a gate flips), amplitude read
+  // and write if a gate has a phase.
+  auto run_cost = [&](size_t begin, size_t len, uint32_t* flags) -> uint32_t {
+    *flags = 0;
+    for (size_t k = begin; k < begin + len; ++k) {
+      if (s->rc.descs[k].flags & kHasPhase) *flags |= kRunPhase;
+      if (s->rc.descs[k].flags & kFlip) *flags |= kRunFlip;
+    }
     const uint32_t kb = s->wide ? 16u : 8u;
-    const uint32_t run_bpe = kb + ((run_flags & kRunFlip) ? kb : 0u) + ((run_flags & kRunPhase) ? 32u : 0u);
+    return kb + ((*flags & kRunFlip) ? kb : 0u) + ((*flags & kRunPhase) ? 32u : 0u);
+  };
+  // hold: the op after the run is a branching gate that is applied; a short
+  // per-entry run is then left in `held` for it.
+  auto flush = [&](bool hold = false) -> int {
+    if (!run_len) return SIM_OK;
+    if (run_done) {
+      run_done = false;
+      st.mono_passes++;
+      run_begin += run_len;
+      run_len = 0;
+      return SIM_OK;
+    }
+    const uint64_t ub = s->nnz_known ? s->nnz_exact : s->nnz_ub;
+    uint32_t run_flags;
+    const uint32_t run_bpe = run_cost(run_begin, run_len, &run_flags);
     BsRun br;
     if (bs_allowed) {
       int rc = ensure_compiled();
@@ -1048,24 +1148,17 @@ int apply_impl(sim_t* s, const sim_gate* gates, size_t n, int32_t* outcomes, sim
                      bs_grid(s, ub));
       st.bitslice_passes++;
     } else {
-      if (run_begin < desc_lo || run_begin + run_len > desc_hi) {
-        // This run and those after it, up to 1024 descriptors, in one copy
-        // (the allocation-free form copies from the compiled descriptors,
-        // which stay in place until the call returns).
-        desc_lo = run_begin;
-        desc_hi = std::min(s->rc.descs.size(), run_begin + std::max<size_t>(run_len, 1024));
-        const MonoDesc* src = s->rc.descs.data();
-        if (!cb.fixed) {
-          HIP_TRY(h_desc.reserve(s->rc.descs.size()));
-          std::memcpy(h_desc.p + desc_lo, s->rc.descs.data() + desc_lo, (desc_hi - desc_lo) * sizeof(MonoDesc));
-          src = h_desc.p;
-        }
-        HIP_TRY(hipMemcpyAsync(cb.descs + desc_lo, src + desc_lo, (desc_hi - desc_lo) * sizeof(MonoDesc),
-                               hipMemcpyHostToDevice, s->stream));
+      int rc = need_descs(run_begin, run_len);
+      if (rc) return rc;
+      held.m.g = cb.descs + run_begin;
+      held.m.ng = (uint32_t)run_len;
+      held.m.run_flags = run_flags;
+      held.m.bytes_per_entry = run_bpe;
+      held.ub = ub;
+      if (!hold || run_len > kHeldMax) {
+        rc = held.run_now();
+        if (rc) return rc;
       }
-      KTimer t_(s, KC_MONO);
-      launch_mono(s->stream, s->wide, s->buf[s->cur], d_nnz(s, s->cur), cb.descs + run_begin, (uint32_t)run_len,
-                  run_flags, run_bpe, s->ctl, mono_grid(s, ub), block_of(s));
     }
     HIP_TRY(hipGetLastError());
     st.mono_passes++;
@@ -1103,16 +1196,105 @@ int apply_impl(sim_t* s, const sim_gate* gates, size_t n, int32_t* outcomes, sim
     });
     return SIM_OK;
   };
+  // A flip keeps its target the same in every entry only if every control is.
+  auto flip_uniform = [](const sim_gate& h, uint64_t& u_lo, uint64_t& u_hi) {
+    if (!h.flip) return;
+    uint64_t& tw = h.target < 64 ? u_lo : u_hi;
+    const uint64_t tb = 1ull << (h.target & 63);
+    if ((tw & tb) && ((h.ctrl.lo & ~u_lo) | (h.ctrl.hi & ~u_hi))) tw &= ~tb;
+  };
+  // Partner mask x (a standard gate's is its target bit).
+  auto partner_mask = [](const sim_gate& h, uint64_t* x_lo, uint64_t* x_hi) {
+    *x_lo = h.x.lo;
+    *x_hi = h.x.hi;
+    if (!*x_lo && !*x_hi) (h.target < 64 ? *x_lo : *x_hi) = 1ull << (h.target & 63);
+  };
+  auto is_split = [&](uint64_t x_lo, uint64_t x_hi, uint64_t u_lo, uint64_t u_hi) {
+    return !(s->cfg.flags & SIM_FLAG_NO_UNIFORM) && ((x_lo & u_lo) | (x_hi & u_hi));
+  };
   size_t i = 0;
+  // What the gate at i can do for the next branching gate while it writes:
+  // the run up to it, if it is short and would run per entry, and its index.
+  // Only for a gate that is certain to be applied and to use the global index.
+  int look_rc = SIM_OK;
+  auto prepare_next = [&](uint64_t ub_out, MonoRun* m, U2Desc* d) -> bool {
+    if (s->cfg.flags & (SIM_FLAG_U2_TWO_PASS | SIM_FLAG_COUNT_INDEX)) return false;
+    if (!(s->cfg.flags & SIM_FLAG_U2_GLOBAL_INDEX) && ub_out <= kLdsU2Max) return false;
+    const size_t most = s->cfg.mono_mode == SIM_MONO_BITSLICE ? 0
+                        : s->cfg.mono_mode == SIM_MONO_DIRECT
+                            ? (size_t)kHeldMax
+                            : std::min<size_t>(kHeldMax, (size_t)(s->cfg.bs_min_gates ? s->cfg.bs_min_gates : 16u) - 1);
+    size_t j = i + 1;
+    while (j < n && gates[j].op == SIM_OP_MONO && j - (i + 1) <= most) ++j;
+    const size_t len = j - (i + 1);
+    if (j == n || len > most || len >= s->cfg.fuse_max || gates[j].op != SIM_OP_U2) return false;
+    if (gates[j].cap && 2 * ub_out > gates[j].cap) return false;
+    uint64_t x_lo, x_hi, u_lo = s->uni_lo, u_hi = s->uni_hi;
+    partner_mask(gates[i], &x_lo, &x_hi);
+    u_lo &= ~x_lo;
+    u_hi &= ~x_hi;
+    for (size_t k = i + 1; k < j; ++k) flip_uniform(gates[k], u_lo, u_hi);
+    partner_mask(gates[j], &x_lo, &x_hi);
+    if (is_split(x_lo, x_hi, u_lo, u_hi)) return false;
+    if (len) {
+      look_rc = need_descs(mono_seen, len);
+      if (look_rc) return false;
+      m->g = cb.descs + mono_seen;
+      m->ng = (uint32_t)len;
+      m->bytes_per_entry = run_cost(mono_seen, len, &m->run_flags);
+      run_done = true;
+    }
+    *d = u2_desc(gates[j], s->cfg.eps);
+    return true;
+  };
+  // Gates since the last read of the entry count whose outputs may not fit,
+  // and what the call was like before each.
+  struct Snap {
+    uint32_t seq;
+    size_t i, meas_seen;
+    int cur;
+    uint64_t uni_lo, uni_hi;
+    sim_stats st;
+  };
+  std::vector<Snap> snaps;
+  auto may_exceed = [&]() -> uint32_t {
+    if (!++s->over_seq) s->over_seq = 1;
+    snaps.push_back(Snap{s->over_seq, i, meas_seen, s->cur, s->uni_lo, s->uni_hi, st});
+    return s->over_seq;
+  };
+  // After a read of the entry count: back to before the gate that did not fit.
+  auto settle = [&]() -> int {
+    if (!s->over) {
+      snaps.clear();
+      return SIM_OK;
+    }
+    for (const Snap& p : snaps)
+      if (p.seq == s->over) {
+        i = p.i;
+        meas_seen = p.meas_seen;
+        s->cur = p.cur;
+        s->uni_lo = p.uni_lo;
+        s->uni_hi = p.uni_hi;
+        st = p.st;
+      }
+    snaps.clear();
+    s->over = 0;
+    s->built = true;   // whatever the launches since then left in the tables
+    int rc = drop_built(s);
+    if (rc) return rc;
+    launch_u2_restore(s->stream, s->ctl, s->cur);
+    HIP_TRY(hipGetLastError());
+    s->nnz_known = false;
+    s->nnz_ub = s->cfg.capacity;
+    run_len = 0;
+    run_done = false;
+    held.m = MonoRun{};
+    return fail(SIM_E_CAPACITY, "branching gate would exceed the state capacity");
+  };
   for (; i < n; ++i) {
     const sim_gate& g = gates[i];
     if (g.op == SIM_OP_MONO) {
-      // A flip keeps its target uniform only if every control is uniform.
-      if (g.flip) {
-        uint64_t& tw = g.target < 64 ? s->uni_lo : s->uni_hi;
-        const uint64_t tb = 1ull << (g.target & 63);
-        if ((tw & tb) && ((g.ctrl.lo & ~s->uni_lo) | (g.ctrl.hi & ~s->uni_hi))) tw &= ~tb;
-      }
+      flip_uniform(g, s->uni_lo, s->uni_hi);
       if (run_len == 0) run_begin = mono_seen;
       ++run_len;
       ++mono_seen;
@@ -1132,6 +1314,7 @@ int apply_impl(sim_t* s, const sim_gate* gates, size_t n, int32_t* outcomes, sim
           if (rc) return rc;
           rc = read_nnz(s, &nnz);
           if (rc) return rc;
+          if ((result = settle())) break;
           st.host_syncs++;
         }
         if (2 * nnz > g.cap) {
@@ -1139,16 +1322,16 @@ int apply_impl(sim_t* s, const sim_gate* gates, size_t n, int32_t* outcomes, sim
           continue;
         }
       }
-      int rc = flush();
+      int rc = flush(true);
       if (rc) return rc;
       bool over = false;
       const bool was_known = s->nnz_known;
-      // Partner mask x (a standard gate's is its target bit).
-      uint64_t x_lo = g.x.lo, x_hi = g.x.hi;
-      if (!x_lo && !x_hi) (g.target < 64 ? x_lo : x_hi) = 1ull << (g.target & 63);
-      const bool split = !(s->cfg.flags & SIM_FLAG_NO_UNIFORM) && ((x_lo & s->uni_lo) | (x_hi & s->uni_hi));
-      rc = run_u2(s, g, &over, split);
-      if (rc) return rc;
+      uint64_t x_lo, x_hi;
+      partner_mask(g, &x_lo, &x_hi);
+      const bool split = is_split(x_lo, x_hi, s->uni_lo, s->uni_hi);
+      rc = run_u2(s, g, &over, U2Plan{split, &held, prepare_next, may_exceed});
+      if (rc || look_rc) return rc ? rc : look_rc;
+      if (s->over && (result = settle())) break;
       if (!was_known && s->nnz_known) st.host_syncs++;
       if (over) {
         result = fail(SIM_E_CAPACITY, "branching gate would exceed the state capacity");
@@ -1169,6 +1352,11 @@ int apply_impl(sim_t* s, const sim_gate* gates, size_t n, int32_t* outcomes, sim
     rc = run_measure(s, g.target, g.u, g.forced, cb.recs + meas_seen, cb.outcomes + meas_seen, &bad, q_next);
     if (rc) return rc;
     if (bad) {
+      // (an empty state here may be that of a gate that did not fit)
+      uint64_t nnz;
+      rc = read_nnz(s, &nnz);
+      if (rc) return rc;
+      if ((result = settle())) break;
       result = fail(SIM_E_STATE, "measurement outcome has zero probability");
       break;
     }
@@ -1184,6 +1372,19 @@ int apply_impl(sim_t* s, const sim_gate* gates, size_t n, int32_t* outcomes, sim
     HIP_TRY(hipMemcpyAsync(outcomes, cb.outcomes, meas_seen * 4, hipMemcpyDeviceToHost, s->stream));
   int rc = read_ctl(s);
   if (rc) return rc;
+  s->over = s->h_ctl->over;
+  if (s->over) {
+    result = settle();
+    rc = read_ctl(s);
+    if (rc) return rc;
+  }
+  // Counters of the last single-pass gate, still staged.
+  for (const auto& p : s->h_ctl->fst)
+    for (const StageCell& f : p) {
+      s->h_ctl->updates += f.updates;
+      s->h_ctl->pruned += f.pruned;
+      s->h_ctl->pruned_mass += f.mass;
+    }
   if (const uint32_t err = s->h_ctl->error) {
     // Cleared whatever the result (a forced zero-probability outcome sets it
     // too), so that it never carries over to a later call.

@@ -17,8 +17,13 @@ int set_error(int code, const std::string& msg);
 // Ops that sim_gates_from_pauli writes for these terms.
 size_t pauli_op_count(const sim_pauli* terms, size_t n);
 
-constexpr uint64_t kEmptySlot = ~0ull;   // hash index: free slot
+constexpr uint64_t kEmptySlot = ~0ull;   // the server's hash index: free slot
+constexpr uint32_t kFreeSlot = ~0u;      // the single-state hash index: free slot (32 bits)
 constexpr uint32_t kNoPartner = ~0u;     // partner look-up miss
+// In the partner array: of an entry with the pivot bit set, its partner's index
+// or kNoPartner; of one with it clear, kHasPartner | epoch of the gate for which
+// it has a partner (anything else: it has none), so the array is never cleared.
+constexpr uint32_t kHasPartner = 1u << 31;
 constexpr int kMaxBlocks = 8192;         // blocks of the chunked (ordered) kernels
 // Entries per block of the chunked kernels: the two-pass branching count and
 // write, and the measurement reduce and write.  The host sizes their grids
@@ -159,9 +164,33 @@ struct U2Desc {
   double2 u[4];                // row-major
 };
 
+// An index table: what its last build used of it.
+struct TabCtl {
+  uint32_t mask, bits;         // slots - 1 (0: nothing used); index bits of a slot
+  uint32_t nopair;             // the gate is known to have no partners: nothing was indexed
+  uint32_t pad;
+};
+
+// Accumulators that every block of a kernel adds to.  Atomics on one address
+// complete one every 10 ns or so across the chip, so 1,000 blocks on one word
+// cost 10 us; the blocks spread over cells in cache lines of their own.
+constexpr uint32_t kLabelCells = 32, kStageCells = 8;
+struct __attribute__((aligned(128))) LabelCell {   // AND and OR of the labels a gate's partner pass saw
+  uint64_t and_lo, and_hi, or_lo, or_hi;
+};
+struct __attribute__((aligned(64))) StageCell {    // counters of a single-pass branching gate
+  uint64_t updates, pruned;
+  double mass;
+};
+
 // Device control block.
 struct Ctl {
   uint64_t nnz[2];             // entries in buffer 0 / 1
+  // A single-pass branching gate whose outputs did not fit: its sequence
+  // number (0: none) and entry count.  Its output count is then 0, so that
+  // later launches do nothing until the host, which reads these words with nnz,
+  // goes back to the state before it.
+  uint64_t over, over_n;
   uint64_t updates;            // sum over applied gates of nnz at input
   uint64_t peak;
   uint64_t pruned;
@@ -175,13 +204,52 @@ struct Ctl {
   uint64_t ix[4];
   uint32_t error;              // bit 0: a measurement had no valid outcome; bit 1: a chained scan gave up
                                // waiting; bit 2: the one-block branching kernel met a state too large for it
-  uint32_t ticket;             // tile counter of the single-pass branching kernel (wraps)
+  uint32_t ticket[2];          // tile counters of the single-pass branching kernel (launches alternate)
+  TabCtl tab[2];               // the two index tables
   double pruned_mass;          // sum of |a|^2 of the entries T_eps dropped
   // Counters of a two-pass branching gate, staged by its count pass and
   // committed by the scan only if the output fits the capacity (a gate
   // rejected for capacity changes no counter).
   uint64_t st_updates, st_pruned;
   double st_mass;
+  // The same of the single pass: launch parity p stages in fst[p], the next
+  // launch (or the host, at the end of a call) commits it.
+  StageCell fst[2][kStageCells];
+  // Of the gate on index table 0 / 1 (not read by the host).
+  LabelCell labels[2][kLabelCells];
+};
+
+// The two index tables as one gate sees them: it builds and probes `slots`
+// and empties what the gate before left in `other`.
+struct IndexTab {
+  uint32_t* slots;
+  uint32_t* other;
+  TabCtl* tc;                  // of `slots` / of `other`
+  TabCtl* tc_other;
+  LabelCell* labels;           // kLabelCells cells, of `slots` / of `other`
+  LabelCell* labels_other;
+  double inv_load;             // slots per entry asked for (rounded up to a power of two)
+  uint64_t max_slots;          // slots of one table
+};
+
+// Longest run handed to a branching gate's kernels: they keep one entry (or
+// pair) per thread where the fused pass keeps four, so a longer run is better
+// off in a pass of its own.
+constexpr uint32_t kHeldMax = 32;
+// A short phase/permutation run handed to the index build (ng = 0: none).
+struct MonoRun {
+  const MonoDesc* g = nullptr;
+  uint32_t ng = 0, run_flags = 0, bytes_per_entry = 0;
+};
+
+// What a single-pass branching gate does for the branching gate after it: the
+// short run between them on each output, and the outputs' index (tab.slots
+// null: nothing).  labels: what the gate's own partner pass saw, if it ran.
+struct NextGate {
+  IndexTab tab;
+  U2Desc d;
+  MonoRun run;
+  const LabelCell* labels;
 };
 
 // Per-measurement record written by the decide kernel.
@@ -294,30 +362,34 @@ hipError_t copy_state_to_host_soa(const uint64_t* lo, const uint64_t* hi, const 
                                   uint64_t* key_lo, uint64_t* key_hi, sim_c64* amps);
 void launch_fill(hipStream_t st, uint64_t* p, uint64_t v, uint64_t n);
 void launch_copy16(hipStream_t st, void* dst, const void* src, uint64_t n16);
-// ctl: where the index counters go (Ctl::ix), or null to count nothing.
-void launch_index_build(hipStream_t st, bool wide, Buf b, const uint64_t* nnz, uint64_t* table, uint64_t mask,
-                        const U2Desc& d, uint32_t* partner, Ctl* ctl, int grid, int block);
-void launch_u2_probe(hipStream_t st, bool wide, Buf b, const uint64_t* nnz, const uint64_t* table, uint64_t mask,
-                     const U2Desc& d, uint32_t* partner, Ctl* ctl, int grid, int block);
+// m: the run applied on the way.  counting: count the work in Ctl::ix.
+void launch_index_build(hipStream_t st, bool wide, Buf b, const uint64_t* nnz, const IndexTab& t, const U2Desc& d,
+                        bool counting, const MonoRun& m, Ctl* ctl, uint64_t ub);
+// epoch: tells this gate's partner marks from earlier ones.
+void launch_u2_probe(hipStream_t st, bool wide, Buf b, const uint64_t* nnz, const IndexTab& t, const U2Desc& d,
+                     uint32_t* partner, uint32_t epoch, bool counting, Ctl* ctl, uint64_t ub);
+// Empty both tables (whatever their last builds used).
+void launch_index_empty(hipStream_t st, const IndexTab& t);
 void launch_u2_count(hipStream_t st, bool wide, Buf b, const uint64_t* nnz, const U2Desc& d, const uint32_t* partner,
-                     uint32_t* tot, Ctl* ctl, int grid, int block);
+                     uint32_t epoch, uint32_t* tot, Ctl* ctl, int grid, int block);
 // cap: the count pass's staged counters are committed only if the total fits.
 void launch_scan(hipStream_t st, uint32_t* tot, int nblocks, uint64_t* nnz_out, Ctl* ctl, uint32_t entry_bytes,
                  uint64_t cap);
 void launch_u2_write(hipStream_t st, bool wide, Buf in, Buf out, const uint64_t* nnz, const uint32_t* partner,
-                     const uint32_t* off, const U2Desc& d, Ctl* ctl, int grid, int block);
-// Entries per block of the single-pass branching kernel (512, 1024 or
-// 2048); it serves states of at most kMaxBlocks tiles of the largest.
-constexpr uint32_t kU2Tile = 2048;
-// The tile for a state of at most ub entries: 512 up to 2^20 entries, 1024 up
-// to kMaxBlocks such tiles, 2048 beyond.
-inline uint32_t u2_tile_for(uint64_t ub) {
-  return ub <= (1ull << 20) ? 512u : ub <= (uint64_t)kMaxBlocks * 1024u ? 1024u : kU2Tile;
-}
-// grid = tiles covering the entry count's bound.
+                     uint32_t epoch, const uint32_t* off, const U2Desc& d, Ctl* ctl, int grid, int block);
+// The single-pass branching kernel serves states of at most kMaxBlocks tiles
+// of kU2Tile entries.
+constexpr uint32_t kU2Tile = 4096;
+// partner: the partner array, or null for a gate known to have none (probed:
+// the partner pass ran, so its finding that there are none is heeded).
+// seq: sequence number of a gate whose outputs may exceed cap, else 0.
+// ub: bound on the entry count.
 void launch_u2_fused(hipStream_t st, bool wide, Buf in, Buf out, const uint64_t* nnz, const uint32_t* partner,
-                     const U2Desc& d, Ctl* ctl, uint64_t* status, uint32_t ticket_base, uint32_t epoch,
-                     uint64_t* nnz_out, uint64_t* table, uint64_t clear_slots, int grid, uint32_t tile);
+                     const U2Desc& d, Ctl* ctl, const TabCtl* tc, uint64_t* status, uint32_t par, uint32_t epoch,
+                     uint64_t* nnz_out, uint64_t cap, uint32_t seq, const NextGate& next, uint64_t ub);
+// Back to the state before a gate that did not fit: its buffer's entry count,
+// and no staged counters, error or mark left.
+void launch_u2_restore(hipStream_t st, Ctl* ctl, int cur);
 // Largest state the one-block branching kernel takes (its partner index and
 // partner slots live in LDS).
 constexpr uint32_t kLdsU2Max = 8192;

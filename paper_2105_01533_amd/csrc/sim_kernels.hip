@@ -14,6 +14,8 @@
 // complex products are (a.re*b.re - a.im*b.im, a.re*b.im + a.im*b.re), sums of
 // two products are evaluated left to right, |a|^2 = re*re + im*im, and the
 // library is compiled with -ffp-contract=off.
+#include <algorithm>
+
 #include "entry_ops.h"
 #include "u2_lds.h"
 
@@ -135,27 +137,8 @@ __global__ __launch_bounds__(256) void k_mono(Buf b, const uint64_t* __restrict_
     }
     for (uint32_t j = 0; j < ng; ++j) {
       const MonoDesc d = g[j];
-      const uint32_t t = d.target;
-      const bool thi = WIDE && t >= 64;
-      const uint64_t tbit = 1ull << (t & 63);
 #pragma unroll
-      for (int i = 0; i < ITEMS; ++i) {
-        bool c = (lo[i] & d.ctrl_lo) == d.ctrl_lo;
-        if (WIDE) c = c && ((hi[i] & d.ctrl_hi) == d.ctrl_hi);
-        const uint64_t w = thi ? hi[i] : lo[i];
-        if (d.flags & kHasPhase) {
-          const double2 m = sel2((w & tbit) != 0, d.m1, d.m0);
-          const double2 r = cmul(a[i], m);
-          a[i] = sel2(c, r, a[i]);
-        }
-        if (d.flags & kFlip) {
-          const uint64_t f = c ? tbit : 0ull;
-          if (thi)
-            hi[i] ^= f;
-          else
-            lo[i] ^= f;
-        }
-      }
+      for (int i = 0; i < ITEMS; ++i) ent::mono_step(d, WIDE, lo[i], hi[i], a[i]);
     }
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) {
@@ -173,16 +156,92 @@ __global__ __launch_bounds__(256) void k_mono(Buf b, const uint64_t* __restrict_
 
 // ---------------------------------------------------------------------------
 // Hash index: open addressing with linear probing over a power-of-two table
-// of 64-bit slots (fingerprint << 32 | entry index), claimed with 64-bit CAS.
-// Labels are unique, so an insert never meets its own label.
+// of 32-bit slots, claimed with CAS: the entry's index in the low bits the
+// state needs, a fingerprint of its label in the rest.  Labels are unique, so
+// an insert never meets its own label.  The table is sized in the kernels, from
+// the entry count on the device: the host knows only a bound, several times
+// the count between two reads, and a table sized for the bound spreads the
+// probes over that much more memory and costs that much more to empty
+// (40-qubit Trotter step, 2,500 gates: 85 -> 76 ms).
 //
-// Only the entries a partner look-up can ask for are indexed: those under
-// the op's controls with the pivot bit clear (the look-ups come from their
-// partners, whose pivot bit is set).  Every entry's partner slot starts empty.
+// The workspace holds two tables.  A gate builds and probes one and empties
+// what the gate before left in the other, so no launch is spent on it, and the
+// gate's own write can index its outputs for the next one.
+struct Geom {
+  uint32_t mask, bits;   // slots - 1; index bits of a slot
+};
+__device__ __forceinline__ Geom index_geom(const IndexTab& t, uint64_t n) {
+  const uint64_t want = (uint64_t)((double)n * t.inv_load) + 2;
+  uint64_t slots = want <= 64 ? 64ull : 1ull << (64 - __clzll(want - 1));
+  if (slots > t.max_slots) slots = t.max_slots;
+  // n < 2^bits, so a slot in use is never all ones (the empty slot).
+  return {(uint32_t)(slots - 1), n ? 64u - __clzll(n) : 1u};
+}
+
+// Index entry i (label lo/hi).
+struct Claim {
+  uint32_t slot, val;
+  bool wanted;
+};
+__device__ __forceinline__ Claim index_claim(const Geom& gm, uint64_t lo, uint64_t hi, uint32_t i, bool wanted) {
+  const uint64_t h = hash_label(lo, hi);
+  return {(uint32_t)h & gm.mask, (uint32_t)((h >> 32) >> gm.bits) << gm.bits | i, wanted};
+}
+// The claim's remaining tries after one that found slot content old.
+__device__ __forceinline__ uint32_t index_settle(uint32_t* slots, const Geom& gm, Claim c, uint32_t old) {
+  uint32_t tries = 1;
+  while (old != kFreeSlot && tries <= gm.mask) {
+    c.slot = (c.slot + 1) & gm.mask;
+    old = atomicCAS(&slots[c.slot], kFreeSlot, c.val);
+    ++tries;
+  }
+  return tries;
+}
+__device__ __forceinline__ uint32_t index_insert(uint32_t* slots, const Geom& gm, uint64_t lo, uint64_t hi,
+                                                 uint32_t i) {
+  const Claim c = index_claim(gm, lo, hi, i, true);
+  return index_settle(slots, gm, c, atomicCAS(&slots[c.slot], kFreeSlot, c.val));
+}
+
+// Empty what the last build left in a table: by all threads of the grid, 16
+// bytes a store (the slots in use are a power of two, at least 64).
+__device__ __forceinline__ void index_empty(uint32_t* slots, const TabCtl* tc) {
+  const uint32_t mask = tc->mask;
+  if (!mask || tc->nopair) return;
+  const uint64_t n4 = ((uint64_t)mask + 1) / 4;
+  uint4* __restrict__ p = reinterpret_cast<uint4*>(slots);
+  const uint4 e = make_uint4(kFreeSlot, kFreeSlot, kFreeSlot, kFreeSlot);
+  for (uint64_t k = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; k < n4; k += (uint64_t)gridDim.x * blockDim.x)
+    p[k] = e;
+}
+
+__global__ __launch_bounds__(256) void k_index_empty(IndexTab t) {
+  index_empty(t.slots, t.tc);
+  index_empty(t.other, t.tc_other);
+}
+
+// The label of the entry before or after this thread's (the wave holds 64
+// consecutive entries; i < n).
+template <bool WIDE>
+__device__ __forceinline__ bool next_to(const Buf& b, uint64_t n, uint64_t i, uint64_t lo, uint64_t hi, uint64_t qlo,
+                                        uint64_t qhi, bool after, bool inside) {
+  const int lane = threadIdx.x & 63;
+  uint64_t l = after ? __shfl_down(lo, 1) : __shfl_up(lo, 1);
+  uint64_t h = WIDE ? (after ? __shfl_down(hi, 1) : __shfl_up(hi, 1)) : 0ull;
+  const bool edge = lane == (after ? 63 : 0);
+  const bool there = after ? i + 1 < n : i > 0 && i < n;
+  if (edge && inside) return false;
+  if (edge && there) {
+    l = b.key_lo[after ? i + 1 : i - 1];
+    if (WIDE) h = b.key_hi[after ? i + 1 : i - 1];
+  }
+  return there && l == qlo && (!WIDE || h == qhi);
+}
+
 // Block sums of two per-thread counters added to dst[0], dst[1] by thread 0
 // (one atomic pair per block); nothing when dst is null (counting off).
 __device__ __forceinline__ void add_counters(unsigned long long* dst, uint32_t a, uint32_t b) {
-  __shared__ uint32_t sh_a[4], sh_b[4];
+  __shared__ uint32_t sh_a[16], sh_b[16];
   if (!dst) return;   // uniform: a kernel argument
   const uint32_t x = block_sum(a, sh_a), y = block_sum(b, sh_b);
   if (threadIdx.x == 0) {
@@ -191,76 +250,189 @@ __device__ __forceinline__ void add_counters(unsigned long long* dst, uint32_t a
   }
 }
 
-template <bool WIDE>
-__global__ __launch_bounds__(256) void k_index_build(Buf b, const uint64_t* __restrict__ nnz_p,
-                                                     unsigned long long* table, uint64_t mask, U2Desc d,
-                                                     uint32_t* __restrict__ partner, unsigned long long* count) {
+// A held run's gates in LDS, loaded all at once: read one by one from memory,
+// each costs the latency of its first touch (0.5 us or more).
+struct RunLds {
+  MonoDesc g[kHeldMax];
+  __device__ __forceinline__ void load(const MonoDesc* __restrict__ src, uint32_t ng) {
+    uint4* dst = reinterpret_cast<uint4*>(g);
+    const uint4* s4 = reinterpret_cast<const uint4*>(src);
+    for (uint32_t k = threadIdx.x; k < ng * (sizeof(MonoDesc) / 16); k += blockDim.x) dst[k] = s4[k];
+    __syncthreads();
+  }
+};
+
+// Index build, with the short phase/permutation run before the gate applied
+// on the way (MONO: the run's gates in order on each entry, as k_mono, in the
+// same pass over the labels).  Only the entries a partner look-up can ask for
+// are indexed: those under the op's controls with the pivot bit clear (the
+// look-ups come from their partners, whose pivot bit is set) whose partner is
+// not the entry next to them in the wave (the two outputs of a pair are written
+// next to each other, and the look-ups look there first).  Bound by the CAS
+// rate, 26 G/s whatever the scope or the table's size (a plain random store
+// runs at 77 G/s, a load at 55-75 G/s): indexing every entry, so that the
+// single pass could look up both partners of a pair and the partner pass go,
+// was slower at every size (2^20 entries of 24 bytes: 33 + 17 + 51 us against
+// 75 + 148).
+template <bool WIDE, bool MONO>
+__global__ __launch_bounds__(256) void k_index_build(Buf b, const uint64_t* __restrict__ nnz_p, IndexTab t, U2Desc d,
+                                                     unsigned long long* count, const MonoDesc* __restrict__ g,
+                                                     uint32_t ng, uint32_t rf, uint32_t bpe, Ctl* ctl) {
+  __shared__ RunLds sg;
   const uint64_t n = *nnz_p;
-  uint32_t inserts = 0, cas = 0;
-  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x) {
-    partner[i] = kNoPartner;
-    const uint64_t lo = b.key_lo[i];
-    const uint64_t hi = WIDE ? b.key_hi[i] : 0ull;
-    bool c = (lo & d.ctrl_lo) == d.ctrl_lo;
-    if (WIDE) c = c && ((hi & d.ctrl_hi) == d.ctrl_hi);
-    const uint64_t w = (WIDE && d.target >= 64) ? hi : lo;
-    if (!c || ((w >> (d.target & 63)) & 1ull)) continue;
-    const uint64_t h = hash_label(lo, hi);
-    const unsigned long long val = ((h >> 32) << 32) | i;
-    uint64_t slot = h & mask;
-    ++inserts;
-    for (uint64_t p = 0; p <= mask; ++p) {
-      ++cas;
-      if (atomicCAS(&table[slot], (unsigned long long)kEmptySlot, val) == kEmptySlot) break;
-      slot = (slot + 1) & mask;
+  const Geom gm = index_geom(t, n);
+  if (MONO) sg.load(g, ng);
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    t.tc->mask = gm.mask;
+    t.tc->bits = gm.bits;
+    t.tc->nopair = 0;
+    if (MONO) {
+      atomicAdd((unsigned long long*)&ctl->updates, (unsigned long long)(n * ng));
+      atomicAdd((unsigned long long*)&ctl->mono_bytes, (unsigned long long)(n * bpe));
+      atomicAdd((unsigned long long*)&ctl->mono_updates, (unsigned long long)(n * ng));
     }
+  }
+  uint32_t inserts = 0, cas = 0;
+  for (uint64_t base = (uint64_t)blockIdx.x * blockDim.x; base < n; base += (uint64_t)gridDim.x * blockDim.x) {
+    const uint64_t i = base + threadIdx.x;
+    const bool ok = i < n;
+    uint64_t lo = 0, hi = 0;
+    if (ok) {
+      lo = b.key_lo[i];
+      hi = WIDE ? b.key_hi[i] : 0ull;
+      if (MONO) {
+        double2 a = make_double2(0.0, 0.0);
+        if (rf & kRunPhase) a = b.amp[i];
+        for (uint32_t j = 0; j < ng; ++j) ent::mono_step(sg.g[j], WIDE, lo, hi, a);
+        if (rf & kRunFlip) {
+          b.key_lo[i] = lo;
+          if (WIDE) b.key_hi[i] = hi;
+        }
+        if (rf & kRunPhase) b.amp[i] = a;
+      }
+    }
+    // Every lane takes part in the neighbours' shuffles (only those inside
+    // the wave: other waves' labels may be before or after the run).
+    const uint64_t qlo = lo ^ d.x_lo, qhi = WIDE ? hi ^ d.x_hi : 0ull;
+    const bool before = next_to<WIDE>(b, n, i, lo, hi, qlo, qhi, false, true);
+    const bool after = next_to<WIDE>(b, n, i, lo, hi, qlo, qhi, true, true);
+    if (!ok || !ent::ctrl_ok(d, lo, hi, WIDE) || ent::pivot_set(d, lo, hi, WIDE)) continue;
+    ++inserts;
+    if (!(before || after) || count) cas += index_insert(t.slots, gm, lo, hi, (uint32_t)i);
   }
   add_counters(count, inserts, cas);
 }
 
+// The index of label lo/hi among the indexed entries, or kNoPartner.
 template <bool WIDE>
-__device__ __forceinline__ uint32_t find_label(const Buf& b, const uint64_t* __restrict__ table, uint64_t mask,
-                                               uint64_t lo, uint64_t hi, uint32_t& steps) {
+__device__ __forceinline__ uint32_t find_label(const Buf& b, const uint32_t* __restrict__ slots, const Geom& gm,
+                                               uint64_t n, uint64_t lo, uint64_t hi, uint32_t& steps) {
   const uint64_t h = hash_label(lo, hi);
-  const uint32_t fp = (uint32_t)(h >> 32);
-  uint64_t slot = h & mask;
-  for (uint64_t p = 0; p <= mask; ++p) {
-    const uint64_t s = table[slot];
+  const uint32_t fp = (uint32_t)((h >> 32) >> gm.bits);
+  const uint32_t idx_mask = (1u << gm.bits) - 1u;
+  uint32_t slot = (uint32_t)h & gm.mask;
+  for (uint64_t p = 0; p <= gm.mask; ++p) {
+    const uint32_t v = slots[slot];
     ++steps;
-    if (s == kEmptySlot) return kNoPartner;
-    if ((uint32_t)(s >> 32) == fp) {
-      const uint32_t j = (uint32_t)s;
-      if (b.key_lo[j] == lo && (!WIDE || b.key_hi[j] == hi)) return j;
+    if (v == kFreeSlot) return kNoPartner;
+    if ((uint32_t)((uint64_t)v >> gm.bits) == fp) {
+      const uint32_t j = v & idx_mask;
+      if (j < n && b.key_lo[j] == lo && (!WIDE || b.key_hi[j] == hi)) return j;
     }
-    slot = (slot + 1) & mask;
+    slot = (slot + 1) & gm.mask;
   }
   return kNoPartner;
 }
 
 // Partner look-up (Sec. 3.1: at most one per label): each entry under the
-// controls with the pivot bit set looks up label ^ x among the indexed
-// entries; when found, both entries record each other (a pivot-0 entry has at
-// most one such partner, so the writes never collide).
+// controls with the pivot bit set finds label ^ x, next to itself or among the
+// indexed entries; when found, it records its partner and marks it (a pivot-0
+// entry has at most one such partner, so the marks never collide).  The pass
+// also forms the AND and OR of all labels, from which the gate's write knows
+// qubits that are the same in every entry, and empties the other table.
 template <bool WIDE>
-__global__ __launch_bounds__(256) void k_u2_probe(Buf b, const uint64_t* __restrict__ nnz_p,
-                                                  const uint64_t* __restrict__ table, uint64_t mask, U2Desc d,
-                                                  uint32_t* __restrict__ partner, unsigned long long* count) {
+__global__ __launch_bounds__(1024) void k_u2_probe(Buf b, const uint64_t* __restrict__ nnz_p, IndexTab t, U2Desc d,
+                                                   uint32_t* __restrict__ partner, uint32_t epoch,
+                                                   unsigned long long* count) {
+  __shared__ uint64_t s_m[4][16];
   const uint64_t n = *nnz_p;
+  const Geom gm{t.tc->mask, t.tc->bits};
+  const bool nopair = t.tc->nopair != 0;
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  if (blockIdx.x == 0 && threadIdx.x < kLabelCells) {   // for the next gate's pass
+    LabelCell& c = t.labels_other[threadIdx.x];
+    c.and_lo = c.and_hi = ~0ull;
+    c.or_lo = c.or_hi = 0;
+  }
   uint32_t lookups = 0, steps = 0;
-  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x) {
-    const uint64_t lo = b.key_lo[i];
-    const uint64_t hi = WIDE ? b.key_hi[i] : 0ull;
-    bool c = (lo & d.ctrl_lo) == d.ctrl_lo;
-    if (WIDE) c = c && ((hi & d.ctrl_hi) == d.ctrl_hi);
-    const uint64_t w = (WIDE && d.target >= 64) ? hi : lo;
-    if (!c || !((w >> (d.target & 63)) & 1ull)) continue;
+  uint64_t m[4] = {~0ull, ~0ull, 0, 0};   // AND and OR of the labels
+  for (uint64_t base = (uint64_t)blockIdx.x * blockDim.x; base < n; base += (uint64_t)gridDim.x * blockDim.x) {
+    const uint64_t i = base + threadIdx.x;
+    const bool ok = i < n;
+    uint64_t lo = 0, hi = 0;
+    if (ok) {
+      lo = b.key_lo[i];
+      hi = WIDE ? b.key_hi[i] : 0ull;
+      m[0] &= lo;
+      m[2] |= lo;
+      if (WIDE) {
+        m[1] &= hi;
+        m[3] |= hi;
+      }
+    }
+    if (nopair) continue;   // uniform
+    const uint64_t qlo = lo ^ d.x_lo, qhi = WIDE ? hi ^ d.x_hi : 0ull;
+    const bool before = next_to<WIDE>(b, n, i, lo, hi, qlo, qhi, false, false);
+    const bool after = next_to<WIDE>(b, n, i, lo, hi, qlo, qhi, true, false);
+    if (!ok || !ent::ctrl_ok(d, lo, hi, WIDE) || !ent::pivot_set(d, lo, hi, WIDE)) continue;
     ++lookups;
-    const uint32_t j = find_label<WIDE>(b, table, mask, lo ^ d.x_lo, WIDE ? (hi ^ d.x_hi) : 0ull, steps);
-    if (j == kNoPartner) continue;
+    uint32_t j = before ? (uint32_t)i - 1u : after ? (uint32_t)i + 1u : kNoPartner;
+    if (j == kNoPartner || count) j = find_label<WIDE>(b, t.slots, gm, n, qlo, qhi, steps);
     partner[i] = j;
-    partner[j] = (uint32_t)i;
+    if (j != kNoPartner) partner[j] = kHasPartner | epoch;
+  }
+  index_empty(t.other, t.tc_other);
+  if ((uint64_t)blockIdx.x * blockDim.x < n) {   // uniform: the block saw an entry
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      m[0] &= __shfl_xor(m[0], o);
+      m[2] |= __shfl_xor(m[2], o);
+      if (WIDE) {
+        m[1] &= __shfl_xor(m[1], o);
+        m[3] |= __shfl_xor(m[3], o);
+      }
+    }
+    if (lane == 0)
+      for (int k = 0; k < 4; ++k) s_m[k][wid] = m[k];
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      for (int w = 1; w < (int)(blockDim.x >> 6); ++w) {
+        m[0] &= s_m[0][w];
+        m[1] &= s_m[1][w];
+        m[2] |= s_m[2][w];
+        m[3] |= s_m[3][w];
+      }
+      LabelCell& c = t.labels[blockIdx.x % kLabelCells];
+      atomicAnd((unsigned long long*)&c.and_lo, (unsigned long long)m[0]);
+      atomicOr((unsigned long long*)&c.or_lo, (unsigned long long)m[2]);
+      if (WIDE) {
+        atomicAnd((unsigned long long*)&c.and_hi, (unsigned long long)m[1]);
+        atomicOr((unsigned long long*)&c.or_hi, (unsigned long long)m[3]);
+      }
+    }
+    __syncthreads();
   }
   add_counters(count, lookups, steps);
+}
+
+// Whether entry (lo, hi) has a partner, from its word of the partner array,
+// and the partner's index if the entry's own pivot bit is set.
+template <bool WIDE>
+__device__ __forceinline__ uint32_t partner_of(const U2Desc& d, uint64_t lo, uint64_t hi, uint32_t word,
+                                               uint32_t epoch) {
+  if (!ent::ctrl_ok(d, lo, hi, WIDE)) return kNoPartner;
+  if (ent::pivot_set(d, lo, hi, WIDE)) return word;
+  return word == (kHasPartner | epoch) ? 0u : kNoPartner;
 }
 
 // The count, write and single-pass kernels take partner == null for a gate
@@ -280,8 +452,8 @@ __device__ __forceinline__ U2Out u2_eval(const Buf& b, const U2Desc& d, uint64_t
 
 template <bool WIDE>
 __global__ __launch_bounds__(256) void k_u2_count(Buf b, const uint64_t* __restrict__ nnz_p, U2Desc d,
-                                                  const uint32_t* __restrict__ partner, uint32_t* __restrict__ tot,
-                                                  Ctl* ctl) {
+                                                  const uint32_t* __restrict__ partner, uint32_t epoch,
+                                                  uint32_t* __restrict__ tot, Ctl* ctl) {
   __shared__ uint32_t sh[256];
   __shared__ double2 shm[4];   // one slot per wave
   const uint64_t n = *nnz_p;
@@ -292,7 +464,8 @@ __global__ __launch_bounds__(256) void k_u2_count(Buf b, const uint64_t* __restr
   for (uint64_t i = begin + threadIdx.x; i < end; i += blockDim.x) {
     const uint64_t lo = b.key_lo[i];
     const uint64_t hi = WIDE ? b.key_hi[i] : 0ull;
-    const U2Out r = u2_eval<WIDE>(b, d, lo, hi, b.amp[i], partner ? partner[i] : kNoPartner);
+    const uint32_t j = partner ? partner_of<WIDE>(d, lo, hi, partner[i], epoch) : kNoPartner;
+    const U2Out r = u2_eval<WIDE>(b, d, lo, hi, b.amp[i], j);
     if (r.mode == 0) {
       const bool k = survives(r.o0, d.eps);
       emit += k ? 1u : 0u;
@@ -368,7 +541,7 @@ __global__ __launch_bounds__(1024) void k_scan(uint32_t* __restrict__ tot, int n
 
 template <bool WIDE>
 __global__ __launch_bounds__(256) void k_u2_write(Buf in, Buf out, const uint64_t* __restrict__ nnz_p,
-                                                  const uint32_t* __restrict__ partner,
+                                                  const uint32_t* __restrict__ partner, uint32_t epoch,
                                                   const uint32_t* __restrict__ off, U2Desc d, Ctl* ctl) {
   __shared__ uint32_t s_wave[16];
   const uint64_t n = *nnz_p;
@@ -387,7 +560,8 @@ __global__ __launch_bounds__(256) void k_u2_write(Buf in, Buf out, const uint64_
     if (i < end) {
       lo = in.key_lo[i];
       hi = WIDE ? in.key_hi[i] : 0ull;
-      r = u2_eval<WIDE>(in, d, lo, hi, in.amp[i], partner ? partner[i] : kNoPartner);
+      const uint32_t j = partner ? partner_of<WIDE>(d, lo, hi, partner[i], epoch) : kNoPartner;
+      r = u2_eval<WIDE>(in, d, lo, hi, in.amp[i], j);
       if (r.mode == 0) {
         k0 = survives(r.o0, d.eps);
       } else if (r.mode == 1) {
@@ -423,170 +597,397 @@ __global__ __launch_bounds__(256) void k_u2_write(Buf in, Buf out, const uint64_
   }
 }
 
-// Single-pass branching gate, for states whose outputs are known to fit:
-// each block evaluates one tile of 256 ITEMS entries once (Eq. 2 with T_eps, the
-// results held in registers) and finds where its outputs go by a chained scan
-// over the tiles: it publishes its tile's output count, adds its
-// predecessors' counts back to the first published inclusive prefix,
-// publishes its own inclusive prefix, then writes.  Blocks take tile numbers
-// from a counter in the order they start, so a tile waited on always belongs
-// to a block already running; the wait is bounded even so (a block that gives
+// Single-pass branching gate: a block evaluates one tile of 1024 ITEMS entries
+// (Eq. 2 with T_eps, the results held in registers) and finds where its
+// outputs go by a chained scan over the tiles: it publishes its tile's output
+// count, adds its predecessors' counts back to the first published inclusive
+// prefix, publishes its own inclusive prefix, writes, and takes the next tile.
+// Tile numbers come from a counter in the order blocks ask for them, so a tile
+// waited on always belongs to a block already running; the wait is bounded even so (a block that gives
 // up sets error bit 2 and its outputs are wrong, but the kernel ends).  A
 // status word packs (epoch, flag, count) and is read and written atomically at
-// device scope, so no fence is needed; the epoch tells this launch's words
-// from those of earlier launches.  Output order is input order, as in the
-// two-pass form.
+// device scope, so no fence is needed; the epoch tells this launch's words from
+// those of earlier launches.  Output order is input order, as in the two-pass
+// form.
+//
+// What bounds it below a few million entries is the counter: atomics on one
+// address complete one every 11.5 ns across the chip, so a tile costs that
+// much whatever its size.  Hence blocks of 1024 threads, the tiles counted from
+// the entry count on the device, and a block past them leaving before it takes
+// a number.  With a number for each
+// 512-entry tile of the bound this pass took 51 us at 2^20 entries of 24 bytes
+// (1 us per 40 tiles), now 22 us.  Two counters alternate between launches,
+// each reset by the launch that uses the other.
+//
+// The tile is 1024 entries up to 2^18 entries (256 tiles: one a CU), 2048 up to
+// 2^19, 4096 beyond (fewer numbers; 2^20 entries of 24 bytes: 22 us against 31
+// with 1024).
+//
+// A gate whose outputs may not fit (seq != 0) writes nothing at or past cap,
+// and if they did not fit reports an empty output and marks Ctl::over; `in`
+// keeps the state.  The counters are staged by launch parity for that reason.
+//
+// NEXT: the short run up to the next branching gate is applied to the outputs
+// and the outputs are indexed for that gate, which saves both a pass of their
+// own (the table is sized for twice the entries, the most there can be).
+// Nothing is indexed if the next gate's partner mask meets a qubit that is the
+// same in every output.
 constexpr uint64_t kStAgg = 1ull << 32, kStPrefix = 2ull << 32;
 constexpr uint32_t kSpinMax = 1u << 22;
+constexpr int kU2Threads = 1024, kU2Waves = kU2Threads / 64;
 
 __device__ __forceinline__ uint64_t st_word(uint32_t epoch, uint64_t flag, uint32_t v) {
   return ((uint64_t)epoch << 34) | flag | v;
 }
 
-// Tiles of 512, 1024 or 2048 entries (ITEMS = 2, 4, 8): the larger tiles hold
-// more registers (2048: two waves per SIMD), the smaller ones put more blocks
-// in flight, which is what states of up to a few million entries need.
-template <bool WIDE, int ITEMS>
-__global__ __launch_bounds__(256) void k_u2_fused(Buf in, Buf out, const uint64_t* __restrict__ nnz_p,
-                                                  const uint32_t* __restrict__ partner, U2Desc d, Ctl* ctl,
-                                                  uint64_t* status, uint32_t ticket_base, uint32_t epoch,
-                                                  uint64_t* nnz_out, uint64_t* __restrict__ table,
-                                                  uint64_t clear_slots) {
-  constexpr int kItems = ITEMS;
-  constexpr uint32_t kTile = 256u * ITEMS;
-  __shared__ uint32_t s_wave[16];
-  __shared__ uint32_t sh[256];
-  __shared__ double2 shm[4];   // one slot per wave
-  __shared__ uint32_t s_tile, s_excl;
-  const uint64_t n = *nnz_p;
-  // This gate is done with the hash index: empty its first clear_slots slots
-  // for the next branching gate (every block, by block index).
-  for (uint64_t k = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; k < clear_slots;
-       k += (uint64_t)gridDim.x * blockDim.x)
-    table[k] = kEmptySlot;
-  if (threadIdx.x == 0) s_tile = atomicAdd(&ctl->ticket, 1u) - ticket_base;
-  __syncthreads();
-  const uint32_t tile = s_tile;
-  if (tile >= gridDim.x) {   // the counter and the host's base disagree: touch nothing
-    if (threadIdx.x == 0) atomicOr(&ctl->error, 2u);
-    return;
-  }
-  const uint64_t begin = (uint64_t)tile * kTile;
-  U2Out r[kItems];
-  uint64_t lo[kItems], hi[kItems];
-  uint32_t pos[kItems];
-  bool k0[kItems], k1[kItems];
-  uint32_t run = 0, dropped = 0;
-  double mass = 0.0;
+// The sum of the output counts of the tiles before `tile`, by one wave: lane l
+// reads the status of tile - 1 - l and of the three tiles 64, 128 and 192
+// before that in one round trip, and counts are added back to the nearest
+// published inclusive prefix (positions before tile 0 count as a prefix of 0).
+__device__ __forceinline__ uint32_t look_back(uint64_t* status, uint32_t tile, uint32_t epoch, uint32_t* error) {
+  const int lane = threadIdx.x & 63;
+  constexpr int kW = 4;
+  uint32_t excl = 0, spins = 0;
+  int64_t hi = (int64_t)tile - 1;
+  while (hi >= 0) {
+    uint64_t v[kW];
 #pragma unroll
-  for (int k = 0; k < kItems; ++k) {
-    const uint64_t i = begin + (uint64_t)k * 256 + threadIdx.x;
-    r[k].mode = 2;
-    k0[k] = k1[k] = false;
-    lo[k] = hi[k] = 0;
-    if (i < n) {
-      lo[k] = in.key_lo[i];
-      hi[k] = WIDE ? in.key_hi[i] : 0ull;
-      r[k] = u2_eval<WIDE>(in, d, lo[k], hi[k], in.amp[i], partner ? partner[i] : kNoPartner);
-      if (r[k].mode == 0) {
-        k0[k] = survives(r[k].o0, d.eps);
-        dropped += k0[k] ? 0u : 1u;
-        mass += ent::dropped_mass(r[k].o0, k0[k]);
-      } else if (r[k].mode == 1) {
-        k0[k] = survives(r[k].o0, d.eps);
-        k1[k] = survives(r[k].o1, d.eps);
-        dropped += (k0[k] ? 0u : 1u) + (k1[k] ? 0u : 1u);
-        mass += ent::dropped_mass(r[k].o0, k0[k]) + ent::dropped_mass(r[k].o1, k1[k]);
-      }
+    for (int w = 0; w < kW; ++w) {
+      const int64_t j = hi - lane - 64 * w;
+      v[w] = st_word(epoch, kStPrefix, 0);
+      if (j >= 0) v[w] = __hip_atomic_load(&status[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    uint32_t tt;
-    pos[k] = run + block_prefix012((k0[k] ? 1u : 0u) + (k1[k] ? 1u : 0u), s_wave, &tt);
-    run += tt;
-  }
-  dropped = block_sum(dropped, sh);
-  mass = block_sum(make_double2(mass, 0.0), shm).x;
-  // Publish this tile's count, then the first wave looks back 64 tiles per
-  // poll (lane l reads tile - 1 - l) and adds counts back to the nearest
-  // published inclusive prefix; positions before tile 0 count as a prefix of 0.
-  if (threadIdx.x == 0) {
-    if (dropped) {
-      atomicAdd((unsigned long long*)&ctl->pruned, (unsigned long long)dropped);
-      atomicAdd(&ctl->pruned_mass, mass);
-    }
-    __hip_atomic_store(&status[tile], st_word(epoch, tile == 0 ? kStPrefix : kStAgg, run), __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_AGENT);
-    if (tile == 0) atomicAdd((unsigned long long*)&ctl->updates, (unsigned long long)n);
-  }
-  if (threadIdx.x < 64) {
-    const int lane = threadIdx.x;
-    uint32_t excl = 0;
-    int64_t hi_tile = (int64_t)tile - 1;
-    uint32_t spins = 0;
-    while (hi_tile >= 0) {
-      const int64_t j = hi_tile - lane;
-      const uint64_t v = j >= 0 ? __hip_atomic_load(&status[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
-                                : st_word(epoch, kStPrefix, 0);
-      const bool ready = (uint32_t)(v >> 34) == epoch;
-      const uint64_t pmask = __ballot(ready && (v & kStPrefix));
+    bool wait = false, done = false;
+#pragma unroll
+    for (int w = 0; w < kW; ++w) {
+      if (wait || done) continue;   // uniform
+      const bool ready = (uint32_t)(v[w] >> 34) == epoch;
+      const uint64_t pmask = __ballot(ready && (v[w] & kStPrefix));
       const uint64_t nready = __ballot(!ready);
       const int first = pmask ? __builtin_ctzll(pmask) : 63;   // nearest prefix in the window, else all 64
       const uint64_t need = first == 63 ? ~0ull : ((2ull << first) - 1);
       if (nready & need) {
-        if (++spins > kSpinMax) {
-          if (lane == 0) atomicOr(&ctl->error, 2u);
-          break;
-        }
-        __builtin_amdgcn_s_sleep(1);
+        wait = true;
         continue;
       }
-      uint32_t x = lane <= first ? (uint32_t)v : 0u;
+      excl += wave_sum(lane <= first ? (uint32_t)v[w] : 0u);
+      done = pmask != 0;
+      hi -= 64;
+    }
+    if (done) break;
+    if (wait) {
+      if (++spins > kSpinMax) {
+        if (lane == 0) atomicOr(error, 2u);
+        break;
+      }
+      __builtin_amdgcn_s_sleep(1);
+    }
+  }
+  return excl;
+}
+
+// The last launch's staged counters join the state's (unless its outputs did
+// not fit) and start over.  A wave's work, a cell a lane: one round trip.
+__device__ __forceinline__ void commit_staged(Ctl* ctl, uint32_t p) {
+  const uint32_t lane = threadIdx.x & 63;
+  uint64_t updates = 0;
+  uint32_t pruned = 0;
+  double mass = 0.0;
+  const bool fits = !ctl->over;
+  if (lane < kStageCells) {
+    StageCell& c = ctl->fst[p][lane];
+    updates = c.updates;
+    pruned = (uint32_t)c.pruned;   // at most two per entry of one gate
+    mass = c.mass;
+    c.updates = c.pruned = 0;
+    c.mass = 0.0;
+  }
+  pruned = wave_sum(pruned);
+  mass = wave_sum(make_double2(mass, 0.0)).x;
+  if (lane != 0 || !fits) return;
+  atomicAdd((unsigned long long*)&ctl->updates, (unsigned long long)updates);   // cell 0 holds them
+  ctl->pruned += pruned;
+  ctl->pruned_mass += mass;
+}
+
+// Whether the next gate's partner mask meets a qubit that is the same in every
+// output of gate d and stays so over the run: those the same in every input
+// but the partner mask's; a flip keeps its target only if its controls are.
+// Every lane of the wave calls it.
+__device__ __forceinline__ bool known_apart(const NextGate& nx, const U2Desc& d, const MonoDesc* run) {
+  if (!nx.labels) return false;
+  static_assert(kLabelCells == 32, "a cell per lane of half a wave");
+  const LabelCell c = nx.labels[threadIdx.x & 31];
+  uint64_t m[4] = {c.and_lo, c.and_hi, c.or_lo, c.or_hi};
 #pragma unroll
-      for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
-      excl += x;
-      if (pmask) break;
-      hi_tile -= 64;
+  for (int o = 16; o > 0; o >>= 1) {
+    m[0] &= __shfl_xor(m[0], o);
+    m[1] &= __shfl_xor(m[1], o);
+    m[2] |= __shfl_xor(m[2], o);
+    m[3] |= __shfl_xor(m[3], o);
+  }
+  uint64_t lo = ~(m[0] ^ m[2]) & ~d.x_lo, hi = ~(m[1] ^ m[3]) & ~d.x_hi;
+  for (uint32_t k = 0; k < nx.run.ng; ++k) {
+    const MonoDesc& g = run[k];
+    if (!(g.flags & kFlip) || !((g.ctrl_lo & ~lo) | (g.ctrl_hi & ~hi))) continue;
+    const uint64_t b = 1ull << (g.target & 63);
+    if (g.target < 64) lo &= ~b;
+    else hi &= ~b;
+  }
+  return ((nx.d.x_lo & lo) | (nx.d.x_hi & hi)) != 0;
+}
+
+struct U2Smem {
+  uint32_t cnt[4 * kU2Waves];   // outputs by item and wave, then their exclusive prefix
+  uint32_t drop[kU2Waves];
+  double mass[kU2Waves];
+  uint32_t tile, excl;
+  bool apart;
+  RunLds run;
+};
+
+template <bool WIDE, int ITEMS, bool NEXT>
+__device__ __forceinline__ void u2_tiles(const Buf& in, const Buf& out, uint64_t n, const uint32_t* __restrict__ partner,
+                                         const U2Desc& d, Ctl* ctl, const TabCtl* tc, uint64_t* status, uint32_t par,
+                                         uint32_t epoch, uint64_t* nnz_out, uint64_t cap, uint32_t seq,
+                                         const NextGate& nx, U2Smem& sm) {
+  constexpr int kItems = ITEMS;
+  constexpr uint32_t kTile = kU2Threads * ITEMS;
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  const uint32_t tiles = (uint32_t)((n + kTile - 1) / kTile);
+  const Geom ng = NEXT ? index_geom(nx.tab, 2 * n <= cap ? 2 * n : cap) : Geom{0, 0};
+  if (blockIdx.x >= tiles) {
+    if (blockIdx.x == 0 && wid == 2) commit_staged(ctl, par ^ 1u);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {   // an empty state: nobody takes a number
+      ctl->ticket[par ^ 1u] = 0;
+      if (NEXT) nx.tab.tc->mask = 0, nx.tab.tc->nopair = 1;
+      *nnz_out = 0;
+    }
+    return;
+  }
+  if (tc && tc->nopair) partner = nullptr;
+  if (threadIdx.x == 0) sm.tile = atomicAdd(&ctl->ticket[par], 1u);
+  if (NEXT) sm.run.load(nx.run.g, nx.run.ng);
+  else __syncthreads();
+  if (NEXT) {
+    if (wid == 1) {
+      const bool y = known_apart(nx, d, sm.run.g);
+      if (lane == 0) sm.apart = y;
+    }
+    __syncthreads();
+  }
+  const bool apart = NEXT && sm.apart;
+  const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+  for (uint32_t tile = sm.tile; tile < tiles;) {
+    // (before the tile's count is published: no later tile can have marked Ctl::over)
+    if (tile == 0 && wid == 2) commit_staged(ctl, par ^ 1u);
+    const uint64_t begin = (uint64_t)tile * kTile;
+    U2Out r[kItems];
+    uint64_t lo[kItems], hi[kItems];
+    double2 a[kItems];
+    uint32_t j[kItems], pre[kItems];
+    bool k0[kItems], k1[kItems];
+#pragma unroll
+    for (int k = 0; k < kItems; ++k) {
+      const uint64_t i = begin + (uint64_t)k * kU2Threads + threadIdx.x;
+      lo[k] = hi[k] = 0;
+      a[k] = make_double2(0.0, 0.0);
+      j[k] = kNoPartner;
+      if (i < n) {
+        if (partner) j[k] = partner[i];
+        lo[k] = in.key_lo[i];
+        hi[k] = WIDE ? in.key_hi[i] : 0ull;
+        a[k] = in.amp[i];
+      }
+    }
+    double2 aj[kItems];
+#pragma unroll
+    for (int k = 0; k < kItems; ++k) {
+      aj[k] = make_double2(0.0, 0.0);
+      if (partner) j[k] = partner_of<WIDE>(d, lo[k], hi[k], j[k], epoch);
+      if (j[k] != kNoPartner && pivot_set<WIDE>(d, lo[k], hi[k])) aj[k] = in.amp[j[k]];
+    }
+    uint32_t dropped = 0;
+    double mass = 0.0;
+#pragma unroll
+    for (int k = 0; k < kItems; ++k) {
+      const uint64_t i = begin + (uint64_t)k * kU2Threads + threadIdx.x;
+      r[k] = ent::u2_eval(d, WIDE, lo[k], hi[k], a[k], j[k] != kNoPartner, aj[k]);
+      if (i >= n) r[k].mode = 2;
+      k0[k] = k1[k] = false;
+      if (r[k].mode != 2) {
+        k0[k] = survives(r[k].o0, d.eps);
+        dropped += k0[k] ? 0u : 1u;
+        mass += ent::dropped_mass(r[k].o0, k0[k]);
+      }
+      if (r[k].mode == 1) {
+        k1[k] = survives(r[k].o1, d.eps);
+        dropped += k1[k] ? 0u : 1u;
+        mass += ent::dropped_mass(r[k].o1, k1[k]);
+      }
+      // A thread emits k0 + k1 entries.
+      const uint64_t b0 = __ballot(k0[k]), b1 = __ballot(k1[k]);
+      pre[k] = __popcll(b0 & lt) + __popcll(b1 & lt);
+      if (lane == 0) sm.cnt[k * kU2Waves + wid] = __popcll(b0) + __popcll(b1);
+    }
+    const bool drops = __ballot(dropped != 0) != 0;   // uniform in the wave
+    uint32_t wd = 0;
+    double wm = 0.0;
+    if (drops) {
+      wd = wave_sum(dropped);
+      wm = wave_sum(make_double2(mass, 0.0)).x;
     }
     if (lane == 0) {
-      if (tile != 0)
-        __hip_atomic_store(&status[tile], st_word(epoch, kStPrefix, excl + run), __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_AGENT);
-      s_excl = excl;
-      if (tile == gridDim.x - 1) {
-        const uint32_t eb = WIDE ? 32u : 24u;
-        const uint64_t total = (uint64_t)excl + run;
-        *nnz_out = total;
-        if (total > ctl->peak) ctl->peak = total;
-        atomicAdd((unsigned long long*)&ctl->pass_bytes[1], (unsigned long long)((n + total) * eb));
-      }
+      sm.drop[wid] = wd;
+      sm.mass[wid] = wm;
     }
-  }
-  __syncthreads();
-  const uint64_t base = s_excl;
+    __syncthreads();
+    if (wid == 0) {
+      // Offsets within the tile (items in order, waves in order within an item),
+      // then the tiles before it.
+      static_assert(kItems * kU2Waves <= 64, "one lane per item and wave");
+      const uint32_t x = lane < kItems * kU2Waves ? sm.cnt[lane] : 0u;
+      uint32_t incl = x;
 #pragma unroll
-  for (int k = 0; k < kItems; ++k) {
-    uint64_t p = base + pos[k];
-    if (r[k].mode == 0) {
-      if (k0[k]) {
-        out.key_lo[p] = lo[k];
-        if (WIDE) out.key_hi[p] = hi[k];
-        out.amp[p] = r[k].o0;
+      for (int o = 1; o < kItems * kU2Waves; o <<= 1) {
+        const uint32_t y = __shfl_up(incl, o);
+        if (lane >= o) incl += y;
       }
-    } else if (r[k].mode == 1) {
-      const bool v = pivot_set<WIDE>(d, lo[k], hi[k]);
-      const uint64_t lo0 = v ? lo[k] ^ d.x_lo : lo[k], hi0 = v ? hi[k] ^ d.x_hi : hi[k];
-      if (k0[k]) {
-        out.key_lo[p] = lo0;
-        if (WIDE) out.key_hi[p] = hi0;
-        out.amp[p] = r[k].o0;
-        ++p;
+      const uint32_t run = __shfl(incl, kItems * kU2Waves - 1);
+      if (lane < kItems * kU2Waves) sm.cnt[lane] = incl - x;
+      if (lane == 0) {
+        __hip_atomic_store(&status[tile], st_word(epoch, tile == 0 ? kStPrefix : kStAgg, run), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+        if (tile == 0) {
+          ctl->ticket[par ^ 1u] = 0;   // for the next launch
+          ctl->fst[par][0].updates = n;
+          if (NEXT) {
+            nx.tab.tc->mask = ng.mask;
+            nx.tab.tc->bits = ng.bits;
+            nx.tab.tc->nopair = apart;
+          }
+        }
       }
-      if (k1[k]) {
-        out.key_lo[p] = lo0 ^ d.x_lo;
-        if (WIDE) out.key_hi[p] = hi0 ^ d.x_hi;
-        out.amp[p] = r[k].o1;
+      const uint32_t excl = look_back(status, tile, epoch, &ctl->error);
+      if (lane == 0) {
+        if (tile != 0)
+          __hip_atomic_store(&status[tile], st_word(epoch, kStPrefix, excl + run), __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_AGENT);
+        sm.excl = excl;
+        if (tile == tiles - 1) {
+          const uint32_t eb = WIDE ? 32u : 24u;
+          const uint64_t total = (uint64_t)excl + run;
+          if (total <= cap) {
+            *nnz_out = total;
+            if (total > ctl->peak) ctl->peak = total;
+            atomicAdd((unsigned long long*)&ctl->pass_bytes[1], (unsigned long long)((n + total) * eb));
+            if (NEXT && nx.run.ng) {
+              atomicAdd((unsigned long long*)&ctl->updates, (unsigned long long)(total * nx.run.ng));
+              atomicAdd((unsigned long long*)&ctl->mono_updates, (unsigned long long)(total * nx.run.ng));
+              atomicAdd((unsigned long long*)&ctl->mono_bytes, (unsigned long long)(total * nx.run.bytes_per_entry));
+            }
+          } else {
+            *nnz_out = 0;
+            ctl->over = seq;
+            ctl->over_n = n;
+          }
+        }
+      }
+    } else if (wid == 1) {
+      const uint32_t td = wave_sum(lane < kU2Waves ? sm.drop[lane] : 0u);
+      const double tm = wave_sum(make_double2(lane < kU2Waves ? sm.mass[lane] : 0.0, 0.0)).x;
+      if (lane == 0 && td) {
+        StageCell& c = ctl->fst[par][tile % kStageCells];
+        atomicAdd((unsigned long long*)&c.pruned, (unsigned long long)td);
+        atomicAdd(&c.mass, tm);
       }
     }
+    __syncthreads();
+    const uint64_t base = sm.excl;
+    Claim claim[NEXT ? 2 * kItems : 1];
+#pragma unroll
+    for (int k = 0; k < kItems; ++k) {
+      const uint64_t p = base + sm.cnt[k * kU2Waves + wid] + pre[k];
+      const bool flipped = r[k].mode == 1 && pivot_set<WIDE>(d, lo[k], hi[k]);
+      uint64_t l0 = flipped ? lo[k] ^ d.x_lo : lo[k], h0 = flipped ? hi[k] ^ d.x_hi : hi[k];
+      uint64_t l1 = l0 ^ d.x_lo, h1 = h0 ^ d.x_hi;
+      double2 a0 = r[k].o0, a1 = r[k].o1;
+      const uint64_t p1 = p + (k0[k] ? 1u : 0u);
+      const bool w0 = k0[k] && p < cap, w1 = k1[k] && p1 < cap;
+      if (NEXT) {
+        for (uint32_t q = 0; q < nx.run.ng; ++q) {
+          const MonoDesc g = sm.run.g[q];
+          ent::mono_step(g, WIDE, l0, h0, a0);
+          ent::mono_step(g, WIDE, l1, h1, a1);
+        }
+        // Partners written next to each other need no index (see k_u2_probe).
+        const bool index = !apart && !(k0[k] && k1[k] && (l0 ^ l1) == nx.d.x_lo && (!WIDE || (h0 ^ h1) == nx.d.x_hi));
+        claim[2 * k] = index_claim(ng, l0, h0, (uint32_t)p,
+                                   index && w0 && ent::ctrl_ok(nx.d, l0, h0, WIDE) &&
+                                       !ent::pivot_set(nx.d, l0, h0, WIDE));
+        claim[2 * k + 1] = index_claim(ng, l1, h1, (uint32_t)p1,
+                                       index && w1 && ent::ctrl_ok(nx.d, l1, h1, WIDE) &&
+                                           !ent::pivot_set(nx.d, l1, h1, WIDE));
+      }
+      if (w0) {
+        out.key_lo[p] = l0;
+        if (WIDE) out.key_hi[p] = h0;
+        out.amp[p] = a0;
+      }
+      if (w1) {
+        out.key_lo[p1] = l1;
+        if (WIDE) out.key_hi[p1] = h1;
+        out.amp[p1] = a1;
+      }
+    }
+    if (NEXT && !apart) {
+      // All first tries in flight together.
+      uint32_t old[2 * kItems];
+#pragma unroll
+      for (int k = 0; k < 2 * kItems; ++k) {
+        old[k] = kFreeSlot;
+        if (claim[k].wanted) old[k] = atomicCAS(&nx.tab.slots[claim[k].slot], kFreeSlot, claim[k].val);
+      }
+#pragma unroll
+      for (int k = 0; k < 2 * kItems; ++k) index_settle(nx.tab.slots, ng, claim[k], old[k]);
+    }
+    if (tiles <= gridDim.x) break;   // a tile for each block: no more to take
+    if (threadIdx.x == 0) sm.tile = atomicAdd(&ctl->ticket[par], 1u);
+    __syncthreads();
+    tile = sm.tile;
   }
+}
+
+// One code path per tile size, chosen by the entry count on the device (the
+// bound may be many times it): a small state's time is mostly latency, the
+// fetch of the kernel's code part of it, so each path is no longer than it
+// has to be (one path of four entries a thread for all sizes: 13 against 9 us
+// at 31,000 entries).
+template <bool WIDE, bool NEXT>
+__global__ __launch_bounds__(kU2Threads) void k_u2_fused(Buf in, Buf out, const uint64_t* __restrict__ nnz_p,
+                                                         const uint32_t* __restrict__ partner, U2Desc d, Ctl* ctl,
+                                                         const TabCtl* tc, uint64_t* status, uint32_t par,
+                                                         uint32_t epoch, uint64_t* nnz_out, uint64_t cap,
+                                                         uint32_t seq, NextGate nx) {
+  __shared__ U2Smem sm;
+  const uint64_t n = *nnz_p;
+#define SPARSESIM_U2_TILES(I) \
+  u2_tiles<WIDE, I, NEXT>(in, out, n, partner, d, ctl, tc, status, par, epoch, nnz_out, cap, seq, nx, sm)
+  if (n <= 256u * kU2Threads) SPARSESIM_U2_TILES(1);
+  else if (n <= 512u * kU2Threads) SPARSESIM_U2_TILES(2);
+  else SPARSESIM_U2_TILES(4);
+#undef SPARSESIM_U2_TILES
+}
+
+__global__ void k_u2_restore(Ctl* ctl, int cur) {
+  ctl->nnz[cur] = ctl->over_n;
+  ctl->over = 0;
+  ctl->error = 0;
+  for (int p = 0; p < 2; ++p)
+    for (StageCell& c : ctl->fst[p]) {
+      c.updates = c.pruned = 0;
+      c.mass = 0.0;
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -857,31 +1258,45 @@ void launch_mono(hipStream_t st, bool wide, Buf b, const uint64_t* nnz, const Mo
                        ctl);
 }
 
-void launch_index_build(hipStream_t st, bool wide, Buf b, const uint64_t* nnz, uint64_t* table, uint64_t mask,
-                        const U2Desc& d, uint32_t* partner, Ctl* ctl, int grid, int block) {
-  auto* t = reinterpret_cast<unsigned long long*>(table);
-  auto* count = ctl ? reinterpret_cast<unsigned long long*>(&ctl->ix[0]) : nullptr;
-  if (wide)
-    hipLaunchKernelGGL(k_index_build<true>, dim3(grid), dim3(block), 0, st, b, nnz, t, mask, d, partner, count);
-  else
-    hipLaunchKernelGGL(k_index_build<false>, dim3(grid), dim3(block), 0, st, b, nnz, t, mask, d, partner, count);
+void launch_index_build(hipStream_t st, bool wide, Buf b, const uint64_t* nnz, const IndexTab& t, const U2Desc& d,
+                        bool counting, const MonoRun& m, Ctl* ctl, uint64_t ub) {
+  auto* count = counting ? reinterpret_cast<unsigned long long*>(&ctl->ix[0]) : nullptr;
+  const int grid = (int)std::max<uint64_t>(1, std::min<uint64_t>((ub + 255) / 256, 4096));
+#define SPARSESIM_BUILD(W, M)                                                                                  \
+  hipLaunchKernelGGL((k_index_build<W, M>), dim3(grid), dim3(256), 0, st, b, nnz, t, d, count, m.g, m.ng, \
+                     m.run_flags, m.bytes_per_entry, ctl)
+  if (wide) {
+    if (m.ng) SPARSESIM_BUILD(true, true);
+    else SPARSESIM_BUILD(true, false);
+  } else {
+    if (m.ng) SPARSESIM_BUILD(false, true);
+    else SPARSESIM_BUILD(false, false);
+  }
+#undef SPARSESIM_BUILD
 }
 
-void launch_u2_probe(hipStream_t st, bool wide, Buf b, const uint64_t* nnz, const uint64_t* table, uint64_t mask,
-                     const U2Desc& d, uint32_t* partner, Ctl* ctl, int grid, int block) {
-  auto* count = ctl ? reinterpret_cast<unsigned long long*>(&ctl->ix[2]) : nullptr;
+void launch_u2_probe(hipStream_t st, bool wide, Buf b, const uint64_t* nnz, const IndexTab& t, const U2Desc& d,
+                     uint32_t* partner, uint32_t epoch, bool counting, Ctl* ctl, uint64_t ub) {
+  auto* count = counting ? reinterpret_cast<unsigned long long*>(&ctl->ix[2]) : nullptr;
+  // Two blocks a CU, whatever the bound: blocks that find no entries cost their launch.
+  const int block = ub <= 1ull << 16 ? 256 : 1024;
+  const int grid = (int)std::max<uint64_t>(1, std::min<uint64_t>((ub + block - 1) / block, 512));
   if (wide)
-    hipLaunchKernelGGL(k_u2_probe<true>, dim3(grid), dim3(block), 0, st, b, nnz, table, mask, d, partner, count);
+    hipLaunchKernelGGL(k_u2_probe<true>, dim3(grid), dim3(block), 0, st, b, nnz, t, d, partner, epoch, count);
   else
-    hipLaunchKernelGGL(k_u2_probe<false>, dim3(grid), dim3(block), 0, st, b, nnz, table, mask, d, partner, count);
+    hipLaunchKernelGGL(k_u2_probe<false>, dim3(grid), dim3(block), 0, st, b, nnz, t, d, partner, epoch, count);
+}
+
+void launch_index_empty(hipStream_t st, const IndexTab& t) {
+  hipLaunchKernelGGL(k_index_empty, dim3(1024), dim3(256), 0, st, t);
 }
 
 void launch_u2_count(hipStream_t st, bool wide, Buf b, const uint64_t* nnz, const U2Desc& d, const uint32_t* partner,
-                     uint32_t* tot, Ctl* ctl, int grid, int block) {
+                     uint32_t epoch, uint32_t* tot, Ctl* ctl, int grid, int block) {
   if (wide)
-    hipLaunchKernelGGL(k_u2_count<true>, dim3(grid), dim3(block), 0, st, b, nnz, d, partner, tot, ctl);
+    hipLaunchKernelGGL(k_u2_count<true>, dim3(grid), dim3(block), 0, st, b, nnz, d, partner, epoch, tot, ctl);
   else
-    hipLaunchKernelGGL(k_u2_count<false>, dim3(grid), dim3(block), 0, st, b, nnz, d, partner, tot, ctl);
+    hipLaunchKernelGGL(k_u2_count<false>, dim3(grid), dim3(block), 0, st, b, nnz, d, partner, epoch, tot, ctl);
 }
 
 void launch_scan(hipStream_t st, uint32_t* tot, int nblocks, uint64_t* nnz_out, Ctl* ctl, uint32_t entry_bytes,
@@ -890,29 +1305,33 @@ void launch_scan(hipStream_t st, uint32_t* tot, int nblocks, uint64_t* nnz_out, 
 }
 
 void launch_u2_write(hipStream_t st, bool wide, Buf in, Buf out, const uint64_t* nnz, const uint32_t* partner,
-                     const uint32_t* off, const U2Desc& d, Ctl* ctl, int grid, int block) {
+                     uint32_t epoch, const uint32_t* off, const U2Desc& d, Ctl* ctl, int grid, int block) {
   if (wide)
-    hipLaunchKernelGGL(k_u2_write<true>, dim3(grid), dim3(block), 0, st, in, out, nnz, partner, off, d, ctl);
+    hipLaunchKernelGGL(k_u2_write<true>, dim3(grid), dim3(block), 0, st, in, out, nnz, partner, epoch, off, d, ctl);
   else
-    hipLaunchKernelGGL(k_u2_write<false>, dim3(grid), dim3(block), 0, st, in, out, nnz, partner, off, d, ctl);
+    hipLaunchKernelGGL(k_u2_write<false>, dim3(grid), dim3(block), 0, st, in, out, nnz, partner, epoch, off, d, ctl);
 }
 
 void launch_u2_fused(hipStream_t st, bool wide, Buf in, Buf out, const uint64_t* nnz, const uint32_t* partner,
-                     const U2Desc& d, Ctl* ctl, uint64_t* status, uint32_t ticket_base, uint32_t epoch,
-                     uint64_t* nnz_out, uint64_t* table, uint64_t clear_slots, int grid, uint32_t tile) {
-#define SPARSESIM_U2F(W, I)                                                                                    \
-  hipLaunchKernelGGL((k_u2_fused<W, I>), dim3(grid), dim3(256), 0, st, in, out, nnz, partner, d, ctl, status, \
-                     ticket_base, epoch, nnz_out, table, clear_slots)
+                     const U2Desc& d, Ctl* ctl, const TabCtl* tc, uint64_t* status, uint32_t par, uint32_t epoch,
+                     uint64_t* nnz_out, uint64_t cap, uint32_t seq, const NextGate& next, uint64_t ub) {
+  // A block fills a CU (16 waves of up to 128 registers): more would only wait for a place.
+  const int grid = (int)std::max<uint64_t>(1, std::min<uint64_t>((ub + kU2Threads - 1) / kU2Threads, 256));
+#define SPARSESIM_U2F(W, N)                                                                                       \
+  hipLaunchKernelGGL((k_u2_fused<W, N>), dim3(grid), dim3(kU2Threads), 0, st, in, out, nnz, partner, d, ctl, tc, \
+                     status, par, epoch, nnz_out, cap, seq, next)
   if (wide) {
-    if (tile == 512) SPARSESIM_U2F(true, 2);
-    else if (tile == 1024) SPARSESIM_U2F(true, 4);
-    else SPARSESIM_U2F(true, 8);
+    if (next.tab.slots) SPARSESIM_U2F(true, true);
+    else SPARSESIM_U2F(true, false);
   } else {
-    if (tile == 512) SPARSESIM_U2F(false, 2);
-    else if (tile == 1024) SPARSESIM_U2F(false, 4);
-    else SPARSESIM_U2F(false, 8);
+    if (next.tab.slots) SPARSESIM_U2F(false, true);
+    else SPARSESIM_U2F(false, false);
   }
 #undef SPARSESIM_U2F
+}
+
+void launch_u2_restore(hipStream_t st, Ctl* ctl, int cur) {
+  hipLaunchKernelGGL(k_u2_restore, dim3(1), dim3(1), 0, st, ctl, cur);
 }
 
 void launch_u2_lds(hipStream_t st, bool wide, Buf in, Buf out, const uint64_t* nnz, const U2Desc& d, Ctl* ctl,
