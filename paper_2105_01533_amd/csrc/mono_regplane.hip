@@ -19,7 +19,7 @@ namespace {
 // reserved register.
 template <bool TURNS>
 __global__ __launch_bounds__(64, 2) __attribute__((amdgpu_num_vgpr(40))) void k_mono_rp(
-    Buf b, const uint64_t* __restrict__ nnz_p, const RpRec* __restrict__ prog, uint32_t nrec, BsRun run,
+    Buf b, const uint64_t* __restrict__ nnz_p, const RpBlock* __restrict__ prog, uint32_t nblk, BsRun run,
     Ctl* ctl) {
   static_assert(rp::kVmax == 230, "the clobber below names the highest plane register");
   asm volatile("" ::: "v230");
@@ -36,7 +36,7 @@ __global__ __launch_bounds__(64, 2) __attribute__((amdgpu_num_vgpr(40))) void k_
   const uint64_t base = (uint64_t)blockIdx.x * 2048;
   if (base >= n) return;
   const uint32_t lim = (uint32_t)(n - base < 2048 ? n - base : 2048);
-  rp::rp_tile<TURNS>(b, base, lim, prog, nrec, run, rp_acc, s_table);
+  rp::rp_tile<TURNS>(b, base, lim, prog, nblk, run, rp_acc, s_table);
 }
 #pragma clang diagnostic pop
 
@@ -74,7 +74,7 @@ hipError_t mono_rp_init() {
   return hipEventCreateWithFlags(&o.ev, hipEventDisableTiming);
 }
 
-void launch_mono_rp(hipStream_t st, Buf b, const uint64_t* nnz, const RpRec* p, uint32_t nrec, const BsRun& run,
+void launch_mono_rp(hipStream_t st, Buf b, const uint64_t* nnz, const RpBlock* p, uint32_t nblk, const BsRun& run,
                     Ctl* ctl, int grid) {
   RpOrder& o = rp_order();
   std::lock_guard<std::mutex> lk(o.mu);
@@ -83,9 +83,9 @@ void launch_mono_rp(hipStream_t st, Buf b, const uint64_t* nnz, const RpRec* p, 
   const bool ordered = cs == hipStreamCaptureStatusNone;
   if (ordered && o.ev && o.last != st) (void)hipStreamWaitEvent(st, o.ev, 0);
   if (run.has_turns)
-    hipLaunchKernelGGL(k_mono_rp<true>, dim3(grid), dim3(64), rp::kTurnAccBytes, st, b, nnz, p, nrec, run, ctl);
+    hipLaunchKernelGGL(k_mono_rp<true>, dim3(grid), dim3(64), rp::kTurnAccBytes, st, b, nnz, p, nblk, run, ctl);
   else
-    hipLaunchKernelGGL(k_mono_rp<false>, dim3(grid), dim3(64), 0, st, b, nnz, p, nrec, run, ctl);
+    hipLaunchKernelGGL(k_mono_rp<false>, dim3(grid), dim3(64), 0, st, b, nnz, p, nblk, run, ctl);
   if (ordered && o.ev && hipEventRecord(o.ev, st) == hipSuccess) o.last = st;
 }
 

@@ -7,30 +7,34 @@
 // is capped below v80 (amdgpu_num_vgpr), so it never allocates v80 and above,
 // and only the inline assembly here touches them.  A gate names its planes by
 // index at run time, so the plane registers are addressed with the GPR
-// indexing mode (s_set_gpr_idx_on / _idx: the index, the low byte of an SGPR,
-// is added to the register number of the instruction's src0 and, when
-// enabled, its vdst).  A CNOT on the tile is then three scalar and two vector
-// instructions, with no LDS round trip and no dependent-latency chain.
+// indexing mode (the low byte of M0 is added to the register number of the
+// operands that M0's bits 12-15 enable), with no LDS round trip.
 //
 // Register map (fixed, assembly only):
 //   v80        P  -- eighth-turn accumulator, weight 4 (one bit per entry)
 //   v81, v82   Q  -- weight-2 counter, 2 bits
 //   v83..v85   R  -- weight-1 counter, 3 bits
-//   v86, v87   temporaries; v88 load address; v89 = 16 x lane
-//   v90..v93   the program chunk in use, v94..v97 the next one
+//   v86..v94   temporaries; v95 prefetch address, v96 prefetch target
 //   v100 + q   plane q; plane nq is all ones, nq + 1 scratch, nq + 2 zero.
 // An eighth-turn op adding k where x holds adds x (k & 1) to R, x ((k >> 1) &
 // 1) to Q and x (k >> 2) to P, so the entry's count is R + 2 Q + 4 P mod 8.
 //
-// The program (RpRec quads, see sim_internal.h) is read 64 quads (1 KiB) at a
-// time with one vector load per lane (lane l holds quad l in v90..v93), the
-// next chunk always in flight, and broadcast with v_readlane: no scalar-cache
-// latency on the path.  Flip and eighth-turn segments run in one assembly
-// loop that reads each segment header and dispatches on its shape; turn and
-// general eighth-turn segments return to C++, which reads their quads through
-// the same chunk registers.  Arbitrary-angle phases (TURN) accumulate exact
-// 64-bit turn fractions per entry in LDS through a 16-entry subset-sum table
-// per group of four ops.
+// What bounds the pass is the latency of one wave's instruction stream: at
+// most two waves share a SIMD (the planes' registers), each in order.  So the
+// interpreter spends as few instructions as it can on each op.  Its program
+// (RpBlock, see sim_internal.h) is read with scalar loads, a 64-byte block
+// ahead into the SGPRs the current block does not use, and every operand field
+// is an index with its operand-enable bits in the form M0 holds them, so
+// that one scalar move or shift both unpacks and selects it: a CNOT is four
+// instructions, a Toffoli six.  A block holds ops of one shape; its first word
+// is the distance from the block handlers' base to the instruction that starts
+// with its first op, so a partly filled block runs no padding and a dispatch
+// is six instructions.  Read with v_readlane and padded to quads, the same
+// programs took 25 ns per CNOT, 31 per Toffoli and 102 per gate of adders (short
+// segments) of one wave; they take 11, 15 and 16 (2^16 entries).  Turn ops do
+// not break the stream either: their conditions are flipped into capture
+// planes and their fractions added eight at a time (random mix of 24 qubits: 68
+// ns per gate, 41 without the capture planes, 31 with them).
 #pragma once
 #include "sim_internal.h"
 
@@ -101,6 +105,21 @@ __device__ __forceinline__ void wr_plane(uint32_t q, uint32_t v) {
       : "m0");
 }
 
+// A capture plane's content; the plane is emptied.
+__device__ __forceinline__ uint32_t take_plane(uint32_t q) {
+  uint32_t r;
+  asm volatile(
+      "s_set_gpr_idx_on %1, gpr_idx(SRC0)\n\t"
+      "v_mov_b32 %0, v100\n\t"
+      "s_set_gpr_idx_on %1, gpr_idx(DST)\n\t"
+      "v_mov_b32 v100, 0\n\t"
+      "s_set_gpr_idx_off"
+      : "=&v"(r)
+      : "s"(q)
+      : "m0");
+  return r;
+}
+
 #define RP_IN(R, X) asm volatile("v_mov_b32 v" #R ", %0" ::"v"(X))
 #define RP_OUT(R, X) asm volatile("v_mov_b32 %0, v" #R : "=v"(X))
 #define RP_IN_WORD0(a) \
@@ -161,192 +180,198 @@ __device__ __forceinline__ v4i buf_rsrc_v4(const void* p, uint32_t n) {
   return r;
 }
 
-// ---- program fetch -----------------------------------------------------------
-// Next quad: the four words of quad `lane` of the current chunk, then advance;
-// past the chunk's last quad the prefetched chunk becomes current and the one
-// after it is requested (at byte offset off of the program, then off += 1 KiB).
-// The program resource returns zeros past its end: an END header.
-#define RP_NEXTQ                                  \
-  "s_add_u32 %[lane], %[lane], 1\n\t"             \
-  "s_cmp_eq_u32 %[lane], 64\n\t"                  \
-  "s_cbranch_scc0 8f\n\t"                         \
-  "s_waitcnt vmcnt(0)\n\t"                        \
-  "v_mov_b32 v90, v94\n\t"                        \
-  "v_mov_b32 v91, v95\n\t"                        \
-  "v_mov_b32 v92, v96\n\t"                        \
-  "v_mov_b32 v93, v97\n\t"                        \
-  "v_add_u32 v88, %[off], v89\n\t"                \
-  "buffer_load_dwordx4 v[94:97], v88, %[rs], 0 offen\n\t" \
-  "s_add_u32 %[off], %[off], 1024\n\t"            \
-  "s_mov_b32 %[lane], 0\n"                        \
-  "8:\n\t"
-// Read a quad into s92..s95 (GPR indexing must be off: v_readlane's source is
-// a VGPR operand).
-#define RP_READQ                                  \
-  "s_set_gpr_idx_off\n\t"                         \
-  "v_readlane_b32 s92, v90, %[lane]\n\t"          \
-  "v_readlane_b32 s93, v91, %[lane]\n\t"          \
-  "v_readlane_b32 s94, v92, %[lane]\n\t"          \
-  "v_readlane_b32 s95, v93, %[lane]\n\t" RP_NEXTQ
+// ---- the interpreter ---------------------------------------------------------
+// Buffers of two blocks: A = s48..s63, B = s64..s79; s80:s81 and s82:s83 are
+// the handlers' bases for a block in A and in B, s84:s85 a handler's address.
+// Fields: bits 0-7 index from v80, bits 12-15 operand enables (1 source 0, 9
+// source 0 and destination); a field is the low or the high half of a word.
+#define RP_LO(W) "s_mov_b32 m0, " W "\n\t"
+#define RP_HI(W) "s_lshr_b32 m0, " W ", 16\n\t"
+#define RP_GET "v_mov_b32_e32 v86, v80\n\t"
+#define RP_AND "v_and_b32_e32 v86, v80, v86\n\t"
+#define RP_XOR "v_xor_b32_e32 v80, v80, v86\n\t"
+// Flips with one, two and three controls: 16, 24 and 32 bytes of code.
+#define RP_F1(W) RP_LO(W) RP_GET RP_HI(W) RP_XOR
+#define RP_F2E(W0, W1) RP_LO(W0) RP_GET RP_HI(W0) RP_AND RP_LO(W1) RP_XOR
+#define RP_F2O(W0, W1) RP_HI(W0) RP_GET RP_LO(W1) RP_AND RP_HI(W1) RP_XOR
+#define RP_F3(W0, W1) RP_LO(W0) RP_GET RP_HI(W0) RP_AND RP_LO(W1) RP_AND RP_HI(W1) RP_XOR
+// Four weight-1 adds at once, by full adders (bitop3 0xe8 majority, 0x96 sum,
+// 0x6a = S2 ^ (S0 & S1), bits indexed S0 * 4 + S1 * 2 + S2): 88 bytes.
+#define RP_T4(W0, W1)                                                                               \
+  RP_LO(W0) "v_mov_b32_e32 v86, v80\n\t" RP_HI(W0) "v_mov_b32_e32 v87, v80\n\t"                 \
+  RP_LO(W1) "v_mov_b32_e32 v90, v80\n\t" RP_HI(W1) "v_mov_b32_e32 v91, v80\n\t"                 \
+  "s_mov_b32 m0, 0\n\t"                                                                           \
+  "v_bitop3_b32 v92, v83, v86, v87 bitop3:0xe8\n\tv_bitop3_b32 v83, v83, v86, v87 bitop3:0x96\n\t" \
+  "v_bitop3_b32 v93, v83, v90, v91 bitop3:0xe8\n\tv_bitop3_b32 v83, v83, v90, v91 bitop3:0x96\n\t" \
+  "v_bitop3_b32 v94, v84, v92, v93 bitop3:0xe8\n\tv_bitop3_b32 v84, v84, v92, v93 bitop3:0x96\n\t" \
+  "v_xor_b32_e32 v85, v85, v94\n\t"
+// A weight-2 add (16 bytes).
+#define RP_S(W) RP_LO(W) "v_bitop3_b32 v82, v80, v81, v82 bitop3:0x6a\n\tv_xor_b32_e32 v81, v80, v81\n\t"
 
-// ---- op bodies -------------------------------------------------------------
-// Op words: t | c0 << 8 | c1 << 16 | c2 << 24 (flips), t (eighth turns).
-// s_set_gpr_idx_* use the low byte of the named SGPR as the plane index, so
-// a right shift by 8 k selects field k.
-#define RP_F1(W)                                  \
-  "s_lshr_b32 s96, " W ", 8\n\t"                  \
-  "s_set_gpr_idx_on s96, gpr_idx(SRC0)\n\t"       \
-  "v_mov_b32 v86, v100\n\t"                       \
-  "s_set_gpr_idx_on " W ", gpr_idx(SRC0,DST)\n\t" \
-  "v_xor_b32 v100, v100, v86\n\t"
-#define RP_F2(W)                                  \
-  "s_lshr_b32 s96, " W ", 8\n\t"                  \
-  "s_lshr_b32 s97, " W ", 16\n\t"                 \
-  "s_set_gpr_idx_on s96, gpr_idx(SRC0)\n\t"       \
-  "v_mov_b32 v86, v100\n\t"                       \
-  "s_set_gpr_idx_idx s97\n\t"                     \
-  "v_and_b32 v86, v100, v86\n\t"                  \
-  "s_set_gpr_idx_on " W ", gpr_idx(SRC0,DST)\n\t" \
-  "v_xor_b32 v100, v100, v86\n\t"
-#define RP_F3(W)                                  \
-  "s_lshr_b32 s96, " W ", 8\n\t"                  \
-  "s_lshr_b32 s97, " W ", 16\n\t"                 \
-  "s_set_gpr_idx_on s96, gpr_idx(SRC0)\n\t"       \
-  "v_mov_b32 v86, v100\n\t"                       \
-  "s_set_gpr_idx_idx s97\n\t"                     \
-  "v_and_b32 v86, v100, v86\n\t"                  \
-  "s_lshr_b32 s97, " W ", 24\n\t"                 \
-  "s_set_gpr_idx_idx s97\n\t"                     \
-  "v_and_b32 v86, v100, v86\n\t"                  \
-  "s_set_gpr_idx_on " W ", gpr_idx(SRC0,DST)\n\t" \
-  "v_xor_b32 v100, v100, v86\n\t"
-// Eighth-turn adds of x = plane t (v100 under SRC0 indexing).  bitop3 truth
-// tables index bits as S0 * 4 + S1 * 2 + S2: 0x6a = S2 ^ (S0 & S1), 0x78 =
-// S0 ^ (S1 & S2).
-#define RP_ADD_P "v_xor_b32 v80, v100, v80\n\t"
-#define RP_ADD_Q "v_bitop3_b32 v82, v100, v81, v82 bitop3:0x6a\n\tv_xor_b32 v81, v100, v81\n\t"
-#define RP_ADD_R1 "v_and_b32 v86, v100, v83\n\tv_xor_b32 v83, v100, v83\n\t"
-#define RP_ADD_R2 "s_set_gpr_idx_off\n\tv_bitop3_b32 v85, v85, v84, v86 bitop3:0x78\n\tv_xor_b32 v84, v84, v86\n\t"
-#define RP_ON(W) "s_set_gpr_idx_on " W ", gpr_idx(SRC0)\n\t"
-#define RP_OB1(W) RP_ON(W) RP_ADD_R1 RP_ADD_R2
-#define RP_OB2(W) RP_ON(W) RP_ADD_Q
-#define RP_OB3(W) RP_ON(W) RP_ADD_R1 RP_ADD_Q RP_ADD_R2
-#define RP_OB4(W) RP_ON(W) RP_ADD_P
-#define RP_OB5(W) RP_ON(W) RP_ADD_R1 RP_ADD_P RP_ADD_R2
-#define RP_OB6(W) RP_ON(W) RP_ADD_Q RP_ADD_P
-#define RP_OB7(W) RP_ON(W) RP_ADD_R1 RP_ADD_Q RP_ADD_P RP_ADD_R2
+// The next block (in the other buffer, header H, handlers' base BASE) once it
+// is there; the one after it is loaded over this one (REGS).
+#define RP_NEXT(REGS, H, BLO, BHI)                          \
+  "s_waitcnt lgkmcnt(0)\n\t"                              \
+  "s_buffer_load_dwordx16 " REGS ", %[rs], %[off]\n\t"    \
+  "s_add_u32 %[off], %[off], 64\n\t"                      \
+  "s_add_u32 s84, " BLO ", " H "\n\t"                     \
+  "s_addc_u32 s85, " BHI ", 0\n\t"                        \
+  "s_setpc_b64 s[84:85]\n\t"
+#define RP_GO_A RP_NEXT("s[64:79]", "s48", "s80", "s81")
+#define RP_GO_B RP_NEXT("s[48:63]", "s64", "s82", "s83")
 
-// A segment loop at label L: each quad is four ops of one shape; count
-// quads, then back to the header reader (label 20).
-#define RP_SEG(L, OP)                             \
-  #L ":\n\t" RP_READQ OP("s92") OP("s93") OP("s94") OP("s95") \
-  "s_sub_u32 %[cnt], %[cnt], 1\n\t"               \
-  "s_cmp_eq_u32 %[cnt], 0\n\t"                    \
-  "s_cbranch_scc0 " #L "b\n\t"                    \
-  "s_branch 20b\n"
-#define RP_CASE(SHAPE, L) "s_cmp_eq_u32 %[shape], " #SHAPE "\n\ts_cbranch_scc1 " #L "f\n\t"
+// The handlers of one buffer (words R0..R15), kRpStride bytes apart, in the
+// order of the shapes.
+#define RP_HANDLERS(GO, R0, R1, R2, R3, R4, R5, R6, R7, R8, R9, R10, R11, R12, R13, R14, R15)                     \
+  "s_mov_b32 %[shape], " R1 "\n\ts_mov_b32 %[cnt], " R2 "\n\ts_branch 9f\n\t"                                  \
+  ".p2align 10\n\t"                                                                                              \
+  RP_F1(R1) RP_F1(R2) RP_F1(R3) RP_F1(R4) RP_F1(R5) RP_F1(R6) RP_F1(R7) RP_F1(R8) RP_F1(R9) RP_F1(R10) RP_F1(R11) \
+  RP_F1(R12) RP_F1(R13) RP_F1(R14) RP_F1(R15) GO                                                                  \
+  ".p2align 10\n\t"                                                                                              \
+  RP_F2E(R1, R2) RP_F2O(R2, R3) RP_F2E(R4, R5) RP_F2O(R5, R6) RP_F2E(R7, R8) RP_F2O(R8, R9) RP_F2E(R10, R11)     \
+  RP_F2O(R11, R12) RP_F2E(R13, R14) RP_F2O(R14, R15) GO                                                          \
+  ".p2align 10\n\t"                                                                                              \
+  RP_F3(R2, R3) RP_F3(R4, R5) RP_F3(R6, R7) RP_F3(R8, R9) RP_F3(R10, R11) RP_F3(R12, R13) RP_F3(R14, R15) GO     \
+  ".p2align 10\n\t"                                                                                              \
+  RP_T4(R2, R3) RP_T4(R4, R5) RP_T4(R6, R7) RP_T4(R8, R9) RP_T4(R10, R11) RP_T4(R12, R13) RP_T4(R14, R15) GO     \
+  ".p2align 10\n\t"                                                                                              \
+  RP_S(R1) RP_S(R2) RP_S(R3) RP_S(R4) RP_S(R5) RP_S(R6) RP_S(R7) RP_S(R8) RP_S(R9) RP_S(R10) RP_S(R11) RP_S(R12)  \
+  RP_S(R13) RP_S(R14) RP_S(R15) GO
 
-// The interpreter: header quads (w0 = shape | quads << 8) and the segments of
-// flips and eighth turns, until a header of another shape (returned in shape,
-// with cnt) is read.
-#define RP_INTERP                                 \
-  "20:\n\t"                                       \
-  "s_set_gpr_idx_off\n\t"                         \
-  "v_readlane_b32 s92, v90, %[lane]\n\t" RP_NEXTQ \
-  "s_and_b32 %[shape], s92, 0xff\n\t"             \
-  "s_lshr_b32 %[cnt], s92, 8\n\t"                 \
-  RP_CASE(1, 21) RP_CASE(2, 22) RP_CASE(3, 23)    \
-  RP_CASE(9, 31) RP_CASE(10, 32) RP_CASE(11, 33) RP_CASE(12, 34) RP_CASE(13, 35) RP_CASE(14, 36) RP_CASE(15, 37) \
-  "s_branch 40f\n"                                \
-  RP_SEG(21, RP_F1) RP_SEG(22, RP_F2) RP_SEG(23, RP_F3)                  \
-  RP_SEG(31, RP_OB1) RP_SEG(32, RP_OB2) RP_SEG(33, RP_OB3) RP_SEG(34, RP_OB4) \
-  RP_SEG(35, RP_OB5) RP_SEG(36, RP_OB6) RP_SEG(37, RP_OB7)             \
-  "40:\n\t"                                       \
-  "s_set_gpr_idx_off"
+static_assert(kRpStride == 1024, "the .p2align of the handlers");
 
 struct Fetch {
-  uint32_t lane, off;
-  v4i rs;
+  uint32_t off;   // byte offset of the next block
+  v4i rs;         // the program: loads past its end return zeros, an END block
 };
 
-// Load chunks 0 and 1 of the program; v89 = 16 x lane.
-__device__ __forceinline__ void fetch_start(Fetch& f, const RpRec* prog, uint32_t nrec, int lane) {
-  f.rs = buf_rsrc_v4(prog, 16u * nrec);
-  f.lane = 0;
-  f.off = 2048;
+// Run blocks from f.off on until one that the caller does itself: its shape
+// and count, with f.off at the block after it.
+__device__ __forceinline__ void interpret(Fetch& f, uint32_t& shape, uint32_t& cnt) {
   asm volatile(
-      "v_lshlrev_b32 v89, 4, %[id]\n\t"
-      "buffer_load_dwordx4 v[90:93], v89, %[rs], 0 offen\n\t"
-      "v_add_u32 v88, 1024, v89\n\t"
-      "buffer_load_dwordx4 v[94:97], v88, %[rs], 0 offen\n\t"
-      "s_waitcnt vmcnt(0)" ::[id] "v"(lane),
-      [rs] "s"(f.rs)
-      : "memory");
-}
-
-__device__ __forceinline__ void next_quad(Fetch& f, uint32_t (&w)[4]) {
-  asm volatile(
+      "s_getpc_b64 s[80:81]\n"
+      "1:\n\t"
+      "s_add_u32 s80, s80, 2f-1b\n\t"
+      "s_addc_u32 s81, s81, 0\n\t"
+      "s_add_u32 s82, s80, 3f-2f\n\t"
+      "s_addc_u32 s83, s81, 0\n\t"
+      "s_buffer_load_dwordx16 s[48:63], %[rs], %[off]\n\t"
+      "s_add_u32 %[off], %[off], 64\n\t"
+      "s_set_gpr_idx_on s80, gpr_idx()\n\t"   // no operand enabled until a field says so
+      RP_GO_A
+      ".p2align 10\n"
+      "2:\n\t"
+      RP_HANDLERS(RP_GO_B, "s48", "s49", "s50", "s51", "s52", "s53", "s54", "s55", "s56", "s57", "s58", "s59", "s60",
+                  "s61", "s62", "s63")
+      ".p2align 10\n"
+      "3:\n\t"
+      RP_HANDLERS(RP_GO_A, "s64", "s65", "s66", "s67", "s68", "s69", "s70", "s71", "s72", "s73", "s74", "s75", "s76",
+                  "s77", "s78", "s79")
+      "9:\n\t"
+      "s_waitcnt lgkmcnt(0)\n\t"   // the load of the block after next
       "s_set_gpr_idx_off\n\t"
-      "v_readlane_b32 %[w0], v90, %[lane]\n\t"
-      "v_readlane_b32 %[w1], v91, %[lane]\n\t"
-      "v_readlane_b32 %[w2], v92, %[lane]\n\t"
-      "v_readlane_b32 %[w3], v93, %[lane]\n\t" RP_NEXTQ
-      : [w0] "=&s"(w[0]), [w1] "=&s"(w[1]), [w2] "=&s"(w[2]), [w3] "=&s"(w[3]), [lane] "+s"(f.lane),
-        [off] "+s"(f.off)
+      "s_sub_u32 %[off], %[off], 64"
+      : [off] "+s"(f.off), [shape] "=&s"(shape), [cnt] "=&s"(cnt)
       : [rs] "s"(f.rs)
-      : "m0", "scc", "memory");
+      : "s48", "s49", "s50", "s51", "s52", "s53", "s54", "s55", "s56", "s57", "s58", "s59", "s60", "s61", "s62",
+        "s63", "s64", "s65", "s66", "s67", "s68", "s69", "s70", "s71", "s72", "s73", "s74", "s75", "s76", "s77",
+        "s78", "s79", "s80", "s81", "s82", "s83", "s84", "s85", "m0", "scc", "memory");
 }
 
-// General eighth-turn ops, two per quad (cond word, k): x = planes t & c0 &
-// c1 & c2, then the weighted adds with k's bits as masks.
-__device__ __forceinline__ void omega_general(Fetch& f, uint32_t nquads) {
-  for (uint32_t i = 0; i < nquads; ++i) {
-    uint32_t w[4];
-    next_quad(f, w);
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const uint32_t c = w[2 * h], k = w[2 * h + 1];
-      const uint32_t x = rd_plane(c) & rd_plane(c >> 8) & rd_plane(c >> 16) & rd_plane(c >> 24);
-      const uint32_t m1 = (k & 1u) ? ~0u : 0u, m2 = (k & 2u) ? ~0u : 0u, m4 = (k & 4u) ? ~0u : 0u;
-      asm volatile(
-          "v_bitop3_b32 v80, %0, %3, v80 bitop3:0x6a\n\t"   // P ^= x & m4
-          "v_and_b32 v86, %2, %0\n\t"
-          "v_bitop3_b32 v82, v82, v81, v86 bitop3:0x78\n\t" // Q += x & m2
-          "v_xor_b32 v81, v81, v86\n\t"
-          "v_and_b32 v86, %1, %0\n\t"
-          "v_and_b32 v87, v83, v86\n\t"                      // R += x & m1
-          "v_xor_b32 v83, v83, v86\n\t"
-          "v_bitop3_b32 v85, v85, v84, v87 bitop3:0x78\n\t"
-          "v_xor_b32 v84, v84, v87" ::"v"(x),
-          "s"(m1), "s"(m2), "s"(m4));
-    }
+// The first waves of a launch bring the program into their XCD's L2: read by
+// the scalar loads alone, each line's first touch would cost its latency.
+__device__ __forceinline__ void prefetch_program(const Fetch& f, uint32_t bytes, int lane) {
+  for (uint32_t o = 0; o < bytes; o += 64 * 64) {
+    asm volatile(
+        "v_lshl_add_u32 v95, %[lane], 6, %[o]\n\t"
+        "buffer_load_dword v96, v95, %[rs], 0 offen" ::[lane] "v"(lane),
+        [o] "s"(o), [rs] "s"(f.rs)
+        : "memory");
   }
 }
 
-// TURN groups: three quads per group of four ops (cond words; fractions of
-// ops 0, 1; of ops 2, 3).  Each entry's accumulator (LDS, acc[64 j + lane])
+// Words of the program at byte offset off, wave-uniform (scalar loads).
+typedef uint32_t v2u __attribute__((ext_vector_type(2)));
+typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+typedef uint32_t v8u __attribute__((ext_vector_type(8)));
+__device__ __forceinline__ v2u words2(const Fetch& f, uint32_t off) {
+  v2u r;
+  asm volatile("s_buffer_load_dwordx2 %0, %1, %2\n\ts_waitcnt lgkmcnt(0)" : "=&s"(r) : "s"(f.rs), "s"(off));
+  return r;
+}
+// A turn group: cond words, fractions (words 0-3 and 4-11 of its block).
+struct TurnWords {
+  v4u cond;
+  v8u tau;
+};
+__device__ __forceinline__ v8u words8(const Fetch& f, uint32_t off) {
+  v8u r;
+  asm volatile("s_buffer_load_dwordx8 %0, %1, %2\n\ts_waitcnt lgkmcnt(0)" : "=&s"(r) : "s"(f.rs), "s"(off));
+  return r;
+}
+__device__ __forceinline__ TurnWords turn_words(const Fetch& f, uint32_t off) {
+  TurnWords r;
+  asm volatile("s_buffer_load_dwordx4 %0, %2, %3\n\ts_buffer_load_dwordx8 %1, %2, %4\n\ts_waitcnt lgkmcnt(0)"
+               : "=&s"(r.cond), "=&s"(r.tau)
+               : "s"(f.rs), "s"(off), "s"(off + 16u));
+  return r;
+}
+
+// General eighth-turn ops, two per quad (cond word, k), from f.off on: x =
+// planes t & c0 & c1 & c2, then the weighted adds with k's bits as masks.
+__device__ __forceinline__ void omega_general(const Fetch& f, uint32_t nquads) {
+  for (uint32_t i = 0; i < 2 * nquads; ++i) {
+    const v2u ck = words2(f, f.off + 8u * i);
+    const uint32_t c = ck.x, k = ck.y;
+    const uint32_t x = rd_plane(c) & rd_plane(c >> 8) & rd_plane(c >> 16) & rd_plane(c >> 24);
+    const uint32_t m1 = (k & 1u) ? ~0u : 0u, m2 = (k & 2u) ? ~0u : 0u, m4 = (k & 4u) ? ~0u : 0u;
+    asm volatile(
+        "v_bitop3_b32 v80, %0, %3, v80 bitop3:0x6a\n\t"   // P ^= x & m4
+        "v_and_b32 v86, %2, %0\n\t"
+        "v_bitop3_b32 v82, v82, v81, v86 bitop3:0x78\n\t" // Q += x & m2
+        "v_xor_b32 v81, v81, v86\n\t"
+        "v_and_b32 v86, %1, %0\n\t"
+        "v_and_b32 v87, v83, v86\n\t"                      // R += x & m1
+        "v_xor_b32 v83, v83, v86\n\t"
+        "v_bitop3_b32 v85, v85, v84, v87 bitop3:0x78\n\t"
+        "v_xor_b32 v84, v84, v87" ::"v"(x),
+        "s"(m1), "s"(m2), "s"(m4));
+  }
+}
+
+// TURN groups: a block per group of four ops (cond words; then the fractions of
+// ops 0..3).  Each entry's accumulator (LDS, acc[64 j + lane])
 // gains the sum of the fractions of the ops whose condition holds for it: per
 // group, one of 16 subset sums, kept in a 16-entry LDS table and read with
 // one 64-bit load per entry.  C groups share one read-modify-write of the
 // accumulators (C tables side by side), which is what bounds the pass on
 // LDS bandwidth.
-template <bool BARE, int C>
-__device__ __forceinline__ void turn_chunk(Fetch& f, uint64_t* acc, uint64_t* table, int lane) {
+// FORM: kRpTB (condition = one plane), kRpTG (four) or kRpTC (captured planes
+// from plane `first` on; the fractions alone, four to 32 bytes).
+template <uint32_t FORM, int C>
+__device__ __forceinline__ void turn_chunk(const Fetch& f, uint32_t off, uint32_t first, uint64_t* acc, uint64_t* table,
+                                           int lane) {
   uint32_t B[C][8];
 #pragma unroll
   for (int c = 0; c < C; ++c) {
-    uint32_t cw[4], t01[4], t23[4];
-    next_quad(f, cw);
-    next_quad(f, t01);
-    next_quad(f, t23);
+    TurnWords tw;
     uint32_t x[4];
+    if (FORM == kRpTC) {
+      tw.tau = words8(f, off + 32u * c);
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      x[u] = rd_plane(cw[u]);
-      if (!BARE) x[u] &= rd_plane(cw[u] >> 8) & rd_plane(cw[u] >> 16) & rd_plane(cw[u] >> 24);
+      for (int u = 0; u < 4; ++u) x[u] = take_plane(first + 4 * c + u);
+    } else {
+      tw = turn_words(f, off + 64u * c);
+      const uint32_t cw[4] = {tw.cond.x, tw.cond.y, tw.cond.z, tw.cond.w};
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        x[u] = rd_plane(cw[u]);
+        if (FORM == kRpTG) x[u] &= rd_plane(cw[u] >> 8) & rd_plane(cw[u] >> 16) & rd_plane(cw[u] >> 24);
+      }
     }
-    const uint64_t tau[4] = {((uint64_t)t01[1] << 32) | t01[0], ((uint64_t)t01[3] << 32) | t01[2],
-                             ((uint64_t)t23[1] << 32) | t23[0], ((uint64_t)t23[3] << 32) | t23[2]};
+    uint64_t tau[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) tau[u] = ((uint64_t)tw.tau[2 * u + 1] << 32) | tw.tau[2 * u];
     // Entry j's offset in table c, 8 x (the ops, bit u = op u, whose
     // condition holds for it), is byte j >> 3 of B[c][j & 7]: bit j of x[u]
     // moves to bit 8 (j >> 3) + 3 + u by one constant shift; the four merge
@@ -398,11 +423,10 @@ __device__ __forceinline__ void turn_chunk(Fetch& f, uint64_t* acc, uint64_t* ta
   }
 }
 
-template <bool BARE>
-__device__ __forceinline__ void turn_groups(Fetch& f, uint32_t ng, uint64_t* acc, uint64_t* table, int lane) {
-  uint32_t g = 0;
-  for (; g + 2 <= ng; g += 2) turn_chunk<BARE, 2>(f, acc, table, lane);
-  if (g < ng) turn_chunk<BARE, 1>(f, acc, table, lane);
+// (programs on too many qubits for capture planes, and ops under four planes)
+template <uint32_t FORM>
+__device__ __forceinline__ void turn_groups(const Fetch& f, uint32_t ng, uint64_t* acc, uint64_t* table, int lane) {
+  for (uint32_t g = 0; g < ng; ++g) turn_chunk<FORM, 1>(f, f.off + 64u * g, 0, acc, table, lane);
 }
 
 // Labels of the tile (word w of each label: bits 32w..32w+31) into planes.
@@ -436,13 +460,13 @@ __device__ __forceinline__ void store_word(const Buf& b, uint64_t base, uint32_t
   for (int j = 0; j < 32; ++j) __builtin_amdgcn_raw_buffer_store_b32(a[j], rs, off, 512 * j, 0);
 }
 
-// Apply a run's program (nrec records) to the tile at base (lim valid
+// Apply a run's program (nblk blocks) to the tile at base (lim valid
 // entries).  TURNS: the kernel provides acc, the wave's turn accumulators in
 // LDS, and table, its subset-sum tables; a run uses them if it has turn ops
 // (the result does not depend on TURNS otherwise).
 template <bool TURNS>
-__device__ __forceinline__ void rp_tile(const Buf& b, uint64_t base, uint32_t lim, const RpRec* prog, uint32_t nrec,
-                                        const BsRun& run, uint64_t* acc, uint64_t* table) {
+__device__ __forceinline__ void rp_tile(const Buf& b, uint64_t base, uint32_t lim,
+                                        const RpBlock* __restrict__ prog, uint32_t nblk, const BsRun& run, uint64_t* acc, uint64_t* table) {
   // The lane number, opaque to the optimizer: values derived from it are
   // formed where used, not kept live across a kernel's loop over tiles.
   int lane = threadIdx.x;
@@ -451,12 +475,16 @@ __device__ __forceinline__ void rp_tile(const Buf& b, uint64_t base, uint32_t li
   const bool turns = TURNS && run.has_turns;
   const uint32_t rw = run.words_read | run.words_write;
   Fetch f;
-  fetch_start(f, prog, nrec, lane);
+  f.rs = buf_rsrc_v4(prog, 64u * nblk);
+  f.off = 0;
+  if (blockIdx.x < 64) prefetch_program(f, 64u * nblk, lane);   // eight waves an XCD
 #pragma unroll
   for (int w = 0; w < 4; ++w)
     if (rw & (1u << w)) load_word(b, base, lim, w, lane);
   wr_plane(nq, ~0u);       // all ones
   wr_plane(nq + 2, 0u);    // zero
+  if (turns)
+    for (uint32_t q = 0; q < rp_capture_planes(nq); ++q) wr_plane(nq + 3 + q, 0u);
   asm volatile(
       "v_mov_b32 v80, 0\n\tv_mov_b32 v81, 0\n\tv_mov_b32 v82, 0\n\t"
       "v_mov_b32 v83, 0\n\tv_mov_b32 v84, 0\n\tv_mov_b32 v85, 0");
@@ -466,24 +494,26 @@ __device__ __forceinline__ void rp_tile(const Buf& b, uint64_t base, uint32_t li
   }
   for (;;) {
     uint32_t shape, cnt;
-    asm volatile(RP_INTERP
-                 : [lane] "+s"(f.lane), [off] "+s"(f.off), [shape] "=&s"(shape), [cnt] "=&s"(cnt)
-                 : [rs] "s"(f.rs)
-                 : "s92", "s93", "s94", "s95", "s96", "s97", "m0", "scc", "memory");
+    interpret(f, shape, cnt);
     if (shape == kRpOG) {
       omega_general(f, cnt);
-    } else if (shape == kRpTB || shape == kRpTG) {
-      if (turns) {
-        if (shape == kRpTB) turn_groups<true>(f, cnt, acc, table, lane);
-        else turn_groups<false>(f, cnt, acc, table, lane);
+      f.off += 64u * ((cnt + 3) / 4);
+    } else if (shape == kRpTC || shape == kRpTB || shape == kRpTG) {
+      if (!turns) break;   // the host never sends turn ops to this variant
+      if (shape == kRpTC) {
+        for (uint32_t g = 0; g < cnt; ++g)
+          turn_chunk<kRpTC, 2>(f, f.off + 64u * g, nq + 3 + 8 * g, acc, table, lane);
+      } else if (shape == kRpTB) {
+        turn_groups<kRpTB>(f, cnt, acc, table, lane);
       } else {
-        break;   // the host never sends turn ops to this variant
+        turn_groups<kRpTG>(f, cnt, acc, table, lane);
       }
+      f.off += 64u * cnt;
     } else {
       break;   // END (zero words past the program) or an unknown shape
     }
   }
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the last prefetch
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the prefetch
   // Labels back to memory (only words some gate flips).
 #pragma unroll
   for (int w = 0; w < 4; ++w)

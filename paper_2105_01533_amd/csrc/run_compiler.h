@@ -63,6 +63,15 @@ struct RunCompiler {
   void schedule(size_t begin, size_t len, std::vector<RpRec>& out, BsRun* br) const;
   // Segments of n bit-sliced ops, appended to out.
   void schedule_range(const BsOp* src, uint32_t n, std::vector<RpRec>& out) const;
+  // The same packed into the blocks the kernel reads, an END block at the end.
+  void program(size_t begin, size_t len, std::vector<RpBlock>& out, BsRun* br) const;
+  // Blocks of a scheduled program (nq: qubits).
+  static void encode_program(const std::vector<RpRec>& recs, uint32_t nq, std::vector<RpBlock>& out);
+  // Blocks the program of n_gates MONO ops may take at most: a controlled gate
+  // is two phase ops of two blocks each and a flip, an uncontrolled one three
+  // blocks of adds and a flip; each gate leaves at most one uncontrolled X to
+  // apply later; an END block.
+  static size_t rp_blocks_bound(size_t n_gates, uint32_t nq) { return 6 * n_gates + nq + 1; }
   // Records the program of n_ops bit-sliced ops on nq qubits may take at most
   // (the rewrite of uncontrolled X gates at most doubles the ops and adds nq;
   // a segment adds a header and up to three padding ops).

@@ -655,4 +655,241 @@ void RunCompiler::schedule_range(const BsOp* src, uint32_t n, std::vector<RpRec>
   }
 }
 
+// ---- blocks of a register-plane program ---------------------------------------
+namespace {
+
+// A flip as the blocks hold it: fields of the controls and of the target.
+struct Flip {
+  uint16_t c[3], t;
+  uint8_t nc;
+};
+
+class BlockWriter {
+ public:
+  BlockWriter(uint32_t nq, std::vector<RpBlock>& out) : nq_(nq), out_(out) {}
+
+  uint32_t src(uint32_t q) const { return kRpSrc | (kRpPlane0 + q); }
+  void flip(const Flip& f) { flips_.push_back(f); }
+  uint32_t ones() const { return src(nq_); }
+
+  // The pending flips, in order, as blocks of the cheapest shapes: an op may
+  // sit in a block of a shape with more controls (the all-ones plane fills
+  // the others), which costs more than its own shape but less than a block of
+  // its own.  Costs are clocks of one wave: an instruction issues every 4.6,
+  // a dispatch takes 65.
+  void flush_flips() {
+    const size_t n = flips_.size();
+    if (!n) return;
+    constexpr uint32_t kBlock = 65, kOp[3] = {18, 28, 37}, kSlots[3] = {15, 10, 7};
+    from_.resize(3 * n);
+    uint32_t best[3] = {kBlock, kBlock, kBlock};   // cost of the ops so far, the last of them in shape k
+    for (size_t i = 0; i < n; ++i) {
+      uint32_t next[3];
+      for (uint32_t k = 0; k < 3; ++k) {
+        next[k] = UINT32_MAX / 2;
+        if (flips_[i].nc > k + 1u) continue;
+        for (uint32_t j = 0; j < 3; ++j) {
+          const uint32_t c = best[j] + (i && j != k ? kBlock : 0u) + kOp[k] + kBlock / kSlots[k];
+          if (c < next[k]) {
+            next[k] = c;
+            from_[3 * i + k] = (uint8_t)j;
+          }
+        }
+      }
+      // (costs are kept relative, so that long lists cannot overflow them)
+      const uint32_t low = std::min(next[0], std::min(next[1], next[2]));
+      for (uint32_t k = 0; k < 3; ++k) best[k] = std::min<uint32_t>(next[k] - low, 1u << 20);
+    }
+    shape_.resize(n);
+    uint32_t k = best[0] <= best[1] && best[0] <= best[2] ? 0u : best[1] <= best[2] ? 1u : 2u;
+    for (size_t i = n; i-- > 0;) {
+      shape_[i] = (uint8_t)k;
+      k = from_[3 * i + k];
+    }
+    for (size_t i = 0; i < n;) {
+      const uint32_t sh = shape_[i];
+      size_t e = i;
+      while (e < n && shape_[e] == sh && e - i < kSlots[sh]) ++e;
+      flip_block(sh, &flips_[i], (uint32_t)(e - i), kSlots[sh]);
+      i = e;
+    }
+    flips_.clear();
+  }
+
+  // Weight-1 and weight-2 adds of planes.
+  void adds(const std::vector<uint16_t>& t, const std::vector<uint16_t>& s) {
+    if (t.empty() && s.empty()) return;
+    flush_flips();
+    const uint32_t groups = (uint32_t)(t.size() + 3) / 4;
+    for (uint32_t g = 0; g < groups; g += 7) {
+      const uint32_t m = std::min<uint32_t>(7, groups - g);
+      RpBlock b = block(kBlkT, (7 - m) * 88);
+      for (uint32_t j = 0; j < 4 * m; ++j) {
+        const size_t i = 4 * (size_t)g + j;
+        half(b, 4 + 4 * (7 - m) + j, i < t.size() ? t[i] : src(nq_ + 2));   // (the zero plane adds nothing)
+      }
+      out_.push_back(b);
+    }
+    for (size_t i = 0; i < s.size(); i += 15) {
+      const uint32_t m = (uint32_t)std::min<size_t>(15, s.size() - i);
+      RpBlock b = block(kBlkS, (15 - m) * 16);
+      for (uint32_t j = 0; j < m; ++j) b.w[1 + 15 - m + j] = s[i + j];
+      out_.push_back(b);
+    }
+  }
+
+  // A turn op: its condition (the AND of n <= 3 planes) goes to the next capture plane.
+  void capture(const uint32_t* q, uint32_t n, uint64_t tau) {
+    Flip f{};
+    for (uint32_t k = 0; k < n; ++k) f.c[f.nc++] = (uint16_t)src(q[k]);
+    f.t = (uint16_t)(kRpSrcDst | (kRpPlane0 + nq_ + 3 + (uint32_t)tau_.size()));
+    flip(f);
+    tau_.push_back(tau);
+    if (tau_.size() == rp_capture_planes(nq_)) flush_turns();
+  }
+  void flush_turns() {
+    if (tau_.empty()) return;
+    tau_.resize((tau_.size() + 7) / 8 * 8, 0);
+    exit(kRpTC, (uint32_t)tau_.size() / 8);
+    for (size_t g = 0; g < tau_.size(); g += 8) {
+      RpBlock b{};
+      std::memcpy(b.w, &tau_[g], sizeof b.w);
+      out_.push_back(b);
+    }
+    tau_.clear();
+  }
+
+  // A segment the handlers do not run: its data blocks follow.
+  void exit(uint32_t shape, uint32_t count) {
+    flush_flips();
+    RpBlock b = block(kBlkExit, 0);
+    b.w[1] = shape;
+    b.w[2] = count;
+    out_.push_back(b);
+  }
+
+ private:
+  static RpBlock block(uint32_t shape, uint32_t skip) {
+    RpBlock b{};
+    b.w[0] = shape * kRpStride + skip;
+    return b;
+  }
+  static void half(RpBlock& b, uint32_t h, uint32_t v) { b.w[h / 2] |= v << (16 * (h & 1)); }
+
+  void flip_block(uint32_t sh, const Flip* f, uint32_t m, uint32_t slots) {
+    constexpr uint32_t kCode[3] = {16, 24, 32};
+    const uint32_t nf = sh + 2;   // halfwords of an op
+    RpBlock b = block(kBlkF1 + sh, (slots - m) * kCode[sh]);
+    const uint32_t h0 = sh == 2 ? 4u : 2u;   // halfword of slot 0
+    for (uint32_t j = 0; j < m; ++j) {
+      const uint32_t h = h0 + nf * (slots - m + j);
+      for (uint32_t c = 0; c <= sh; ++c) half(b, h + c, c < f[j].nc ? f[j].c[c] : ones());
+      half(b, h + sh + 1, f[j].t);
+    }
+    out_.push_back(b);
+  }
+
+  uint32_t nq_;
+  std::vector<RpBlock>& out_;
+  std::vector<Flip> flips_;
+  std::vector<uint8_t> from_, shape_;
+  std::vector<uint64_t> tau_;
+};
+
+}  // namespace
+
+void RunCompiler::encode_program(const std::vector<RpRec>& recs, uint32_t nq, std::vector<RpBlock>& out) {
+  BlockWriter w(nq, out);
+  const uint32_t scratch = nq + 1, zero = nq + 2;
+  std::vector<uint16_t> t, s;
+  for (size_t pc = 0; pc < recs.size();) {
+    const uint32_t shape = recs[pc].w[0] & 0xffu, cnt = recs[pc].w[0] >> 8;
+    const RpRec* body = &recs[pc + 1];
+    if (shape >= kRpF1 && shape <= kRpF3) {
+      for (uint32_t i = 0; i < 4 * cnt; ++i) {
+        const uint32_t v = body[i / 4].w[i % 4], target = v & 0xffu;
+        if (target == scratch) continue;   // padding
+        Flip f{};
+        f.t = (uint16_t)(kRpSrcDst | (kRpPlane0 + target));
+        for (uint32_t c = 0; c < shape; ++c) {
+          const uint32_t q = (v >> (8 * (c + 1))) & 0xffu;
+          if (q != nq || (c + 1 == shape && f.nc == 0)) f.c[f.nc++] = (uint16_t)w.src(q);   // (all-ones drops out)
+        }
+        w.flip(f);
+      }
+      pc += 1 + cnt;
+    } else if (shape > kRpOB && shape < kRpOB + 8) {
+      // This and the eighth-turn segments after it: all commute.
+      t.clear();
+      s.clear();
+      for (; pc < recs.size(); pc += 1 + (recs[pc].w[0] >> 8)) {
+        const uint32_t sh = recs[pc].w[0] & 0xffu, k = sh - kRpOB;
+        if (!(sh > kRpOB && sh < kRpOB + 8)) break;
+        for (uint32_t i = 0; i < 4 * (recs[pc].w[0] >> 8); ++i) {
+          const uint32_t q = recs[pc + 1 + i / 4].w[i % 4];
+          if (q == zero) continue;   // padding
+          if (k & 1u) t.push_back((uint16_t)w.src(q));
+          if (k & 2u) s.push_back((uint16_t)w.src(q));
+          if (k & 4u) {
+            Flip f{};
+            f.c[f.nc++] = (uint16_t)w.src(q);
+            f.t = (uint16_t)kRpSrcDst;   // v80, the weight-4 accumulator
+            w.flip(f);
+          }
+        }
+      }
+      w.adds(t, s);
+    } else if ((shape == kRpTB || shape == kRpTG) && rp_capture_planes(nq)) {
+      for (uint32_t i = 0; i < 4 * cnt; ++i) {
+        const RpRec* g = body + 3 * (i / 4);
+        const uint32_t v = g[0].w[i % 4];
+        uint64_t tau;
+        std::memcpy(&tau, &g[1 + (i % 4) / 2].w[2 * (i % 2)], 8);
+        uint32_t q[4], n = 0;
+        for (uint32_t k = 0; k < (shape == kRpTB ? 1u : 4u); ++k) {
+          const uint32_t x = (v >> (8 * k)) & 0xffu;
+          if (x != nq) q[n++] = x;
+        }
+        if (n && q[0] == zero) continue;   // padding
+        if (n <= 3) {
+          w.capture(q, n, tau);
+          continue;
+        }
+        // Four planes: a group of its own.
+        w.exit(kRpTG, 1);
+        RpBlock b{};
+        b.w[0] = v;
+        for (uint32_t k = 1; k < 4; ++k) b.w[k] = zero | zero << 8 | zero << 16 | zero << 24;
+        std::memcpy(&b.w[4], &tau, 8);
+        out.push_back(b);
+      }
+      pc += 1 + 3 * (size_t)cnt;
+    } else if (shape == kRpTB || shape == kRpTG) {
+      w.exit(shape, cnt);
+      for (uint32_t g = 0; g < cnt; ++g) {
+        RpBlock b{};
+        std::memcpy(b.w, body + 3 * g, 3 * sizeof(RpRec));
+        out.push_back(b);
+      }
+      pc += 1 + 3 * (size_t)cnt;
+    } else {   // kRpOG
+      w.exit(shape, cnt);
+      for (uint32_t q = 0; q < cnt; q += 4) {
+        RpBlock b{};
+        std::memcpy(b.w, body + q, std::min<uint32_t>(4, cnt - q) * sizeof(RpRec));
+        out.push_back(b);
+      }
+      pc += 1 + cnt;
+    }
+  }
+  w.flush_turns();
+  w.exit(kRpEnd, 0);
+}
+
+void RunCompiler::program(size_t begin, size_t len, std::vector<RpBlock>& out, BsRun* br) const {
+  std::vector<RpRec> recs;
+  schedule(begin, len, recs, br);
+  encode_program(recs, n_qubits, out);
+}
+
 }  // namespace sparsesim

@@ -211,7 +211,7 @@ struct Request {
     bool rp = false;                  // a register-plane program (prog), else groups (grp)
     BsRun br{};
     std::vector<BsGroup> grp;
-    std::vector<RpRec> prog;
+    std::vector<RpBlock> prog;
   } ahead;
   bool large = false;                 // runs on the large-state lane
   int lane_rc = SIM_OK;               // the lane's result code
@@ -316,16 +316,16 @@ int capture_tick(srv_t* s) {
 // alone and in any mix.  A MONO op compiles to at most three bit-sliced ops;
 // the rewrite of uncontrolled X gates at most doubles them and adds one per
 // qubit; a group holds at least one op; a register-plane program has at most
-// rp_records_bound records.
+// rp_blocks_bound blocks.
 uint64_t arena_run_cap(const srv_t* s, const Request& r) {
   const uint64_t groups = s->cfg.arena_bytes / sizeof(BsGroup);
   const uint64_t by_groups = groups > r.cfg.n_qubits ? (groups - r.cfg.n_qubits) / (2 * 3) : 1;
   const uint64_t by_desc = s->cfg.arena_bytes / sizeof(MonoDesc);
-  // A register-plane program of L ops has at most rp_records_bound(3 L, nq)
-  // records: 8 (6 L + nq) + 16.
-  const uint64_t recs = s->cfg.arena_bytes / sizeof(RpRec);
-  const uint64_t fixed = 8ull * r.cfg.n_qubits + 16;
-  const uint64_t by_prog = recs > fixed ? (recs - fixed) / 48 : 1;
+  // A register-plane program of L ops has at most rp_blocks_bound(L, nq)
+  // blocks: 6 L + nq + 1.
+  const uint64_t blocks = s->cfg.arena_bytes / sizeof(RpBlock);
+  const uint64_t fixed = r.cfg.n_qubits + 1ull;
+  const uint64_t by_prog = blocks > fixed ? (blocks - fixed) / 6 : 1;
   return std::max<uint64_t>(1, std::min({by_groups, by_desc, by_prog}));
 }
 
@@ -567,7 +567,7 @@ void bg_main(srv_t* s) {
         compile_request(r);
         break;
       case BG_GROUP:
-        if (r.ahead.rp) r.rc.schedule(r.ahead.b, r.ahead.len, r.ahead.prog, &r.ahead.br);
+        if (r.ahead.rp) r.rc.program(r.ahead.b, r.ahead.len, r.ahead.prog, &r.ahead.br);
         else r.rc.group(r.ahead.b, r.ahead.len, r.ahead.grp, &r.ahead.br);
         r.ahead.valid = true;
         break;
@@ -916,13 +916,13 @@ int srv_tick(srv_t* s, uint32_t* running, uint32_t* queued) {
     bool rp = false;     // bit-sliced run on the register-plane kernel (prog), else groups
     BsRun br{};
     std::vector<BsGroup> grp;
-    std::vector<RpRec> prog;
+    std::vector<RpBlock> prog;
   };
   // Register-plane runs of this tick: (request, arena offset, records, run).
   struct RpItem {
     Request* r;
     size_t off;
-    uint32_t nrec;
+    uint32_t nblk;
     BsRun br;
   };
   std::vector<RpItem> rp_items;
@@ -970,7 +970,7 @@ int srv_tick(srv_t* s, uint32_t* running, uint32_t* queued) {
     const auto t_g = std::chrono::steady_clock::now();
     HostPool::get().run(to_group.size(), [&](size_t t) {
       Seg& sg = segs[to_group[t]];
-      if (sg.rp) sg.r->rc.schedule(sg.b, sg.len, sg.prog, &sg.br);
+      if (sg.rp) sg.r->rc.program(sg.b, sg.len, sg.prog, &sg.br);
       else sg.r->rc.group(sg.b, sg.len, sg.grp, &sg.br);
     });
     s->stats.group_ms += ms_since(t_g);
@@ -1076,7 +1076,7 @@ int srv_tick(srv_t* s, uint32_t* running, uint32_t* queued) {
       // is left is deferred whole to the next tick (never cut: that would
       // change its rounding); every run fits an empty arena (arena_run_cap).
       const size_t bytes = !bsl ? len * sizeof(MonoDesc)
-                           : sg.rp ? sg.prog.size() * sizeof(RpRec)
+                           : sg.rp ? sg.prog.size() * sizeof(RpBlock)
                                    : sg.grp.size() * sizeof(BsGroup);
       r->deferred = arena_used + al(bytes) > s->cfg.arena_bytes;
       if (r->deferred) {
@@ -1216,7 +1216,7 @@ int srv_tick(srv_t* s, uint32_t* running, uint32_t* queued) {
       Request* r = x.r;
       const int grid = (int)std::max<uint64_t>(1, (r->nnz + 2047) / 2048);
       launch_mono_rp(s->stream, r->buf[r->cur], &s->d_ctl[r->slot].nnz[r->cur],
-                     reinterpret_cast<const RpRec*>(s->d_tick + s->arena_off + x.off), x.nrec, x.br, s->d_rpctl, grid);
+                     reinterpret_cast<const RpBlock*>(s->d_tick + s->arena_off + x.off), x.nblk, x.br, s->d_rpctl, grid);
       SRV_HIP(hipGetLastError());
     }
     // Only the kernel families that have items this tick.

@@ -281,9 +281,9 @@ struct sim_t {
   DevVec<MonoDesc> descs;
   DevVec<BsGroup> grp_ops;     // grouped bit-sliced ops of the current call (LDS-plane kernel)
   std::vector<BsGroup> h_grp;
-  DevVec<RpRec> rp_prog;       // register-plane programs of the current call
-  std::vector<RpRec> h_rp;     // the program of the run being prepared
-  std::vector<RpRec> h_rp_call; // sim_apply_gates_static: the programs uploaded since the last drain
+  DevVec<RpBlock> rp_prog;       // register-plane programs of the current call
+  std::vector<RpBlock> h_rp;     // the program of the run being prepared
+  std::vector<RpBlock> h_rp_call; // sim_apply_gates_static: the programs uploaded since the last drain
   std::vector<sim_gate> conv;  // sim_apply_ops: converted ops, kept between calls
   RunCompiler rc;              // MONO descriptors and bytecode of the current call
   DevVec<MeasRec> recs;
@@ -893,8 +893,8 @@ struct CallBufs {
   MonoDesc* descs = nullptr;
   MeasRec* recs = nullptr;
   int32_t* outcomes = nullptr;
-  RpRec* rp = nullptr;         // fixed: the program ring
-  size_t rp_cap = 0;           // records
+  RpBlock* rp = nullptr;         // fixed: the program ring
+  size_t rp_cap = 0;           // blocks
 };
 
 int apply_impl(sim_t* s, const sim_gate* gates, size_t n, int32_t* outcomes, sim_stats* stats, CallBufs cb) {
@@ -966,7 +966,7 @@ int apply_impl(sim_t* s, const sim_gate* gates, size_t n, int32_t* outcomes, sim
   // Register-plane programs go through pinned staging into rp_prog at
   // rp_used; when a run's program does not fit, the stream is drained (every
   // earlier program has been read) and filling starts over at 0.
-  Staging<RpRec> h_rp_pin(s->stream);
+  Staging<RpBlock> h_rp_pin(s->stream);
   size_t rp_used = 0;
   const bool use_rp = !(s->cfg.flags & SIM_FLAG_BS_LDS);
   size_t desc_lo = 0, desc_hi = 0;   // descriptors [desc_lo, desc_hi) are on the device
@@ -985,10 +985,10 @@ int apply_impl(sim_t* s, const sim_gate* gates, size_t n, int32_t* outcomes, sim
     compiled = true;
     if (use_rp && cb.fixed) {
       s->h_rp_call.clear();
-      s->h_rp_call.reserve(std::min(cb.rp_cap, 4 * s->rc.ops.size() + 64));
+      s->h_rp_call.reserve(std::min(cb.rp_cap, s->rc.ops.size() / 2 + 64));
     } else if (use_rp) {
-      HIP_TRY(s->rp_prog.reserve(4 * s->rc.ops.size() + 64));
-      HIP_TRY(h_rp_pin.reserve(4 * s->rc.ops.size() + 64));
+      HIP_TRY(s->rp_prog.reserve(s->rc.ops.size() / 2 + 64));
+      HIP_TRY(h_rp_pin.reserve(s->rc.ops.size() / 2 + 64));
       cb.rp = s->rp_prog.p;
       cb.rp_cap = s->rp_prog.n;
     } else {
@@ -1010,7 +1010,7 @@ int apply_impl(sim_t* s, const sim_gate* gates, size_t n, int32_t* outcomes, sim
     bool ready = false;          // t has run (or runs) for [begin, begin + len)
     size_t begin = 0, len = 0;
     std::vector<BsGroup> grp;
-    std::vector<RpRec> rp;       // register-plane program (use_rp)
+    std::vector<RpBlock> rp;       // register-plane program (use_rp)
     BsRun delta{};               // run constants the grouping moved (see RunCompiler::group)
     void join() {
       if (t.joinable()) t.join();
@@ -1083,7 +1083,7 @@ int apply_impl(sim_t* s, const sim_gate* gates, size_t n, int32_t* outcomes, sim
           spec.ready = false;
         } else {
           s->h_rp.clear();
-          s->rc.schedule(run_begin, run_len, s->h_rp, &br);
+          s->rc.program(run_begin, run_len, s->h_rp, &br);
         }
       }
       const size_t nr = s->h_rp.size();
@@ -1099,10 +1099,10 @@ int apply_impl(sim_t* s, const sim_gate* gates, size_t n, int32_t* outcomes, sim
         }
         const size_t h0 = s->h_rp_call.size();
         s->h_rp_call.insert(s->h_rp_call.end(), s->h_rp.begin(), s->h_rp.end());
-        HIP_TRY(hipMemcpyAsync(cb.rp + rp_used, s->h_rp_call.data() + h0, nr * sizeof(RpRec), hipMemcpyHostToDevice,
+        HIP_TRY(hipMemcpyAsync(cb.rp + rp_used, s->h_rp_call.data() + h0, nr * sizeof(RpBlock), hipMemcpyHostToDevice,
                                s->stream));
       } else {
-        if (rp_used + nr > s->rp_prog.n || (rp_used + nr) * sizeof(RpRec) > h_rp_pin.bytes) {
+        if (rp_used + nr > s->rp_prog.n || (rp_used + nr) * sizeof(RpBlock) > h_rp_pin.bytes) {
           HIP_TRY(timed_sync(s));
           rp_used = 0;
           HIP_TRY(s->rp_prog.reserve(2 * nr));
@@ -1110,8 +1110,8 @@ int apply_impl(sim_t* s, const sim_gate* gates, size_t n, int32_t* outcomes, sim
           cb.rp = s->rp_prog.p;
           cb.rp_cap = s->rp_prog.n;
         }
-        std::memcpy(h_rp_pin.p + rp_used, s->h_rp.data(), nr * sizeof(RpRec));
-        HIP_TRY(hipMemcpyAsync(cb.rp + rp_used, h_rp_pin.p + rp_used, nr * sizeof(RpRec), hipMemcpyHostToDevice,
+        std::memcpy(h_rp_pin.p + rp_used, s->h_rp.data(), nr * sizeof(RpBlock));
+        HIP_TRY(hipMemcpyAsync(cb.rp + rp_used, h_rp_pin.p + rp_used, nr * sizeof(RpBlock), hipMemcpyHostToDevice,
                                s->stream));
       }
       {
@@ -1191,7 +1191,7 @@ int apply_impl(sim_t* s, const sim_gate* gates, size_t n, int32_t* outcomes, sim
       spec.grp.clear();
       spec.rp.clear();
       spec.delta = BsRun{};
-      if (use_rp) s->rc.schedule(spec.begin, spec.len, spec.rp, &spec.delta);
+      if (use_rp) s->rc.program(spec.begin, spec.len, spec.rp, &spec.delta);
       else s->rc.group(spec.begin, spec.len, spec.grp, &spec.delta);
     });
     return SIM_OK;
@@ -1443,8 +1443,8 @@ int sim_apply_gates_static(sim_t* s, const sim_gate* gates, size_t n, int32_t* o
   cb.recs = reinterpret_cast<MeasRec*>(base + kStaticDescBytes);
   cb.outcomes = reinterpret_cast<int32_t*>(base + kStaticDescBytes + kStaticRecBytes);
   const size_t rp_off = (kStaticDescBytes + kStaticRecBytes + kStaticOutBytes + 255) / 256 * 256;
-  cb.rp = reinterpret_cast<RpRec*>(base + rp_off);
-  cb.rp_cap = (kStaticScratchBytes - rp_off) / sizeof(RpRec);
+  cb.rp = reinterpret_cast<RpBlock*>(base + rp_off);
+  cb.rp_cap = (kStaticScratchBytes - rp_off) / sizeof(RpBlock);
   s->no_alloc = true;
   rc = apply_impl(s, gates, n, outcomes, stats, cb);
   s->no_alloc = false;

@@ -112,8 +112,9 @@ __host__ __device__ constexpr uint32_t bs_pack_a(uint32_t op, uint32_t k, uint32
 __host__ __device__ constexpr uint32_t bs_pack_b(uint32_t p2) { return p2 << 8; }
 __host__ __device__ constexpr uint32_t bs_shape(uint32_t a0) { return (a0 >> 5) & 7u; }
 
-// Register-plane program (the fused pass with planes held in VGPRs): a list
-// of 16-byte quads.  A segment header quad (shape | count << 8, 0, 0, 0) is
+// Register-plane program (the fused pass with planes held in VGPRs), as the
+// scheduler writes it: a list of 16-byte quads, which encode_program packs
+// into the blocks the kernel reads.  A segment header quad (shape | count << 8, 0, 0, 0) is
 // followed by count quads of ops, all of one shape:
 //   F1, F2, F3  flips with 1, 2, 3 control planes, four per quad, one word
 //               each: t | c0 << 8 | c1 << 16 | c2 << 24; plane t ^= AND of the
@@ -127,8 +128,7 @@ __host__ __device__ constexpr uint32_t bs_shape(uint32_t a0) { return (a0 >> 5) 
 //               cond words, then the four 64-bit turn fractions (lo, hi
 //               words); TB: condition = plane t alone (cond = t), TG: AND of
 //               the four planes of cond.  count = groups.
-// A zero header (END) ends the program; the kernel reads the program through
-// a buffer resource that returns zeros past its end.  Planes nq, nq + 1,
+// A zero header (END) ends the program.  Planes nq, nq + 1,
 // nq + 2 are all-ones, scratch and zero; padding ops name them so that they
 // change nothing.
 constexpr uint32_t kRpEnd = 0, kRpF1 = 1, kRpF2 = 2, kRpF3 = 3, kRpOG = 5, kRpTB = 6, kRpTG = 7, kRpOB = 8;
@@ -136,6 +136,41 @@ struct RpRec {
   uint32_t w[4];
 };
 static_assert(sizeof(RpRec) == 16, "RpRec is 16 bytes");
+
+// A 64-byte block of a register-plane program.  Word 0 is where the kernel's
+// handlers start on it: shape * kRpStride + the bytes of code of the op slots
+// not used (ops fill a block's last slots).  A field is 16 bits, an index
+// from v80 and operand enables: kRpSrc | i for a plane read, kRpSrcDst | i for
+// a plane flipped; i = kRpPlane0 + q for plane q, or an accumulator's.  Slots:
+//   kBlkF1  15 flips with one control, a word each: control, target
+//   kBlkF2  10 flips with two controls, three halfwords each from word 1 on
+//   kBlkF3  7 flips with three controls, two words each from word 2 on
+//   kBlkT   7 groups of four weight-1 adds, two words (four planes) each from word 2 on
+//   kBlkS   15 weight-2 adds, a word (a plane) each
+//   kBlkExit  a segment the handlers do not run: word 1 its shape (kRpOG, kRpTB,
+//           kRpTG, kRpTC; 0 ends the program), word 2 its count; its data are
+//           the blocks after it (kRpOG: four quads a block; kRpTB, kRpTG: a
+//           group's three quads a block; kRpTC: eight turn fractions a block)
+// A weight-4 add is a flip of the accumulator v80 (index 0).  A turn op is
+// captured: its condition is flipped into an empty capture plane, and when
+// those are full (and at the end) a kRpTC segment of count groups of eight
+// adds the captured planes' fractions, in plane order, and empties them.  The
+// capture planes follow the zero plane (rp_capture_planes of them).  The kernel reads
+// the program through a buffer resource that returns zeros past its end: an
+// exit with shape 0.
+constexpr uint32_t kBlkExit = 0, kBlkF1 = 1, kBlkF2 = 2, kBlkF3 = 3, kBlkT = 4, kBlkS = 5;
+constexpr uint32_t kRpTC = 16;
+// Capture planes of a program on nq qubits: as many eights as the plane
+// registers leave, at most kRpCaptureMax (0: turn ops are not captured).
+constexpr uint32_t kRpCaptureMax = 16;
+__host__ __device__ constexpr uint32_t rp_capture_planes(uint32_t nq) {
+  return 128u - nq >= kRpCaptureMax ? kRpCaptureMax : (128u - nq) / 8u * 8u;
+}
+constexpr uint32_t kRpStride = 1024, kRpSrc = 0x1000, kRpSrcDst = 0x9000, kRpPlane0 = 20;
+struct RpBlock {
+  uint32_t w[16];
+};
+static_assert(sizeof(RpBlock) == 64, "RpBlock is 64 bytes");
 
 // Run-level parameters of a bit-sliced pass.
 struct BsRun {
@@ -346,7 +381,7 @@ void launch_mono_bs(hipStream_t st, Buf b, const uint64_t* nnz, const BsGroup* g
                     Ctl* ctl, int grid);
 // Register-plane fused pass: one 2048-entry tile per block; grid covers the
 // entry count's upper bound.
-void launch_mono_rp(hipStream_t st, Buf b, const uint64_t* nnz, const RpRec* prog, uint32_t nrec, const BsRun& run,
+void launch_mono_rp(hipStream_t st, Buf b, const uint64_t* nnz, const RpBlock* prog, uint32_t nblk, const BsRun& run,
                     Ctl* ctl, int grid);
 // Set-up of the register-plane passes' cross-stream ordering on the current
 // device (once per device; called by sim_create).
