@@ -448,7 +448,13 @@ struct U2Plan {
   std::function<uint32_t()> may_exceed;   // called for a gate whose outputs may not fit: its sequence number
 };
 
-// Branching op: index, partner look-ups, single pass (or count, scan, write),
+// Whether a gate on at most ub entries runs in one block with its index in LDS.
+bool small_gate(const sim_t* s, uint64_t ub) {
+  return 2 * ub <= s->cfg.capacity && ub <= kLdsU2Max &&
+         !(s->cfg.flags & (SIM_FLAG_U2_TWO_PASS | SIM_FLAG_U2_GLOBAL_INDEX));
+}
+
+// Branching op on the global index: index, partner look-ups, single pass (or count, scan, write),
 // swap.  A single pass whose outputs may not fit is launched all the same and
 // found out at the next read of the entry count (Ctl::over); the two-pass form
 // waits for the total (*over).
@@ -468,20 +474,6 @@ int run_u2(sim_t* s, const sim_gate& g, bool* over, const U2Plan& plan) {
   const uint64_t* nnz_in = d_nnz(s, s->cur);
   const U2Desc d = u2_desc(g, s->cfg.eps);
   const int G = chunk_grid(ub);
-  if (!check && !(s->cfg.flags & (SIM_FLAG_U2_TWO_PASS | SIM_FLAG_U2_GLOBAL_INDEX)) && ub <= kLdsU2Max) {
-    // Small state (2 ub <= capacity): the whole gate in one block, its
-    // partner index in LDS; the global index is not touched.
-    if (int rc = plan.before->run_now()) return rc;
-    {
-      KTimer t_(s, KC_U2_LDS);
-      launch_u2_lds(s->stream, s->wide, s->buf[s->cur], s->buf[other], nnz_in, d, s->ctl, d_nnz(s, other));
-    }
-    HIP_TRY(hipGetLastError());
-    s->cur = other;
-    s->nnz_known = false;
-    s->nnz_ub = std::min<uint64_t>(2 * ub, cap);
-    return SIM_OK;
-  }
   const bool counting = s->cfg.flags & SIM_FLAG_COUNT_INDEX;
   const bool single = !two_pass && ub <= kSingleMax;
   const bool split = plan.split && !s->built;
@@ -1213,21 +1205,91 @@ int apply_impl(sim_t* s, const sim_gate* gates, size_t n, int32_t* outcomes, sim
     return !(s->cfg.flags & SIM_FLAG_NO_UNIFORM) && ((x_lo & u_lo) | (x_hi & u_hi));
   };
   size_t i = 0;
+  // Runs of at most held_most ops can be handed to a branching gate's kernels:
+  // those that run per entry, whole.
+  const size_t held_most =
+      std::min<size_t>({s->cfg.mono_mode == SIM_MONO_BITSLICE ? 0 : (size_t)kHeldMax,
+                        s->cfg.mono_mode == SIM_MONO_AUTO ? (size_t)(s->cfg.bs_min_gates ? s->cfg.bs_min_gates : 16u) - 1
+                                                          : (size_t)kHeldMax,
+                        (size_t)s->cfg.fuse_max - 1});
+  // The end of the run at j, or past held_most ops of it.
+  auto run_end = [&](size_t j) {
+    const size_t b = j;
+    while (j < n && gates[j].op == SIM_OP_MONO && j - b <= held_most) ++j;
+    return j;
+  };
+  // The applied branching gate at i on a small state, and what follows it as
+  // far as it is certain to run on one too, as one launch; i ends at the last
+  // op taken.
+  auto run_chain = [&](bool split) -> int {
+    Chain ch;
+    ch.n = ch.n_ops = 0;
+    ch.ops = nullptr;
+    uint64_t ub = s->nnz_known ? s->nnz_exact : s->nnz_ub;
+    const int cur = s->cur;
+    auto add = [&](const MonoRun& m, const sim_gate* g) {
+      ChainStep& p = ch.s[ch.n++];
+      if (g) p.d = u2_desc(*g, s->cfg.eps);
+      if (!ch.n_ops) ch.ops = m.g;   // (the chain's runs follow each other in the descriptor array)
+      ch.n_ops += m.ng;
+      p.ng = m.ng;
+      p.bytes_per_entry = m.bytes_per_entry;
+      p.gate = g != nullptr;
+      if (!g) return;
+      uint64_t x_lo, x_hi;
+      partner_mask(*g, &x_lo, &x_hi);
+      s->uni_lo &= ~x_lo;
+      s->uni_hi &= ~x_hi;
+      st.u2_applied++;
+      if (split) st.u2_split++;
+      ub *= 2;
+      s->cur ^= 1;
+    };
+    add(held.take(), &gates[i]);
+    while (ch.n < kChainSteps) {
+      const size_t b = i + 1, j = run_end(b), len = j - b;
+      if (len > held_most || ch.n_ops + len > kChainOps) break;
+      const sim_gate* g = j < n && gates[j].op == SIM_OP_U2 ? &gates[j] : nullptr;
+      if (g ? !small_gate(s, ub) || (g->cap && 2 * ub > g->cap) : len == 0) break;
+      MonoRun m;
+      if (len) {
+        int rc = need_descs(mono_seen, len);
+        if (rc) return rc;
+        m.g = cb.descs + mono_seen;
+        m.ng = (uint32_t)len;
+        m.bytes_per_entry = run_cost(mono_seen, len, &m.run_flags);
+        mono_seen += len;
+        st.mono_passes++;
+        for (size_t k = b; k < j; ++k) flip_uniform(gates[k], s->uni_lo, s->uni_hi);
+      }
+      if (g) {
+        uint64_t x_lo, x_hi;
+        partner_mask(*g, &x_lo, &x_hi);
+        split = is_split(x_lo, x_hi, s->uni_lo, s->uni_hi);
+      }
+      add(m, g);
+      i = g ? j : j - 1;
+      if (!g) break;
+    }
+    s->k_launches[KC_U2_LDS] += ch.n - 1 - (ch.s[ch.n - 1].gate ? 0 : 1);   // (a gate each; the timer counts one)
+    {
+      KTimer t_(s, KC_U2_LDS);
+      launch_u2_chain(s->stream, s->wide, s->buf[cur], s->buf[cur ^ 1], s->ctl->nnz, cur, ch, s->ctl);
+    }
+    HIP_TRY(hipGetLastError());
+    s->nnz_known = false;
+    s->nnz_ub = ub;
+    return SIM_OK;
+  };
   // What the gate at i can do for the next branching gate while it writes:
   // the run up to it, if it is short and would run per entry, and its index.
   // Only for a gate that is certain to be applied and to use the global index.
   int look_rc = SIM_OK;
   auto prepare_next = [&](uint64_t ub_out, MonoRun* m, U2Desc* d) -> bool {
     if (s->cfg.flags & (SIM_FLAG_U2_TWO_PASS | SIM_FLAG_COUNT_INDEX)) return false;
-    if (!(s->cfg.flags & SIM_FLAG_U2_GLOBAL_INDEX) && ub_out <= kLdsU2Max) return false;
-    const size_t most = s->cfg.mono_mode == SIM_MONO_BITSLICE ? 0
-                        : s->cfg.mono_mode == SIM_MONO_DIRECT
-                            ? (size_t)kHeldMax
-                            : std::min<size_t>(kHeldMax, (size_t)(s->cfg.bs_min_gates ? s->cfg.bs_min_gates : 16u) - 1);
-    size_t j = i + 1;
-    while (j < n && gates[j].op == SIM_OP_MONO && j - (i + 1) <= most) ++j;
-    const size_t len = j - (i + 1);
-    if (j == n || len > most || len >= s->cfg.fuse_max || gates[j].op != SIM_OP_U2) return false;
+    if (small_gate(s, ub_out)) return false;
+    const size_t j = run_end(i + 1), len = j - (i + 1);
+    if (j == n || len > held_most || gates[j].op != SIM_OP_U2) return false;
     if (gates[j].cap && 2 * ub_out > gates[j].cap) return false;
     uint64_t x_lo, x_hi, u_lo = s->uni_lo, u_hi = s->uni_hi;
     partner_mask(gates[i], &x_lo, &x_hi);
@@ -1329,6 +1391,11 @@ int apply_impl(sim_t* s, const sim_gate* gates, size_t n, int32_t* outcomes, sim
       uint64_t x_lo, x_hi;
       partner_mask(g, &x_lo, &x_hi);
       const bool split = is_split(x_lo, x_hi, s->uni_lo, s->uni_hi);
+      if (small_gate(s, s->nnz_known ? s->nnz_exact : s->nnz_ub)) {
+        rc = run_chain(split);
+        if (rc) return rc;
+        continue;
+      }
       rc = run_u2(s, g, &over, U2Plan{split, &held, prepare_next, may_exceed});
       if (rc || look_rc) return rc ? rc : look_rc;
       if (s->over && (result = settle())) break;

@@ -428,11 +428,24 @@ void launch_u2_restore(hipStream_t st, Ctl* ctl, int cur);
 // Largest state the one-block branching kernel takes (its partner index and
 // partner slots live in LDS).
 constexpr uint32_t kLdsU2Max = 8192;
-// One block: a branching gate on a state of at most kLdsU2Max entries, index
-// and look-up in LDS; outputs, their order and the counters as the
-// multi-kernel path's single pass (pruned_mass up to summation order).
-void launch_u2_lds(hipStream_t st, bool wide, Buf in, Buf out, const uint64_t* nnz, const U2Desc& d, Ctl* ctl,
-                   uint64_t* nnz_out);
+// A chain of branching gates on a state of at most kLdsU2Max entries at each,
+// in one block (index and look-up in LDS) and one launch: each step a short
+// phase/permutation run (ng = 0: none), then a gate (gate = 0: the chain's
+// last run alone).  Outputs, their order and the counters as the multi-kernel
+// path's (pruned_mass up to summation order).  Buffers alternate from `in`; the
+// counts go to nnz[cur ^ 1], nnz[cur], ...
+constexpr uint32_t kChainSteps = 16, kChainOps = 128;
+struct ChainStep {
+  U2Desc d;
+  uint32_t ng, bytes_per_entry, gate, pad;
+};
+struct Chain {
+  uint32_t n, n_ops;      // steps; ops of all runs
+  const MonoDesc* ops;    // one run after the other
+  ChainStep s[kChainSteps];
+};
+static_assert(sizeof(Chain) <= 3584, "passed as a kernel argument");
+void launch_u2_chain(hipStream_t st, bool wide, Buf in, Buf out, uint64_t* nnz, int cur, const Chain& chain, Ctl* ctl);
 void launch_measure_reduce(hipStream_t st, bool wide, Buf b, const uint64_t* nnz, uint32_t q, BlockScratch s,
                            int grid, int block);
 void launch_measure_decide(hipStream_t st, const double2* part, const uint32_t* cnt1, uint32_t* off, int nblocks,

@@ -991,32 +991,244 @@ __global__ void k_u2_restore(Ctl* ctl, int cur) {
 }
 
 // ---------------------------------------------------------------------------
-// Branching gate on a state of at most kLdsU2Max entries in one block, its
+// Branching gates on a state of at most kLdsU2Max entries in one block, their
 // partner index in LDS (lds::u2_block): same outputs, order and counters as
-// the index-build / probe / single-pass kernels, in one launch.
+// the index-build / probe / single-pass kernels.  A launch runs a chain of
+// gates with the short runs between them: a launch costs the host 6 us and the
+// GPU two or three with nothing to do, and a gate on a few entries is little
+// more than its chain of memory round trips (8 us).  While the state has at
+// most kResident entries it therefore stays in LDS from gate to gate, and with
+// it the chain's descriptors: 3 us per gate.  A 12-qubit circuit's 10 gates
+// with runs between them: 17 launches and 120 us of kernels; in one launch
+// over memory 84 us, over LDS 32.
+constexpr uint32_t kResident = 1024;
+struct ResidentBuf {
+  uint64_t lo[2 * kResident], hi[2 * kResident];
+  double2 amp[2 * kResident];
+};
+struct ResidentSmem {
+  ResidentBuf buf[2];
+  uint32_t tab[2 * kResident];
+  uint32_t par[kResident];
+};
+struct ChainSmem {
+  union {
+    ResidentSmem r;
+    lds::Smem g;
+  };
+  MonoDesc g_run[kChainOps];
+  ChainStep step[kChainSteps];
+  uint32_t wave[lds::kWaves];
+};
+static_assert(kResident == (uint32_t)lds::kThreads, "an entry per thread");
+static_assert(sizeof(ChainSmem) <= 160 * 1024, "LDS of a block");
+
+// What a thread counted over the resident gates.
+struct ChainCount {
+  uint32_t dropped = 0, ix[4] = {};
+  double mass = 0.0;
+};
+
+// One gate on the n <= kResident entries of `in`, preceded by the run at run;
+// returns the number of outputs.
 template <bool WIDE>
-__global__ __launch_bounds__(1024) void k_u2_lds(Buf in, Buf out, const uint64_t* __restrict__ nnz_p, U2Desc d,
-                                                 Ctl* ctl, uint64_t* nnz_out) {
-  __shared__ lds::Smem sm;
-  const uint64_t n = *nnz_p;
-  if (n > kLdsU2Max) {   // the host launches this kernel only below the bound
-    if (threadIdx.x == 0) atomicOr(&ctl->error, 4u);
-    return;
-  }
-  // Outputs number at most 2 n, which the host has checked against the
-  // capacity, so the bound passed here never refuses a write.
-  const lds::Totals t = lds::u2_block<WIDE>(in, out, (uint32_t)n, d, ~0ull, sm);
-  if (threadIdx.x == 0) {
-    if (t.dropped) {
-      atomicAdd((unsigned long long*)&ctl->pruned, (unsigned long long)t.dropped);
-      atomicAdd(&ctl->pruned_mass, t.mass);
+__device__ __forceinline__ uint32_t u2_resident(ResidentBuf& in, ResidentBuf& out, uint32_t n, const U2Desc& d,
+                                                const MonoDesc* run, uint32_t ng, ChainSmem& sm, ChainCount& cnt) {
+  constexpr uint32_t kMask = 2 * kResident - 1;
+  const uint32_t i = threadIdx.x, lane = i & 63, wid = i >> 6;
+  uint64_t lo = 0, hi = 0;
+  double2 a = make_double2(0.0, 0.0);
+  sm.r.tab[i] = 0u;
+  sm.r.tab[i + kResident] = 0u;
+  if (i < n) {
+    lo = in.lo[i];
+    hi = WIDE ? in.hi[i] : 0ull;
+    a = in.amp[i];
+    for (uint32_t q = 0; q < ng; ++q) ent::mono_step(run[q], WIDE, lo, hi, a);
+    if (ng) {
+      in.lo[i] = lo;
+      if (WIDE) in.hi[i] = hi;
+      in.amp[i] = a;
     }
-    atomicAdd((unsigned long long*)&ctl->updates, (unsigned long long)n);
-    for (int k = 0; k < 4; ++k)
-      if (t.ix[k]) atomicAdd((unsigned long long*)&ctl->ix[k], (unsigned long long)t.ix[k]);
-    *nnz_out = t.out;
-    if (t.out > ctl->peak) ctl->peak = t.out;
-    atomicAdd((unsigned long long*)&ctl->pass_bytes[4], (unsigned long long)((n + t.out) * (WIDE ? 32u : 24u)));
+    sm.r.par[i] = kNoPartner;
+  }
+  const bool under = i < n && ent::ctrl_ok(d, lo, hi, WIDE);
+  const bool piv = ent::pivot_set(d, lo, hi, WIDE);
+  const uint64_t h = hash_label(lo ^ (piv ? d.x_lo : 0ull), WIDE ? hi ^ (piv ? d.x_hi : 0ull) : 0ull);
+  const uint32_t fp = (uint32_t)(h >> (32 + lds::kIdxBits)), slot0 = (uint32_t)h & kMask;
+  __syncthreads();
+  if (under && !piv) {
+    const uint32_t val = fp << lds::kIdxBits | (i + 1u);
+    ++cnt.ix[0];
+    for (uint32_t p = 0; p <= kMask; ++p) {
+      ++cnt.ix[1];
+      if (atomicCAS(&sm.r.tab[(slot0 + p) & kMask], 0u, val) == 0u) break;
+    }
+  }
+  __syncthreads();
+  uint32_t j = kNoPartner;
+  if (under && piv) {
+    const uint64_t qlo = lo ^ d.x_lo, qhi = WIDE ? hi ^ d.x_hi : 0ull;
+    ++cnt.ix[2];
+    for (uint32_t p = 0; p <= kMask; ++p) {
+      const uint32_t v = sm.r.tab[(slot0 + p) & kMask];
+      ++cnt.ix[3];
+      if (v == 0u) break;
+      const uint32_t c = (v & lds::kIdxMask) - 1u;
+      if ((v >> lds::kIdxBits) == fp && in.lo[c] == qlo && (!WIDE || in.hi[c] == qhi)) {
+        j = c;
+        sm.r.par[c] = i;
+        break;
+      }
+    }
+  }
+  __syncthreads();
+  if (under && !piv) j = sm.r.par[i];
+  double2 aj = make_double2(0.0, 0.0);
+  if (piv && j != kNoPartner) aj = in.amp[j];
+  U2Out r = ent::u2_eval(d, WIDE, lo, hi, a, j != kNoPartner, aj);
+  if (i >= n) r.mode = 2;
+  const bool k0 = r.mode != 2 && survives(r.o0, d.eps), k1 = r.mode == 1 && survives(r.o1, d.eps);
+  cnt.dropped += (r.mode != 2 && !k0 ? 1u : 0u) + (r.mode == 1 && !k1 ? 1u : 0u);
+  if (r.mode != 2) cnt.mass += ent::dropped_mass(r.o0, k0);
+  if (r.mode == 1) cnt.mass += ent::dropped_mass(r.o1, k1);
+  const uint64_t b0 = __ballot(k0), b1 = __ballot(k1), lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+  if (lane == 0) sm.wave[wid] = __popcll(b0) + __popcll(b1);
+  __syncthreads();
+  // Every wave: the waves' counts, scanned; its own offset is the one before it.
+  uint32_t incl = lane < (uint32_t)lds::kWaves ? sm.wave[lane] : 0u;
+#pragma unroll
+  for (int o = 1; o < lds::kWaves; o <<= 1) {
+    const uint32_t y = __shfl_up(incl, o);
+    if (lane >= (uint32_t)o) incl += y;
+  }
+  const uint32_t total = __shfl(incl, lds::kWaves - 1);
+  const uint32_t before = wid ? __shfl(incl, wid - 1) : 0u;
+  uint32_t p = before + __popcll(b0 & lt) + __popcll(b1 & lt);
+  const bool flipped = r.mode == 1 && piv;
+  const uint64_t lo0 = flipped ? lo ^ d.x_lo : lo, hi0 = flipped ? hi ^ d.x_hi : hi;
+  if (k0) {
+    out.lo[p] = lo0;
+    if (WIDE) out.hi[p] = hi0;
+    out.amp[p] = r.o0;
+    ++p;
+  }
+  if (k1) {
+    out.lo[p] = lo0 ^ d.x_lo;
+    if (WIDE) out.hi[p] = hi0 ^ d.x_hi;
+    out.amp[p] = r.o1;
+  }
+  __syncthreads();   // (the next gate reads `out`, and writes sm.wave)
+  return __builtin_amdgcn_readfirstlane(total);
+}
+
+template <bool WIDE>
+__global__ __launch_bounds__(1024) void k_u2_chain(Buf in, Buf out, uint64_t* nnz, int cur, Chain chain, Ctl* ctl) {
+  __shared__ ChainSmem sm;
+  auto count = [](uint64_t* p, uint64_t v) {
+    if (v) atomicAdd((unsigned long long*)p, (unsigned long long)v);
+  };
+  constexpr uint32_t kEntry = WIDE ? 32u : 24u;
+  const uint64_t n0 = nnz[cur];
+  // The chain into LDS: its steps (from the kernel arguments) and its runs' gates.
+  {
+    const uint32_t* src = reinterpret_cast<const uint32_t*>(chain.s);
+    uint32_t* dst = reinterpret_cast<uint32_t*>(sm.step);
+    for (uint32_t k = threadIdx.x; k < chain.n * (uint32_t)(sizeof(ChainStep) / 4); k += lds::kThreads) dst[k] = src[k];
+    const uint4* g4 = reinterpret_cast<const uint4*>(chain.ops);
+    uint4* d4 = reinterpret_cast<uint4*>(sm.g_run);
+    for (uint32_t k = threadIdx.x; k < chain.n_ops * (uint32_t)(sizeof(MonoDesc) / 16); k += lds::kThreads) d4[k] = g4[k];
+  }
+  uint32_t n = __builtin_amdgcn_readfirstlane((uint32_t)(n0 > kLdsU2Max ? kLdsU2Max + 1 : n0));
+  bool resident = false;   // uniform, as all that follows from n
+  uint32_t rb = 0;         // the LDS buffer with the state
+  __syncthreads();
+  ChainCount cnt;
+  uint64_t updates = 0, mono_updates = 0, mono_bytes = 0, bytes = 0, peak = 0;
+  // The n entries through a run of ng gates: in the device buffer of their
+  // parity, or from LDS to it.
+  auto run_out = [&](const MonoDesc* run, uint32_t ng) {
+    const ResidentBuf& b = sm.r.buf[rb];
+    for (uint32_t i = threadIdx.x; i < n; i += lds::kThreads) {
+      uint64_t lo = resident ? b.lo[i] : in.key_lo[i], hi = 0;
+      if (WIDE) hi = resident ? b.hi[i] : in.key_hi[i];
+      double2 a = resident ? b.amp[i] : in.amp[i];
+      for (uint32_t j = 0; j < ng; ++j) ent::mono_step(run[j], WIDE, lo, hi, a);
+      in.key_lo[i] = lo;
+      if (WIDE) in.key_hi[i] = hi;
+      in.amp[i] = a;
+    }
+    __syncthreads();
+    resident = false;
+  };
+  uint32_t op = 0;
+#pragma unroll 1
+  for (uint32_t k = 0; k < chain.n; ++k) {
+    const ChainStep& st = sm.step[k];
+    const uint32_t ng = __builtin_amdgcn_readfirstlane(st.ng), gate = __builtin_amdgcn_readfirstlane(st.gate);
+    if (gate && n > kLdsU2Max) {   // the host launches this kernel only below the bound
+      if (threadIdx.x == 0) atomicOr(&ctl->error, 4u);
+      break;
+    }
+    updates += (uint64_t)n * (ng + gate);
+    mono_updates += (uint64_t)n * ng;
+    mono_bytes += (uint64_t)n * st.bytes_per_entry;
+    const MonoDesc* run = sm.g_run + op;
+    op += ng;
+    if (!gate) {
+      run_out(run, ng);
+      break;
+    }
+    uint32_t m;
+    if (n <= kResident) {
+      if (!resident && threadIdx.x < n) {
+        ResidentBuf& b = sm.r.buf[rb];
+        b.lo[threadIdx.x] = in.key_lo[threadIdx.x];
+        if (WIDE) b.hi[threadIdx.x] = in.key_hi[threadIdx.x];
+        b.amp[threadIdx.x] = in.amp[threadIdx.x];
+      }
+      resident = true;
+      m = u2_resident<WIDE>(sm.r.buf[rb], sm.r.buf[rb ^ 1], n, st.d, run, ng, sm, cnt);
+      rb ^= 1;
+    } else {
+      if (resident || ng) run_out(run, ng);
+      // Outputs number at most 2 n, which the host has checked against the
+      // capacity, so the bound passed here never refuses a write.
+      const lds::Totals t = lds::u2_block<WIDE, 2>(in, out, n, st.d, ~0ull, sm.g);
+      if (threadIdx.x == 0) {
+        cnt.dropped += t.dropped;
+        cnt.mass += t.mass;
+        for (int q = 0; q < 4; ++q) cnt.ix[q] += t.ix[q];
+      }
+      m = __builtin_amdgcn_readfirstlane(t.out);
+    }
+    bytes += (uint64_t)(n + m) * kEntry;
+    n = m;
+    if (n > peak) peak = n;
+    cur ^= 1;
+    const Buf b = in;
+    in = out;
+    out = b;
+  }
+  if (resident) run_out(nullptr, 0);
+  // Sums of what the threads counted: waves by shuffles, then one atomic each.
+  const uint32_t dropped = lds::wave_u(cnt.dropped);
+  const double mass = lds::wave_d(cnt.mass);
+  uint32_t ix[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) ix[q] = lds::wave_u(cnt.ix[q]);
+  if ((threadIdx.x & 63) == 0) {
+    count(&ctl->pruned, dropped);
+    if (dropped) atomicAdd(&ctl->pruned_mass, mass);
+    for (int q = 0; q < 4; ++q) count(&ctl->ix[q], ix[q]);
+  }
+  if (threadIdx.x == 0) {
+    nnz[cur] = n;
+    count(&ctl->updates, updates);
+    count(&ctl->mono_updates, mono_updates);
+    count(&ctl->mono_bytes, mono_bytes);
+    count(&ctl->pass_bytes[4], bytes);
+    if (peak > ctl->peak) ctl->peak = peak;
   }
 }
 
@@ -1334,12 +1546,12 @@ void launch_u2_restore(hipStream_t st, Ctl* ctl, int cur) {
   hipLaunchKernelGGL(k_u2_restore, dim3(1), dim3(1), 0, st, ctl, cur);
 }
 
-void launch_u2_lds(hipStream_t st, bool wide, Buf in, Buf out, const uint64_t* nnz, const U2Desc& d, Ctl* ctl,
-                   uint64_t* nnz_out) {
+void launch_u2_chain(hipStream_t st, bool wide, Buf in, Buf out, uint64_t* nnz, int cur, const Chain& chain,
+                     Ctl* ctl) {
   if (wide)
-    hipLaunchKernelGGL(k_u2_lds<true>, dim3(1), dim3(lds::kThreads), 0, st, in, out, nnz, d, ctl, nnz_out);
+    hipLaunchKernelGGL(k_u2_chain<true>, dim3(1), dim3(lds::kThreads), 0, st, in, out, nnz, cur, chain, ctl);
   else
-    hipLaunchKernelGGL(k_u2_lds<false>, dim3(1), dim3(lds::kThreads), 0, st, in, out, nnz, d, ctl, nnz_out);
+    hipLaunchKernelGGL(k_u2_chain<false>, dim3(1), dim3(lds::kThreads), 0, st, in, out, nnz, cur, chain, ctl);
 }
 
 void launch_measure_reduce(hipStream_t st, bool wide, Buf b, const uint64_t* nnz, uint32_t q, BlockScratch s,

@@ -9,29 +9,35 @@
 // therefore those of the index-build / probe / write kernels, in one launch
 // and with no global index to fill, probe or empty.  A slot holds an 18-bit
 // fingerprint above entry index + 1 (kIdxBits = 14 bits; 0 = empty); the table has twice
-// as many slots as the largest state, so it is at most half full and every
+// as many slots as the block takes entries, so it is at most half full and every
 // probe sequence meets an empty slot.
+//
+// Latency bounds it, the fetch of the kernel's own code not least: unrolled
+// for 8 entries per thread the gate is 40 KB of straight code, fetched cold
+// by every launch (8.6 us for a gate on a few dozen entries).  The entries per
+// thread are therefore chosen by the entry count (u2_block): 1 to 1,024
+// entries, 2, 4, 8 beyond, of which only the path taken is fetched.
 #pragma once
 #include "entry_ops.h"
 
 namespace sparsesim {
 namespace lds {
 
-constexpr uint32_t kSlots = 2 * kLdsU2Max;
+constexpr uint32_t kMaxSlots = 2 * kLdsU2Max;
 constexpr int kThreads = 1024;
-constexpr int kItems = (int)(kLdsU2Max / kThreads);
+constexpr int kMaxItems = (int)(kLdsU2Max / kThreads);
 constexpr int kWaves = kThreads / 64;
 constexpr int kIdxBits = 14;
 constexpr uint32_t kIdxMask = (1u << kIdxBits) - 1u;
-static_assert(kLdsU2Max < (1u << kIdxBits) && kItems * kThreads == (int)kLdsU2Max, "index field of a slot");
+static_assert(kLdsU2Max < (1u << kIdxBits) && kMaxItems * kThreads == (int)kLdsU2Max, "index field of a slot");
 
 // LDS of one block (about 96 KB); declared by the kernel, whatever the label
 // width, so that both widths share it.
 struct Smem {
-  uint32_t tab[kSlots];
+  uint32_t tab[kMaxSlots];
   uint32_t par[kLdsU2Max];
   uint32_t wave[kWaves];
-  uint32_t red_u[kWaves];
+  uint32_t red_u[5][kWaves];
   double red_d[kWaves];
 };
 
@@ -62,34 +68,25 @@ __device__ __forceinline__ uint32_t prefix012(uint32_t e, Smem& sm, uint32_t* to
   return woff + pre;
 }
 
-// Block sums in a fixed order: a butterfly in each wave, then the waves in
-// order.  Every thread calls them and gets the sum.
-__device__ __forceinline__ uint32_t sum_u(uint32_t v, Smem& sm) {
+// Sum over a wave, the same in every lane.
+__device__ __forceinline__ uint32_t wave_u(uint32_t v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-  if ((threadIdx.x & 63) == 0) sm.red_u[threadIdx.x >> 6] = v;
-  __syncthreads();
-  uint32_t r = 0;
-  for (int w = 0; w < kWaves; ++w) r += sm.red_u[w];
-  __syncthreads();
-  return r;
+  return v;
 }
-__device__ __forceinline__ double sum_d(double v, Smem& sm) {
+__device__ __forceinline__ double wave_d(double v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-  if ((threadIdx.x & 63) == 0) sm.red_d[threadIdx.x >> 6] = v;
-  __syncthreads();
-  double r = sm.red_d[0];
-  for (int w = 1; w < kWaves; ++w) r += sm.red_d[w];
-  __syncthreads();
-  return r;
+  return v;
 }
 
 // The gate on entries [0, n) of `in` (n <= kLdsU2Max, blockDim.x ==
 // kThreads), written to `out` (which holds cap entries).
-template <bool WIDE>
-__device__ Totals u2_block(const Buf& in, const Buf& out, uint32_t n, const U2Desc& d, uint64_t cap, Smem& sm) {
-  constexpr uint32_t kMask = kSlots - 1;
+template <bool WIDE, int ITEMS>
+__device__ __forceinline__ Totals u2_items(const Buf& in, const Buf& out, uint32_t n, const U2Desc& d, uint64_t cap,
+                                           Smem& sm) {
+  constexpr int kItems = ITEMS;
+  constexpr uint32_t kSlots = 2u * ITEMS * kThreads, kMask = kSlots - 1;
   for (uint32_t k = threadIdx.x; k < kSlots; k += kThreads) sm.tab[k] = 0u;
   uint32_t inserts = 0, cas = 0, lookups = 0, steps = 0;
   uint64_t lo[kItems], hi[kItems];
@@ -201,15 +198,35 @@ __device__ Totals u2_block(const Buf& in, const Buf& out, uint32_t n, const U2De
       }
     }
   }
+  // The block's sums: each wave's to LDS, then every wave adds the waves' up.
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  const uint32_t v[5] = {dropped, inserts, cas, lookups, steps};
+#pragma unroll
+  for (int k = 0; k < 5; ++k) {
+    const uint32_t w = wave_u(v[k]);
+    if (lane == 0) sm.red_u[k][wid] = w;
+  }
+  mass = wave_d(mass);
+  if (lane == 0) sm.red_d[wid] = mass;
+  __syncthreads();
   Totals t;
   t.out = run;
-  t.dropped = sum_u(dropped, sm);
-  t.mass = sum_d(mass, sm);
-  t.ix[0] = sum_u(inserts, sm);
-  t.ix[1] = sum_u(cas, sm);
-  t.ix[2] = sum_u(lookups, sm);
-  t.ix[3] = sum_u(steps, sm);
+  t.dropped = wave_u(lane < kWaves ? sm.red_u[0][lane] : 0u);
+  t.mass = wave_d(lane < kWaves ? sm.red_d[lane] : 0.0);
+#pragma unroll
+  for (int k = 0; k < 4; ++k) t.ix[k] = wave_u(lane < kWaves ? sm.red_u[k + 1][lane] : 0u);
+  __syncthreads();
   return t;
+}
+
+// Entries in registers: 1, 2, 4 or 8 a thread, at least MIN.
+template <bool WIDE, int MIN = 1>
+__device__ __forceinline__ Totals u2_block(const Buf& in, const Buf& out, uint32_t n, const U2Desc& d, uint64_t cap,
+                                           Smem& sm) {
+  if (MIN <= 1 && n <= 1 * kThreads) return u2_items<WIDE, 1>(in, out, n, d, cap, sm);
+  if (n <= 2 * kThreads) return u2_items<WIDE, 2>(in, out, n, d, cap, sm);
+  if (n <= 4 * kThreads) return u2_items<WIDE, 4>(in, out, n, d, cap, sm);
+  return u2_items<WIDE, 8>(in, out, n, d, cap, sm);
 }
 
 }  // namespace lds
