@@ -256,6 +256,9 @@ int sim_set_basis(sim_t* s, sim_key k);
  * keys or bits above n_qubits -> SIM_E_ARG; n > capacity -> SIM_E_CAPACITY. */
 int sim_import_state(sim_t* s, const sim_key* keys, const sim_c64* amps, uint64_t n);
 
+/* The same from separate arrays of n label words (key_hi may be NULL: zeros). */
+int sim_import_state_soa(sim_t* s, const uint64_t* key_lo, const uint64_t* key_hi, const sim_c64* amps, uint64_t n);
+
 /* Convert n standard-gate records into sim_gate ops (host only). */
 int sim_gates_from_ops(const sim_op* ops, size_t n, sim_gate* out);
 
@@ -354,6 +357,10 @@ int sim_export_state(sim_t* s, sim_key* keys, sim_c64* amps, uint64_t cap, uint6
  * not wanted; zeros for <= 64 qubits), amps[i] its amplitude.  Arrays of cap
  * entries, caller-owned; sizes and errors as sim_export_state. */
 int sim_export_state_soa(sim_t* s, uint64_t* key_lo, uint64_t* key_hi, sim_c64* amps, uint64_t cap, uint64_t* nnz);
+
+/* sim_export_state_soa with the entries in ascending order of (hi, lo), sorted
+ * on the device (the stored state keeps its order). */
+int sim_export_state_sorted(sim_t* s, uint64_t* key_lo, uint64_t* key_hi, sim_c64* amps, uint64_t cap, uint64_t* nnz);
 
 /* Device addresses of the current state buffers (key_lo, key_hi, amp) and
  * the device nnz word, for zero-copy inspection (read only); valid until the

@@ -399,7 +399,7 @@ hipError_t copy_out(Request& r) {
   const Buf& b = r.buf[r.cur];
   const bool wide = r.cfg.n_qubits > 64;
   const hipError_t e = copy_state_to_host_soa(b.key_lo, wide ? b.key_hi : nullptr, b.amp, r.nnz, r.res_lo.get(),
-                                              wide ? r.res_hi.get() : nullptr, r.res_amp.get());
+                                              wide ? r.res_hi.get() : nullptr, r.res_amp.get(), nullptr);
   if (e == hipSuccess) r.copied = true;
   return e;
 }

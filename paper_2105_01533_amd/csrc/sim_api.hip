@@ -723,47 +723,52 @@ int sim_set_basis(sim_t* s, sim_key k) {
   return SIM_OK;
 }
 
-int sim_import_state(sim_t* s, const sim_key* keys, const sim_c64* amps, uint64_t n) {
+namespace {
+
+int import_state(sim_t* s, const uint64_t* lo, const uint64_t* hi, size_t stride, const sim_c64* amps, uint64_t n) {
   if (!s) return fail(SIM_E_ARG, "null handle");
   if (n > s->cfg.capacity) return fail(SIM_E_CAPACITY, "import larger than capacity");
-  if (n && (!keys || !amps)) return fail(SIM_E_ARG, "null import arrays");
-  std::vector<uint64_t> lo(n), hi(n);
-  for (uint64_t i = 0; i < n; ++i) {
-    if (!key_in_range(s, keys[i].lo, keys[i].hi)) return fail(SIM_E_ARG, "import key has bits above n_qubits");
-    lo[i] = keys[i].lo;
-    hi[i] = keys[i].hi;
-  }
-  {
-    std::vector<sim_key> sorted(keys, keys + n);
-    std::sort(sorted.begin(), sorted.end(), [](const sim_key& a, const sim_key& b) {
-      return a.hi != b.hi ? a.hi < b.hi : a.lo < b.lo;
-    });
-    for (uint64_t i = 1; i < n; ++i)
-      if (sorted[i].lo == sorted[i - 1].lo && sorted[i].hi == sorted[i - 1].hi)
-        return fail(SIM_E_ARG, "duplicate key in import");
-  }
+  if (n && (!lo || !amps)) return fail(SIM_E_ARG, "null import arrays");
+  if (int rc = drop_built(s)) return rc;   // (left by a call that failed)
+  // Into the other buffer, which becomes the state's once the labels have
+  // proved distinct and in range.
+  const int to = s->cur ^ 1;
+  const Buf& b = s->buf[to];
+  const uint32_t q = s->cfg.n_qubits;
+  const uint64_t out_lo = q < 64 ? ~0ull << q : 0ull, out_hi = q <= 64 ? ~0ull : q < 128 ? ~0ull << (q - 64) : 0ull;
+  LabelCell seen;
+  HIP_TRY(copy_state_to_device(lo, hi, stride, amps, n, out_lo, out_hi, b, s->wide, s->stream, &seen));
+  if ((seen.or_lo & out_lo) || (seen.or_hi & out_hi)) return fail(SIM_E_ARG, "import key has bits above n_qubits");
+  const IndexTab t = index_tab(s, s->half);
+  auto* found = reinterpret_cast<TabCtl*>(s->h_pinned + 4);
+  launch_import_check(s->stream, s->wide, b, n, t, d_nnz(s, to));
+  HIP_TRY(hipGetLastError());
+  HIP_TRY(hipMemcpyAsync(found, t.tc, sizeof *found, hipMemcpyDeviceToHost, s->stream));
+  launch_index_empty(s->stream, t);
+  HIP_TRY(hipGetLastError());
   HIP_TRY(timed_sync(s));
-  const Buf& b = s->buf[s->cur];
-  if (n) {
-    HIP_TRY(hipMemcpy(b.key_lo, lo.data(), n * 8, hipMemcpyHostToDevice));
-    if (s->wide) HIP_TRY(hipMemcpy(b.key_hi, hi.data(), n * 8, hipMemcpyHostToDevice));
-    HIP_TRY(hipMemcpy(b.amp, amps, n * 16, hipMemcpyHostToDevice));
+  if (found->dup) {
+    found->dup = 0;
+    HIP_TRY(hipMemcpyAsync(&t.tc->dup, &found->dup, sizeof found->dup, hipMemcpyHostToDevice, s->stream));
+    HIP_TRY(timed_sync(s));
+    return fail(SIM_E_ARG, "duplicate key in import");
   }
-  s->h_pinned[2] = n;
-  HIP_TRY(hipMemcpyAsync(d_nnz(s, s->cur), s->h_pinned + 2, 8, hipMemcpyHostToDevice, s->stream));
-  HIP_TRY(timed_sync(s));
+  s->cur = to;
   s->nnz_known = true;
   s->nnz_exact = s->nnz_ub = n;
-  uint64_t and_lo = ~0ull, and_hi = ~0ull, or_lo = 0, or_hi = 0;
-  for (uint64_t i = 0; i < n; ++i) {
-    and_lo &= lo[i];
-    and_hi &= hi[i];
-    or_lo |= lo[i];
-    or_hi |= hi[i];
-  }
-  s->uni_lo = ~(and_lo ^ or_lo);   // bits equal in every imported label (all, for none)
-  s->uni_hi = ~(and_hi ^ or_hi);
+  s->uni_lo = ~(seen.and_lo ^ seen.or_lo);   // bits equal in every imported label
+  s->uni_hi = ~(seen.and_hi ^ seen.or_hi);
   return SIM_OK;
+}
+
+}  // namespace
+
+int sim_import_state(sim_t* s, const sim_key* keys, const sim_c64* amps, uint64_t n) {
+  return import_state(s, keys ? &keys->lo : nullptr, keys ? &keys->hi : nullptr, sizeof(sim_key) / 8, amps, n);
+}
+
+int sim_import_state_soa(sim_t* s, const uint64_t* key_lo, const uint64_t* key_hi, const sim_c64* amps, uint64_t n) {
+  return import_state(s, key_lo, key_hi, 1, amps, n);
 }
 
 namespace {
@@ -1600,11 +1605,13 @@ int sim_export_state(sim_t* s, sim_key* keys, sim_c64* amps, uint64_t cap, uint6
   if (!n) return SIM_OK;
   if (!keys || !amps) return fail(SIM_E_ARG, "null export arrays");
   const Buf& b = s->buf[s->cur];
-  HIP_TRY(copy_state_to_host(b.key_lo, s->wide ? b.key_hi : nullptr, b.amp, n, keys, amps));
+  HIP_TRY(copy_state_to_host(b.key_lo, s->wide ? b.key_hi : nullptr, b.amp, n, keys, amps, s->stream));
   return SIM_OK;
 }
 
-int sim_export_state_soa(sim_t* s, uint64_t* key_lo, uint64_t* key_hi, sim_c64* amps, uint64_t cap, uint64_t* nnz) {
+namespace {
+
+int export_soa(sim_t* s, uint64_t* key_lo, uint64_t* key_hi, sim_c64* amps, uint64_t cap, uint64_t* nnz, bool sorted) {
   if (!s || !nnz) return fail(SIM_E_ARG, "null argument");
   uint64_t n;
   int rc = read_nnz(s, &n);
@@ -1613,9 +1620,27 @@ int sim_export_state_soa(sim_t* s, uint64_t* key_lo, uint64_t* key_hi, sim_c64* 
   if (cap < n) return fail(SIM_E_BUFFER, "export buffer smaller than nnz");
   if (!n) return SIM_OK;
   if (!key_lo || !amps) return fail(SIM_E_ARG, "null export arrays");
-  const Buf& b = s->buf[s->cur];
-  HIP_TRY(copy_state_to_host_soa(b.key_lo, s->wide ? b.key_hi : nullptr, b.amp, n, key_lo, key_hi, amps));
+  Buf b = s->buf[s->cur];
+  if (sorted && n > 1) {
+    // In the other buffer, which holds nothing between calls.  The partner
+    // array is scratch: the words written (below 2^31) are no gate's mark.
+    const Buf to = s->buf[s->cur ^ 1];
+    launch_sort_state(s->stream, s->wide, b, to, n, s->partner);
+    HIP_TRY(hipGetLastError());
+    b = to;
+  }
+  HIP_TRY(copy_state_to_host_soa(b.key_lo, s->wide ? b.key_hi : nullptr, b.amp, n, key_lo, key_hi, amps, s->stream));
   return SIM_OK;
+}
+
+}  // namespace
+
+int sim_export_state_soa(sim_t* s, uint64_t* key_lo, uint64_t* key_hi, sim_c64* amps, uint64_t cap, uint64_t* nnz) {
+  return export_soa(s, key_lo, key_hi, amps, cap, nnz, false);
+}
+
+int sim_export_state_sorted(sim_t* s, uint64_t* key_lo, uint64_t* key_hi, sim_c64* amps, uint64_t cap, uint64_t* nnz) {
+  return export_soa(s, key_lo, key_hi, amps, cap, nnz, true);
 }
 
 int sim_device_state(sim_t* s, uint64_t** key_lo, uint64_t** key_hi, double** amp, uint64_t** dn) {

@@ -203,7 +203,7 @@ struct U2Desc {
 struct TabCtl {
   uint32_t mask, bits;         // slots - 1 (0: nothing used); index bits of a slot
   uint32_t nopair;             // the gate is known to have no partners: nothing was indexed
-  uint32_t pad;
+  uint32_t dup;                // an import met two equal labels (0 between calls)
 };
 
 // Accumulators that every block of a kernel adds to.  Atomics on one address
@@ -389,12 +389,26 @@ hipError_t mono_rp_init();
 // n entries of a device state (key_lo, key_hi or null for <= 64 qubits, amp)
 // into host key records and amplitudes, through the calling thread's pinned
 // staging buffer; safe to call from several host threads at once.
+// On stream st, which it waits for.
 hipError_t copy_state_to_host(const uint64_t* lo, const uint64_t* hi, const double2* amp, uint64_t n, sim_key* keys,
-                              sim_c64* amps);
+                              sim_c64* amps, hipStream_t st);
 // The same into separate arrays (key_hi may be null: high words not wanted;
 // zeros are written for a null hi).
 hipError_t copy_state_to_host_soa(const uint64_t* lo, const uint64_t* hi, const double2* amp, uint64_t n,
-                                  uint64_t* key_lo, uint64_t* key_hi, sim_c64* amps);
+                                  uint64_t* key_lo, uint64_t* key_hi, sim_c64* amps, hipStream_t st);
+// n host entries (label words every `stride` words; hi may be null: zeros)
+// into the device arrays b, through the same staging; seen: the AND and OR of
+// the labels.  Returns early, without the rest of the copy,
+// when a label has a bit of out_lo / out_hi (the caller looks at `seen`).
+// The last chunk is left in flight on st.
+hipError_t copy_state_to_device(const uint64_t* lo, const uint64_t* hi, size_t stride, const sim_c64* amps, uint64_t n,
+                                uint64_t out_lo, uint64_t out_hi, Buf b, bool wide, hipStream_t st, LabelCell* seen);
+// The n entries of `in` into `out`, in ascending order of (hi, lo).  idx: n
+// words of scratch.
+void launch_sort_state(hipStream_t st, bool wide, Buf in, Buf out, uint64_t n, uint32_t* idx);
+// Index all n labels of b; t.tc->dup is set when two are equal.  n also goes
+// to *nnz_out.
+void launch_import_check(hipStream_t st, bool wide, Buf b, uint64_t n, const IndexTab& t, uint64_t* nnz_out);
 void launch_fill(hipStream_t st, uint64_t* p, uint64_t v, uint64_t n);
 void launch_copy16(hipStream_t st, void* dst, const void* src, uint64_t n16);
 // m: the run applied on the way.  counting: count the work in Ctl::ix.

@@ -1,5 +1,6 @@
 // Copy of a device state (structure of arrays) to host records, shared by
-// state export (sim_export_state) and the server's result copies.
+// state export (sim_export_state) and the server's result copies, and of host
+// records to a device state (sim_import_state).
 //
 // A device-to-host copy into pageable memory goes through the runtime's own
 // staging and serialises across host threads; here each calling thread owns a
@@ -20,6 +21,9 @@ namespace sparsesim {
 namespace {
 
 constexpr size_t kStageBytes = 16u << 20;   // per host thread, kept for the process's lifetime
+// Entries a task of the host pool takes at least: half a megabyte, 50 us or
+// more (fresh pages of the caller's arrays included) against 10 to wake it.
+constexpr size_t kPart = 1u << 14;
 
 struct Stage {
   char* p = nullptr;
@@ -46,7 +50,8 @@ namespace {
 // Chunks of the state through the staging buffer; emit(b, m, s_lo, s_hi,
 // s_amp, pb, pe) writes entries [pb, pe) of the chunk that starts at entry b.
 template <class Emit>
-hipError_t staged_copy(const uint64_t* lo, const uint64_t* hi, const double2* amp, uint64_t n, Emit&& emit) {
+hipError_t staged_copy(const uint64_t* lo, const uint64_t* hi, const double2* amp, uint64_t n, hipStream_t st,
+                       Emit&& emit) {
   if (!n) return hipSuccess;
   char* stage = nullptr;
   hipError_t e = stage_of_thread(&stage);
@@ -58,13 +63,15 @@ hipError_t staged_copy(const uint64_t* lo, const uint64_t* hi, const double2* am
     auto* s_lo = reinterpret_cast<const uint64_t*>(stage);
     auto* s_hi = reinterpret_cast<const uint64_t*>(stage + 8 * m);
     auto* s_amp = reinterpret_cast<const double2*>(stage + (hi ? 16 : 8) * m);
-    e = hipMemcpy(stage, lo + b, 8 * m, hipMemcpyDeviceToHost);
-    if (e == hipSuccess && hi) e = hipMemcpy(stage + 8 * m, hi + b, 8 * m, hipMemcpyDeviceToHost);
-    if (e == hipSuccess) e = hipMemcpy(const_cast<double2*>(s_amp), amp + b, 16 * m, hipMemcpyDeviceToHost);
+    e = hipMemcpyAsync(stage, lo + b, 8 * m, hipMemcpyDeviceToHost, st);
+    if (e == hipSuccess && hi) e = hipMemcpyAsync(stage + 8 * m, hi + b, 8 * m, hipMemcpyDeviceToHost, st);
+    if (e == hipSuccess) e = hipMemcpyAsync(const_cast<double2*>(s_amp), amp + b, 16 * m, hipMemcpyDeviceToHost, st);
+    const hipError_t done = hipStreamSynchronize(st);   // (also after an error: the stage is used again)
+    if (e == hipSuccess) e = done;
     if (e != hipSuccess) return e;
     // On the host thread pool (on this thread alone when it is itself one of
     // the pool's tasks).
-    parallel_parts(m, 1u << 16, [&](size_t pb, size_t pe, size_t) { emit(b, s_lo, hi ? s_hi : nullptr, s_amp, pb, pe); });
+    parallel_parts(m, kPart, [&](size_t pb, size_t pe, size_t) { emit(b, s_lo, hi ? s_hi : nullptr, s_amp, pb, pe); });
   }
   return hipSuccess;
 }
@@ -72,8 +79,8 @@ hipError_t staged_copy(const uint64_t* lo, const uint64_t* hi, const double2* am
 }  // namespace
 
 hipError_t copy_state_to_host(const uint64_t* lo, const uint64_t* hi, const double2* amp, uint64_t n, sim_key* keys,
-                              sim_c64* amps) {
-  return staged_copy(lo, hi, amp, n,
+                              sim_c64* amps, hipStream_t st) {
+  return staged_copy(lo, hi, amp, n, st,
                      [&](uint64_t b, const uint64_t* s_lo, const uint64_t* s_hi, const double2* s_amp, size_t pb, size_t pe) {
                        for (size_t k = pb; k < pe; ++k) keys[b + k] = sim_key{s_lo[k], s_hi ? s_hi[k] : 0};
                        std::memcpy(amps + b + pb, s_amp + pb, 16 * (pe - pb));
@@ -81,8 +88,8 @@ hipError_t copy_state_to_host(const uint64_t* lo, const uint64_t* hi, const doub
 }
 
 hipError_t copy_state_to_host_soa(const uint64_t* lo, const uint64_t* hi, const double2* amp, uint64_t n,
-                                  uint64_t* key_lo, uint64_t* key_hi, sim_c64* amps) {
-  return staged_copy(lo, hi, amp, n,
+                                  uint64_t* key_lo, uint64_t* key_hi, sim_c64* amps, hipStream_t st) {
+  return staged_copy(lo, hi, amp, n, st,
                      [&](uint64_t b, const uint64_t* s_lo, const uint64_t* s_hi, const double2* s_amp, size_t pb, size_t pe) {
                        std::memcpy(key_lo + b + pb, s_lo + pb, 8 * (pe - pb));
                        if (key_hi) {
@@ -91,6 +98,54 @@ hipError_t copy_state_to_host_soa(const uint64_t* lo, const uint64_t* hi, const 
                        }
                        std::memcpy(amps + b + pb, s_amp + pb, 16 * (pe - pb));
                      });
+}
+
+hipError_t copy_state_to_device(const uint64_t* lo, const uint64_t* hi, size_t stride, const sim_c64* amps, uint64_t n,
+                                uint64_t out_lo, uint64_t out_hi, Buf b, bool wide, hipStream_t st, LabelCell* seen) {
+  *seen = LabelCell{~0ull, ~0ull, 0, 0};
+  if (!n) return hipSuccess;
+  char* stage = nullptr;
+  hipError_t e = stage_of_thread(&stage);
+  if (e != hipSuccess) return e;
+  const size_t per_entry = wide ? 32 : 24;
+  const uint64_t chunk = kStageBytes / per_entry;
+  for (uint64_t c = 0; c < n; c += chunk) {
+    const uint64_t m = std::min<uint64_t>(chunk, n - c);
+    auto* s_lo = reinterpret_cast<uint64_t*>(stage);
+    auto* s_hi = reinterpret_cast<uint64_t*>(stage + 8 * m);
+    char* s_amp = stage + (wide ? 16 : 8) * m;
+    LabelCell part[HostPool::kMaxThreads];
+    for (LabelCell& p : part) p = LabelCell{~0ull, ~0ull, 0, 0};
+    parallel_parts(m, kPart, [&](size_t pb, size_t pe, size_t t) {
+      LabelCell v{~0ull, ~0ull, 0, 0};
+      for (size_t k = pb; k < pe; ++k) {
+        const sim_key q{lo[(c + k) * stride], hi ? hi[(c + k) * stride] : 0};
+        v.and_lo &= q.lo;
+        v.and_hi &= q.hi;
+        v.or_lo |= q.lo;
+        v.or_hi |= q.hi;
+        s_lo[k] = q.lo;
+        if (wide) s_hi[k] = q.hi;
+      }
+      std::memcpy(s_amp + 16 * pb, amps + c + pb, 16 * (pe - pb));
+      part[t] = v;
+    });
+    for (const LabelCell& p : part) {
+      seen->and_lo &= p.and_lo;
+      seen->and_hi &= p.and_hi;
+      seen->or_lo |= p.or_lo;
+      seen->or_hi |= p.or_hi;
+    }
+    if ((seen->or_lo & out_lo) || (seen->or_hi & out_hi)) return hipSuccess;
+    e = hipMemcpyAsync(b.key_lo + c, s_lo, 8 * m, hipMemcpyHostToDevice, st);
+    if (e == hipSuccess && wide) e = hipMemcpyAsync(b.key_hi + c, s_hi, 8 * m, hipMemcpyHostToDevice, st);
+    if (e == hipSuccess) e = hipMemcpyAsync(b.amp + c, s_amp, 16 * m, hipMemcpyHostToDevice, st);
+    // The stage is used again by the next chunk; after the last one the caller waits.
+    const hipError_t done = c + m < n || e != hipSuccess ? hipStreamSynchronize(st) : hipSuccess;
+    if (e == hipSuccess) e = done;
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 }  // namespace sparsesim

@@ -84,6 +84,7 @@ def _load():
         "sim_destroy": (i32, [vp]),
         "sim_set_basis": (i32, [vp, sim_key]),
         "sim_import_state": (i32, [vp, vp, vp, u64]),
+        "sim_import_state_soa": (i32, [vp, vp, vp, vp, u64]),
         "sim_gates_from_ops": (i32, [vp, sz, vp]),
         "sim_commute_ops": (i32, [vp, sz, ctypes.c_uint32, vp, sz, ctypes.POINTER(sz)]),
         "sim_gates_from_pauli": (i32, [vp, sz, ctypes.c_uint32, vp, sz, ctypes.POINTER(sz)]),
@@ -96,6 +97,7 @@ def _load():
         "sim_sync": (i32, [vp]),
         "sim_export_state": (i32, [vp, vp, vp, u64, ctypes.POINTER(u64)]),
         "sim_export_state_soa": (i32, [vp, vp, vp, vp, u64, ctypes.POINTER(u64)]),
+        "sim_export_state_sorted": (i32, [vp, vp, vp, vp, u64, ctypes.POINTER(u64)]),
         "sim_device_state": (i32, [vp, vp, vp, vp, vp]),
         "sim_set_tuning": (i32, [vp, vp]),
         "sim_device_copy": (i32, [vp, vp, sz, vp]),
@@ -152,10 +154,19 @@ def sim_set_basis(h, lo: int = 0, hi: int = 0):
 
 
 def sim_import_state(h, lo, hi, amp):
-    keys = np.empty(len(lo), KEY_DTYPE)
+    if all(isinstance(x, np.ndarray) and x.dtype == np.uint64 and x.shape == (len(lo),) for x in (lo, hi)):
+        return sim_import_state_soa(h, lo, hi, amp)
+    keys = np.empty(len(lo), KEY_DTYPE)   # anything that can be assigned to them
     keys["lo"], keys["hi"] = lo, hi
     amp = np.ascontiguousarray(amp, dtype=np.complex128)
     _check(_lib.sim_import_state(h, _ptr(keys), _ptr(amp), len(keys)), "sim_import_state")
+
+
+def sim_import_state_soa(h, lo, hi, amp):
+    """lo, hi: arrays of label words, passed as they are."""
+    lo, hi = np.ascontiguousarray(lo, dtype=np.uint64), np.ascontiguousarray(hi, dtype=np.uint64)
+    amp = np.ascontiguousarray(amp, dtype=np.complex128)
+    _check(_lib.sim_import_state_soa(h, _ptr(lo), _ptr(hi), _ptr(amp), len(lo)), "sim_import_state")
 
 
 def sim_gates_from_ops(ops: np.ndarray) -> np.ndarray:
@@ -269,15 +280,23 @@ def sim_export_state(h, sort: bool = True):
 
 def sim_export_state_soa(h, sort: bool = True):
     """(lo, hi, amp) numpy arrays; sorted ascending by (hi, lo) when sort."""
+    if sort:
+        return sim_export_state_sorted(h)
+    return _export(h, _lib.sim_export_state_soa, "sim_export_state_soa")
+
+
+def sim_export_state_sorted(h):
+    """(lo, hi, amp) numpy arrays in ascending order of (hi, lo), sorted on the device."""
+    return _export(h, _lib.sim_export_state_sorted, "sim_export_state_sorted")
+
+
+def _export(h, call, name):
     n = sim_nnz(h)
     lo, hi = np.empty(n, np.uint64), np.empty(n, np.uint64)
     amp = np.empty(n, np.complex128)
     got = ctypes.c_uint64()
-    _check(_lib.sim_export_state_soa(h, _ptr(lo), _ptr(hi), _ptr(amp), n, ctypes.byref(got)), "sim_export_state_soa")
+    _check(call(h, _ptr(lo), _ptr(hi), _ptr(amp), n, ctypes.byref(got)), name)
     assert got.value == n
-    if sort:
-        order = np.lexsort((lo, hi))
-        lo, hi, amp = lo[order], hi[order], amp[order]
     return lo, hi, amp
 
 
