@@ -53,6 +53,8 @@ struct RunCompiler {
   // to out; the run constants of br (from run_params) take the phase the
   // rewrite of uncontrolled X gates moves into them.
   void group(size_t begin, size_t len, std::vector<BsGroup>& out, BsRun* br) const;
+  // The bit-sliced ops of MONO ops [begin, begin+len) as defer_x leaves them; br as for group().
+  void rewrite(size_t begin, size_t len, std::vector<BsOp>& out, BsRun* br) const;
   // The ops with uncontrolled X gates carried to the end of the run, and the
   // eighth turns and turns that become run constants.
   void defer_x(const BsOp* in, uint32_t n, std::vector<BsOp>& out, uint32_t* d_omega, uint64_t* d_turn) const;

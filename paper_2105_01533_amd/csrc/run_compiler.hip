@@ -94,6 +94,11 @@ uint64_t turn_of(const double2& m) {
 uint8_t word_bit(uint32_t q) { return (uint8_t)(1u << (q >> 5)); }
 
 constexpr unsigned kHostThreads = HostPool::kMaxThreads;
+// Ops that a host thread compiles (25 ns each) or schedules and packs (100 ns
+// each) at least: 50 to 100 us of work, where waking the pool takes 10.  Cutting a
+// run costs the kernel the segments that would have reached over the cut: one
+// block in 60 at 24 qubits.
+constexpr size_t kCompilePart = 2048, kSchedulePart = 1024;
 
 }  // namespace
 
@@ -177,7 +182,7 @@ void RunCompiler::compile(uint32_t nq) {
   part_ops.resize(kHostThreads);
   for (auto& v : part_ops) v.clear();
   std::vector<size_t> pb(kHostThreads, 0), pe(kHostThreads, 0);
-  parallel_parts(n_mono, 16384, [&](size_t b, size_t e, size_t p) {
+  parallel_parts(n_mono, kCompilePart, [&](size_t b, size_t e, size_t p) {
     // Appends go to a vector on this thread's stack (neighbouring vectors in
     // part_ops share cache lines); its storage is kept in part_ops between calls.
     std::vector<BsOp> out;
@@ -237,9 +242,8 @@ bool RunCompiler::run_params(size_t begin, size_t len, uint32_t mono_mode, uint3
 // controls are preferred, because the kernel reads only those planes for them.
 // Large runs are grouped in parts on host threads (ops never move between
 // parts, so the parts' groups concatenate in order).
-void RunCompiler::group(size_t begin, size_t len, std::vector<BsGroup>& out, BsRun* br) const {
+void RunCompiler::rewrite(size_t begin, size_t len, std::vector<BsOp>& xo, BsRun* br) const {
   const uint32_t i0 = start[begin], i1 = start[begin + len];
-  std::vector<BsOp> xo;
   uint32_t d_omega = 0;
   uint64_t d_turn = 0;
   defer_x(ops.data() + i0, i1 - i0, xo, &d_omega, &d_turn);
@@ -247,6 +251,11 @@ void RunCompiler::group(size_t begin, size_t len, std::vector<BsGroup>& out, BsR
     br->g_omega = (br->g_omega + d_omega) & 7u;
     br->g_turn += d_turn;
   }
+}
+
+void RunCompiler::group(size_t begin, size_t len, std::vector<BsGroup>& out, BsRun* br) const {
+  std::vector<BsOp> xo;
+  rewrite(begin, len, xo, br);
   const uint32_t n = (uint32_t)xo.size();
   const size_t g0 = out.size();
   if (n < 2 * 2048) {
@@ -500,66 +509,49 @@ void RunCompiler::group_range(const BsOp* src, uint32_t n, std::vector<BsGroup>&
 // Eighth-turn ops conditioned on their target alone all commute, so a
 // segment of them is split by k into sub-segments (one add sequence each).
 void RunCompiler::schedule(size_t begin, size_t len, std::vector<RpRec>& out, BsRun* br) const {
-  const uint32_t i0 = start[begin], i1 = start[begin + len];
   std::vector<BsOp> xo;
-  uint32_t d_omega = 0;
-  uint64_t d_turn = 0;
-  defer_x(ops.data() + i0, i1 - i0, xo, &d_omega, &d_turn);
-  if (br) {
-    br->g_omega = (br->g_omega + d_omega) & 7u;
-    br->g_turn += d_turn;
-  }
+  rewrite(begin, len, xo, br);
   const uint32_t n = (uint32_t)xo.size();
-  if (n < 2 * 2048) {
-    schedule_range(xo.data(), n, out);
-  } else {
-    std::vector<std::vector<RpRec>> parts(kHostThreads);
-    parallel_parts(n, 2048, [&](size_t b, size_t e, size_t p) {
-      std::vector<RpRec> mine;
-      schedule_range(xo.data() + b, (uint32_t)(e - b), mine);
-      parts[p].swap(mine);
-    });
-    for (auto& v : parts) out.insert(out.end(), v.begin(), v.end());
-  }
+  std::vector<std::vector<RpRec>> parts(kHostThreads);
+  parallel_parts(n, kSchedulePart, [&](size_t b, size_t e, size_t p) {
+    std::vector<RpRec> mine;   // (the parts' vectors share cache lines)
+    schedule_range(xo.data() + b, (uint32_t)(e - b), mine);
+    parts[p].swap(mine);
+  });
+  for (auto& v : parts) out.insert(out.end(), v.begin(), v.end());
 }
 
 void RunCompiler::schedule_range(const BsOp* src, uint32_t n, std::vector<RpRec>& out) const {
   const uint32_t ones = n_qubits, scratch = n_qubits + 1, zero = n_qubits + 2;
-  struct Mask {
-    uint64_t lo = 0, hi = 0;
-    void set(uint32_t q) { (q < 64 ? lo : hi) |= 1ull << (q & 63); }
-    bool meets(const Mask& o) const { return ((lo & o.lo) | (hi & o.hi)) != 0; }
-    void add(const Mask& o) {
-      lo |= o.lo;
-      hi |= o.hi;
-    }
-  };
-  struct Item {
-    Mask r, w;
-    uint32_t shape;   // kRpF1..F3, kRpOB (any k), kRpOG, kRpTB, kRpTG
-  };
   if (n == 0) return;
-  std::vector<Item> items(n);
-  std::vector<uint32_t> nxt(n + 1), prv(n + 1);
+  // Pending ops as a linked list in op order: link[0] is the first one's
+  // number + 1, link[j + 1] that of the one after op j (0: none).  Words an op
+  // reads and writes (a flip also reads what it writes), and its shape.
+  struct Item {
+    uint64_t r[2], w[2];
+    uint32_t shape, next;
+  };
+  std::vector<Item> items(n + 1);
+  uint64_t written[2] = {0, 0}, tested[2] = {0, 0};   // by any flip; by any phase op
   for (uint32_t i = 0; i < n; ++i) {
     const BsOp& o = src[i];
-    Item& it = items[i];
-    for (int c = 0; c < o.nctrl; ++c) it.r.set(o.ctrl[c]);
-    if (o.cmode || o.op == kBsFlip) it.r.set(o.target);
-    if (o.op == kBsFlip) it.w.set(o.target);
+    Item& it = items[i + 1];
+    it = Item{{0, 0}, {0, 0}, 0, i + 2};
+    auto set = [](uint64_t (&m)[2], uint32_t q) { m[q >> 6] |= 1ull << (q & 63); };
+    for (int c = 0; c < o.nctrl; ++c) set(it.r, o.ctrl[c]);
+    if (o.cmode || o.op == kBsFlip) set(it.r, o.target);
+    if (o.op == kBsFlip) set(it.w, o.target);
+    for (int h = 0; h < 2; ++h) {
+      written[h] |= it.w[h];
+      if (o.op != kBsFlip) tested[h] |= it.r[h];
+    }
     const bool bare = o.nctrl == 0 && o.cmode;
     it.shape = o.op == kBsFlip    ? (o.nctrl <= 1 ? kRpF1 : o.nctrl == 2 ? kRpF2 : kRpF3)
                : o.op == kBsOmega ? (bare ? kRpOB : kRpOG)
                                   : (bare ? kRpTB : kRpTG);
-    nxt[i] = i + 1;
-    prv[i + 1] = i;
   }
-  prv[0] = n;
-  nxt[n] = 0;
-  auto unlink = [&](uint32_t j) {
-    nxt[prv[j]] = nxt[j];
-    prv[nxt[j]] = prv[j];
-  };
+  items[n].next = 0;
+  items[0].next = 1;
   // A condition word: the target (or all-ones) plane and three control slots.
   auto cond_word = [&](const BsOp& o) {
     uint32_t c[3] = {ones, ones, ones};
@@ -578,26 +570,41 @@ void RunCompiler::schedule_range(const BsOp* src, uint32_t n, std::vector<RpRec>
       out.push_back(r);
     }
   };
-  constexpr uint32_t kWindow = 256;
-  std::vector<uint32_t> sel, words;
-  sel.reserve(kWindow);
+  // (Twice the window: 1 % fewer segments, no fewer blocks, 15 % more time.)
+  constexpr uint32_t kWindow = 128;
+  uint32_t sel[kWindow + 1];
+  std::vector<uint32_t> words;
   words.reserve(kWindow);
-  while (nxt[n] != n) {
-    const uint32_t shape = items[nxt[n]].shape;
-    sel.clear();
-    Mask br, bw;   // reads / writes of the pending ops passed over
-    uint32_t seen = 0;
-    for (uint32_t j = nxt[n]; j != n && seen < kWindow; j = nxt[j], ++seen) {
+  while (items[0].next) {
+    const uint32_t shape = items[items[0].next].shape;
+    const bool flips = shape == kRpF1 || shape == kRpF2 || shape == kRpF3;
+    // Planes touched, and planes written, by the pending ops passed over.  No
+    // op joins any more once the planes that its kind writes (a flip) or tests
+    // (a phase op) are all among them: on few qubits that is within some tens
+    // of ops.
+    uint64_t br[2] = {0, 0}, bw[2] = {0, 0};
+    uint32_t ns = 0, last = 0;
+    for (uint32_t j = items[0].next, seen = 0; j && seen < kWindow; ++seen) {
       const Item& it = items[j];
-      if (it.shape == shape && !it.w.meets(br) && !it.w.meets(bw) && !it.r.meets(bw)) {
-        sel.push_back(j);
+      const uint64_t clash = (it.w[0] & br[0]) | (it.w[1] & br[1]) | (it.r[0] & bw[0]) | (it.r[1] & bw[1]);
+      const bool in = it.shape == shape && clash == 0;
+      const uint64_t pass = in ? 0 : ~0ull;
+      sel[ns] = j - 1;
+      ns += in;
+      const uint32_t next = it.next;
+      if (in) {
+        items[last].next = next;   // out of the list
       } else {
-        br.add(it.r);
-        bw.add(it.w);
+        last = j;
+        br[0] |= it.r[0] & pass;
+        br[1] |= it.r[1] & pass;
+        bw[0] |= it.w[0] & pass;
+        bw[1] |= it.w[1] & pass;
+        const uint64_t left = flips ? (written[0] & ~br[0]) | (written[1] & ~br[1]) : (tested[0] & ~bw[0]) | (tested[1] & ~bw[1]);
+        if (!left) break;
       }
+      j = next;
     }
-    for (uint32_t j : sel) unlink(j);
-    const uint32_t ns = (uint32_t)sel.size();
     if (shape == kRpTB || shape == kRpTG) {
       const uint32_t ng = (ns + 3) / 4;
       header(shape, ng);
@@ -637,15 +644,15 @@ void RunCompiler::schedule_range(const BsOp* src, uint32_t n, std::vector<RpRec>
       // All commute: one sub-segment per k (padding ops read the zero plane).
       for (uint32_t k = 1; k < 8; ++k) {
         words.clear();
-        for (uint32_t j : sel)
-          if (((uint32_t)src[j].arg & 7u) == k) words.push_back(src[j].target);
+        for (uint32_t q = 0; q < ns; ++q)
+          if (((uint32_t)src[sel[q]].arg & 7u) == k) words.push_back(src[sel[q]].target);
         if (!words.empty()) word_quads(kRpOB + k, words, zero);
       }
       continue;
     }
     words.clear();
-    for (uint32_t j : sel) {
-      const BsOp& o = src[j];
+    for (uint32_t k = 0; k < ns; ++k) {
+      const BsOp& o = src[sel[k]];
       uint32_t c[3] = {ones, ones, ones};
       for (int q = 0; q < o.nctrl; ++q) c[q] = o.ctrl[q];
       words.push_back((uint32_t)o.target | c[0] << 8 | c[1] << 16 | c[2] << 24);
@@ -796,9 +803,8 @@ class BlockWriter {
   std::vector<uint64_t> tau_;
 };
 
-}  // namespace
-
-void RunCompiler::encode_program(const std::vector<RpRec>& recs, uint32_t nq, std::vector<RpBlock>& out) {
+// The blocks of some segments, without an END block.
+void encode_segments(const std::vector<RpRec>& recs, uint32_t nq, std::vector<RpBlock>& out) {
   BlockWriter w(nq, out);
   const uint32_t scratch = nq + 1, zero = nq + 2;
   std::vector<uint16_t> t, s;
@@ -883,13 +889,34 @@ void RunCompiler::encode_program(const std::vector<RpRec>& recs, uint32_t nq, st
     }
   }
   w.flush_turns();
-  w.exit(kRpEnd, 0);
+  w.flush_flips();
+}
+
+void end_program(uint32_t nq, std::vector<RpBlock>& out) { BlockWriter(nq, out).exit(kRpEnd, 0); }
+
+}  // namespace
+
+void RunCompiler::encode_program(const std::vector<RpRec>& recs, uint32_t nq, std::vector<RpBlock>& out) {
+  encode_segments(recs, nq, out);
+  end_program(nq, out);
 }
 
 void RunCompiler::program(size_t begin, size_t len, std::vector<RpBlock>& out, BsRun* br) const {
-  std::vector<RpRec> recs;
-  schedule(begin, len, recs, br);
-  encode_program(recs, n_qubits, out);
+  std::vector<BsOp> xo;
+  rewrite(begin, len, xo, br);
+  std::vector<std::vector<RpBlock>> parts(kHostThreads);
+  parallel_parts(xo.size(), kSchedulePart, [&](size_t b, size_t e, size_t p) {
+    std::vector<RpRec> recs;
+    std::vector<RpBlock> mine;
+    schedule_range(xo.data() + b, (uint32_t)(e - b), recs);
+    encode_segments(recs, n_qubits, mine);
+    parts[p].swap(mine);
+  });
+  size_t total = out.size() + 1;
+  for (const auto& v : parts) total += v.size();
+  out.reserve(total);
+  for (const auto& v : parts) out.insert(out.end(), v.begin(), v.end());
+  end_program(n_qubits, out);
 }
 
 }  // namespace sparsesim

@@ -32,6 +32,10 @@ using namespace sparsesim;
 
 namespace {
 
+// Gates a host thread converts, validates or describes at least (10 to 20 ns
+// each, where waking the pool takes 10 us).
+constexpr size_t kGatePart = 4096;
+
 thread_local std::string g_last_error;
 
 int fail(int code, const std::string& msg) {
@@ -828,7 +832,7 @@ bool convert_op(const sim_op& o, sim_gate& out) {
 int sim_gates_from_ops(const sim_op* ops, size_t n, sim_gate* out) {
   if (n && (!ops || !out)) return fail(SIM_E_ARG, "null op arrays");
   std::vector<size_t> bad(HostPool::kMaxThreads, SIZE_MAX);
-  parallel_parts(n, 16384, [&](size_t b, size_t e, size_t p) {
+  parallel_parts(n, kGatePart, [&](size_t b, size_t e, size_t p) {
     for (size_t i = b; i < e; ++i)
       if (!convert_op(ops[i], out[i])) {
         bad[p] = i;
@@ -907,7 +911,7 @@ int apply_impl(sim_t* s, const sim_gate* gates, size_t n, int32_t* outcomes, sim
     // classes and build the phase/permutation descriptors, on the host pool.
     std::vector<size_t> bad(HostPool::kMaxThreads, SIZE_MAX), pm(HostPool::kMaxThreads + 1, 0),
         pmeas(HostPool::kMaxThreads, 0);
-    parallel_parts(n, 16384, [&](size_t b, size_t e, size_t p) {
+    parallel_parts(n, kGatePart, [&](size_t b, size_t e, size_t p) {
       std::string why;
       size_t mono = 0, meas = 0;   // counted locally: the shared arrays are written once per part
       for (size_t i = b; i < e; ++i) {
@@ -929,7 +933,7 @@ int apply_impl(sim_t* s, const sim_gate* gates, size_t n, int32_t* outcomes, sim
     }
     n_mono = pm[HostPool::kMaxThreads];
     s->rc.descs.resize(n_mono);
-    parallel_parts(n, 16384, [&](size_t b, size_t e, size_t p) {
+    parallel_parts(n, kGatePart, [&](size_t b, size_t e, size_t p) {
       for (size_t i = b, k = pm[p]; i < e; ++i)
         if (gates[i].op == SIM_OP_MONO) s->rc.descs[k++] = mono_desc(gates[i]);
     });
