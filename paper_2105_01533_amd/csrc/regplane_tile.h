@@ -34,7 +34,7 @@
 // segments) of one wave; they take 11, 15 and 16 (2^16 entries).  Turn ops do
 // not break the stream either: their conditions are flipped into capture
 // planes and their fractions added eight at a time (random mix of 24 qubits: 68
-// ns per gate, 41 without the capture planes, 31 with them).
+// ns per gate, 41 without the capture planes, 26 with them).
 #pragma once
 #include "sim_internal.h"
 
@@ -103,21 +103,6 @@ __device__ __forceinline__ void wr_plane(uint32_t q, uint32_t v) {
       "s_set_gpr_idx_off" ::"s"(q),
       "v"(v)
       : "m0");
-}
-
-// A capture plane's content; the plane is emptied.
-__device__ __forceinline__ uint32_t take_plane(uint32_t q) {
-  uint32_t r;
-  asm volatile(
-      "s_set_gpr_idx_on %1, gpr_idx(SRC0)\n\t"
-      "v_mov_b32 %0, v100\n\t"
-      "s_set_gpr_idx_on %1, gpr_idx(DST)\n\t"
-      "v_mov_b32 v100, 0\n\t"
-      "s_set_gpr_idx_off"
-      : "=&v"(r)
-      : "s"(q)
-      : "m0");
-  return r;
 }
 
 #define RP_IN(R, X) asm volatile("v_mov_b32 v" #R ", %0" ::"v"(X))
@@ -299,16 +284,14 @@ __device__ __forceinline__ v2u words2(const Fetch& f, uint32_t off) {
   asm volatile("s_buffer_load_dwordx2 %0, %1, %2\n\ts_waitcnt lgkmcnt(0)" : "=&s"(r) : "s"(f.rs), "s"(off));
   return r;
 }
+// The fractions of captured ops: uniform, read through the constant address
+// space (scalar loads that the compiler waits for).
+typedef const __attribute__((address_space(4))) uint64_t* TurnPtr;
 // A turn group: cond words, fractions (words 0-3 and 4-11 of its block).
 struct TurnWords {
   v4u cond;
   v8u tau;
 };
-__device__ __forceinline__ v8u words8(const Fetch& f, uint32_t off) {
-  v8u r;
-  asm volatile("s_buffer_load_dwordx8 %0, %1, %2\n\ts_waitcnt lgkmcnt(0)" : "=&s"(r) : "s"(f.rs), "s"(off));
-  return r;
-}
 __device__ __forceinline__ TurnWords turn_words(const Fetch& f, uint32_t off) {
   TurnWords r;
   asm volatile("s_buffer_load_dwordx4 %0, %2, %3\n\ts_buffer_load_dwordx8 %1, %2, %4\n\ts_waitcnt lgkmcnt(0)"
@@ -343,90 +326,198 @@ __device__ __forceinline__ void omega_general(const Fetch& f, uint32_t nquads) {
 // ops 0..3).  Each entry's accumulator (LDS, acc[64 j + lane])
 // gains the sum of the fractions of the ops whose condition holds for it: per
 // group, one of 16 subset sums, kept in a 16-entry LDS table and read with
-// one 64-bit load per entry.  C groups share one read-modify-write of the
-// accumulators (C tables side by side), which is what bounds the pass on
-// LDS bandwidth.
-// FORM: kRpTB (condition = one plane), kRpTG (four) or kRpTC (captured planes
-// from plane `first` on; the fractions alone, four to 32 bytes).
-template <uint32_t FORM, int C>
-__device__ __forceinline__ void turn_chunk(const Fetch& f, uint32_t off, uint32_t first, uint64_t* acc, uint64_t* table,
-                                           int lane) {
-  uint32_t B[C][8];
+// one 64-bit load per entry.
+// FORM: kRpTB (condition = one plane) or kRpTG (four).
+template <uint32_t FORM>
+__device__ __forceinline__ void turn_group(const Fetch& f, uint32_t off, uint64_t* acc, uint64_t* table, int lane) {
+  uint32_t B[8];
+  const TurnWords tw = turn_words(f, off);
+  const uint32_t cw[4] = {tw.cond.x, tw.cond.y, tw.cond.z, tw.cond.w};
+  uint32_t x[4];
 #pragma unroll
-  for (int c = 0; c < C; ++c) {
-    TurnWords tw;
-    uint32_t x[4];
-    if (FORM == kRpTC) {
-      tw.tau = words8(f, off + 32u * c);
-#pragma unroll
-      for (int u = 0; u < 4; ++u) x[u] = take_plane(first + 4 * c + u);
-    } else {
-      tw = turn_words(f, off + 64u * c);
-      const uint32_t cw[4] = {tw.cond.x, tw.cond.y, tw.cond.z, tw.cond.w};
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        x[u] = rd_plane(cw[u]);
-        if (FORM == kRpTG) x[u] &= rd_plane(cw[u] >> 8) & rd_plane(cw[u] >> 16) & rd_plane(cw[u] >> 24);
-      }
-    }
-    uint64_t tau[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) tau[u] = ((uint64_t)tw.tau[2 * u + 1] << 32) | tw.tau[2 * u];
-    // Entry j's offset in table c, 8 x (the ops, bit u = op u, whose
-    // condition holds for it), is byte j >> 3 of B[c][j & 7]: bit j of x[u]
-    // moves to bit 8 (j >> 3) + 3 + u by one constant shift; the four merge
-    // under disjoint byte-lane masks.
-#pragma unroll
-    for (int w = 0; w < 8; ++w) {
-      uint32_t v = 0;
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int sh = w - 3 - u;
-        const uint32_t y = sh >= 0 ? x[u] >> sh : x[u] << -sh;
-        v |= y & (0x01010101u << (3 + u));
-      }
-      B[c][w] = v;
-    }
-    // Table entry m (lane m < 16) is the sum of the fractions named by m's
-    // bits.  (The lane number is made opaque here so that the four masks are
-    // formed where they are used, not kept live across the whole tile.)
-    int l = lane;
-    asm volatile("" : "+v"(l));
-    uint64_t S = 0;
-#pragma unroll
-    for (int u = 0; u < 4; ++u) S += tau[u] & (0ull - (uint64_t)((l >> u) & 1));
-    if (l < 16) table[16 * c + l] = S;   // the wave's LDS accesses complete in order
-    __builtin_amdgcn_sched_barrier(0);  // one group's planes at a time
+  for (int u = 0; u < 4; ++u) {
+    x[u] = rd_plane(cw[u]);
+    if (FORM == kRpTG) x[u] &= rd_plane(cw[u] >> 8) & rd_plane(cw[u] >> 16) & rd_plane(cw[u] >> 24);
   }
+  uint64_t tau[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) tau[u] = ((uint64_t)tw.tau[2 * u + 1] << 32) | tw.tau[2 * u];
+  // Entry j's offset in the table, 8 x (the ops, bit u = op u, whose
+  // condition holds for it), is byte j >> 3 of B[j & 7]: bit j of x[u]
+  // moves to bit 8 (j >> 3) + 3 + u by one constant shift; the four merge
+  // under disjoint byte-lane masks.
+#pragma unroll
+  for (int w = 0; w < 8; ++w) {
+    uint32_t v = 0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int sh = w - 3 - u;
+      const uint32_t y = sh >= 0 ? x[u] >> sh : x[u] << -sh;
+      v |= y & (0x01010101u << (3 + u));
+    }
+    B[w] = v;
+  }
+  // Table entry m (lane m < 16) is the sum of the fractions named by m's
+  // bits.  (The lane number is made opaque here so that the four masks are
+  // formed where they are used, not kept live across the whole tile.)
+  int l = lane;
+  asm volatile("" : "+v"(l));
+  uint64_t S = 0;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) S += tau[u] & (0ull - (uint64_t)((l >> u) & 1));
+  if (l < 16) table[l] = S;   // the wave's LDS accesses complete in order
+  __builtin_amdgcn_sched_barrier(0);
   const char* tb = reinterpret_cast<const char*>(table);
 #pragma unroll
   for (int j0 = 0; j0 < 32; j0 += 4) {
-    uint64_t a[4], v[C][4];
+    uint64_t a[4], v[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       const int j = j0 + k;
       a[k] = acc[64 * j + lane];
-#pragma unroll
-      for (int c = 0; c < C; ++c)
-        v[c][k] = *reinterpret_cast<const uint64_t*>(tb + 128 * c + __builtin_amdgcn_ubfe(B[c][j & 7], 8 * (j >> 3), 8));
+      v[k] = *reinterpret_cast<const uint64_t*>(tb + __builtin_amdgcn_ubfe(B[j & 7], 8 * (j >> 3), 8));
     }
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      uint64_t t = a[k];
-#pragma unroll
-      for (int c = 0; c < C; ++c) t += v[c][k];
-      acc[64 * (j0 + k) + lane] = t;
-    }
+    for (int k = 0; k < 4; ++k) acc[64 * (j0 + k) + lane] = a[k] + v[k];
     // Keep the blocks apart (otherwise every entry's table address is formed
     // up front, and they do not fit the registers).
     __builtin_amdgcn_sched_barrier(0);
   }
 }
 
+// Eight planes from q on.
+__device__ __forceinline__ void rd_planes8(uint32_t q, uint32_t (&x)[8]) {
+  asm volatile(
+      "s_set_gpr_idx_on %8, gpr_idx(SRC0)\n\t"
+      "v_mov_b32 %0, v100\n\tv_mov_b32 %1, v101\n\tv_mov_b32 %2, v102\n\tv_mov_b32 %3, v103\n\t"
+      "v_mov_b32 %4, v104\n\tv_mov_b32 %5, v105\n\tv_mov_b32 %6, v106\n\tv_mov_b32 %7, v107\n\t"
+      "s_set_gpr_idx_off"
+      : "=v"(x[0]), "=v"(x[1]), "=v"(x[2]), "=v"(x[3]), "=v"(x[4]), "=v"(x[5]), "=v"(x[6]), "=v"(x[7])
+      : "s"(q)
+      : "m0");
+}
+__device__ __forceinline__ void clear_planes8(uint32_t q) {
+  asm volatile(
+      "s_set_gpr_idx_on %0, gpr_idx(DST)\n\t"
+      "v_mov_b32 v100, 0\n\tv_mov_b32 v101, 0\n\tv_mov_b32 v102, 0\n\tv_mov_b32 v103, 0\n\t"
+      "v_mov_b32 v104, 0\n\tv_mov_b32 v105, 0\n\tv_mov_b32 v106, 0\n\tv_mov_b32 v107, 0\n\t"
+      "s_set_gpr_idx_off" ::"s"(q)
+      : "m0");
+}
+
+// Byte b of B[w]: bit u says that the condition x[u] holds for entry 8 b + 4 H
+// + w (an 8 x 8 bit transpose in each byte, Warren, Hacker's Delight, Sec. 7-3,
+// of which a half is needed).
+template <int H>
+__device__ __forceinline__ void turn_index(const uint32_t (&x)[8], uint32_t (&B)[4]) {
+  auto merge = [](uint32_t m, uint32_t p, uint32_t q) { return (p & m) | (q & ~m); };
+  uint32_t y[4], z[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+    y[k] = H ? merge(0x0f0f0f0fu, x[k] >> 4, x[k + 4]) : merge(0x0f0f0f0fu, x[k], x[k + 4] << 4);
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    z[k] = merge(0x33333333u, y[k], y[k + 2] << 2);
+    z[k + 2] = merge(0x33333333u, y[k] >> 2, y[k + 2]);
+  }
+#pragma unroll
+  for (int k = 0; k < 4; k += 2) {
+    B[k] = merge(0x55555555u, z[k], z[k + 1] << 1);
+    B[k + 1] = merge(0x55555555u, z[k] >> 1, z[k + 1]);
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k) asm volatile("" : "+v"(B[k]));   // (formed once, not per byte)
+}
+
+// Entry m of a table of 256: the sum of the fractions that m's bits name.
+__device__ __forceinline__ void turn_table(const uint64_t (&t)[8], uint64_t* table, int lane) {
+  int l = lane;
+  asm volatile("" : "+v"(l));   // (the bits' masks are formed here, not kept live)
+  uint64_t s = 0;
+#pragma unroll
+  for (int u = 0; u < 6; ++u) {
+    uint32_t m = (uint32_t)__builtin_amdgcn_sbfe(l, u, 1);
+    asm volatile("" : "+v"(m));   // (a mask and two ands, not a compare and two selects)
+    s += (uint64_t)((uint32_t)(t[u] >> 32) & m) << 32 | ((uint32_t)t[u] & m);
+    asm volatile("" : "+v"(s));   // (one fraction at a time: registers are short)
+  }
+  table[l] = s;   // the wave's LDS accesses complete in order
+  table[l + 64] = s + t[6];
+  table[l + 128] = s + t[7];
+  table[l + 192] = s + t[6] + t[7];
+}
+
+// Captured turn ops, ng groups of eight: op u of group g has its condition in
+// plane first + 8 g + u, its fraction at tau[8 g + u].  The 16 entries j (of
+// the lane's 32) with bit 2 of j equal to H, in registers over all groups; only
+// j < nj exist.  Per group an entry adds one of the 256 subset sums of its
+// fractions, read from LDS; while a group's sums are on their way the next
+// group's indices and table are made.  Two 16-entry tables and a
+// read-modify-write of LDS accumulators per group took 69 instructions an op
+// and 64 cycles of LDS, this takes 36 and 32.  Captures included, an Rz costs one
+// wave 110 ns on 24 qubits and 135 on 100 (24 capture planes), where it cost 197
+// and 190, and two waves of a SIMD 230 instead of 316; on 256 entries 56
+// instead of 196.  What is left is the latency of the tables (LDS, written and
+// read) and, with every flush of the capture planes, 0.5 us of leaving and
+// entering the interpreter.
+template <int H>
+__device__ __forceinline__ void captured_half(TurnPtr tau, uint32_t ng, uint32_t first, uint32_t nj, uint64_t* acc,
+                                              uint64_t* table, int lane) {
+  uint64_t a[16], t[8];
+  uint32_t x[8], B[4];
+#pragma unroll
+  for (int u = 0; u < 8; ++u) t[u] = tau[u];
+  rd_planes8(first, x);
+  turn_index<H>(x, B);
+  turn_table(t, table, lane);
+#pragma unroll
+  for (int i = 0; i < 16; ++i) a[i] = acc[64 * (8 * (i >> 2) + 4 * H + (i & 3)) + lane];
+  const bool upper = nj > 16u + 4u * H;
+  for (uint32_t g = 0; g < ng; ++g) {
+    // (After the last group: its own planes once more, unused, and the program's
+    // next block, which the interpreter then finds in the scalar cache.)
+    const uint32_t gn = g + 1 < ng ? g + 1 : g;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) t[u] = tau[8 * g + 8 + u];
+    uint64_t v[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = table[(B[i & 3] >> (8 * (i >> 2))) & 0xffu];
+    __builtin_amdgcn_sched_barrier(0);
+    uint32_t C[4];
+    rd_planes8(first + 8 * gn, x);
+    turn_index<H>(x, C);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) a[i] += v[i];
+    __builtin_amdgcn_sched_barrier(0);
+    if (upper) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) v[i] = table[(B[i & 3] >> (8 * (i >> 2) + 16)) & 0xffu];
+      __builtin_amdgcn_sched_barrier(0);
+      turn_table(t, table, lane);   // (over what the reads above, issued before, still use)
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) a[8 + i] += v[i];
+    } else {
+      turn_table(t, table, lane);
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) B[k] = C[k];
+  }
+#pragma unroll
+  for (int i = 0; i < 16; ++i) acc[64 * (8 * (i >> 2) + 4 * H + (i & 3)) + lane] = a[i];
+}
+__device__ __forceinline__ void captured_turns(TurnPtr tau, uint32_t ng, uint32_t first, uint32_t nj, uint64_t* acc,
+                                               uint64_t* table, int lane) {
+  captured_half<0>(tau, ng, first, nj, acc, table, lane);
+  if (nj > 4) captured_half<1>(tau, ng, first, nj, acc, table, lane);
+  for (uint32_t g = 0; g < ng; ++g) clear_planes8(first + 8 * g);
+}
+
 // (programs on too many qubits for capture planes, and ops under four planes)
 template <uint32_t FORM>
 __device__ __forceinline__ void turn_groups(const Fetch& f, uint32_t ng, uint64_t* acc, uint64_t* table, int lane) {
-  for (uint32_t g = 0; g < ng; ++g) turn_chunk<FORM, 1>(f, f.off + 64u * g, 0, acc, table, lane);
+  for (uint32_t g = 0; g < ng; ++g) turn_group<FORM>(f, f.off + 64u * g, acc, table, lane);
 }
 
 // Labels of the tile (word w of each label: bits 32w..32w+31) into planes.
@@ -484,7 +575,7 @@ __device__ __forceinline__ void rp_tile(const Buf& b, uint64_t base, uint32_t li
   wr_plane(nq, ~0u);       // all ones
   wr_plane(nq + 2, 0u);    // zero
   if (turns)
-    for (uint32_t q = 0; q < rp_capture_planes(nq); ++q) wr_plane(nq + 3 + q, 0u);
+    for (uint32_t q = 0; q < rp_capture_planes(nq); q += 8) clear_planes8(nq + 3 + q);
   asm volatile(
       "v_mov_b32 v80, 0\n\tv_mov_b32 v81, 0\n\tv_mov_b32 v82, 0\n\t"
       "v_mov_b32 v83, 0\n\tv_mov_b32 v84, 0\n\tv_mov_b32 v85, 0");
@@ -501,8 +592,8 @@ __device__ __forceinline__ void rp_tile(const Buf& b, uint64_t base, uint32_t li
     } else if (shape == kRpTC || shape == kRpTB || shape == kRpTG) {
       if (!turns) break;   // the host never sends turn ops to this variant
       if (shape == kRpTC) {
-        for (uint32_t g = 0; g < cnt; ++g)
-          turn_chunk<kRpTC, 2>(f, f.off + 64u * g, nq + 3 + 8 * g, acc, table, lane);
+        captured_turns(reinterpret_cast<TurnPtr>(reinterpret_cast<uint64_t>(prog) + f.off), cnt, nq + 3, (lim + 63) / 64,
+                       acc, table, lane);
       } else if (shape == kRpTB) {
         turn_groups<kRpTB>(f, cnt, acc, table, lane);
       } else {

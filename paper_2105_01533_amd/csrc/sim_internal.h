@@ -162,7 +162,7 @@ constexpr uint32_t kBlkExit = 0, kBlkF1 = 1, kBlkF2 = 2, kBlkF3 = 3, kBlkT = 4, 
 constexpr uint32_t kRpTC = 16;
 // Capture planes of a program on nq qubits: as many eights as the plane
 // registers leave, at most kRpCaptureMax (0: turn ops are not captured).
-constexpr uint32_t kRpCaptureMax = 16;
+constexpr uint32_t kRpCaptureMax = 64;
 __host__ __device__ constexpr uint32_t rp_capture_planes(uint32_t nq) {
   return 128u - nq >= kRpCaptureMax ? kRpCaptureMax : (128u - nq) / 8u * 8u;
 }
