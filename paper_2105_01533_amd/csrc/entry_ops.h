@@ -38,7 +38,8 @@ __device__ __forceinline__ uint64_t hash_label(uint64_t lo, uint64_t hi) {
   return k;
 }
 
-__device__ __forceinline__ bool ctrl_ok(const U2Desc& d, uint64_t lo, uint64_t hi, bool wide) {
+template <class Desc>
+__device__ __forceinline__ bool ctrl_ok(const Desc& d, uint64_t lo, uint64_t hi, bool wide) {
   return (lo & d.ctrl_lo) == d.ctrl_lo && (!wide || (hi & d.ctrl_hi) == d.ctrl_hi);
 }
 

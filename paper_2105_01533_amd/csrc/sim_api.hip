@@ -452,10 +452,39 @@ struct U2Plan {
   std::function<uint32_t()> may_exceed;   // called for a gate whose outputs may not fit: its sequence number
 };
 
-// Whether a gate on at most ub entries runs in one block with its index in LDS.
-bool small_gate(const sim_t* s, uint64_t ub) {
+// Whether a gate on at most ub entries runs on an index in LDS, and whether in
+// one block, the state in LDS too.
+bool lds_gate(const sim_t* s, uint64_t ub) {
   return 2 * ub <= s->cfg.capacity && ub <= kLdsU2Max &&
          !(s->cfg.flags & (SIM_FLAG_U2_TWO_PASS | SIM_FLAG_U2_GLOBAL_INDEX));
+}
+bool small_gate(const sim_t* s, uint64_t ub) { return lds_gate(s, ub) && ub <= kChainMax; }
+
+// The number by which the next branching gate's words in the status and partner
+// arrays are known.
+void next_epoch(sim_t* s) {
+  if (++s->u2_epoch < (1u << 30)) return;   // epochs are 30 bits: start over on cleared words
+  launch_fill(s->stream, s->status, 0ull, kMaxBlocks);
+  launch_fill(s->stream, reinterpret_cast<uint64_t*>(s->partner), ~0ull, (s->cfg.capacity + 1) / 2);
+  s->u2_epoch = 1;
+}
+
+// A branching gate on at most kLdsU2Max entries in one launch.
+int run_u2_lds(sim_t* s, const sim_gate& g, HeldRun* before) {
+  const uint64_t ub = s->nnz_known ? s->nnz_exact : s->nnz_ub;
+  if (before->m.ng > kLdsRun)
+    if (int rc = before->run_now()) return rc;
+  next_epoch(s);
+  {
+    KTimer t_(s, KC_U2_LDS);
+    launch_u2_lds_tiles(s->stream, s->wide, s->buf[s->cur], s->buf[s->cur ^ 1], d_nnz(s, s->cur), d_nnz(s, s->cur ^ 1),
+                        u2_desc(g, s->cfg.eps), before->take(), s->status, s->u2_epoch, s->ctl, ub);
+  }
+  HIP_TRY(hipGetLastError());
+  s->cur ^= 1;
+  s->nnz_known = false;
+  s->nnz_ub = 2 * ub;
+  return SIM_OK;
 }
 
 // Branching op on the global index: index, partner look-ups, single pass (or count, scan, write),
@@ -483,11 +512,7 @@ int run_u2(sim_t* s, const sim_gate& g, bool* over, const U2Plan& plan) {
   const bool split = plan.split && !s->built;
   const uint32_t* partner = split ? nullptr : s->partner;
   const TabCtl* tc = nullptr;
-  if (++s->u2_epoch >= (1u << 30)) {   // epochs are 30 bits: start over on cleared words
-    launch_fill(s->stream, s->status, 0ull, kMaxBlocks);
-    launch_fill(s->stream, reinterpret_cast<uint64_t*>(s->partner), ~0ull, (cap + 1) / 2);
-    s->u2_epoch = 1;
-  }
+  next_epoch(s);
   if (!split) {
     const IndexTab tab = index_tab(s, s->half);
     tc = tab.tc;
@@ -1296,7 +1321,7 @@ int apply_impl(sim_t* s, const sim_gate* gates, size_t n, int32_t* outcomes, sim
   int look_rc = SIM_OK;
   auto prepare_next = [&](uint64_t ub_out, MonoRun* m, U2Desc* d) -> bool {
     if (s->cfg.flags & (SIM_FLAG_U2_TWO_PASS | SIM_FLAG_COUNT_INDEX)) return false;
-    if (small_gate(s, ub_out)) return false;
+    if (lds_gate(s, ub_out)) return false;
     const size_t j = run_end(i + 1), len = j - (i + 1);
     if (j == n || len > held_most || gates[j].op != SIM_OP_U2) return false;
     if (gates[j].cap && 2 * ub_out > gates[j].cap) return false;
@@ -1405,7 +1430,9 @@ int apply_impl(sim_t* s, const sim_gate* gates, size_t n, int32_t* outcomes, sim
         if (rc) return rc;
         continue;
       }
-      rc = run_u2(s, g, &over, U2Plan{split, &held, prepare_next, may_exceed});
+      rc = lds_gate(s, was_known ? s->nnz_exact : s->nnz_ub)
+               ? run_u2_lds(s, g, &held)
+               : run_u2(s, g, &over, U2Plan{split, &held, prepare_next, may_exceed});
       if (rc || look_rc) return rc ? rc : look_rc;
       if (s->over && (result = settle())) break;
       if (!was_known && s->nnz_known) st.host_syncs++;

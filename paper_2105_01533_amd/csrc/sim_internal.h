@@ -439,16 +439,18 @@ void launch_u2_fused(hipStream_t st, bool wide, Buf in, Buf out, const uint64_t*
 // Back to the state before a gate that did not fit: its buffer's entry count,
 // and no staged counters, error or mark left.
 void launch_u2_restore(hipStream_t st, Ctl* ctl, int cur);
-// Largest state the one-block branching kernel takes (its partner index and
-// partner slots live in LDS).
+// Largest state whose partner index the branching kernels build in LDS.
 constexpr uint32_t kLdsU2Max = 8192;
-// A chain of branching gates on a state of at most kLdsU2Max entries at each,
-// in one block (index and look-up in LDS) and one launch: each step a short
+// A chain of branching gates on a state of at most kChainMax entries at each,
+// in one block, the state in LDS, and one launch: each step a short
 // phase/permutation run (ng = 0: none), then a gate (gate = 0: the chain's
 // last run alone).  Outputs, their order and the counters as the multi-kernel
-// path's (pruned_mass up to summation order).  Buffers alternate from `in`; the
-// counts go to nnz[cur ^ 1], nnz[cur], ...
-constexpr uint32_t kChainSteps = 16, kChainOps = 128;
+// form's.  The largest state whose outputs fit the LDS.
+constexpr uint32_t kChainMax = 2048;
+// Longest run that the branching kernel over several blocks applies before its
+// gate (each block applies the run's flips to every label).
+constexpr uint32_t kLdsRun = 8;
+constexpr uint32_t kChainSteps = 16, kChainOps = 64;
 struct ChainStep {
   U2Desc d;
   uint32_t ng, bytes_per_entry, gate, pad;
@@ -460,6 +462,9 @@ struct Chain {
 };
 static_assert(sizeof(Chain) <= 3584, "passed as a kernel argument");
 void launch_u2_chain(hipStream_t st, bool wide, Buf in, Buf out, uint64_t* nnz, int cur, const Chain& chain, Ctl* ctl);
+// One branching gate on a state of at most kLdsU2Max entries (ub bounds it).
+void launch_u2_lds_tiles(hipStream_t st, bool wide, Buf in, Buf out, const uint64_t* nnz_in, uint64_t* nnz_out,
+                         const U2Desc& d, const MonoRun& m, uint64_t* status, uint32_t epoch, Ctl* ctl, uint64_t ub);
 void launch_measure_reduce(hipStream_t st, bool wide, Buf b, const uint64_t* nnz, uint32_t q, BlockScratch s,
                            int grid, int block);
 void launch_measure_decide(hipStream_t st, const double2* part, const uint32_t* cnt1, uint32_t* off, int nblocks,

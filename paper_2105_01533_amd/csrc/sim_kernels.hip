@@ -1023,237 +1023,257 @@ __global__ void k_u2_restore(Ctl* ctl, int cur) {
 }
 
 // ---------------------------------------------------------------------------
-// Branching gates on a state of at most kLdsU2Max entries in one block, their
-// partner index in LDS (lds::u2_block): same outputs, order and counters as
-// the index-build / probe / single-pass kernels.  A launch runs a chain of
-// gates with the short runs between them: a launch costs the host 6 us and the
-// GPU two or three with nothing to do, and a gate on a few entries is little
-// more than its chain of memory round trips (8 us).  While the state has at
-// most kResident entries it therefore stays in LDS from gate to gate, and with
-// it the chain's descriptors: 3 us per gate.  A 12-qubit circuit's 10 gates
-// with runs between them: 17 launches and 120 us of kernels; in one launch
-// over memory 84 us, over LDS 32.
-constexpr uint32_t kResident = 1024;
-struct ResidentBuf {
-  uint64_t lo[2 * kResident], hi[2 * kResident];
-  double2 amp[2 * kResident];
-};
-struct ResidentSmem {
-  ResidentBuf buf[2];
-  uint32_t tab[2 * kResident];
-  uint32_t par[kResident];
-};
-struct ChainSmem {
-  union {
-    ResidentSmem r;
-    lds::Smem g;
-  };
-  MonoDesc g_run[kChainOps];
-  ChainStep step[kChainSteps];
-  uint32_t wave[lds::kWaves];
-};
-static_assert(kResident == (uint32_t)lds::kThreads, "an entry per thread");
-static_assert(sizeof(ChainSmem) <= 160 * 1024, "LDS of a block");
-
-// What a thread counted over the resident gates.
-struct ChainCount {
+// What a thread counted over the gates of a launch; waves add theirs up by
+// shuffles, then one atomic a counter (block sums through LDS were no faster).
+struct BlockCount {
   uint32_t dropped = 0, ix[4] = {};
   double mass = 0.0;
 };
-
-// One gate on the n <= kResident entries of `in`, preceded by the run at run;
-// returns the number of outputs.
-template <bool WIDE>
-__device__ __forceinline__ uint32_t u2_resident(ResidentBuf& in, ResidentBuf& out, uint32_t n, const U2Desc& d,
-                                                const MonoDesc* run, uint32_t ng, ChainSmem& sm, ChainCount& cnt) {
-  constexpr uint32_t kMask = 2 * kResident - 1;
-  const uint32_t i = threadIdx.x, lane = i & 63, wid = i >> 6;
-  uint64_t lo = 0, hi = 0;
-  double2 a = make_double2(0.0, 0.0);
-  sm.r.tab[i] = 0u;
-  sm.r.tab[i + kResident] = 0u;
-  if (i < n) {
-    lo = in.lo[i];
-    hi = WIDE ? in.hi[i] : 0ull;
-    a = in.amp[i];
-    for (uint32_t q = 0; q < ng; ++q) ent::mono_step(run[q], WIDE, lo, hi, a);
-    if (ng) {
-      in.lo[i] = lo;
-      if (WIDE) in.hi[i] = hi;
-      in.amp[i] = a;
-    }
-    sm.r.par[i] = kNoPartner;
+__device__ __forceinline__ void add_counts(const BlockCount& c, Ctl* ctl) {
+  const uint32_t dropped = lds::wave_u(c.dropped);
+  const double mass = lds::wave_d(c.mass);
+  uint32_t ix[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) ix[q] = lds::wave_u(c.ix[q]);
+  if (threadIdx.x & 63) return;
+  if (dropped) {
+    atomicAdd((unsigned long long*)&ctl->pruned, (unsigned long long)dropped);
+    atomicAdd(&ctl->pruned_mass, mass);
   }
-  const bool under = i < n && ent::ctrl_ok(d, lo, hi, WIDE);
-  const bool piv = ent::pivot_set(d, lo, hi, WIDE);
-  const uint64_t h = hash_label(lo ^ (piv ? d.x_lo : 0ull), WIDE ? hi ^ (piv ? d.x_hi : 0ull) : 0ull);
-  const uint32_t fp = (uint32_t)(h >> (32 + lds::kIdxBits)), slot0 = (uint32_t)h & kMask;
+  for (int q = 0; q < 4; ++q)
+    if (ix[q]) atomicAdd((unsigned long long*)&ctl->ix[q], (unsigned long long)ix[q]);
+}
+
+// Branching gates on a state of at most kChainMax entries in one block, the
+// state and its partner index in LDS from gate to gate: same outputs, order and
+// counters as the index-build / probe / single-pass kernels.  A launch runs a
+// chain of gates with the short runs between them: a launch costs the host 6
+// us and the GPU two or three with nothing to do, and a gate on a few entries
+// over memory is little more than its chain of round trips (8 us).  A 12-qubit
+// circuit's 10 gates with runs between them: 17 launches and 120 us of kernels;
+// in one launch over memory 84 us, over LDS 27.  What bounds it is one CU's
+// instruction issue, so waves without entries skip theirs: 4 us a gate up to
+// 512 entries, 6 at 2048, where the kernels over many CUs take 14 to 16 and
+// their launches 20.
+struct ChainSmem {
+  uint64_t lo[2 * kChainMax], hi[2 * kChainMax];   // a gate's inputs, then its outputs
+  double2 amp[2 * kChainMax];
+  uint32_t tab[2 * kChainMax];
+  uint16_t par[kChainMax];
+  MonoDesc g_run[kChainOps];
+  ChainStep step[kChainSteps];
+  uint32_t wave[kChainMax / 64];
+};
+static_assert(sizeof(ChainSmem) <= 160 * 1024, "LDS of a block");
+constexpr uint16_t kNobody = 0xffff;   // in ChainSmem::par
+
+// One gate on the n <= ITEMS * 1024 entries in sm, preceded by the run at run;
+// returns the number of outputs.
+template <bool WIDE, int ITEMS>
+__device__ __forceinline__ uint32_t u2_resident(ChainSmem& sm, uint32_t n, const U2Desc& d, const MonoDesc* run,
+                                                uint32_t ng, BlockCount& cnt) {
+  constexpr uint32_t kWaves = 16;
+  const uint32_t lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t kMask = (n <= 32 ? 64u : 2u << (32 - __clz(n - 1))) - 1u;   // at least two slots an entry
+  uint64_t lo[ITEMS], hi[ITEMS];
+  double2 a[ITEMS];
+  bool under[ITEMS], piv[ITEMS];
+  for (uint32_t k = threadIdx.x; k <= kMask; k += 1024) sm.tab[k] = 0u;
+#pragma unroll
+  for (int k = 0; k < ITEMS; ++k) {
+    const uint32_t i = k * 1024 + threadIdx.x;
+    under[k] = piv[k] = false;
+    lo[k] = hi[k] = 0;
+    a[k] = make_double2(0.0, 0.0);
+    if (k * 1024 + wid * 64 >= n) continue;   // uniform: a wave without entries
+    if (i < n) {
+      lo[k] = sm.lo[i];
+      hi[k] = WIDE ? sm.hi[i] : 0ull;
+      a[k] = sm.amp[i];
+      for (uint32_t q = 0; q < ng; ++q) ent::mono_step(run[q], WIDE, lo[k], hi[k], a[k]);
+      if (ng) {
+        sm.lo[i] = lo[k];
+        if (WIDE) sm.hi[i] = hi[k];
+        sm.amp[i] = a[k];
+      }
+      sm.par[i] = kNobody;
+      under[k] = ent::ctrl_ok(d, lo[k], hi[k], WIDE);
+      piv[k] = ent::pivot_set(d, lo[k], hi[k], WIDE);
+    }
+  }
   __syncthreads();
-  if (under && !piv) {
-    const uint32_t val = fp << lds::kIdxBits | (i + 1u);
+  // Index the pivot-clear entries under the controls; the others under them
+  // look up label ^ x, which makes the two each other's partner.
+#pragma unroll
+  for (int k = 0; k < ITEMS; ++k) {
+    if (!under[k] || piv[k]) continue;
+    const uint32_t i = k * 1024 + threadIdx.x;
+    const uint32_t h = lds::hash<WIDE>(lo[k], hi[k]);
+    const uint32_t val = (h >> lds::kIdxBits) << lds::kIdxBits | (i + 1u);
     ++cnt.ix[0];
     for (uint32_t p = 0; p <= kMask; ++p) {
       ++cnt.ix[1];
-      if (atomicCAS(&sm.r.tab[(slot0 + p) & kMask], 0u, val) == 0u) break;
+      if (atomicCAS(&sm.tab[(h + p) & kMask], 0u, val) == 0u) break;
     }
   }
   __syncthreads();
-  uint32_t j = kNoPartner;
-  if (under && piv) {
-    const uint64_t qlo = lo ^ d.x_lo, qhi = WIDE ? hi ^ d.x_hi : 0ull;
+  uint32_t j[ITEMS];
+#pragma unroll
+  for (int k = 0; k < ITEMS; ++k) {
+    j[k] = kNobody;
+    if (!under[k] || !piv[k]) continue;
+    const uint64_t qlo = lo[k] ^ d.x_lo, qhi = WIDE ? hi[k] ^ d.x_hi : 0ull;
+    const uint32_t h = lds::hash<WIDE>(qlo, qhi);
+    const uint32_t fp = h >> lds::kIdxBits;
     ++cnt.ix[2];
     for (uint32_t p = 0; p <= kMask; ++p) {
-      const uint32_t v = sm.r.tab[(slot0 + p) & kMask];
+      const uint32_t v = sm.tab[(h + p) & kMask];
       ++cnt.ix[3];
       if (v == 0u) break;
       const uint32_t c = (v & lds::kIdxMask) - 1u;
-      if ((v >> lds::kIdxBits) == fp && in.lo[c] == qlo && (!WIDE || in.hi[c] == qhi)) {
-        j = c;
-        sm.r.par[c] = i;
+      if ((v >> lds::kIdxBits) == fp && sm.lo[c] == qlo && (!WIDE || sm.hi[c] == qhi)) {
+        j[k] = c;
+        sm.par[c] = 0;   // (it is somebody's)
         break;
       }
     }
   }
   __syncthreads();
-  if (under && !piv) j = sm.r.par[i];
-  double2 aj = make_double2(0.0, 0.0);
-  if (piv && j != kNoPartner) aj = in.amp[j];
-  U2Out r = ent::u2_eval(d, WIDE, lo, hi, a, j != kNoPartner, aj);
-  if (i >= n) r.mode = 2;
-  const bool k0 = r.mode != 2 && survives(r.o0, d.eps), k1 = r.mode == 1 && survives(r.o1, d.eps);
-  cnt.dropped += (r.mode != 2 && !k0 ? 1u : 0u) + (r.mode == 1 && !k1 ? 1u : 0u);
-  if (r.mode != 2) cnt.mass += ent::dropped_mass(r.o0, k0);
-  if (r.mode == 1) cnt.mass += ent::dropped_mass(r.o1, k1);
-  const uint64_t b0 = __ballot(k0), b1 = __ballot(k1), lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-  if (lane == 0) sm.wave[wid] = __popcll(b0) + __popcll(b1);
-  __syncthreads();
-  // Every wave: the waves' counts, scanned; its own offset is the one before it.
-  uint32_t incl = lane < (uint32_t)lds::kWaves ? sm.wave[lane] : 0u;
+  U2Out r[ITEMS];
+  bool k0[ITEMS], k1[ITEMS];
+  uint64_t b0[ITEMS], b1[ITEMS];
 #pragma unroll
-  for (int o = 1; o < lds::kWaves; o <<= 1) {
+  for (int k = 0; k < ITEMS; ++k) {
+    const uint32_t i = k * 1024 + threadIdx.x;
+    k0[k] = k1[k] = false;
+    b0[k] = b1[k] = 0;
+    r[k].mode = 2;
+    uint32_t kept = 0;
+    if (k * 1024 + wid * 64 < n) {
+      if (i < n) {
+        if (under[k] && !piv[k]) j[k] = sm.par[i];
+        double2 aj = make_double2(0.0, 0.0);
+        if (piv[k] && j[k] != kNobody) aj = sm.amp[j[k]];
+        r[k] = ent::u2_eval(d, WIDE, lo[k], hi[k], a[k], j[k] != kNobody, aj);
+        k0[k] = r[k].mode != 2 && survives(r[k].o0, d.eps);
+        k1[k] = r[k].mode == 1 && survives(r[k].o1, d.eps);
+        if (r[k].mode != 2 && !k0[k]) {
+          ++cnt.dropped;
+          cnt.mass += ent::dropped_mass(r[k].o0, false);
+        }
+        if (r[k].mode == 1 && !k1[k]) {
+          ++cnt.dropped;
+          cnt.mass += ent::dropped_mass(r[k].o1, false);
+        }
+      }
+      b0[k] = __ballot(k0[k]);
+      b1[k] = __ballot(k1[k]);
+      kept = __popcll(b0[k]) + __popcll(b1[k]);
+    }
+    if (lane == 0) sm.wave[k * kWaves + wid] = kept;
+  }
+  __syncthreads();   // (the inputs have been read)
+  // Every wave scans the waves' counts; its own offset is the sum before it.
+  uint32_t incl = lane < ITEMS * kWaves ? sm.wave[lane] : 0u;
+#pragma unroll
+  for (int o = 1; o < ITEMS * (int)kWaves; o <<= 1) {
     const uint32_t y = __shfl_up(incl, o);
     if (lane >= (uint32_t)o) incl += y;
   }
-  const uint32_t total = __shfl(incl, lds::kWaves - 1);
-  const uint32_t before = wid ? __shfl(incl, wid - 1) : 0u;
-  uint32_t p = before + __popcll(b0 & lt) + __popcll(b1 & lt);
-  const bool flipped = r.mode == 1 && piv;
-  const uint64_t lo0 = flipped ? lo ^ d.x_lo : lo, hi0 = flipped ? hi ^ d.x_hi : hi;
-  if (k0) {
-    out.lo[p] = lo0;
-    if (WIDE) out.hi[p] = hi0;
-    out.amp[p] = r.o0;
-    ++p;
+  const uint32_t total = __builtin_amdgcn_readlane(incl, ITEMS * kWaves - 1);
+  const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+#pragma unroll
+  for (int k = 0; k < ITEMS; ++k) {
+    if (k * 1024 + wid * 64 >= n) continue;
+    const uint32_t w = k * kWaves + wid;
+    uint32_t p = (w ? __builtin_amdgcn_readlane(incl, w - 1) : 0u) + __popcll(b0[k] & lt) + __popcll(b1[k] & lt);
+    const bool flipped = r[k].mode == 1 && piv[k];
+    const uint64_t lo0 = flipped ? lo[k] ^ d.x_lo : lo[k], hi0 = flipped ? hi[k] ^ d.x_hi : hi[k];
+    if (k0[k]) {
+      sm.lo[p] = lo0;
+      if (WIDE) sm.hi[p] = hi0;
+      sm.amp[p] = r[k].o0;
+      ++p;
+    }
+    if (k1[k]) {
+      sm.lo[p] = lo0 ^ d.x_lo;
+      if (WIDE) sm.hi[p] = hi0 ^ d.x_hi;
+      sm.amp[p] = r[k].o1;
+    }
   }
-  if (k1) {
-    out.lo[p] = lo0 ^ d.x_lo;
-    if (WIDE) out.hi[p] = hi0 ^ d.x_hi;
-    out.amp[p] = r.o1;
-  }
-  __syncthreads();   // (the next gate reads `out`, and writes sm.wave)
-  return __builtin_amdgcn_readfirstlane(total);
+  __syncthreads();
+  return total;
 }
 
 template <bool WIDE>
 __global__ __launch_bounds__(1024) void k_u2_chain(Buf in, Buf out, uint64_t* nnz, int cur, Chain chain, Ctl* ctl) {
+  const int cur0 = cur;
   __shared__ ChainSmem sm;
   auto count = [](uint64_t* p, uint64_t v) {
     if (v) atomicAdd((unsigned long long*)p, (unsigned long long)v);
   };
   constexpr uint32_t kEntry = WIDE ? 32u : 24u;
   const uint64_t n0 = nnz[cur];
-  // The chain into LDS: its steps (from the kernel arguments) and its runs' gates.
+  uint32_t n = __builtin_amdgcn_readfirstlane((uint32_t)(n0 > kChainMax ? kChainMax + 1 : n0));
+  if (n > kChainMax) {   // the host launches this kernel only below the bound
+    if (threadIdx.x == 0) atomicOr(&ctl->error, 4u);
+    return;
+  }
+  // The chain into LDS: its steps (from the kernel arguments), its runs' gates and the state.
   {
     const uint32_t* src = reinterpret_cast<const uint32_t*>(chain.s);
     uint32_t* dst = reinterpret_cast<uint32_t*>(sm.step);
-    for (uint32_t k = threadIdx.x; k < chain.n * (uint32_t)(sizeof(ChainStep) / 4); k += lds::kThreads) dst[k] = src[k];
+    for (uint32_t k = threadIdx.x; k < chain.n * (uint32_t)(sizeof(ChainStep) / 4); k += 1024) dst[k] = src[k];
     const uint4* g4 = reinterpret_cast<const uint4*>(chain.ops);
     uint4* d4 = reinterpret_cast<uint4*>(sm.g_run);
-    for (uint32_t k = threadIdx.x; k < chain.n_ops * (uint32_t)(sizeof(MonoDesc) / 16); k += lds::kThreads) d4[k] = g4[k];
+    for (uint32_t k = threadIdx.x; k < chain.n_ops * (uint32_t)(sizeof(MonoDesc) / 16); k += 1024) d4[k] = g4[k];
   }
-  uint32_t n = __builtin_amdgcn_readfirstlane((uint32_t)(n0 > kLdsU2Max ? kLdsU2Max + 1 : n0));
-  bool resident = false;   // uniform, as all that follows from n
-  uint32_t rb = 0;         // the LDS buffer with the state
+  for (uint32_t i = threadIdx.x; i < n; i += 1024) {
+    sm.lo[i] = in.key_lo[i];
+    if (WIDE) sm.hi[i] = in.key_hi[i];
+    sm.amp[i] = in.amp[i];
+  }
   __syncthreads();
-  ChainCount cnt;
+  BlockCount cnt;
   uint64_t updates = 0, mono_updates = 0, mono_bytes = 0, bytes = 0, peak = 0;
-  // The n entries through a run of ng gates: in the device buffer of their
-  // parity, or from LDS to it.
-  auto run_out = [&](const MonoDesc* run, uint32_t ng) {
-    const ResidentBuf& b = sm.r.buf[rb];
-    for (uint32_t i = threadIdx.x; i < n; i += lds::kThreads) {
-      uint64_t lo = resident ? b.lo[i] : in.key_lo[i], hi = 0;
-      if (WIDE) hi = resident ? b.hi[i] : in.key_hi[i];
-      double2 a = resident ? b.amp[i] : in.amp[i];
-      for (uint32_t j = 0; j < ng; ++j) ent::mono_step(run[j], WIDE, lo, hi, a);
-      in.key_lo[i] = lo;
-      if (WIDE) in.key_hi[i] = hi;
-      in.amp[i] = a;
-    }
-    __syncthreads();
-    resident = false;
-  };
-  uint32_t op = 0;
+  uint32_t op = 0, tail = 0;   // tail: gates of a run after the last branching gate
 #pragma unroll 1
   for (uint32_t k = 0; k < chain.n; ++k) {
     const ChainStep& st = sm.step[k];
     const uint32_t ng = __builtin_amdgcn_readfirstlane(st.ng), gate = __builtin_amdgcn_readfirstlane(st.gate);
-    if (gate && n > kLdsU2Max) {   // the host launches this kernel only below the bound
-      if (threadIdx.x == 0) atomicOr(&ctl->error, 4u);
-      break;
-    }
     updates += (uint64_t)n * (ng + gate);
     mono_updates += (uint64_t)n * ng;
     mono_bytes += (uint64_t)n * st.bytes_per_entry;
-    const MonoDesc* run = sm.g_run + op;
-    op += ng;
     if (!gate) {
-      run_out(run, ng);
+      tail = ng;
       break;
     }
+    const MonoDesc* run = sm.g_run + op;
+    op += ng;
     uint32_t m;
-    if (n <= kResident) {
-      if (!resident && threadIdx.x < n) {
-        ResidentBuf& b = sm.r.buf[rb];
-        b.lo[threadIdx.x] = in.key_lo[threadIdx.x];
-        if (WIDE) b.hi[threadIdx.x] = in.key_hi[threadIdx.x];
-        b.amp[threadIdx.x] = in.amp[threadIdx.x];
-      }
-      resident = true;
-      m = u2_resident<WIDE>(sm.r.buf[rb], sm.r.buf[rb ^ 1], n, st.d, run, ng, sm, cnt);
-      rb ^= 1;
-    } else {
-      if (resident || ng) run_out(run, ng);
-      // Outputs number at most 2 n, which the host has checked against the
-      // capacity, so the bound passed here never refuses a write.
-      const lds::Totals t = lds::u2_block<WIDE, 2>(in, out, n, st.d, ~0ull, sm.g);
-      if (threadIdx.x == 0) {
-        cnt.dropped += t.dropped;
-        cnt.mass += t.mass;
-        for (int q = 0; q < 4; ++q) cnt.ix[q] += t.ix[q];
-      }
-      m = __builtin_amdgcn_readfirstlane(t.out);
+    if (n <= 1024) {
+      m = u2_resident<WIDE, 1>(sm, n, st.d, run, ng, cnt);
+    } else if (n <= kChainMax) {
+      m = u2_resident<WIDE, 2>(sm, n, st.d, run, ng, cnt);
+    } else {   // (as above: the host's bound rules it out)
+      if (threadIdx.x == 0) atomicOr(&ctl->error, 4u);
+      break;
     }
     bytes += (uint64_t)(n + m) * kEntry;
     n = m;
     if (n > peak) peak = n;
     cur ^= 1;
-    const Buf b = in;
-    in = out;
-    out = b;
   }
-  if (resident) run_out(nullptr, 0);
-  // Sums of what the threads counted: waves by shuffles, then one atomic each.
-  const uint32_t dropped = lds::wave_u(cnt.dropped);
-  const double mass = lds::wave_d(cnt.mass);
-  uint32_t ix[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) ix[q] = lds::wave_u(cnt.ix[q]);
-  if ((threadIdx.x & 63) == 0) {
-    count(&ctl->pruned, dropped);
-    if (dropped) atomicAdd(&ctl->pruned_mass, mass);
-    for (int q = 0; q < 4; ++q) count(&ctl->ix[q], ix[q]);
+  const Buf to = cur == cur0 ? in : out;
+  for (uint32_t i = threadIdx.x; i < n; i += 1024) {
+    uint64_t lo = sm.lo[i], hi = WIDE ? sm.hi[i] : 0ull;
+    double2 a = sm.amp[i];
+    for (uint32_t q = 0; q < tail; ++q) ent::mono_step(sm.g_run[op + q], WIDE, lo, hi, a);
+    to.key_lo[i] = lo;
+    if (WIDE) to.key_hi[i] = hi;
+    to.amp[i] = a;
   }
+  add_counts(cnt, ctl);
   if (threadIdx.x == 0) {
     nnz[cur] = n;
     count(&ctl->updates, updates);
@@ -1261,6 +1281,193 @@ __global__ __launch_bounds__(1024) void k_u2_chain(Buf in, Buf out, uint64_t* nn
     count(&ctl->mono_bytes, mono_bytes);
     count(&ctl->pass_bytes[4], bytes);
     if (peak > ctl->peak) ctl->peak = peak;
+  }
+}
+
+// A branching gate on a state of at most kLdsU2Max entries in one launch: every
+// block reads all labels (from L2), indexes those with the pivot bit clear in
+// its own LDS and looks the others' partners up there, so that it knows the
+// partners of its own 1024 entries without waiting for the other blocks; it
+// evaluates these and writes their outputs after those of the blocks before it
+// (look_back).  m: a run of at most kLdsRun gates before the gate, applied to
+// whatever is read (the state's buffer keeps the entries before the run).
+// Outputs, order and counters (an entry's insert or look-up counts in its own
+// block) as the three kernels' of the global index, which at these sizes are
+// their launches (three of 5 to 7 us and 20 us of host time) and round trips;
+// one block with the index in LDS took 22 us at 4096 entries and 45 at 8192, this
+// 16 and 28: the probes of one CU's LDS by all entries.
+struct LdsTileSmem {
+  uint32_t tab[2 * kLdsU2Max];
+  uint64_t lo[1024], hi[1024];   // the block's own labels
+  uint32_t has[1024];            // whether an own entry with the pivot bit clear has a partner
+  MonoDesc run[kLdsRun];
+  uint32_t wave[16], before;
+};
+template <bool WIDE>
+__global__ __launch_bounds__(1024) void k_u2_lds_tiles(Buf in, Buf out, const uint64_t* __restrict__ nnz_in,
+                                                       uint64_t* nnz_out, U2Desc d, MonoRun m, uint64_t* status,
+                                                       uint32_t epoch, Ctl* ctl) {
+  __shared__ LdsTileSmem sm;
+  auto count = [](uint64_t* p, uint64_t v) {
+    if (v) atomicAdd((unsigned long long*)p, (unsigned long long)v);
+  };
+  constexpr uint32_t kEntry = WIDE ? 32u : 24u;
+  const uint64_t n0 = *nnz_in;
+  if (n0 > kLdsU2Max) {   // the host launches this kernel only below the bound
+    if (threadIdx.x == 0) atomicOr(&ctl->error, 4u);
+    return;
+  }
+  const uint32_t n = (uint32_t)n0, blocks = n ? (n + 1023) / 1024 : 1u, b = blockIdx.x;
+  if (b >= blocks) return;
+  const uint32_t lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t kMask = (n <= 32 ? 64u : 2u << (32 - __clz(n - 1))) - 1u;   // at least two slots an entry
+  for (uint32_t k = threadIdx.x; k < m.ng * (uint32_t)(sizeof(MonoDesc) / 16); k += 1024)
+    reinterpret_cast<uint4*>(sm.run)[k] = reinterpret_cast<const uint4*>(m.g)[k];
+  for (uint32_t k = threadIdx.x; k <= kMask; k += 1024) sm.tab[k] = 0u;
+  const uint32_t own = b * 1024 + threadIdx.x;
+  double2 a = make_double2(0.0, 0.0);
+  if (own < n) a = in.amp[own];
+  __syncthreads();
+  const bool flips = m.run_flags & kRunFlip;
+  constexpr uint32_t kRounds = kLdsU2Max / 1024;
+  uint64_t l[kRounds], h2[kRounds];   // the thread's label of each 1024
+#pragma unroll
+  for (uint32_t k = 0; k < kRounds; ++k) {
+    const uint32_t i = k * 1024 + threadIdx.x;
+    l[k] = i < n ? in.key_lo[i] : 0ull;
+    h2[k] = WIDE && i < n ? in.key_hi[i] : 0ull;
+  }
+  uint64_t lo = 0, hi = 0;            // of its own entry
+  if (own < n) {
+    lo = in.key_lo[own];
+    hi = WIDE ? in.key_hi[own] : 0ull;
+    for (uint32_t q = 0; q < m.ng; ++q) ent::mono_step(sm.run[q], WIDE, lo, hi, a);
+    sm.lo[threadIdx.x] = lo;
+    if (WIDE) sm.hi[threadIdx.x] = hi;
+    sm.has[threadIdx.x] = 0u;
+  }
+  uint32_t inserts = 0, cas = 0, lookups = 0, steps = 0;
+#pragma unroll
+  for (uint32_t k = 0; k < kRounds; ++k) {
+    const uint32_t i = k * 1024 + threadIdx.x;
+    if (k * 1024 + wid * 64 >= n) break;   // uniform
+    if (flips) {
+      for (uint32_t q = 0; q < m.ng; ++q)
+        if (sm.run[q].flags & kFlip) {
+          const uint64_t f = ent::ctrl_ok(sm.run[q], l[k], h2[k], WIDE) ? 1ull << (sm.run[q].target & 63) : 0ull;
+          if (WIDE && sm.run[q].target >= 64) h2[k] ^= f;
+          else l[k] ^= f;
+        }
+    }
+    if (i >= n || !ent::ctrl_ok(d, l[k], h2[k], WIDE) || ent::pivot_set(d, l[k], h2[k], WIDE)) continue;
+    const uint32_t h = lds::hash<WIDE>(l[k], h2[k]);
+    const uint32_t val = (h >> lds::kIdxBits) << lds::kIdxBits | (i + 1u);
+    uint32_t p = 0;
+    while (atomicCAS(&sm.tab[(h + p) & kMask], 0u, val) != 0u && p < kMask) ++p;
+    if (k == b) {
+      ++inserts;
+      cas += p + 1;
+    }
+  }
+  __syncthreads();
+  // Each entry under the controls with the pivot bit set looks up label ^ x: a
+  // partner among the block's own entries learns of it.
+  const bool under = own < n && ent::ctrl_ok(d, lo, hi, WIDE), piv = ent::pivot_set(d, lo, hi, WIDE);
+#pragma unroll
+  for (uint32_t k = 0; k < kRounds; ++k) {
+    const uint32_t i = k * 1024 + threadIdx.x;
+    if (k * 1024 + wid * 64 >= n) break;   // uniform
+    if (i >= n || !ent::ctrl_ok(d, l[k], h2[k], WIDE) || !ent::pivot_set(d, l[k], h2[k], WIDE)) continue;
+    const uint64_t qlo = l[k] ^ d.x_lo, qhi = WIDE ? h2[k] ^ d.x_hi : 0ull;
+    const uint32_t h = lds::hash<WIDE>(qlo, qhi);
+    const uint32_t fp = h >> lds::kIdxBits;
+    for (uint32_t p = 0; p <= kMask; ++p) {
+      const uint32_t v = sm.tab[(h + p) & kMask];
+      if (v == 0u) break;
+      const uint32_t mine = (v & lds::kIdxMask) - 1u - b * 1024;
+      if ((v >> lds::kIdxBits) == fp && mine < 1024 && sm.lo[mine] == qlo && (!WIDE || sm.hi[mine] == qhi)) {
+        sm.has[mine] = 1u;
+        break;
+      }
+    }
+  }
+  // The own entry, if it emits the pair, takes its partner's amplitude from
+  // wherever it is.
+  bool has = false;
+  double2 aj = make_double2(0.0, 0.0);
+  if (under && piv) {
+    const uint64_t qlo = lo ^ d.x_lo, qhi = WIDE ? hi ^ d.x_hi : 0ull;
+    const uint32_t h = lds::hash<WIDE>(qlo, qhi);
+    const uint32_t fp = h >> lds::kIdxBits;
+    ++lookups;
+    for (uint32_t p = 0; p <= kMask; ++p) {
+      const uint32_t v = sm.tab[(h + p) & kMask];
+      ++steps;
+      if (v == 0u) break;
+      if ((v >> lds::kIdxBits) != fp) continue;
+      const uint32_t c = (v & lds::kIdxMask) - 1u;
+      uint64_t cl = in.key_lo[c], ch = WIDE ? in.key_hi[c] : 0ull;
+      aj = in.amp[c];
+      for (uint32_t q = 0; q < m.ng; ++q) ent::mono_step(sm.run[q], WIDE, cl, ch, aj);
+      has = cl == qlo && (!WIDE || ch == qhi);
+      if (has) break;
+    }
+  }
+  __syncthreads();
+  if (under && !piv) has = sm.has[threadIdx.x] != 0u;
+  U2Out r = ent::u2_eval(d, WIDE, lo, hi, a, has, aj);
+  if (own >= n) r.mode = 2;
+  const bool k0 = r.mode != 2 && survives(r.o0, d.eps), k1 = r.mode == 1 && survives(r.o1, d.eps);
+  const uint32_t dropped = (r.mode != 2 && !k0 ? 1u : 0u) + (r.mode == 1 && !k1 ? 1u : 0u);
+  const double mass = (r.mode != 2 ? ent::dropped_mass(r.o0, k0) : 0.0) + (r.mode == 1 ? ent::dropped_mass(r.o1, k1) : 0.0);
+  const uint64_t b0 = __ballot(k0), b1 = __ballot(k1), lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+  if (lane == 0) sm.wave[wid] = __popcll(b0) + __popcll(b1);
+  __syncthreads();
+  uint32_t incl = lane < 16 ? sm.wave[lane] : 0u;
+#pragma unroll
+  for (int o = 1; o < 16; o <<= 1) {
+    const uint32_t y = __shfl_up(incl, o);
+    if (lane >= (uint32_t)o) incl += y;
+  }
+  const uint32_t total = __builtin_amdgcn_readlane(incl, 15);
+  if (wid == 0) {
+    if (lane == 0)
+      __hip_atomic_store(&status[b], st_word(epoch, b == 0 ? kStPrefix : kStAgg, total), __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_AGENT);
+    const uint32_t before = look_back(status, b, epoch, &ctl->error);
+    if (lane == 0) sm.before = before;
+  }
+  __syncthreads();
+  uint32_t p = sm.before + (wid ? __builtin_amdgcn_readlane(incl, wid - 1) : 0u) + __popcll(b0 & lt) + __popcll(b1 & lt);
+  const bool flipped = r.mode == 1 && piv;
+  const uint64_t lo0 = flipped ? lo ^ d.x_lo : lo, hi0 = flipped ? hi ^ d.x_hi : hi;
+  if (k0) {
+    out.key_lo[p] = lo0;
+    if (WIDE) out.key_hi[p] = hi0;
+    out.amp[p] = r.o0;
+    ++p;
+  }
+  if (k1) {
+    out.key_lo[p] = lo0 ^ d.x_lo;
+    if (WIDE) out.key_hi[p] = hi0 ^ d.x_hi;
+    out.amp[p] = r.o1;
+  }
+  BlockCount cnt;
+  cnt.dropped = dropped;
+  cnt.mass = mass;
+  cnt.ix[0] = inserts;
+  cnt.ix[1] = cas;
+  cnt.ix[2] = lookups;
+  cnt.ix[3] = steps;
+  add_counts(cnt, ctl);
+  if (threadIdx.x == 0 && b == blocks - 1) {
+    const uint64_t n_out = sm.before + total;
+    *nnz_out = n_out;
+    if (n_out > ctl->peak) ctl->peak = n_out;
+    count(&ctl->updates, (uint64_t)n * (m.ng + 1));
+    count(&ctl->mono_updates, (uint64_t)n * m.ng);
+    count(&ctl->mono_bytes, (uint64_t)n * (m.ng ? m.bytes_per_entry : 0u));
+    count(&ctl->pass_bytes[4], (n + n_out) * kEntry);
   }
 }
 
@@ -1590,6 +1797,17 @@ void launch_u2_chain(hipStream_t st, bool wide, Buf in, Buf out, uint64_t* nnz, 
     hipLaunchKernelGGL(k_u2_chain<true>, dim3(1), dim3(lds::kThreads), 0, st, in, out, nnz, cur, chain, ctl);
   else
     hipLaunchKernelGGL(k_u2_chain<false>, dim3(1), dim3(lds::kThreads), 0, st, in, out, nnz, cur, chain, ctl);
+}
+
+void launch_u2_lds_tiles(hipStream_t st, bool wide, Buf in, Buf out, const uint64_t* nnz_in, uint64_t* nnz_out,
+                         const U2Desc& d, const MonoRun& m, uint64_t* status, uint32_t epoch, Ctl* ctl, uint64_t ub) {
+  const int grid = (int)std::max<uint64_t>(1, (ub + 1023) / 1024);
+  if (wide)
+    hipLaunchKernelGGL(k_u2_lds_tiles<true>, dim3(grid), dim3(1024), 0, st, in, out, nnz_in, nnz_out, d, m, status,
+                       epoch, ctl);
+  else
+    hipLaunchKernelGGL(k_u2_lds_tiles<false>, dim3(grid), dim3(1024), 0, st, in, out, nnz_in, nnz_out, d, m, status,
+                       epoch, ctl);
 }
 
 void launch_measure_reduce(hipStream_t st, bool wide, Buf b, const uint64_t* nnz, uint32_t q, BlockScratch s,

@@ -1,9 +1,10 @@
 // A branching gate on a small state in one block, with the partner index in
-// LDS (Sec. 3.1): shared by the single-state kernel (sim_kernels.hip) and
-// the batched tick (batch_kernels.hip).  Device code only.
+// LDS (Sec. 3.1), for the batched tick (batch_kernels.hip); its hash and its sums
+// are also those of the single state's LDS-index kernels (sim_kernels.hip).
+// Device code only.
 //
 // The same entries are indexed as by the global index (under the controls,
-// pivot bit clear), by the same label hash; the same look-ups (label ^ x from
+// pivot bit clear); the same look-ups (label ^ x from
 // the pivot-set entries) pair them; Eq. 2 is evaluated by ent::u2_eval and the
 // outputs are written in entry order.  The outputs and their order are
 // therefore those of the index-build / probe / write kernels, in one launch
@@ -33,6 +34,20 @@ static_assert(kLdsU2Max < (1u << kIdxBits) && kMaxItems * kThreads == (int)kLdsU
 
 // LDS of one block (about 96 KB); declared by the kernel, whatever the label
 // width, so that both widths share it.
+// Hash of a label for the index in LDS, the slot from its low bits and the
+// fingerprint from the high ones: 32-bit products, which the SIMD multiplies in a
+// fifth of the time of the 64-bit finalizer that the index in memory uses (one
+// CU hashes the whole state, 128 waves at 8192 entries).  Odd multipliers from
+// the roots of 2, 3, 5 and 7 and the golden ratio.
+template <bool WIDE>
+__device__ __forceinline__ uint32_t hash(uint64_t lo, uint64_t hi) {
+  uint32_t h = (uint32_t)lo * 0x6A09E667u + (uint32_t)(lo >> 32) * 0xBB67AE85u;
+  if (WIDE) h += (uint32_t)hi * 0x3C6EF373u + (uint32_t)(hi >> 32) * 0xA54FF53Bu;
+  h ^= h >> 15;
+  h *= 0x9E3779B9u;
+  return h ^ h >> 16;
+}
+
 struct Smem {
   uint32_t tab[kMaxSlots];
   uint32_t par[kLdsU2Max];
@@ -106,9 +121,9 @@ __device__ __forceinline__ Totals u2_items(const Buf& in, const Buf& out, uint32
   for (int k = 0; k < kItems; ++k) {
     const uint32_t i = (uint32_t)k * kThreads + threadIdx.x;
     if (i >= n || !ent::ctrl_ok(d, lo[k], hi[k], WIDE) || ent::pivot_set(d, lo[k], hi[k], WIDE)) continue;
-    const uint64_t h = ent::hash_label(lo[k], hi[k]);
-    const uint32_t val = ((uint32_t)(h >> (32 + kIdxBits)) << kIdxBits) | (i + 1u);
-    uint32_t slot = (uint32_t)h & kMask;
+    const uint32_t h = hash<WIDE>(lo[k], hi[k]);
+    const uint32_t val = ((h >> kIdxBits) << kIdxBits) | (i + 1u);
+    uint32_t slot = h & kMask;
     ++inserts;
     for (uint32_t p = 0; p < kSlots; ++p) {
       ++cas;
@@ -124,9 +139,9 @@ __device__ __forceinline__ Totals u2_items(const Buf& in, const Buf& out, uint32
     const uint32_t i = (uint32_t)k * kThreads + threadIdx.x;
     if (i >= n || !ent::ctrl_ok(d, lo[k], hi[k], WIDE) || !ent::pivot_set(d, lo[k], hi[k], WIDE)) continue;
     const uint64_t qlo = lo[k] ^ d.x_lo, qhi = WIDE ? (hi[k] ^ d.x_hi) : 0ull;
-    const uint64_t h = ent::hash_label(qlo, qhi);
-    const uint32_t fp = (uint32_t)(h >> (32 + kIdxBits));
-    uint32_t slot = (uint32_t)h & kMask;
+    const uint32_t h = hash<WIDE>(qlo, qhi);
+    const uint32_t fp = (h >> kIdxBits);
+    uint32_t slot = h & kMask;
     ++lookups;
     for (uint32_t p = 0; p < kSlots; ++p) {
       const uint32_t v = sm.tab[slot];
@@ -219,11 +234,11 @@ __device__ __forceinline__ Totals u2_items(const Buf& in, const Buf& out, uint32
   return t;
 }
 
-// Entries in registers: 1, 2, 4 or 8 a thread, at least MIN.
-template <bool WIDE, int MIN = 1>
+// Entries in registers: 1, 2, 4 or 8 a thread.
+template <bool WIDE>
 __device__ __forceinline__ Totals u2_block(const Buf& in, const Buf& out, uint32_t n, const U2Desc& d, uint64_t cap,
                                            Smem& sm) {
-  if (MIN <= 1 && n <= 1 * kThreads) return u2_items<WIDE, 1>(in, out, n, d, cap, sm);
+  if (n <= 1 * kThreads) return u2_items<WIDE, 1>(in, out, n, d, cap, sm);
   if (n <= 2 * kThreads) return u2_items<WIDE, 2>(in, out, n, d, cap, sm);
   if (n <= 4 * kThreads) return u2_items<WIDE, 4>(in, out, n, d, cap, sm);
   return u2_items<WIDE, 8>(in, out, n, d, cap, sm);
