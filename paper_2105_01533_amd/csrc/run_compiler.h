@@ -43,6 +43,12 @@ struct RunCompiler {
   // passes) at more host time; the batched server, which groups on its
   // critical path, uses a narrower one.
   uint32_t pair_window = 128;
+  // Ops that a host thread compiles (25 ns each) or schedules and packs (100 ns
+  // each) at least: 50 to 100 us of work, where waking the pool takes 10.
+  // Cutting a run costs the kernel the segments that would have reached over the
+  // cut: one block in 60 at 24 qubits.  The batched server, whose requests are
+  // compiled on threads of their own while its ticks use the pool, cuts later.
+  uint32_t compile_part = 2048, schedule_part = 1024;
 
   // Fill ops/start/info from descs.
   void compile(uint32_t nq);

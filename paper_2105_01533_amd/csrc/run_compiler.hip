@@ -94,11 +94,6 @@ uint64_t turn_of(const double2& m) {
 uint8_t word_bit(uint32_t q) { return (uint8_t)(1u << (q >> 5)); }
 
 constexpr unsigned kHostThreads = HostPool::kMaxThreads;
-// Ops that a host thread compiles (25 ns each) or schedules and packs (100 ns
-// each) at least: 50 to 100 us of work, where waking the pool takes 10.  Cutting a
-// run costs the kernel the segments that would have reached over the cut: one
-// block in 60 at 24 qubits.
-constexpr size_t kCompilePart = 2048, kSchedulePart = 1024;
 
 }  // namespace
 
@@ -182,7 +177,7 @@ void RunCompiler::compile(uint32_t nq) {
   part_ops.resize(kHostThreads);
   for (auto& v : part_ops) v.clear();
   std::vector<size_t> pb(kHostThreads, 0), pe(kHostThreads, 0);
-  parallel_parts(n_mono, kCompilePart, [&](size_t b, size_t e, size_t p) {
+  parallel_parts(n_mono, compile_part, [&](size_t b, size_t e, size_t p) {
     // Appends go to a vector on this thread's stack (neighbouring vectors in
     // part_ops share cache lines); its storage is kept in part_ops between calls.
     std::vector<BsOp> out;
@@ -513,7 +508,7 @@ void RunCompiler::schedule(size_t begin, size_t len, std::vector<RpRec>& out, Bs
   rewrite(begin, len, xo, br);
   const uint32_t n = (uint32_t)xo.size();
   std::vector<std::vector<RpRec>> parts(kHostThreads);
-  parallel_parts(n, kSchedulePart, [&](size_t b, size_t e, size_t p) {
+  parallel_parts(n, schedule_part, [&](size_t b, size_t e, size_t p) {
     std::vector<RpRec> mine;   // (the parts' vectors share cache lines)
     schedule_range(xo.data() + b, (uint32_t)(e - b), mine);
     parts[p].swap(mine);
@@ -905,7 +900,7 @@ void RunCompiler::program(size_t begin, size_t len, std::vector<RpBlock>& out, B
   std::vector<BsOp> xo;
   rewrite(begin, len, xo, br);
   std::vector<std::vector<RpBlock>> parts(kHostThreads);
-  parallel_parts(xo.size(), kSchedulePart, [&](size_t b, size_t e, size_t p) {
+  parallel_parts(xo.size(), schedule_part, [&](size_t b, size_t e, size_t p) {
     std::vector<RpRec> recs;
     std::vector<RpBlock> mine;
     schedule_range(xo.data() + b, (uint32_t)(e - b), recs);

@@ -399,7 +399,7 @@ hipError_t copy_out(Request& r) {
   const Buf& b = r.buf[r.cur];
   const bool wide = r.cfg.n_qubits > 64;
   const hipError_t e = copy_state_to_host_soa(b.key_lo, wide ? b.key_hi : nullptr, b.amp, r.nnz, r.res_lo.get(),
-                                              wide ? r.res_hi.get() : nullptr, r.res_amp.get(), nullptr);
+                                              wide ? r.res_hi.get() : nullptr, r.res_amp.get(), nullptr, 1u << 16);
   if (e == hipSuccess) r.copied = true;
   return e;
 }
@@ -433,6 +433,8 @@ void compile_request(Request& r) {
       r.mono_op.push_back(i);
     }
   r.rc.pair_window = 64;   // grouping happens on the tick's critical path
+  r.rc.compile_part = 16384;
+  r.rc.schedule_part = 2048;
   if (r.cfg.mono_mode != SIM_MONO_DIRECT) r.rc.compile(r.cfg.n_qubits);
   else r.rc.n_qubits = r.cfg.n_qubits;
   r.compiled = true;

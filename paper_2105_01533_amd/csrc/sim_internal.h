@@ -386,6 +386,10 @@ void launch_mono_rp(hipStream_t st, Buf b, const uint64_t* nnz, const RpBlock* p
 // Set-up of the register-plane passes' cross-stream ordering on the current
 // device (once per device; called by sim_create).
 hipError_t mono_rp_init();
+// Entries that a host thread copies at least: half a megabyte, 50 us or more (fresh
+// pages of the caller's arrays included), where waking the pool takes 10.  (The
+// server's copies, beside its ticks' own use of the pool, take more.)
+constexpr size_t kCopyPart = 1u << 14;
 // n entries of a device state (key_lo, key_hi or null for <= 64 qubits, amp)
 // into host key records and amplitudes, through the calling thread's pinned
 // staging buffer; safe to call from several host threads at once.
@@ -395,7 +399,8 @@ hipError_t copy_state_to_host(const uint64_t* lo, const uint64_t* hi, const doub
 // The same into separate arrays (key_hi may be null: high words not wanted;
 // zeros are written for a null hi).
 hipError_t copy_state_to_host_soa(const uint64_t* lo, const uint64_t* hi, const double2* amp, uint64_t n,
-                                  uint64_t* key_lo, uint64_t* key_hi, sim_c64* amps, hipStream_t st);
+                                  uint64_t* key_lo, uint64_t* key_hi, sim_c64* amps, hipStream_t st,
+                                  size_t part = kCopyPart);
 // n host entries (label words every `stride` words; hi may be null: zeros)
 // into the device arrays b, through the same staging; seen: the AND and OR of
 // the labels.  Returns early, without the rest of the copy,

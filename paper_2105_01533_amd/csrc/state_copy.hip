@@ -21,9 +21,6 @@ namespace sparsesim {
 namespace {
 
 constexpr size_t kStageBytes = 16u << 20;   // per host thread, kept for the process's lifetime
-// Entries a task of the host pool takes at least: half a megabyte, 50 us or
-// more (fresh pages of the caller's arrays included) against 10 to wake it.
-constexpr size_t kPart = 1u << 14;
 
 struct Stage {
   char* p = nullptr;
@@ -51,7 +48,7 @@ namespace {
 // s_amp, pb, pe) writes entries [pb, pe) of the chunk that starts at entry b.
 template <class Emit>
 hipError_t staged_copy(const uint64_t* lo, const uint64_t* hi, const double2* amp, uint64_t n, hipStream_t st,
-                       Emit&& emit) {
+                       size_t part, Emit&& emit) {
   if (!n) return hipSuccess;
   char* stage = nullptr;
   hipError_t e = stage_of_thread(&stage);
@@ -71,7 +68,7 @@ hipError_t staged_copy(const uint64_t* lo, const uint64_t* hi, const double2* am
     if (e != hipSuccess) return e;
     // On the host thread pool (on this thread alone when it is itself one of
     // the pool's tasks).
-    parallel_parts(m, kPart, [&](size_t pb, size_t pe, size_t) { emit(b, s_lo, hi ? s_hi : nullptr, s_amp, pb, pe); });
+    parallel_parts(m, part, [&](size_t pb, size_t pe, size_t) { emit(b, s_lo, hi ? s_hi : nullptr, s_amp, pb, pe); });
   }
   return hipSuccess;
 }
@@ -80,7 +77,7 @@ hipError_t staged_copy(const uint64_t* lo, const uint64_t* hi, const double2* am
 
 hipError_t copy_state_to_host(const uint64_t* lo, const uint64_t* hi, const double2* amp, uint64_t n, sim_key* keys,
                               sim_c64* amps, hipStream_t st) {
-  return staged_copy(lo, hi, amp, n, st,
+  return staged_copy(lo, hi, amp, n, st, kCopyPart,
                      [&](uint64_t b, const uint64_t* s_lo, const uint64_t* s_hi, const double2* s_amp, size_t pb, size_t pe) {
                        for (size_t k = pb; k < pe; ++k) keys[b + k] = sim_key{s_lo[k], s_hi ? s_hi[k] : 0};
                        std::memcpy(amps + b + pb, s_amp + pb, 16 * (pe - pb));
@@ -88,8 +85,9 @@ hipError_t copy_state_to_host(const uint64_t* lo, const uint64_t* hi, const doub
 }
 
 hipError_t copy_state_to_host_soa(const uint64_t* lo, const uint64_t* hi, const double2* amp, uint64_t n,
-                                  uint64_t* key_lo, uint64_t* key_hi, sim_c64* amps, hipStream_t st) {
-  return staged_copy(lo, hi, amp, n, st,
+                                  uint64_t* key_lo, uint64_t* key_hi, sim_c64* amps, hipStream_t st,
+                                  size_t part) {
+  return staged_copy(lo, hi, amp, n, st, part,
                      [&](uint64_t b, const uint64_t* s_lo, const uint64_t* s_hi, const double2* s_amp, size_t pb, size_t pe) {
                        std::memcpy(key_lo + b + pb, s_lo + pb, 8 * (pe - pb));
                        if (key_hi) {
@@ -116,7 +114,7 @@ hipError_t copy_state_to_device(const uint64_t* lo, const uint64_t* hi, size_t s
     char* s_amp = stage + (wide ? 16 : 8) * m;
     LabelCell part[HostPool::kMaxThreads];
     for (LabelCell& p : part) p = LabelCell{~0ull, ~0ull, 0, 0};
-    parallel_parts(m, kPart, [&](size_t pb, size_t pe, size_t t) {
+    parallel_parts(m, kCopyPart, [&](size_t pb, size_t pe, size_t t) {
       LabelCell v{~0ull, ~0ull, 0, 0};
       for (size_t k = pb; k < pe; ++k) {
         const sim_key q{lo[(c + k) * stride], hi ? hi[(c + k) * stride] : 0};
