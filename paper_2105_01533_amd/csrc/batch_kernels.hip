@@ -394,7 +394,7 @@ __global__ __launch_bounds__(256) void kb_m_reduce(const BTick* __restrict__ hdr
   __shared__ uint32_t shu[256];
   const int n = (int)hdr->n_meas;
   if (n == 0) return;
-  const BItem* m = items + hdr->n_mono + hdr->n_u2;
+  const BItem* m = items + hdr->item0 + hdr->n_mono + hdr->n_u2;
   const uint32_t* u0 = units + hdr->meas_u0;
   const uint32_t total = u0[n];
   for (uint32_t u = blockIdx.x; u < total; u += gridDim.x) {
@@ -433,7 +433,7 @@ __global__ __launch_bounds__(256) void kb_m_decide(const BTick* __restrict__ hdr
   __shared__ uint32_t shu[256];
   __shared__ int s_o;
   const int n = (int)hdr->n_meas;
-  const BItem* m = items + hdr->n_mono + hdr->n_u2;
+  const BItem* m = items + hdr->item0 + hdr->n_mono + hdr->n_u2;
   const uint32_t* u0 = units + hdr->meas_u0;
   for (int i = blockIdx.x; i < n; i += gridDim.x) {
     const BItem& it = m[i];
@@ -498,7 +498,7 @@ __global__ __launch_bounds__(256) void kb_m_write(const BTick* __restrict__ hdr,
   __shared__ uint32_t s_wave[4];
   const int n = (int)hdr->n_meas;
   if (n == 0) return;
-  const BItem* m = items + hdr->n_mono + hdr->n_u2;
+  const BItem* m = items + hdr->item0 + hdr->n_mono + hdr->n_u2;
   const uint32_t* u0 = units + hdr->meas_u0;
   const uint32_t total = u0[n];
   for (uint32_t u = blockIdx.x; u < total; u += gridDim.x) {
@@ -535,10 +535,36 @@ __global__ __launch_bounds__(256) void kb_m_write(const BTick* __restrict__ hdr,
   }
 }
 
+// ---- a tick's work list and new requests ---------------------------------------
+// One launch for what were four copies a tick (header and items, later
+// headers, unit offsets, ops), each 3 us and as long again before the next:
+// the kernel reads the pinned buffer over the bus.
+__global__ __launch_bounds__(256) void kb_upload(char* __restrict__ dst, const char* __restrict__ src, BUpload u) {
+  for (uint32_t k = 0; k < u.n; ++k) {
+    uint4* d = reinterpret_cast<uint4*>(dst + u.r[k].off);
+    const uint4* s = reinterpret_cast<const uint4*>(src + u.r[k].off);
+    for (uint64_t w = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; w < u.r[k].words;
+         w += (uint64_t)gridDim.x * blockDim.x)
+      d[w] = s[w];
+  }
+}
+
+__global__ __launch_bounds__(64) void kb_init(BInits in) {
+  if (threadIdx.x >= in.n) return;
+  const BInit& r = in.r[threadIdx.x];
+  r.b.key_lo[0] = r.lo;
+  if (r.b.key_hi) r.b.key_hi[0] = r.hi;
+  r.b.amp[0] = make_double2(1.0, 0.0);
+  SlotCtl c{};
+  c.nnz[0] = 1;
+  c.outcome = -1;
+  *r.ctl = c;
+}
+
 }  // namespace
 
-// A tick's kernels, in order, on fixed grids (capturable); families with no
-// items this tick can be left out.
+// A tick's kernels but the measurements', in order, on fixed grids (capturable);
+// families with no items this tick can be left out.
 void launch_batch_tick(hipStream_t st, const BTick* hdr, const BItem* items, const uint32_t* units, int grid,
                        uint32_t families) {
   const size_t lds = (size_t)kMaxPlanes * 64 * 4;
@@ -553,13 +579,28 @@ void launch_batch_tick(hipStream_t st, const BTick* hdr, const BItem* items, con
   }
   if (families & kFamU2s)
     hipLaunchKernelGGL(kb_u2_lds, dim3(grid < 256 ? grid : 256), dim3(lds::kThreads), 0, st, hdr, items);
-  if (families & kFamMeas) launch_batch_meas(st, hdr, items, units, grid);
 }
 
-void launch_batch_meas(hipStream_t st, const BTick* hdr, const BItem* items, const uint32_t* units, int grid) {
-  hipLaunchKernelGGL(kb_m_reduce, dim3(grid), dim3(256), 0, st, hdr, items, units);
-  hipLaunchKernelGGL(kb_m_decide, dim3(grid), dim3(256), 0, st, hdr, items, units);
-  hipLaunchKernelGGL(kb_m_write, dim3(grid), dim3(256), 0, st, hdr, items, units);
+void launch_batch_upload(hipStream_t st, char* dst, const char* src, const BUpload& u) {
+  uint64_t words = 0;
+  for (uint32_t k = 0; k < u.n; ++k) words = u.r[k].words > words ? u.r[k].words : words;
+  const uint64_t blocks = (words + 255) / 256;
+  hipLaunchKernelGGL(kb_upload, dim3((uint32_t)(blocks < 1 ? 1 : blocks < 1024 ? blocks : 1024)), dim3(256), 0, st, dst,
+                     src, u);
+}
+
+void launch_batch_init(hipStream_t st, const BInits& init) {
+  hipLaunchKernelGGL(kb_init, dim3(1), dim3(64), 0, st, init);
+}
+
+void launch_batch_meas(hipStream_t st, const BTick* hdr, const BTick* later, uint32_t rounds, const BItem* items,
+                       const uint32_t* units, int grid) {
+  for (uint32_t j = 0; j < rounds; ++j) {
+    const BTick* h = j ? later + (j - 1) : hdr;
+    hipLaunchKernelGGL(kb_m_reduce, dim3(grid), dim3(256), 0, st, h, items, units);
+    hipLaunchKernelGGL(kb_m_decide, dim3(grid), dim3(256), 0, st, h, items, units);
+    hipLaunchKernelGGL(kb_m_write, dim3(grid), dim3(256), 0, st, h, items, units);
+  }
 }
 
 }  // namespace sparsesim

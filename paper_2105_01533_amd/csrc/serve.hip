@@ -6,8 +6,9 @@
 // Each tick takes one segment from every running request -- a fused
 // phase/permutation run, one branching gate, or one measurement, exactly as
 // the single-state engine would cut it, a run together with the gate right
-// after it -- uploads one work list, replays the
-// captured tick graph, and reads back every slot's control words.  Finished
+// after it -- uploads one work list in one launch, runs the families of
+// kernels that have items (fused runs, then branching gates and measurements
+// side by side), and reads back every slot's control words.  Finished
 // requests are copied to host memory and their device memory is returned to
 // the pool, which lets queued requests in on the next tick.
 //
@@ -255,10 +256,15 @@ struct srv_t {
   size_t items_off = 0, units_off = 0, arena_off = 0, tick_bytes = 0;
   size_t max_items = 0, max_units = 0;   // capacity of the item and unit areas
   size_t chain_hdr_off = 0;               // headers of a tick's later measurement rounds
-  // One captured graph per non-empty set of kernel families (index = family
-  // mask), so a tick replays only the kernels it has items for.
-  hipGraph_t graph[16] = {};
-  hipGraphExec_t exec[16] = {};
+  // The launches a tick has many of, captured: the six kernels of the branching
+  // gates on the global index [0], and the measurements' three for each of 1 ..
+  // kMaxChain rounds.
+  hipGraph_t graph[1 + kMaxChain] = {};
+  hipGraphExec_t exec[1 + kMaxChain] = {};
+  // Branching gates run beside the measurements: on streams of their own from
+  // the end of the fused runs (ev[0]) until the tick's end (ev[1], ev[2]).
+  hipStream_t side[2] = {};
+  hipEvent_t ev[3] = {};
   int grid = 2048;
   uint32_t run_ops = 4096;            // longest fused run per request per tick (ops)
   uint64_t next_id = 1;
@@ -298,14 +304,14 @@ int capture_tick(srv_t* s) {
   const auto* hdr = reinterpret_cast<const BTick*>(s->d_tick);
   const auto* items = reinterpret_cast<const BItem*>(s->d_tick + s->items_off);
   const auto* units = reinterpret_cast<const uint32_t*>(s->d_tick + s->units_off);
+  const auto* later = reinterpret_cast<const BTick*>(s->d_tick + s->chain_hdr_off);
   if (s->cfg.flags & SRV_FLAG_NO_GRAPH) return SIM_OK;
-  for (uint32_t m = 1; m <= kFamAll; ++m) {
+  for (uint32_t k = 0; k <= kMaxChain; ++k) {
     SRV_HIP(hipStreamBeginCapture(s->stream, hipStreamCaptureModeThreadLocal));
-    launch_batch_tick(s->stream, hdr, items, units, s->grid, m);
-    hipGraph_t g = nullptr;
-    SRV_HIP(hipStreamEndCapture(s->stream, &g));
-    s->graph[m] = g;
-    SRV_HIP(hipGraphInstantiate(&s->exec[m], s->graph[m], nullptr, nullptr, 0));
+    if (k == 0) launch_batch_tick(s->stream, hdr, items, units, s->grid, kFamU2);
+    else launch_batch_meas(s->stream, hdr, later, k, items, units, s->grid);
+    SRV_HIP(hipStreamEndCapture(s->stream, &s->graph[k]));
+    SRV_HIP(hipGraphInstantiate(&s->exec[k], s->graph[k], nullptr, nullptr, 0));
   }
   return SIM_OK;
 }
@@ -331,7 +337,7 @@ uint64_t arena_run_cap(const srv_t* s, const Request& r) {
 
 // Bit-sliced fused runs of states of at least this many entries take the
 // register-plane kernel, one launch per run on the server's stream ahead of
-// the tick's graph (two waves per SIMD on 2048-entry tiles, about twice the
+// the tick's kernels (two waves per SIMD on 2048-entry tiles, about twice the
 // LDS-plane tile's speed on large states; the two give the same bits).
 constexpr uint64_t kRpMinEntries = 1ull << 16;
 
@@ -613,15 +619,12 @@ void bg_shutdown(srv_t* s) {
   s->bg_threads.clear();
 }
 
-// Admission uploads read from these (and from the request and the pinned
-// control words), which outlive the copies.
-const double kUnitAmp[2] = {1.0, 0.0};
-
 // Admits queued requests in FIFO order while memory and slots last.  Their
 // circuits are compiled in the background from submission on; a request
 // takes no segment until that is done.
 int admit(srv_t* s) {
   lane_admit(s);
+  BInits init;
   while (!s->queue.empty() && !s->free_slots.empty()) {
     Request& r = *s->reqs[s->queue.front()];
     size_t off;
@@ -649,14 +652,19 @@ int admit(srv_t* s) {
     c.nnz[0] = 1;
     c.outcome = -1;
     s->h_ctl[r.slot] = c;
-    SRV_HIP(hipMemcpyAsync(&s->d_ctl[r.slot], &s->h_ctl[r.slot], sizeof(SlotCtl), hipMemcpyHostToDevice,
-                           s->stream));
-    SRV_HIP(hipMemcpyAsync(r.buf[0].key_lo, &r.basis.lo, 8, hipMemcpyHostToDevice, s->stream));
-    if (wide) SRV_HIP(hipMemcpyAsync(r.buf[0].key_hi, &r.basis.hi, 8, hipMemcpyHostToDevice, s->stream));
-    SRV_HIP(hipMemcpyAsync(r.buf[0].amp, kUnitAmp, 16, hipMemcpyHostToDevice, s->stream));
+    init.r[init.n++] = BInit{&s->d_ctl[r.slot], r.buf[0], r.basis.lo, r.basis.hi};
+    if (init.n == kInitMax) {
+      launch_batch_init(s->stream, init);
+      SRV_HIP(hipGetLastError());
+      init.n = 0;
+    }
     r.state = SRV_RUNNING;
     s->running.push_back(&r);
     s->stats.admitted++;
+  }
+  if (init.n) {
+    launch_batch_init(s->stream, init);
+    SRV_HIP(hipGetLastError());
   }
   return SIM_OK;
 }
@@ -732,6 +740,8 @@ int srv_create(const srv_config* cfg, void* stream, void* pool, size_t pool_byte
   SRV_HIP(hipStreamSynchronize(s->stream));
   int rc = capture_tick(s.get());
   if (rc) return rc;
+  for (hipStream_t& st : s->side) SRV_HIP(hipStreamCreateWithFlags(&st, hipStreamNonBlocking));
+  for (hipEvent_t& e : s->ev) SRV_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
   if (s->lane_cap) {
     const int nw = cfg->lane_workers ? (int)cfg->lane_workers : 8;
     s->lane_depth = nw + 1;
@@ -765,10 +775,17 @@ int srv_destroy(srv_t* s) {
   }
   for (hipStream_t st : s->lane_streams) (void)hipStreamDestroy(st);
   (void)hipStreamSynchronize(s->stream);
-  for (int m = 0; m < 16; ++m) {
-    if (s->exec[m]) (void)hipGraphExecDestroy(s->exec[m]);
-    if (s->graph[m]) (void)hipGraphDestroy(s->graph[m]);
-  }
+  for (hipGraphExec_t e : s->exec)
+    if (e) (void)hipGraphExecDestroy(e);
+  for (hipGraph_t g : s->graph)
+    if (g) (void)hipGraphDestroy(g);
+  for (hipStream_t st : s->side)
+    if (st) {
+      (void)hipStreamSynchronize(st);
+      (void)hipStreamDestroy(st);
+    }
+  for (hipEvent_t e : s->ev)
+    if (e) (void)hipEventDestroy(e);
   if (s->d_tick) (void)hipFree(s->d_tick);
   if (s->h_tick) (void)hipHostFree(s->h_tick);
   if (s->d_ctl) (void)hipFree(s->d_ctl);
@@ -1042,8 +1059,7 @@ int srv_tick(srv_t* s, uint32_t* running, uint32_t* queued) {
   // A branching gate or measurement that comes right after a fused run joins
   // the run's tick: the run works in place and keeps the entry count (so the
   // cap's skip decisions before the gate are the ones the next tick would
-  // make), register-plane runs go before the graph, and the graph runs the
-  // fused kernels before the branching and measurement kernels.  What is
+  // make), fused runs go first, branching and measurement kernels after them.  What is
   // paired depends on the request alone; its kernels and their inputs are
   // those of two ticks, so results are unchanged.
   auto pair_gate = [&](Request* r, const BItem& base) {
@@ -1108,7 +1124,7 @@ int srv_tick(srv_t* s, uint32_t* running, uint32_t* queued) {
         s->stats.bitslice_runs++;
       }
       if (bsl && sg.rp) {
-        // Its own launch ahead of the graph; the request has no item in it.
+        // Its own launch ahead of the tick's kernels; the request has no item there.
         std::memcpy(arena + arena_used, sg.prog.data(), bytes);
         rp_items.push_back(RpItem{r, arena_used, (uint32_t)sg.prog.size(), sg.br});
         arena_used += al(bytes);
@@ -1193,7 +1209,6 @@ int srv_tick(srv_t* s, uint32_t* running, uint32_t* queued) {
       for (const BItem& it : *v) items[ni++] = it;
     // Each later round: its header (only measurement items), first-unit
     // array and items after everything before it.
-    std::vector<size_t> later_i0(later.size());
     auto* later_hdr = reinterpret_cast<BTick*>(s->h_tick + s->chain_hdr_off);
     for (size_t j = 0; j < later.size(); ++j) {
       std::memset(&later_hdr[j], 0, sizeof(BTick));
@@ -1201,19 +1216,18 @@ int srv_tick(srv_t* s, uint32_t* running, uint32_t* queued) {
       later_hdr[j].meas_u0 = w;
       prefix(units + w, later[j], chunks);
       w += (uint32_t)later[j].size() + 1;
-      later_i0[j] = ni;
+      later_hdr[j].item0 = (uint32_t)ni;
       for (const BItem& it : later[j]) items[ni++] = it;
     }
-    SRV_HIP(hipMemcpyAsync(s->d_tick, s->h_tick, s->items_off + ni * sizeof(BItem), hipMemcpyHostToDevice,
-                           s->stream));
-    if (!later.empty())
-      SRV_HIP(hipMemcpyAsync(s->d_tick + s->chain_hdr_off, later_hdr, later.size() * sizeof(BTick),
-                             hipMemcpyHostToDevice, s->stream));
-    SRV_HIP(hipMemcpyAsync(s->d_tick + s->units_off, units, w * sizeof(uint32_t), hipMemcpyHostToDevice, s->stream));
-    if (arena_used)
-      SRV_HIP(hipMemcpyAsync(s->d_tick + s->arena_off, arena, arena_used, hipMemcpyHostToDevice, s->stream));
+    BUpload up;
+    up.add(0, s->items_off + ni * sizeof(BItem));
+    up.add(s->units_off, w * sizeof(uint32_t));
+    if (!later.empty()) up.add(s->chain_hdr_off, later.size() * sizeof(BTick));
+    if (arena_used) up.add(s->arena_off, arena_used);
+    launch_batch_upload(s->stream, s->d_tick, s->h_tick, up);
+    SRV_HIP(hipGetLastError());
     // Register-plane runs first, on the same stream: each finishes before the
-    // graph's kernels start, and no two run at once.
+    // tick's other kernels start, and no two run at once.
     for (const RpItem& x : rp_items) {
       Request* r = x.r;
       const int grid = (int)std::max<uint64_t>(1, (r->nnz + 2047) / 2048);
@@ -1221,25 +1235,37 @@ int srv_tick(srv_t* s, uint32_t* running, uint32_t* queued) {
                      reinterpret_cast<const RpBlock*>(s->d_tick + s->arena_off + x.off), x.nblk, x.br, s->d_rpctl, grid);
       SRV_HIP(hipGetLastError());
     }
-    // Only the kernel families that have items this tick.
-    const uint32_t fam = (nm ? kFamMono : 0u) | (nu ? kFamU2 : 0u) | (ns ? kFamU2s : 0u) | (nq ? kFamMeas : 0u);
-    if (fam == 0) {
-      // only register-plane runs this tick
-    } else if (s->exec[fam]) {
-      SRV_HIP(hipGraphLaunch(s->exec[fam], s->stream));
-    } else {
-      launch_batch_tick(s->stream, reinterpret_cast<const BTick*>(s->d_tick),
-                        reinterpret_cast<const BItem*>(s->d_tick + s->items_off),
-                        reinterpret_cast<const uint32_t*>(s->d_tick + s->units_off), s->grid, fam);
+    // Only the kernel families that have items this tick.  Branching gates and
+    // measurements come after the fused runs (they may be of the same request)
+    // and are of different requests each: the measurements' rounds, or what
+    // there is instead, stay on the tick's stream, the other families run
+    // beside them.  (24 requests of 2^8 to 2^16 entries: 70 us of kernels of
+    // the global index, 30 of the LDS index and 80 of four rounds of
+    // measurements, one after the other; now 95.)
+    const auto* d_hdr = reinterpret_cast<const BTick*>(s->d_tick);
+    const auto* d_items = reinterpret_cast<const BItem*>(s->d_tick + s->items_off);
+    const auto* d_units = reinterpret_cast<const uint32_t*>(s->d_tick + s->units_off);
+    if (nm) launch_batch_tick(s->stream, d_hdr, d_items, d_units, s->grid, kFamMono);
+    const bool beside[2] = {nu && (nq || ns), ns && nq};   // the global index; the LDS index
+    if (beside[0] || beside[1]) SRV_HIP(hipEventRecord(s->ev[0], s->stream));
+    for (int k = 0; k < 2; ++k) {
+      if (!(k ? ns : nu)) continue;
+      const hipStream_t st = beside[k] ? s->side[k] : s->stream;
+      if (beside[k]) SRV_HIP(hipStreamWaitEvent(st, s->ev[0], 0));
+      if (k == 0 && s->exec[0]) SRV_HIP(hipGraphLaunch(s->exec[0], st));
+      else launch_batch_tick(st, d_hdr, d_items, d_units, s->grid, k ? kFamU2s : kFamU2);
+      SRV_HIP(hipGetLastError());
+      if (beside[k]) SRV_HIP(hipEventRecord(s->ev[1 + k], st));
+    }
+    if (nq) {
+      if (s->exec[rounds]) SRV_HIP(hipGraphLaunch(s->exec[rounds], s->stream));
+      else
+        launch_batch_meas(s->stream, d_hdr, reinterpret_cast<const BTick*>(s->d_tick + s->chain_hdr_off), rounds, d_items,
+                          d_units, s->grid);
       SRV_HIP(hipGetLastError());
     }
-    // Later measurement rounds, in order, after the graph.
-    for (size_t j = 0; j < later.size(); ++j) {
-      launch_batch_meas(s->stream, reinterpret_cast<const BTick*>(s->d_tick + s->chain_hdr_off) + j,
-                        reinterpret_cast<const BItem*>(s->d_tick + s->items_off) + later_i0[j],
-                        reinterpret_cast<const uint32_t*>(s->d_tick + s->units_off), s->grid);
-      SRV_HIP(hipGetLastError());
-    }
+    for (int k = 0; k < 2; ++k)
+      if (beside[k]) SRV_HIP(hipStreamWaitEvent(s->stream, s->ev[1 + k], 0));
     int max_slot = -1;
     for (Request* r : s->running) max_slot = std::max(max_slot, r->slot);
     SRV_HIP(hipMemcpyAsync(s->h_ctl, s->d_ctl, (size_t)(max_slot + 1) * sizeof(SlotCtl), hipMemcpyDeviceToHost,

@@ -360,17 +360,45 @@ struct BTick {
   uint32_t n_u2s;              // small branching items (one block each, index in LDS), after the
                                // measurement items
   uint32_t mono_u0, fill_u0, build_u0, chunk_u0, meas_u0;
-  uint32_t pad2[3];
+  uint32_t item0;              // first of this header's items
+  uint32_t pad2[2];
 };
 
 // Kernel families of a tick: fused runs; branching gates on the global index;
 // branching gates of small states (LDS index); measurements.
-constexpr uint32_t kFamMono = 1, kFamU2 = 2, kFamU2s = 4, kFamMeas = 8, kFamAll = 15;
+constexpr uint32_t kFamMono = 1, kFamU2 = 2, kFamU2s = 4, kFamMeas = 8;
 // The kernels of the families in `families`, in tick order.
 void launch_batch_tick(hipStream_t st, const BTick* hdr, const BItem* items, const uint32_t* units, int grid,
                        uint32_t families);
-// The measurement kernels alone (a later step of measurement chains).
-void launch_batch_meas(hipStream_t st, const BTick* hdr, const BItem* items, const uint32_t* units, int grid);
+// Up to four ranges of the tick buffer, from pinned host memory: 16-byte words
+// (byte offsets and lengths are rounded up to them).
+struct BUpload {
+  uint32_t n = 0;
+  struct {
+    uint64_t off, words;
+  } r[4];
+  void add(uint64_t off, uint64_t bytes) {
+    r[n].off = off;
+    r[n++].words = (bytes + 15) / 16;
+  }
+};
+void launch_batch_upload(hipStream_t st, char* dst, const char* src, const BUpload& u);
+// Basis states and control words of newly admitted requests.
+struct BInit {
+  SlotCtl* ctl;
+  Buf b;
+  uint64_t lo, hi;
+};
+constexpr uint32_t kInitMax = 16;
+struct BInits {
+  uint32_t n = 0, pad = 0;
+  BInit r[kInitMax];
+};
+void launch_batch_init(hipStream_t st, const BInits& init);
+// The measurement kernels of `rounds` steps of measurement chains: the tick's
+// own header, then those at later.
+void launch_batch_meas(hipStream_t st, const BTick* hdr, const BTick* later, uint32_t rounds, const BItem* items,
+                       const uint32_t* units, int grid);
 
 
 // ---- launchers (sim_kernels.hip) -------------------------------------------
