@@ -453,10 +453,10 @@ int sim_kernel_stats_reset(sim_t* s);
  * with the partner index in LDS; this flag sends them through the global
  * index kernels like larger states (same outputs, same order). */
 #define SRV_FLAG_U2_GLOBAL_INDEX 2u
-/* Bit-sliced fused runs of states of at least 65,536 entries run on the
- * register-plane kernel, one launch per run on the server's stream ahead of
- * the tick's graph; this flag keeps them on the graph's LDS-plane tile (the
- * same results, bit for bit). */
+/* Bit-sliced fused runs take the register-plane kernels, those of a tick in one
+ * launch (with a large-state lane, only those of states of at least 65,536
+ * entries); this flag keeps them on the LDS-plane tile (the same results, bit
+ * for bit). */
 #define SRV_FLAG_NO_RP 4u
 /* A branching gate or measurement that directly follows a request's fused
  * run joins the run's tick (the fused kernels run first, in place, and keep

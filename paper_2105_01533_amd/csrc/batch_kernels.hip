@@ -88,17 +88,8 @@ __device__ __forceinline__ uint32_t prefix012(uint32_t e, uint32_t* s_wave, uint
 }
 
 // ---- fused runs: one 2048-entry tile per unit, one wave per block ----------
-// Bit-sliced runs take the register-plane tile (its planes in v100 and up,
-// which the compiler may not allocate: amdgpu_num_vgpr counts pairs on
-// gfx950, 40 = v0..v79; the clobber makes the kernel's VGPR count cover
-// 131 planes).
-
-// Fused runs: one unit (kChunk entries of one state) per block iteration, on
-// the LDS-plane bit-sliced tile, or per entry for runs that form cannot take.
-// (The register-plane tile of the single-state engine is not used here: its
-// GPR-indexed plane accesses gave results that depended on which other
-// states' tiles shared a SIMD, while the LDS-plane tile reproduces the
-// single-state results in any mix.)
+// On the LDS-plane bit-sliced tile (SRV_FLAG_NO_RP; otherwise bit-sliced runs
+// take kb_mono_rp), or per entry for runs that form cannot take.
 __global__ __launch_bounds__(64, 2) void kb_mono(const BTick* __restrict__ hdr, const BItem* __restrict__ items,
                                               const uint32_t* __restrict__ units) {
   extern __shared__ uint32_t lds_all[];

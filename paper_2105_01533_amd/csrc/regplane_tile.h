@@ -15,6 +15,7 @@
 //   v81, v82   Q  -- weight-2 counter, 2 bits
 //   v83..v85   R  -- weight-1 counter, 3 bits
 //   v86..v94   temporaries; v95 prefetch address, v96 prefetch target
+//   v97        the lane number (kept here, it costs the compiler no register)
 //   v100 + q   plane q; plane nq is all ones, nq + 1 scratch, nq + 2 zero.
 // An eighth-turn op adding k where x holds adds x (k & 1) to R, x ((k >> 1) &
 // 1) to Q and x (k >> 2) to P, so the entry's count is R + 2 Q + 4 P mod 8.
@@ -47,8 +48,8 @@ namespace rp {
 // allocations (132 and 164 VGPRs, three waves per SIMD) gave results on
 // multi-million-entry states that differed from run to run, as did two waves
 // of different programs on one SIMD; waves of one program at most two per
-// SIMD reproduce the LDS-plane pass bit for bit (the launcher keeps passes
-// apart).  The 132-register form also loaded a label's second word
+// SIMD reproduce the LDS-plane pass bit for bit, as does one wave a SIMD of any
+// programs (the launchers keep passes apart).  The 132-register form also loaded a label's second word
 // (v132..v163) past its allocation.
 constexpr uint32_t kVmax = 230;
 constexpr uint32_t kTurnAccBytes = 32 * 64 * 8;   // per wave: 32 entries x 64 lanes x 64-bit turns
@@ -103,6 +104,12 @@ __device__ __forceinline__ void wr_plane(uint32_t q, uint32_t v) {
       "s_set_gpr_idx_off" ::"s"(q),
       "v"(v)
       : "m0");
+}
+
+__device__ __forceinline__ int lane_now() {
+  int l;
+  asm volatile("v_mov_b32 %0, v97" : "=v"(l));
+  return l;
 }
 
 #define RP_IN(R, X) asm volatile("v_mov_b32 v" #R ", %0" ::"v"(X))
@@ -430,9 +437,8 @@ __device__ __forceinline__ void turn_index(const uint32_t (&x)[8], uint32_t (&B)
 }
 
 // Entry m of a table of 256: the sum of the fractions that m's bits name.
-__device__ __forceinline__ void turn_table(const uint64_t (&t)[8], uint64_t* table, int lane) {
-  int l = lane;
-  asm volatile("" : "+v"(l));   // (the bits' masks are formed here, not kept live)
+__device__ __forceinline__ void turn_table(const uint64_t (&t)[8], uint64_t* table) {
+  const int l = lane_now();   // (the bits' masks are formed here, not kept live)
   uint64_t s = 0;
 #pragma unroll
   for (int u = 0; u < 6; ++u) {
@@ -462,14 +468,15 @@ __device__ __forceinline__ void turn_table(const uint64_t (&t)[8], uint64_t* tab
 // entering the interpreter.
 template <int H>
 __device__ __forceinline__ void captured_half(TurnPtr tau, uint32_t ng, uint32_t first, uint32_t nj, uint64_t* acc,
-                                              uint64_t* table, int lane) {
+                                              uint64_t* table) {
+  const int lane = lane_now();
   uint64_t a[16], t[8];
   uint32_t x[8], B[4];
 #pragma unroll
   for (int u = 0; u < 8; ++u) t[u] = tau[u];
   rd_planes8(first, x);
   turn_index<H>(x, B);
-  turn_table(t, table, lane);
+  turn_table(t, table);
 #pragma unroll
   for (int i = 0; i < 16; ++i) a[i] = acc[64 * (8 * (i >> 2) + 4 * H + (i & 3)) + lane];
   const bool upper = nj > 16u + 4u * H;
@@ -479,38 +486,44 @@ __device__ __forceinline__ void captured_half(TurnPtr tau, uint32_t ng, uint32_t
     const uint32_t gn = g + 1 < ng ? g + 1 : g;
 #pragma unroll
     for (int u = 0; u < 8; ++u) t[u] = tau[8 * g + 8 + u];
-    uint64_t v[8];
+    uint64_t v[12];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] = table[(B[i & 3] >> (8 * (i >> 2))) & 0xffu];
+    for (int i = 0; i < 4; ++i) v[i] = table[B[i] & 0xffu];
     __builtin_amdgcn_sched_barrier(0);
     uint32_t C[4];
     rd_planes8(first + 8 * gn, x);
     turn_index<H>(x, C);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) a[i] += v[i];
-    __builtin_amdgcn_sched_barrier(0);
+    for (int i = 0; i < 4; ++i) a[i] += v[i];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = table[(B[i] >> 8) & 0xffu];
     if (upper) {
 #pragma unroll
-      for (int i = 0; i < 8; ++i) v[i] = table[(B[i & 3] >> (8 * (i >> 2) + 16)) & 0xffu];
+      for (int i = 4; i < 12; ++i) v[i] = table[(B[i & 3] >> (8 + 2 * (i & 12))) & 0xffu];
       __builtin_amdgcn_sched_barrier(0);
-      turn_table(t, table, lane);   // (over what the reads above, issued before, still use)
+      turn_table(t, table);   // (over what the reads above, issued before, still use)
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int i = 0; i < 8; ++i) a[8 + i] += v[i];
+      for (int i = 4; i < 12; ++i) a[4 + i] += v[i];
     } else {
-      turn_table(t, table, lane);
+      __builtin_amdgcn_sched_barrier(0);
+      turn_table(t, table);
+      __builtin_amdgcn_sched_barrier(0);
     }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) a[4 + i] += v[i];
 #pragma unroll
     for (int k = 0; k < 4; ++k) B[k] = C[k];
   }
+  const int lane_end = lane_now();
 #pragma unroll
-  for (int i = 0; i < 16; ++i) acc[64 * (8 * (i >> 2) + 4 * H + (i & 3)) + lane] = a[i];
+  for (int i = 0; i < 16; ++i) acc[64 * (8 * (i >> 2) + 4 * H + (i & 3)) + lane_end] = a[i];
 }
 __device__ __forceinline__ void captured_turns(TurnPtr tau, uint32_t ng, uint32_t first, uint32_t nj, uint64_t* acc,
-                                               uint64_t* table, int lane) {
-  captured_half<0>(tau, ng, first, nj, acc, table, lane);
-  if (nj > 4) captured_half<1>(tau, ng, first, nj, acc, table, lane);
+                                               uint64_t* table) {
+  captured_half<0>(tau, ng, first, nj, acc, table);
+  if (nj > 4) captured_half<1>(tau, ng, first, nj, acc, table);
   for (uint32_t g = 0; g < ng; ++g) clear_planes8(first + 8 * g);
 }
 
@@ -554,24 +567,30 @@ __device__ __forceinline__ void store_word(const Buf& b, uint64_t base, uint32_t
 // Apply a run's program (nblk blocks) to the tile at base (lim valid
 // entries).  TURNS: the kernel provides acc, the wave's turn accumulators in
 // LDS, and table, its subset-sum tables; a run uses them if it has turn ops
-// (the result does not depend on TURNS otherwise).
-template <bool TURNS>
-__device__ __forceinline__ void rp_tile(const Buf& b, uint64_t base, uint32_t lim,
-                                        const RpBlock* __restrict__ prog, uint32_t nblk, const BsRun& run, uint64_t* acc, uint64_t* table) {
-  // The lane number, opaque to the optimizer: values derived from it are
-  // formed where used, not kept live across a kernel's loop over tiles.
-  int lane = threadIdx.x;
-  asm volatile("" : "+v"(lane));
-  const uint32_t nq = run.n_planes;
-  const bool turns = TURNS && run.has_turns;
-  const uint32_t rw = run.words_read | run.words_write;
+// (the result does not depend on TURNS otherwise).  prefetch: bring the program
+// into the XCD's L2 first.
+// get: the state's arrays and the run's parameters, asked for before and again
+// after the program (kept over it they take scalar registers it needs).
+struct RpArgs {
+  Buf b;
+  BsRun run;
+};
+template <bool TURNS, class Get>
+__device__ __forceinline__ void rp_tile(Get&& get, uint64_t base, uint32_t lim, const RpBlock* __restrict__ prog,
+                                        uint32_t nblk, bool prefetch, uint64_t* acc, uint64_t* table) {
+  const RpArgs before = get();
+  const Buf& b = before.b;
+  asm volatile("v_mov_b32 v97, %0" ::"v"(threadIdx.x));
+  const uint32_t nq = before.run.n_planes;
+  const bool turns = TURNS && before.run.has_turns;
+  const uint32_t rw = before.run.words_read | before.run.words_write;
   Fetch f;
   f.rs = buf_rsrc_v4(prog, 64u * nblk);
   f.off = 0;
-  if (blockIdx.x < 64) prefetch_program(f, 64u * nblk, lane);   // eight waves an XCD
+  if (prefetch) prefetch_program(f, 64u * nblk, lane_now());
 #pragma unroll
   for (int w = 0; w < 4; ++w)
-    if (rw & (1u << w)) load_word(b, base, lim, w, lane);
+    if (rw & (1u << w)) load_word(b, base, lim, w, lane_now());
   wr_plane(nq, ~0u);       // all ones
   wr_plane(nq + 2, 0u);    // zero
   if (turns)
@@ -580,6 +599,7 @@ __device__ __forceinline__ void rp_tile(const Buf& b, uint64_t base, uint32_t li
       "v_mov_b32 v80, 0\n\tv_mov_b32 v81, 0\n\tv_mov_b32 v82, 0\n\t"
       "v_mov_b32 v83, 0\n\tv_mov_b32 v84, 0\n\tv_mov_b32 v85, 0");
   if (turns) {
+    const int lane = lane_now();
 #pragma unroll
     for (int j = 0; j < 32; ++j) acc[64 * j + lane] = 0;
   }
@@ -593,11 +613,11 @@ __device__ __forceinline__ void rp_tile(const Buf& b, uint64_t base, uint32_t li
       if (!turns) break;   // the host never sends turn ops to this variant
       if (shape == kRpTC) {
         captured_turns(reinterpret_cast<TurnPtr>(reinterpret_cast<uint64_t>(prog) + f.off), cnt, nq + 3, (lim + 63) / 64,
-                       acc, table, lane);
+                       acc, table);
       } else if (shape == kRpTB) {
-        turn_groups<kRpTB>(f, cnt, acc, table, lane);
+        turn_groups<kRpTB>(f, cnt, acc, table, lane_now());
       } else {
-        turn_groups<kRpTG>(f, cnt, acc, table, lane);
+        turn_groups<kRpTG>(f, cnt, acc, table, lane_now());
       }
       f.off += 64u * cnt;
     } else {
@@ -605,10 +625,12 @@ __device__ __forceinline__ void rp_tile(const Buf& b, uint64_t base, uint32_t li
     }
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the prefetch
+  const RpArgs after = get();
+  const BsRun& run = after.run;
   // Labels back to memory (only words some gate flips).
 #pragma unroll
   for (int w = 0; w < 4; ++w)
-    if (run.words_write & (1u << w)) store_word(b, base, lim, w, (int)nq, lane);
+    if (run.words_write & (1u << w)) store_word(after.b, base, lim, w, (int)nq, lane_now());
   if (!run.has_phase) return;
   uint32_t P, Q0, Q1, R0, R1, R2;
   asm volatile(
@@ -616,7 +638,8 @@ __device__ __forceinline__ void rp_tile(const Buf& b, uint64_t base, uint32_t li
       "v_mov_b32 %3, v83\n\tv_mov_b32 %4, v84\n\tv_mov_b32 %5, v85"
       : "=v"(P), "=v"(Q0), "=v"(Q1), "=v"(R0), "=v"(R1), "=v"(R2));
   // One complex multiply per amplitude by the accumulated phase.
-  double2* amp = b.amp + base + lane;
+  const int lane = lane_now();
+  double2* amp = after.b.amp + base + lane;
 #pragma unroll 1
   for (int j = 0; j < 32; ++j) {
     if (64u * j + lane >= lim) break;

@@ -335,14 +335,16 @@ uint64_t arena_run_cap(const srv_t* s, const Request& r) {
   return std::max<uint64_t>(1, std::min({by_groups, by_desc, by_prog}));
 }
 
-// Bit-sliced fused runs of states of at least this many entries take the
-// register-plane kernel, one launch per run on the server's stream ahead of
-// the tick's kernels (two waves per SIMD on 2048-entry tiles, about twice the
-// LDS-plane tile's speed on large states; the two give the same bits).
-constexpr uint64_t kRpMinEntries = 1ull << 16;
+// Bit-sliced fused runs take the register-plane kernels, those of a tick in one
+// launch (a wave a SIMD, see kb_mono_rp), or, of a state of more tiles than
+// there are SIMDs, in one of its own (two waves a SIMD) ahead of it.  The
+// LDS-plane tile (SRV_FLAG_NO_RP) gives the same bits.  Register-plane passes
+// wait for those of other streams, so beside a large-state lane, whose passes
+// take as long as ticks do, small states keep to the LDS-plane tile.
+constexpr uint64_t kRpAlone = 1024ull * 2048 + 1, kRpBesideLane = 1ull << 16;
 
 bool use_rp(const srv_t* s, uint64_t nnz) {
-  return !(s->cfg.flags & SRV_FLAG_NO_RP) && nnz >= kRpMinEntries;
+  return !(s->cfg.flags & SRV_FLAG_NO_RP) && (!s->lane_cap || nnz >= kRpBesideLane);
 }
 
 // Position in a request's op list.
@@ -723,7 +725,7 @@ int srv_create(const srv_config* cfg, void* stream, void* pool, size_t pool_byte
   for (int k = (int)ns - 1; k >= 0; --k) s->free_slots.push_back(k);
   // A tick has at most two first-round items per running request (a fused
   // run and the branching gate or measurement paired with it) and
-  // n_mono + 3 n_u2 + n_meas + 5 <= 4 ns + 5 unit offsets for them; each of
+  // n_mono + 3 n_u2 + n_meas + n_rp + 6 <= 4 ns + 6 unit offsets for them; each of
   // the kMaxChain - 1 later measurement rounds adds at most one item per
   // request and ns + 1 unit offsets.
   s->max_items = (2 + (kMaxChain - 1)) * ns;
@@ -922,7 +924,7 @@ int srv_tick(srv_t* s, uint32_t* running, uint32_t* queued) {
   char* arena = s->h_tick + s->arena_off;
   size_t arena_used = 0;
   std::vector<Request*> mono, u2, meas;
-  std::vector<BItem> mono_items, u2_items, meas_items, u2s_items;
+  std::vector<BItem> mono_items, u2_items, meas_items, u2s_items, rpb_items;
   std::vector<Request*> done_now;
   // Every request's next segment; the fused runs that take the bit-sliced
   // form are grouped on the host thread pool, one request per task (runs of
@@ -1123,7 +1125,15 @@ int srv_tick(srv_t* s, uint32_t* running, uint32_t* queued) {
         r->st.bitslice_passes++;
         s->stats.bitslice_runs++;
       }
-      if (bsl && sg.rp) {
+      if (bsl && sg.rp && r->nnz < kRpAlone) {
+        std::memcpy(arena + arena_used, sg.prog.data(), bytes);
+        it.prog = reinterpret_cast<const RpBlock*>(s->d_tick + s->arena_off + arena_used);
+        it.ngroups = (uint32_t)sg.prog.size();
+        it.run = sg.br;
+        arena_used += al(bytes);
+        rpb_items.push_back(it);
+        s->stats.rp_runs++;
+      } else if (bsl && sg.rp) {
         // Its own launch ahead of the tick's kernels; the request has no item there.
         std::memcpy(arena + arena_used, sg.prog.data(), bytes);
         rp_items.push_back(RpItem{r, arena_used, (uint32_t)sg.prog.size(), sg.br});
@@ -1157,7 +1167,7 @@ int srv_tick(srv_t* s, uint32_t* running, uint32_t* queued) {
   }
   const uint32_t nm = (uint32_t)mono_items.size(), nu = (uint32_t)u2_items.size(), nq = (uint32_t)meas_items.size();
   const uint32_t ns = (uint32_t)u2s_items.size();
-  const uint32_t nrp = (uint32_t)rp_items.size();
+  const uint32_t nrp = (uint32_t)rp_items.size(), nrb = (uint32_t)rpb_items.size();
   // Later measurement rounds: round j holds step j of every chain longer
   // than j (the count before the chain bounds its units).
   uint32_t rounds = 1;
@@ -1170,15 +1180,16 @@ int srv_tick(srv_t* s, uint32_t* running, uint32_t* queued) {
     n_later += v.size();
     later_units += v.size() + 1;
   }
-  if (nm + nu + nq + ns + nrp) {
-    const size_t n_units = (size_t)nm + 3 * (size_t)nu + nq + 5;
-    if ((size_t)nm + nu + nq + ns + n_later > s->max_items || n_units + later_units > s->max_units)
+  if (nm + nu + nq + ns + nrp + nrb) {
+    const size_t n_units = (size_t)nm + 3 * (size_t)nu + nq + nrb + 6;
+    if ((size_t)nm + nu + nq + ns + nrb + n_later > s->max_items || n_units + later_units > s->max_units)
       return sfail(SIM_E_NOMEM, "tick work list exceeds its area");
     std::memset(hdr, 0, sizeof(BTick));
     hdr->n_mono = nm;
     hdr->n_u2 = nu;
     hdr->n_meas = nq;
     hdr->n_u2s = ns;
+    hdr->n_rp = nrb;
     uint32_t w = 0;
     auto prefix = [&](uint32_t* at, const std::vector<BItem>& v, auto units_of) {
       uint32_t acc = 0;
@@ -1204,8 +1215,11 @@ int srv_tick(srv_t* s, uint32_t* running, uint32_t* queued) {
     hdr->meas_u0 = w;
     prefix(units + w, meas_items, chunks);
     w += nq + 1;
+    hdr->rp_u0 = w;
+    prefix(units + w, rpb_items, chunks);
+    w += nrb + 1;
     size_t ni = 0;
-    for (const auto& v : {&mono_items, &u2_items, &meas_items, &u2s_items})
+    for (const auto& v : {&mono_items, &u2_items, &meas_items, &u2s_items, &rpb_items})
       for (const BItem& it : *v) items[ni++] = it;
     // Each later round: its header (only measurement items), first-unit
     // array and items after everything before it.
@@ -1246,6 +1260,10 @@ int srv_tick(srv_t* s, uint32_t* running, uint32_t* queued) {
     const auto* d_items = reinterpret_cast<const BItem*>(s->d_tick + s->items_off);
     const auto* d_units = reinterpret_cast<const uint32_t*>(s->d_tick + s->units_off);
     if (nm) launch_batch_tick(s->stream, d_hdr, d_items, d_units, s->grid, kFamMono);
+    if (nrb) {
+      launch_batch_mono_rp(s->stream, d_hdr, d_items, d_units, units[hdr->rp_u0 + nrb]);
+      SRV_HIP(hipGetLastError());
+    }
     const bool beside[2] = {nu && (nq || ns), ns && nq};   // the global index; the LDS index
     if (beside[0] || beside[1]) SRV_HIP(hipEventRecord(s->ev[0], s->stream));
     for (int k = 0; k < 2; ++k) {
@@ -1282,7 +1300,7 @@ int srv_tick(srv_t* s, uint32_t* running, uint32_t* queued) {
       s->stats.wait_ms += ms_since(t_w);
     }
     s->stats.ticks++;
-    s->stats.items += nm + nu + nq + ns + nrp + n_later;
+    s->stats.items += nm + nu + nq + ns + nrp + nrb + n_later;
     // Fold the results back.
     std::vector<std::pair<Request*, int>> failed;
     for (Request* r : u2) {
@@ -1321,7 +1339,7 @@ int srv_tick(srv_t* s, uint32_t* running, uint32_t* queued) {
   }
   rc = fold_copies(s);
   if (rc) return rc;
-  if (nm + nu + nq + ns + nrp == 0 && (waiting || !s->copying.empty())) {
+  if (nm + nu + nq + ns + nrp + nrb == 0 && (waiting || !s->copying.empty())) {
     // Nothing launched: wait (briefly) for the background work instead of spinning.
     const auto t_w = std::chrono::steady_clock::now();
     bg_wait_any(s, 200);

@@ -335,6 +335,7 @@ struct BItem {
   const BsGroup* gops;         // bit-sliced (LDS-plane) groups (gops != null) ...
   uint32_t ngroups, n_dops;
   const MonoDesc* dops;        // ... or per-entry descriptors
+  const RpBlock* prog;         // ... or a register-plane program of ngroups blocks
   BsRun run;
   uint32_t run_flags;
   uint32_t chain;              // measurement: its step in a chain of the tick (0: first; later steps
@@ -361,7 +362,7 @@ struct BTick {
                                // measurement items
   uint32_t mono_u0, fill_u0, build_u0, chunk_u0, meas_u0;
   uint32_t item0;              // first of this header's items
-  uint32_t pad2[2];
+  uint32_t n_rp, rp_u0;        // fused runs on register planes, after the LDS-index items
 };
 
 // Kernel families of a tick: fused runs; branching gates on the global index;
@@ -370,6 +371,8 @@ constexpr uint32_t kFamMono = 1, kFamU2 = 2, kFamU2s = 4, kFamMeas = 8;
 // The kernels of the families in `families`, in tick order.
 void launch_batch_tick(hipStream_t st, const BTick* hdr, const BItem* items, const uint32_t* units, int grid,
                        uint32_t families);
+// (tiles: all items')
+void launch_batch_mono_rp(hipStream_t st, const BTick* hdr, const BItem* items, const uint32_t* units, uint32_t tiles);
 // Up to four ranges of the tick buffer, from pinned host memory: 16-byte words
 // (byte offsets and lengths are rounded up to them).
 struct BUpload {
