@@ -87,9 +87,9 @@ __device__ __forceinline__ uint32_t prefix012(uint32_t e, uint32_t* s_wave, uint
   return woff + pre;
 }
 
-// ---- fused runs: one 2048-entry tile per unit, one wave per block ----------
-// On the LDS-plane bit-sliced tile (SRV_FLAG_NO_RP; otherwise bit-sliced runs
-// take kb_mono_rp), or per entry for runs that form cannot take.
+// ---- fused runs on the LDS-plane bit-sliced tile (SRV_FLAG_NO_RP, or beside a
+// large-state lane; otherwise they take kb_mono_rp): one 2048-entry tile per
+// unit, one wave per block ------------------------------------------------------
 __global__ __launch_bounds__(64, 2) void kb_mono(const BTick* __restrict__ hdr, const BItem* __restrict__ items,
                                               const uint32_t* __restrict__ units) {
   extern __shared__ uint32_t lds_all[];
@@ -103,40 +103,66 @@ __global__ __launch_bounds__(64, 2) void kb_mono(const BTick* __restrict__ hdr, 
     const BItem& it = items[i];
     const uint64_t base = (uint64_t)(u - u0[i]) * kChunk;
     const uint32_t lim = (uint32_t)(it.nnz - base < kChunk ? it.nnz - base : kChunk);
-    if (it.gops) {
-      if (it.run.has_turns)
-        bs::bs_tile<true>(it.in, base, lim, it.gops, it.ngroups, it.run, L);
-      else
-        bs::bs_tile<false>(it.in, base, lim, it.gops, it.ngroups, it.run, L);
-      continue;
-    }
+    if (it.run.has_turns)
+      bs::bs_tile<true>(it.in, base, lim, it.gops, it.ngroups, it.run, L);
+    else
+      bs::bs_tile<false>(it.in, base, lim, it.gops, it.ngroups, it.run, L);
+  }
+}
+
+// ---- fused runs per entry (short ones, and those the bit planes cannot take) ---
+// Eight entries a thread in registers, the run's descriptors through LDS.  A
+// wave's 2048 entries one after the other, each reading the descriptors anew,
+// took 68 us for a tick's runs of up to 15 gates; this 15.
+constexpr uint32_t kEachDescs = 64;
+__global__ __launch_bounds__(256) void kb_mono_each(const BTick* __restrict__ hdr, const BItem* __restrict__ items,
+                                                    const uint32_t* __restrict__ units) {
+  __shared__ MonoDesc sg[kEachDescs];
+  const int n = (int)hdr->n_each;
+  if (n == 0) return;
+  const BItem* each = items + hdr->n_mono + hdr->n_u2 + hdr->n_meas + hdr->n_u2s + hdr->n_rp;
+  const uint32_t* u0 = units + hdr->each_u0;
+  const uint32_t total = u0[n];
+  constexpr int kItems = kChunk / 256;
+  for (uint32_t u = blockIdx.x; u < total; u += gridDim.x) {
+    const int i = find_item(u0, n, u);
+    const BItem& it = each[i];
+    const uint64_t base = (uint64_t)(u - u0[i]) * kChunk;
+    const uint32_t lim = (uint32_t)(it.nnz - base < kChunk ? it.nnz - base : kChunk);
     const bool phase = it.run_flags & kRunPhase, flip = it.run_flags & kRunFlip;
-    for (uint32_t e = threadIdx.x; e < lim; e += 64) {
-      const uint64_t idx = base + e;
-      uint64_t lo = it.in.key_lo[idx], hi = it.wide ? it.in.key_hi[idx] : 0ull;
-      double2 a = make_double2(0.0, 0.0);
-      if (phase) a = it.in.amp[idx];
-      for (uint32_t k = 0; k < it.n_dops; ++k) {
-        const MonoDesc d = it.dops[k];
-        const bool c = (lo & d.ctrl_lo) == d.ctrl_lo && (!it.wide || (hi & d.ctrl_hi) == d.ctrl_hi);
-        const bool thi = it.wide && d.target >= 64;
-        const uint64_t tbit = 1ull << (d.target & 63);
-        const uint64_t w = thi ? hi : lo;
-        if (d.flags & kHasPhase) {
-          const double2 r = ent::cmul(a, ent::sel2((w & tbit) != 0, d.m1, d.m0));
-          a = ent::sel2(c, r, a);
-        }
-        if (d.flags & kFlip) {
-          const uint64_t f = c ? tbit : 0ull;
-          if (thi) hi ^= f;
-          else lo ^= f;
-        }
+    uint64_t lo[kItems], hi[kItems];
+    double2 a[kItems];
+#pragma unroll
+    for (int k = 0; k < kItems; ++k) {
+      const uint32_t e = k * 256 + threadIdx.x;
+      lo[k] = hi[k] = 0;
+      a[k] = make_double2(0.0, 0.0);
+      if (e >= lim) continue;
+      lo[k] = it.in.key_lo[base + e];
+      if (it.wide) hi[k] = it.in.key_hi[base + e];
+      if (phase) a[k] = it.in.amp[base + e];
+    }
+    for (uint32_t d0 = 0; d0 < it.n_dops; d0 += kEachDescs) {
+      const uint32_t nd = it.n_dops - d0 < kEachDescs ? it.n_dops - d0 : kEachDescs;
+      __syncthreads();   // (the descriptors before these have been used)
+      for (uint32_t w = threadIdx.x; w < nd * (uint32_t)(sizeof(MonoDesc) / 16); w += 256)
+        reinterpret_cast<uint4*>(sg)[w] = reinterpret_cast<const uint4*>(it.dops + d0)[w];
+      __syncthreads();
+      for (uint32_t q = 0; q < nd; ++q) {
+#pragma unroll
+        for (int k = 0; k < kItems; ++k)
+          if ((uint32_t)k * 256 < lim) ent::mono_step(sg[q], it.wide != 0, lo[k], hi[k], a[k]);
       }
+    }
+#pragma unroll
+    for (int k = 0; k < kItems; ++k) {
+      const uint32_t e = k * 256 + threadIdx.x;
+      if (e >= lim) continue;
       if (flip) {
-        it.in.key_lo[idx] = lo;
-        if (it.wide) it.in.key_hi[idx] = hi;
+        it.in.key_lo[base + e] = lo[k];
+        if (it.wide) it.in.key_hi[base + e] = hi[k];
       }
-      if (phase) it.in.amp[idx] = a;
+      if (phase) it.in.amp[base + e] = a[k];
     }
   }
 }
@@ -560,6 +586,7 @@ void launch_batch_tick(hipStream_t st, const BTick* hdr, const BItem* items, con
                        uint32_t families) {
   const size_t lds = (size_t)kMaxPlanes * 64 * 4;
   if (families & kFamMono) hipLaunchKernelGGL(kb_mono, dim3(grid), dim3(64), lds, st, hdr, items, units);
+  if (families & kFamEach) hipLaunchKernelGGL(kb_mono_each, dim3(grid), dim3(256), 0, st, hdr, items, units);
   if (families & kFamU2) {
     hipLaunchKernelGGL(kb_fill, dim3(grid), dim3(256), 0, st, hdr, items, units);
     hipLaunchKernelGGL(kb_build, dim3(grid), dim3(256), 0, st, hdr, items, units);

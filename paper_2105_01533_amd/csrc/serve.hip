@@ -725,7 +725,7 @@ int srv_create(const srv_config* cfg, void* stream, void* pool, size_t pool_byte
   for (int k = (int)ns - 1; k >= 0; --k) s->free_slots.push_back(k);
   // A tick has at most two first-round items per running request (a fused
   // run and the branching gate or measurement paired with it) and
-  // n_mono + 3 n_u2 + n_meas + n_rp + 6 <= 4 ns + 6 unit offsets for them; each of
+  // n_mono + 3 n_u2 + n_meas + n_rp + n_each + 7 <= 4 ns + 7 unit offsets for them; each of
   // the kMaxChain - 1 later measurement rounds adds at most one item per
   // request and ns + 1 unit offsets.
   s->max_items = (2 + (kMaxChain - 1)) * ns;
@@ -924,7 +924,7 @@ int srv_tick(srv_t* s, uint32_t* running, uint32_t* queued) {
   char* arena = s->h_tick + s->arena_off;
   size_t arena_used = 0;
   std::vector<Request*> mono, u2, meas;
-  std::vector<BItem> mono_items, u2_items, meas_items, u2s_items, rpb_items;
+  std::vector<BItem> mono_items, u2_items, meas_items, u2s_items, rpb_items, each_items;
   std::vector<Request*> done_now;
   // Every request's next segment; the fused runs that take the bit-sliced
   // form are grouped on the host thread pool, one request per task (runs of
@@ -1151,7 +1151,7 @@ int srv_tick(srv_t* s, uint32_t* running, uint32_t* queued) {
           it.n_dops = (uint32_t)len;
         }
         arena_used += al(bytes);
-        mono_items.push_back(it);
+        (bsl ? mono_items : each_items).push_back(it);
       }
       if (!pair_gate(r, base)) mono.push_back(r);
     } else {
@@ -1168,6 +1168,7 @@ int srv_tick(srv_t* s, uint32_t* running, uint32_t* queued) {
   const uint32_t nm = (uint32_t)mono_items.size(), nu = (uint32_t)u2_items.size(), nq = (uint32_t)meas_items.size();
   const uint32_t ns = (uint32_t)u2s_items.size();
   const uint32_t nrp = (uint32_t)rp_items.size(), nrb = (uint32_t)rpb_items.size();
+  const uint32_t ne = (uint32_t)each_items.size();
   // Later measurement rounds: round j holds step j of every chain longer
   // than j (the count before the chain bounds its units).
   uint32_t rounds = 1;
@@ -1180,9 +1181,9 @@ int srv_tick(srv_t* s, uint32_t* running, uint32_t* queued) {
     n_later += v.size();
     later_units += v.size() + 1;
   }
-  if (nm + nu + nq + ns + nrp + nrb) {
-    const size_t n_units = (size_t)nm + 3 * (size_t)nu + nq + nrb + 6;
-    if ((size_t)nm + nu + nq + ns + nrb + n_later > s->max_items || n_units + later_units > s->max_units)
+  if (nm + nu + nq + ns + nrp + nrb + ne) {
+    const size_t n_units = (size_t)nm + 3 * (size_t)nu + nq + nrb + ne + 7;
+    if ((size_t)nm + nu + nq + ns + nrb + ne + n_later > s->max_items || n_units + later_units > s->max_units)
       return sfail(SIM_E_NOMEM, "tick work list exceeds its area");
     std::memset(hdr, 0, sizeof(BTick));
     hdr->n_mono = nm;
@@ -1190,6 +1191,7 @@ int srv_tick(srv_t* s, uint32_t* running, uint32_t* queued) {
     hdr->n_meas = nq;
     hdr->n_u2s = ns;
     hdr->n_rp = nrb;
+    hdr->n_each = ne;
     uint32_t w = 0;
     auto prefix = [&](uint32_t* at, const std::vector<BItem>& v, auto units_of) {
       uint32_t acc = 0;
@@ -1218,8 +1220,11 @@ int srv_tick(srv_t* s, uint32_t* running, uint32_t* queued) {
     hdr->rp_u0 = w;
     prefix(units + w, rpb_items, chunks);
     w += nrb + 1;
+    hdr->each_u0 = w;
+    prefix(units + w, each_items, chunks);
+    w += ne + 1;
     size_t ni = 0;
-    for (const auto& v : {&mono_items, &u2_items, &meas_items, &u2s_items, &rpb_items})
+    for (const auto& v : {&mono_items, &u2_items, &meas_items, &u2s_items, &rpb_items, &each_items})
       for (const BItem& it : *v) items[ni++] = it;
     // Each later round: its header (only measurement items), first-unit
     // array and items after everything before it.
@@ -1260,6 +1265,7 @@ int srv_tick(srv_t* s, uint32_t* running, uint32_t* queued) {
     const auto* d_items = reinterpret_cast<const BItem*>(s->d_tick + s->items_off);
     const auto* d_units = reinterpret_cast<const uint32_t*>(s->d_tick + s->units_off);
     if (nm) launch_batch_tick(s->stream, d_hdr, d_items, d_units, s->grid, kFamMono);
+    if (ne) launch_batch_tick(s->stream, d_hdr, d_items, d_units, s->grid, kFamEach);
     if (nrb) {
       launch_batch_mono_rp(s->stream, d_hdr, d_items, d_units, units[hdr->rp_u0 + nrb]);
       SRV_HIP(hipGetLastError());
@@ -1300,7 +1306,7 @@ int srv_tick(srv_t* s, uint32_t* running, uint32_t* queued) {
       s->stats.wait_ms += ms_since(t_w);
     }
     s->stats.ticks++;
-    s->stats.items += nm + nu + nq + ns + nrp + nrb + n_later;
+    s->stats.items += nm + nu + nq + ns + nrp + nrb + ne + n_later;
     // Fold the results back.
     std::vector<std::pair<Request*, int>> failed;
     for (Request* r : u2) {
@@ -1339,7 +1345,7 @@ int srv_tick(srv_t* s, uint32_t* running, uint32_t* queued) {
   }
   rc = fold_copies(s);
   if (rc) return rc;
-  if (nm + nu + nq + ns + nrp + nrb == 0 && (waiting || !s->copying.empty())) {
+  if (nm + nu + nq + ns + nrp + nrb + ne == 0 && (waiting || !s->copying.empty())) {
     // Nothing launched: wait (briefly) for the background work instead of spinning.
     const auto t_w = std::chrono::steady_clock::now();
     bg_wait_any(s, 200);

@@ -363,11 +363,14 @@ struct BTick {
   uint32_t mono_u0, fill_u0, build_u0, chunk_u0, meas_u0;
   uint32_t item0;              // first of this header's items
   uint32_t n_rp, rp_u0;        // fused runs on register planes, after the LDS-index items
+  uint32_t n_each, each_u0;    // fused runs per entry, after those
+  uint32_t pad2[2];
 };
 
-// Kernel families of a tick: fused runs; branching gates on the global index;
+// Kernel families of a tick: fused runs on LDS planes, and per entry (kFamEach);
+// branching gates on the global index;
 // branching gates of small states (LDS index); measurements.
-constexpr uint32_t kFamMono = 1, kFamU2 = 2, kFamU2s = 4, kFamMeas = 8;
+constexpr uint32_t kFamMono = 1, kFamU2 = 2, kFamU2s = 4, kFamMeas = 8, kFamEach = 16;
 // The kernels of the families in `families`, in tick order.
 void launch_batch_tick(hipStream_t st, const BTick* hdr, const BItem* items, const uint32_t* units, int grid,
                        uint32_t families);
