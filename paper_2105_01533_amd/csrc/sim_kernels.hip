@@ -778,13 +778,19 @@ struct U2Smem {
   RunLds run;
 };
 
-template <bool WIDE, int ITEMS, bool NEXT>
+// T: threads that take part (the others have left), ITEMS entries each.
+template <bool WIDE, int T, int ITEMS, bool NEXT>
 __device__ __forceinline__ void u2_tiles(const Buf& in, const Buf& out, uint64_t n, const uint32_t* __restrict__ partner,
                                          const U2Desc& d, Ctl* ctl, const TabCtl* tc, uint64_t* status, uint32_t par,
                                          uint32_t epoch, uint64_t* nnz_out, uint64_t cap, uint32_t seq,
                                          const NextGate& nx, U2Smem& sm) {
   constexpr int kItems = ITEMS;
-  constexpr uint32_t kTile = kU2Threads * ITEMS;
+  constexpr uint32_t kTile = T * ITEMS;
+  constexpr int kW = T / 64;
+  // Small tiles are numbered by block: there are no more of them than blocks,
+  // and 256 numbers from one counter would take 3 us.  (Blocks start in order, and a
+  // tile waits for those before it only.)
+  constexpr bool kTicket = T == kU2Threads;
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   const uint32_t tiles = (uint32_t)((n + kTile - 1) / kTile);
   const Geom ng = NEXT ? index_geom(nx.tab, 2 * n <= cap ? 2 * n : cap) : Geom{0, 0};
@@ -798,7 +804,7 @@ __device__ __forceinline__ void u2_tiles(const Buf& in, const Buf& out, uint64_t
     return;
   }
   if (tc && tc->nopair) partner = nullptr;
-  if (threadIdx.x == 0) sm.tile = atomicAdd(&ctl->ticket[par], 1u);
+  if (kTicket && threadIdx.x == 0) sm.tile = atomicAdd(&ctl->ticket[par], 1u);
   if (NEXT) sm.run.load(nx.run.g, nx.run.ng);
   else __syncthreads();
   if (NEXT) {
@@ -810,7 +816,7 @@ __device__ __forceinline__ void u2_tiles(const Buf& in, const Buf& out, uint64_t
   }
   const bool apart = NEXT && sm.apart;
   const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-  for (uint32_t tile = sm.tile; tile < tiles;) {
+  for (uint32_t tile = kTicket ? sm.tile : blockIdx.x; tile < tiles;) {
     // (before the tile's count is published: no later tile can have marked Ctl::over)
     if (tile == 0 && wid == 2) commit_staged(ctl, par ^ 1u);
     const uint64_t begin = (uint64_t)tile * kTile;
@@ -821,7 +827,7 @@ __device__ __forceinline__ void u2_tiles(const Buf& in, const Buf& out, uint64_t
     bool k0[kItems], k1[kItems];
 #pragma unroll
     for (int k = 0; k < kItems; ++k) {
-      const uint64_t i = begin + (uint64_t)k * kU2Threads + threadIdx.x;
+      const uint64_t i = begin + (uint64_t)k * T + threadIdx.x;
       lo[k] = hi[k] = 0;
       a[k] = make_double2(0.0, 0.0);
       j[k] = kNoPartner;
@@ -843,7 +849,7 @@ __device__ __forceinline__ void u2_tiles(const Buf& in, const Buf& out, uint64_t
     double mass = 0.0;
 #pragma unroll
     for (int k = 0; k < kItems; ++k) {
-      const uint64_t i = begin + (uint64_t)k * kU2Threads + threadIdx.x;
+      const uint64_t i = begin + (uint64_t)k * T + threadIdx.x;
       r[k] = ent::u2_eval(d, WIDE, lo[k], hi[k], a[k], j[k] != kNoPartner, aj[k]);
       if (i >= n) r[k].mode = 2;
       k0[k] = k1[k] = false;
@@ -860,7 +866,7 @@ __device__ __forceinline__ void u2_tiles(const Buf& in, const Buf& out, uint64_t
       // A thread emits k0 + k1 entries.
       const uint64_t b0 = __ballot(k0[k]), b1 = __ballot(k1[k]);
       pre[k] = __popcll(b0 & lt) + __popcll(b1 & lt);
-      if (lane == 0) sm.cnt[k * kU2Waves + wid] = __popcll(b0) + __popcll(b1);
+      if (lane == 0) sm.cnt[k * kW + wid] = __popcll(b0) + __popcll(b1);
     }
     const bool drops = __ballot(dropped != 0) != 0;   // uniform in the wave
     uint32_t wd = 0;
@@ -877,16 +883,16 @@ __device__ __forceinline__ void u2_tiles(const Buf& in, const Buf& out, uint64_t
     if (wid == 0) {
       // Offsets within the tile (items in order, waves in order within an item),
       // then the tiles before it.
-      static_assert(kItems * kU2Waves <= 64, "one lane per item and wave");
-      const uint32_t x = lane < kItems * kU2Waves ? sm.cnt[lane] : 0u;
+      static_assert(kItems * kW <= 64, "one lane per item and wave");
+      const uint32_t x = lane < kItems * kW ? sm.cnt[lane] : 0u;
       uint32_t incl = x;
 #pragma unroll
-      for (int o = 1; o < kItems * kU2Waves; o <<= 1) {
+      for (int o = 1; o < kItems * kW; o <<= 1) {
         const uint32_t y = __shfl_up(incl, o);
         if (lane >= o) incl += y;
       }
-      const uint32_t run = __shfl(incl, kItems * kU2Waves - 1);
-      if (lane < kItems * kU2Waves) sm.cnt[lane] = incl - x;
+      const uint32_t run = __shfl(incl, kItems * kW - 1);
+      if (lane < kItems * kW) sm.cnt[lane] = incl - x;
       if (lane == 0) {
         __hip_atomic_store(&status[tile], st_word(epoch, tile == 0 ? kStPrefix : kStAgg, run), __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_AGENT);
@@ -926,8 +932,8 @@ __device__ __forceinline__ void u2_tiles(const Buf& in, const Buf& out, uint64_t
         }
       }
     } else if (wid == 1) {
-      const uint32_t td = wave_sum(lane < kU2Waves ? sm.drop[lane] : 0u);
-      const double tm = wave_sum(make_double2(lane < kU2Waves ? sm.mass[lane] : 0.0, 0.0)).x;
+      const uint32_t td = wave_sum(lane < kW ? sm.drop[lane] : 0u);
+      const double tm = wave_sum(make_double2(lane < kW ? sm.mass[lane] : 0.0, 0.0)).x;
       if (lane == 0 && td) {
         StageCell& c = ctl->fst[par][tile % kStageCells];
         atomicAdd((unsigned long long*)&c.pruned, (unsigned long long)td);
@@ -939,7 +945,7 @@ __device__ __forceinline__ void u2_tiles(const Buf& in, const Buf& out, uint64_t
     Claim claim[NEXT ? 2 * kItems : 1];
 #pragma unroll
     for (int k = 0; k < kItems; ++k) {
-      const uint64_t p = base + sm.cnt[k * kU2Waves + wid] + pre[k];
+      const uint64_t p = base + sm.cnt[k * kW + wid] + pre[k];
       const bool flipped = r[k].mode == 1 && pivot_set<WIDE>(d, lo[k], hi[k]);
       uint64_t l0 = flipped ? lo[k] ^ d.x_lo : lo[k], h0 = flipped ? hi[k] ^ d.x_hi : hi[k];
       uint64_t l1 = l0 ^ d.x_lo, h1 = h0 ^ d.x_hi;
@@ -983,7 +989,7 @@ __device__ __forceinline__ void u2_tiles(const Buf& in, const Buf& out, uint64_t
 #pragma unroll
       for (int k = 0; k < 2 * kItems; ++k) index_settle(nx.tab.slots, ng, claim[k], old[k]);
     }
-    if (tiles <= gridDim.x) break;   // a tile for each block: no more to take
+    if (!kTicket || tiles <= gridDim.x) break;   // a tile for each block: no more to take
     if (threadIdx.x == 0) sm.tile = atomicAdd(&ctl->ticket[par], 1u);
     __syncthreads();
     tile = sm.tile;
@@ -1003,11 +1009,21 @@ __global__ __launch_bounds__(kU2Threads) void k_u2_fused(Buf in, Buf out, const 
                                                          uint32_t seq, NextGate nx) {
   __shared__ U2Smem sm;
   const uint64_t n = *nnz_p;
-#define SPARSESIM_U2_TILES(I) \
-  u2_tiles<WIDE, I, NEXT>(in, out, n, partner, d, ctl, tc, status, par, epoch, nnz_out, cap, seq, nx, sm)
-  if (n <= 256u * kU2Threads) SPARSESIM_U2_TILES(1);
-  else if (n <= 512u * kU2Threads) SPARSESIM_U2_TILES(2);
-  else SPARSESIM_U2_TILES(4);
+#define SPARSESIM_U2_TILES(T, I) \
+  u2_tiles<WIDE, T, I, NEXT>(in, out, n, partner, d, ctl, tc, status, par, epoch, nnz_out, cap, seq, nx, sm)
+  if (n <= 256u * 256) {
+    if (threadIdx.x >= 256) return;
+    SPARSESIM_U2_TILES(256, 1);
+  } else if (n <= 256u * 512) {
+    if (threadIdx.x >= 512) return;
+    SPARSESIM_U2_TILES(512, 1);
+  } else if (n <= 256u * kU2Threads) {
+    SPARSESIM_U2_TILES(kU2Threads, 1);
+  } else if (n <= 512u * kU2Threads) {
+    SPARSESIM_U2_TILES(kU2Threads, 2);
+  } else {
+    SPARSESIM_U2_TILES(kU2Threads, 4);
+  }
 #undef SPARSESIM_U2_TILES
 }
 
@@ -1773,7 +1789,7 @@ void launch_u2_fused(hipStream_t st, bool wide, Buf in, Buf out, const uint64_t*
                      const U2Desc& d, Ctl* ctl, const TabCtl* tc, uint64_t* status, uint32_t par, uint32_t epoch,
                      uint64_t* nnz_out, uint64_t cap, uint32_t seq, const NextGate& next, uint64_t ub) {
   // A block fills a CU (16 waves of up to 128 registers): more would only wait for a place.
-  const int grid = (int)std::max<uint64_t>(1, std::min<uint64_t>((ub + kU2Threads - 1) / kU2Threads, 256));
+  const int grid = (int)std::max<uint64_t>(1, std::min<uint64_t>((ub + 255) / 256, 256));
 #define SPARSESIM_U2F(W, N)                                                                                       \
   hipLaunchKernelGGL((k_u2_fused<W, N>), dim3(grid), dim3(kU2Threads), 0, st, in, out, nnz, partner, d, ctl, tc, \
                      status, par, epoch, nnz_out, cap, seq, next)
