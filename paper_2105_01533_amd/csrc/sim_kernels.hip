@@ -1497,7 +1497,7 @@ __global__ __launch_bounds__(256) void k_measure_reduce(Buf b, const uint64_t* _
   __shared__ uint32_t shu[256];
   const uint64_t n = *nnz_p;
   uint64_t begin, end;
-  chunk_range(n, kMeasChunk, begin, end);
+  chunk_range(n, meas_chunk(n), begin, end);
   double p0 = 0.0, p1 = 0.0;
   uint32_t c1 = 0;
   const bool qhi = WIDE && q >= 64;
@@ -1544,7 +1544,7 @@ __global__ __launch_bounds__(1024) void k_measure_decide(const double2* __restri
   // Per-block kept counts need each block's input length: its uniform chunk,
   // or (in_off given) the range the previous measurement's write block
   // produced.  Thread t owns blocks [t per, (t + 1) per).
-  const uint64_t chunk = chunk_len(n, nb, kMeasChunk);
+  const uint64_t chunk = chunk_len(n, nb, meas_chunk(n));
   const int per = (nb + 1023) / 1024;
   const int first = threadIdx.x * per;
   uint32_t c1[kPer], len[kPer];
@@ -1652,7 +1652,7 @@ __global__ __launch_bounds__(256) void k_measure_write(Buf in, Buf out, const ui
     begin = in_off[blockIdx.x];
     end = blockIdx.x + 1 < gridDim.x ? in_off[blockIdx.x + 1] : n;
   } else {
-    chunk_range(n, kMeasChunk, begin, end);
+    chunk_range(n, meas_chunk(n), begin, end);
   }
   const int o = rec->outcome;
   const double scale = rec->scale;
