@@ -1266,8 +1266,9 @@ int srv_tick(srv_t* s, uint32_t* running, uint32_t* queued) {
     const auto* d_units = reinterpret_cast<const uint32_t*>(s->d_tick + s->units_off);
     if (nm) launch_batch_tick(s->stream, d_hdr, d_items, d_units, s->grid, kFamMono);
     if (ne) launch_batch_tick(s->stream, d_hdr, d_items, d_units, s->grid, kFamEach);
-    if (nrb) {
-      launch_batch_mono_rp(s->stream, d_hdr, d_items, d_units, units[hdr->rp_u0 + nrb]);
+    // (No tiles: the runs are all of states that were pruned to nothing.)
+    if (const uint32_t tiles = units[hdr->rp_u0 + nrb]) {
+      launch_batch_mono_rp(s->stream, d_hdr, d_items, d_units, tiles);
       SRV_HIP(hipGetLastError());
     }
     const bool beside[2] = {nu && (nq || ns), ns && nq};   // the global index; the LDS index

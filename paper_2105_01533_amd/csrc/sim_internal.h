@@ -390,7 +390,7 @@ constexpr uint32_t kFamMono = 1, kFamU2 = 2, kFamU2s = 4, kFamMeas = 8, kFamEach
 // The kernels of the families in `families`, in tick order.
 void launch_batch_tick(hipStream_t st, const BTick* hdr, const BItem* items, const uint32_t* units, int grid,
                        uint32_t families);
-// (tiles: all items')
+// (tiles: all items', at least one)
 void launch_batch_mono_rp(hipStream_t st, const BTick* hdr, const BItem* items, const uint32_t* units, uint32_t tiles);
 // Up to four ranges of the tick buffer, from pinned host memory: 16-byte words
 // (byte offsets and lengths are rounded up to them).
