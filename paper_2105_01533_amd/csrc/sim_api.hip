@@ -251,6 +251,7 @@ struct sim_t {
   uint64_t* status = nullptr;
   uint32_t u2_epoch = 0;
   uint32_t u2_par = 0;
+  uint32_t lds_par = 0;           // the same of the LDS-index kernel over several blocks
   // The index table the next gate uses (0 or 1); the other one is emptied by
   // that gate (both are emptied at creation).  built: the gate before has
   // indexed its outputs into it.
@@ -478,9 +479,10 @@ int run_u2_lds(sim_t* s, const sim_gate& g, HeldRun* before) {
   {
     KTimer t_(s, KC_U2_LDS);
     launch_u2_lds_tiles(s->stream, s->wide, s->buf[s->cur], s->buf[s->cur ^ 1], d_nnz(s, s->cur), d_nnz(s, s->cur ^ 1),
-                        u2_desc(g, s->cfg.eps), before->take(), s->status, s->u2_epoch, s->ctl, ub);
+                        u2_desc(g, s->cfg.eps), before->take(), s->status, s->lds_par, s->u2_epoch, s->ctl, ub);
   }
   HIP_TRY(hipGetLastError());
+  s->lds_par ^= 1u;
   s->cur ^= 1;
   s->nnz_known = false;
   s->nnz_ub = 2 * ub;

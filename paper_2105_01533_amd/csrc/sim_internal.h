@@ -256,6 +256,7 @@ struct Ctl {
   uint32_t error;              // bit 0: a measurement had no valid outcome; bit 1: a chained scan gave up
                                // waiting; bit 2: the one-block branching kernel met a state too large for it
   uint32_t ticket[2];          // tile counters of the single-pass branching kernel (launches alternate)
+  uint32_t lds_ticket[2];      // those of the LDS-index kernel over several blocks
   TabCtl tab[2];               // the two index tables
   double pruned_mass;          // sum of |a|^2 of the entries T_eps dropped
   // Counters of a two-pass branching gate, staged by its count pass and
@@ -519,7 +520,8 @@ static_assert(sizeof(Chain) <= 3584, "passed as a kernel argument");
 void launch_u2_chain(hipStream_t st, bool wide, Buf in, Buf out, uint64_t* nnz, int cur, const Chain& chain, Ctl* ctl);
 // One branching gate on a state of at most kLdsU2Max entries (ub bounds it).
 void launch_u2_lds_tiles(hipStream_t st, bool wide, Buf in, Buf out, const uint64_t* nnz_in, uint64_t* nnz_out,
-                         const U2Desc& d, const MonoRun& m, uint64_t* status, uint32_t epoch, Ctl* ctl, uint64_t ub);
+                         const U2Desc& d, const MonoRun& m, uint64_t* status, uint32_t par, uint32_t epoch, Ctl* ctl,
+                         uint64_t ub);
 void launch_measure_reduce(hipStream_t st, bool wide, Buf b, const uint64_t* nnz, uint32_t q, BlockScratch s,
                            int grid, int block);
 void launch_measure_decide(hipStream_t st, const double2* part, const uint32_t* cnt1, uint32_t* off, int nblocks,

@@ -629,14 +629,17 @@ __global__ __launch_bounds__(256) void k_u2_write(Buf in, Buf out, const uint64_
   }
 }
 
-// Single-pass branching gate: a block evaluates one tile of 1024 ITEMS entries
+// Single-pass branching gate: a block evaluates one tile of T ITEMS entries
 // (Eq. 2 with T_eps, the results held in registers) and finds where its
 // outputs go by a chained scan over the tiles: it publishes its tile's output
 // count, adds its predecessors' counts back to the first published inclusive
 // prefix, publishes its own inclusive prefix, writes, and takes the next tile.
 // Tile numbers come from a counter in the order blocks ask for them, so a tile
-// waited on always belongs to a block already running; the wait is bounded even so (a block that gives
-// up sets error bit 2 and its outputs are wrong, but the kernel ends).  A
+// waited on always belongs to a block already running, whatever else runs on
+// the device: each die starts its share of a grid by itself, and one filled with
+// another handle's waiting blocks could keep a tile numbered by its block from
+// ever starting.  The wait is bounded even so (a block that gives up sets error
+// bit 2 and its outputs are wrong, but the kernel ends).  A
 // status word packs (epoch, flag, count) and is read and written atomically at
 // device scope, so no fence is needed; the epoch tells this launch's words from
 // those of earlier launches.  Output order is input order, as in the two-pass
@@ -651,9 +654,11 @@ __global__ __launch_bounds__(256) void k_u2_write(Buf in, Buf out, const uint64_
 // (1 us per 40 tiles), now 22 us.  Two counters alternate between launches,
 // each reset by the launch that uses the other.
 //
-// The tile is 1024 entries up to 2^18 entries (256 tiles: one a CU), 2048 up to
-// 2^19, 4096 beyond (fewer numbers; 2^20 entries of 24 bytes: 22 us against 31
-// with 1024).
+// The tile is 256 entries up to 2^16 entries, 512 up to 2^17, 1024 up to 2^18
+// (up to 256 tiles: one a CU), 2048 up to 2^19, 4096 beyond (fewer numbers; 2^20
+// entries of 24 bytes: 22 us against 31 with 1024).  The two small tiles take 5 %
+// off a 40-qubit Trotter step (55.0 -> 52.5 ms) though each of up to 256 tiles
+// waits for its number; numbered by block they would take 1 to 3 % more off.
 //
 // A gate whose outputs may not fit (seq != 0) writes nothing at or past cap,
 // and if they did not fit reports an empty output and marks Ctl::over; `in`
@@ -787,10 +792,6 @@ __device__ __forceinline__ void u2_tiles(const Buf& in, const Buf& out, uint64_t
   constexpr int kItems = ITEMS;
   constexpr uint32_t kTile = T * ITEMS;
   constexpr int kW = T / 64;
-  // Small tiles are numbered by block: there are no more of them than blocks,
-  // and 256 numbers from one counter would take 3 us.  (Blocks start in order, and a
-  // tile waits for those before it only.)
-  constexpr bool kTicket = T == kU2Threads;
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   const uint32_t tiles = (uint32_t)((n + kTile - 1) / kTile);
   const Geom ng = NEXT ? index_geom(nx.tab, 2 * n <= cap ? 2 * n : cap) : Geom{0, 0};
@@ -804,7 +805,7 @@ __device__ __forceinline__ void u2_tiles(const Buf& in, const Buf& out, uint64_t
     return;
   }
   if (tc && tc->nopair) partner = nullptr;
-  if (kTicket && threadIdx.x == 0) sm.tile = atomicAdd(&ctl->ticket[par], 1u);
+  if (threadIdx.x == 0) sm.tile = atomicAdd(&ctl->ticket[par], 1u);
   if (NEXT) sm.run.load(nx.run.g, nx.run.ng);
   else __syncthreads();
   if (NEXT) {
@@ -816,7 +817,7 @@ __device__ __forceinline__ void u2_tiles(const Buf& in, const Buf& out, uint64_t
   }
   const bool apart = NEXT && sm.apart;
   const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-  for (uint32_t tile = kTicket ? sm.tile : blockIdx.x; tile < tiles;) {
+  for (uint32_t tile = sm.tile; tile < tiles;) {
     // (before the tile's count is published: no later tile can have marked Ctl::over)
     if (tile == 0 && wid == 2) commit_staged(ctl, par ^ 1u);
     const uint64_t begin = (uint64_t)tile * kTile;
@@ -989,7 +990,7 @@ __device__ __forceinline__ void u2_tiles(const Buf& in, const Buf& out, uint64_t
 #pragma unroll
       for (int k = 0; k < 2 * kItems; ++k) index_settle(nx.tab.slots, ng, claim[k], old[k]);
     }
-    if (!kTicket || tiles <= gridDim.x) break;   // a tile for each block: no more to take
+    if (tiles <= gridDim.x) break;   // a tile for each block: no more to take
     if (threadIdx.x == 0) sm.tile = atomicAdd(&ctl->ticket[par], 1u);
     __syncthreads();
     tile = sm.tile;
@@ -1305,7 +1306,8 @@ __global__ __launch_bounds__(1024) void k_u2_chain(Buf in, Buf out, uint64_t* nn
 // its own LDS and looks the others' partners up there, so that it knows the
 // partners of its own 1024 entries without waiting for the other blocks; it
 // evaluates these and writes their outputs after those of the blocks before it
-// (look_back).  m: a run of at most kLdsRun gates before the gate, applied to
+// (look_back; blocks are numbered from a counter as in the single pass, while
+// their label loads are on the way).  m: a run of at most kLdsRun gates before the gate, applied to
 // whatever is read (the state's buffer keeps the entries before the run).
 // Outputs, order and counters (an entry's insert or look-up counts in its own
 // block) as the three kernels' of the global index, which at these sizes are
@@ -1317,12 +1319,12 @@ struct LdsTileSmem {
   uint64_t lo[1024], hi[1024];   // the block's own labels
   uint32_t has[1024];            // whether an own entry with the pivot bit clear has a partner
   MonoDesc run[kLdsRun];
-  uint32_t wave[16], before;
+  uint32_t wave[16], before, tile;
 };
 template <bool WIDE>
 __global__ __launch_bounds__(1024) void k_u2_lds_tiles(Buf in, Buf out, const uint64_t* __restrict__ nnz_in,
                                                        uint64_t* nnz_out, U2Desc d, MonoRun m, uint64_t* status,
-                                                       uint32_t epoch, Ctl* ctl) {
+                                                       uint32_t par, uint32_t epoch, Ctl* ctl) {
   __shared__ LdsTileSmem sm;
   auto count = [](uint64_t* p, uint64_t v) {
     if (v) atomicAdd((unsigned long long*)p, (unsigned long long)v);
@@ -1330,20 +1332,21 @@ __global__ __launch_bounds__(1024) void k_u2_lds_tiles(Buf in, Buf out, const ui
   constexpr uint32_t kEntry = WIDE ? 32u : 24u;
   const uint64_t n0 = *nnz_in;
   if (n0 > kLdsU2Max) {   // the host launches this kernel only below the bound
-    if (threadIdx.x == 0) atomicOr(&ctl->error, 4u);
+    if (threadIdx.x == 0) {
+      atomicOr(&ctl->error, 4u);
+      ctl->lds_ticket[par ^ 1u] = 0;
+    }
     return;
   }
-  const uint32_t n = (uint32_t)n0, blocks = n ? (n + 1023) / 1024 : 1u, b = blockIdx.x;
-  if (b >= blocks) return;
+  const uint32_t n = (uint32_t)n0, blocks = n ? (n + 1023) / 1024 : 1u;
+  if (blockIdx.x >= blocks) return;
+  uint32_t ticket = 0;
+  if (threadIdx.x == 0) ticket = atomicAdd(&ctl->lds_ticket[par], 1u);
   const uint32_t lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t kMask = (n <= 32 ? 64u : 2u << (32 - __clz(n - 1))) - 1u;   // at least two slots an entry
   for (uint32_t k = threadIdx.x; k < m.ng * (uint32_t)(sizeof(MonoDesc) / 16); k += 1024)
     reinterpret_cast<uint4*>(sm.run)[k] = reinterpret_cast<const uint4*>(m.g)[k];
   for (uint32_t k = threadIdx.x; k <= kMask; k += 1024) sm.tab[k] = 0u;
-  const uint32_t own = b * 1024 + threadIdx.x;
-  double2 a = make_double2(0.0, 0.0);
-  if (own < n) a = in.amp[own];
-  __syncthreads();
   const bool flips = m.run_flags & kRunFlip;
   constexpr uint32_t kRounds = kLdsU2Max / 1024;
   uint64_t l[kRounds], h2[kRounds];   // the thread's label of each 1024
@@ -1353,8 +1356,14 @@ __global__ __launch_bounds__(1024) void k_u2_lds_tiles(Buf in, Buf out, const ui
     l[k] = i < n ? in.key_lo[i] : 0ull;
     h2[k] = WIDE && i < n ? in.key_hi[i] : 0ull;
   }
+  if (threadIdx.x == 0) sm.tile = ticket;
+  __syncthreads();
+  const uint32_t b = __builtin_amdgcn_readfirstlane(sm.tile), own = b * 1024 + threadIdx.x;
+  if (b == 0 && threadIdx.x == 0) ctl->lds_ticket[par ^ 1u] = 0;   // for the next launch
+  double2 a = make_double2(0.0, 0.0);
   uint64_t lo = 0, hi = 0;            // of its own entry
   if (own < n) {
+    a = in.amp[own];
     lo = in.key_lo[own];
     hi = WIDE ? in.key_hi[own] : 0ull;
     for (uint32_t q = 0; q < m.ng; ++q) ent::mono_step(sm.run[q], WIDE, lo, hi, a);
@@ -1816,14 +1825,15 @@ void launch_u2_chain(hipStream_t st, bool wide, Buf in, Buf out, uint64_t* nnz, 
 }
 
 void launch_u2_lds_tiles(hipStream_t st, bool wide, Buf in, Buf out, const uint64_t* nnz_in, uint64_t* nnz_out,
-                         const U2Desc& d, const MonoRun& m, uint64_t* status, uint32_t epoch, Ctl* ctl, uint64_t ub) {
+                         const U2Desc& d, const MonoRun& m, uint64_t* status, uint32_t par, uint32_t epoch, Ctl* ctl,
+                         uint64_t ub) {
   const int grid = (int)std::max<uint64_t>(1, (ub + 1023) / 1024);
   if (wide)
     hipLaunchKernelGGL(k_u2_lds_tiles<true>, dim3(grid), dim3(1024), 0, st, in, out, nnz_in, nnz_out, d, m, status,
-                       epoch, ctl);
+                       par, epoch, ctl);
   else
     hipLaunchKernelGGL(k_u2_lds_tiles<false>, dim3(grid), dim3(1024), 0, st, in, out, nnz_in, nnz_out, d, m, status,
-                       epoch, ctl);
+                       par, epoch, ctl);
 }
 
 void launch_measure_reduce(hipStream_t st, bool wide, Buf b, const uint64_t* nnz, uint32_t q, BlockScratch s,
