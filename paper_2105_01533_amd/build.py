@@ -73,6 +73,37 @@ def check_regplane_asm(text: str, regplane_only: str | None = None) -> list[str]
     return bad
 
 
+# What the register-plane kernels must be given: the architectural VGPRs up to
+# the highest plane register, and, for the kernel whose waves run different
+# programs side by side, more registers than half of a SIMD's 512, so that no two
+# of its waves share one (waves of different programs on a SIMD have given results
+# that depended on the pairing).  Both rest on registers the source names as
+# clobbered; a compiler that drops them would give wrong results with no error.
+PLANE_VGPRS = 231
+ALONE_KERNELS = ("kb_mono_rp",)
+SIMD_VGPRS = 512
+
+
+def check_regplane_alloc(text: str) -> list[str]:
+    """Kernels of the assembly whose register allocation is too small, and
+    ALONE_KERNELS that it does not hold."""
+    import re
+
+    bad, seen = [], set()
+    for m in re.finditer(r"^\s*\.amdhsa_kernel (\S+)$(.*?)^\s*\.end_amdhsa_kernel", text, re.M | re.S):
+        name, body = m.group(1), m.group(2)
+        total, arch = (int(x.group(1)) if (x := re.search(rf"\.amdhsa_{f}\s+(\d+)", body)) else 0
+                       for f in ("next_free_vgpr", "accum_offset"))
+        if min(total, arch) < PLANE_VGPRS:
+            bad.append(f"{name}: {min(total, arch)} VGPRs, the planes need {PLANE_VGPRS}")
+        for k in ALONE_KERNELS:
+            if k in name:
+                seen.add(k)
+                if 2 * total <= SIMD_VGPRS:
+                    bad.append(f"{name}: {total} registers, two waves fit a SIMD")
+    return bad + [f"{k}: not found" for k in ALONE_KERNELS if k not in seen]
+
+
 def _compile_cmd(src: str, out: str, *extra: str) -> list[str]:
     return [HIPCC, *FLAGS, *EXTRA_FLAGS.get(src, []), *extra, "-o", out, os.path.join(CSRC, src)]
 
@@ -105,11 +136,12 @@ def build(verbose: bool = False) -> str:
         subprocess.check_call([*(c for c in _compile_cmd(src, asm) if c != "-fPIC"), "--offload-device-only", "-S"],
                               stderr=subprocess.DEVNULL)
         with open(asm) as f:
-            bad += [f"{src}: {b}" for b in check_regplane_asm(f.read())]
+            text = f.read()
+        bad += [f"{src}: {b}" for b in check_regplane_asm(text) + check_regplane_alloc(text)]
         os.remove(asm)
     if bad:
         os.remove(tmp)
-        raise RuntimeError("register-plane pass: compiler code touches its reserved registers:\n" + "\n".join(bad[:20]))
+        raise RuntimeError("register-plane pass: its registers are not its own:\n" + "\n".join(bad[:20]))
     os.replace(tmp, LIB)
     return LIB
 

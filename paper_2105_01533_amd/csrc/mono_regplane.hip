@@ -44,7 +44,8 @@ __global__ __launch_bounds__(64, 2) __attribute__((amdgpu_num_vgpr(40))) void k_
 // The fused runs of a batched tick: unit u is a tile of the state of item
 // find_item(u), with that item's program.  Waves of different programs must
 // not share a SIMD (see launch_mono_rp): the AGPRs named here make the wave's
-// share of the registers more than half of a SIMD's, so that one fits.  The
+// share of the registers more than half of a SIMD's, so that one fits (the build
+// fails if it is not: check_regplane_alloc).  The
 // tick's fused runs were the latency of the LDS-plane tile, 70 ns a gate; the
 // register planes take 26 (2048 entries, 24 qubits): 45 us a tick of 24 requests
 // instead of 135.
