@@ -1471,6 +1471,14 @@ int apply_impl(sim_t* s, const sim_gate* gates, size_t n, int32_t* outcomes, sim
     int rc = flush();
     if (rc) return rc;
   }
+  if (outcomes && meas_seen && !snaps.empty()) {
+    // A gate that did not fit takes back the measurements after it, whose
+    // outcomes are not the caller's to see.
+    uint64_t nnz;
+    int rc = read_nnz(s, &nnz);
+    if (rc) return rc;
+    if ((rc = settle())) result = rc;
+  }
   if (outcomes && meas_seen)
     HIP_TRY(hipMemcpyAsync(outcomes, cb.outcomes, meas_seen * 4, hipMemcpyDeviceToHost, s->stream));
   int rc = read_ctl(s);
