@@ -282,6 +282,7 @@ struct sim_t {
   BlockScratch bs;
   Ctl* ctl;
   uint64_t* h_pinned;          // [0] nnz readback, [1..] scratch
+  uint32_t* h_over;            // pinned: Ctl::over_seen
   Ctl* h_ctl;                  // pinned mirror of ctl
   DevVec<MonoDesc> descs;
   DevVec<BsGroup> grp_ops;     // grouped bit-sliced ops of the current call (LDS-plane kernel)
@@ -695,11 +696,14 @@ int sim_create(const sim_config* cfg, void* stream, void* workspace, size_t ws_b
   s->bs.part = reinterpret_cast<double2*>(s->ws + s->L.part);
   s->ctl = reinterpret_cast<Ctl*>(s->ws + s->L.ctl);
   s->status = reinterpret_cast<uint64_t*>(s->ws + s->L.status);
-  if (hipHostMalloc(&s->h_pinned, 64) != hipSuccess || hipHostMalloc(&s->h_ctl, sizeof(Ctl)) != hipSuccess) {
+  if (hipHostMalloc(&s->h_pinned, 64 + 64) != hipSuccess || hipHostMalloc(&s->h_ctl, sizeof(Ctl)) != hipSuccess) {
     sim_destroy(s);
     return fail(SIM_E_NOMEM, "pinned host allocation failed");
   }
   std::memset(s->h_ctl, 0, sizeof(Ctl));
+  s->h_over = reinterpret_cast<uint32_t*>(s->h_pinned + 8);
+  *s->h_over = 0;
+  s->h_ctl->over_seen = s->h_over;
   for (auto& t : s->h_ctl->labels)
     for (LabelCell& c : t) c.and_lo = c.and_hi = ~0ull;
   if (hipMemcpyAsync(s->ctl, s->h_ctl, sizeof(Ctl), hipMemcpyHostToDevice, s->stream) != hipSuccess) {
@@ -925,6 +929,7 @@ struct CallBufs {
 
 int apply_impl(sim_t* s, const sim_gate* gates, size_t n, int32_t* outcomes, sim_stats* stats, CallBufs cb) {
   s->mchain.valid = false;
+  *s->h_over = 0;
   if (int rc = drop_built(s)) return rc;   // (left by a call that failed)
   sim_stats st;
   std::memset(&st, 0, sizeof st);
@@ -1315,12 +1320,26 @@ int apply_impl(sim_t* s, const sim_gate* gates, size_t n, int32_t* outcomes, sim
     s->nnz_ub = ub;
     return SIM_OK;
   };
+  // Gates since the last read of the entry count whose outputs may not fit,
+  // and what the call was like before each.  At kSnapMax of them the count is
+  // read (and a gate that did not fit shows itself in h_over before that), so
+  // that a call does not run on for long on the empty state such a gate leaves.
+  struct Snap {
+    uint32_t seq;
+    size_t i, meas_seen;
+    int cur;
+    uint64_t uni_lo, uni_hi;
+    sim_stats st;
+  };
+  constexpr size_t kSnapMax = 256;
+  std::vector<Snap> snaps;
   // What the gate at i can do for the next branching gate while it writes:
   // the run up to it, if it is short and would run per entry, and its index.
   // Only for a gate that is certain to be applied and to use the global index.
   int look_rc = SIM_OK;
   auto prepare_next = [&](uint64_t ub_out, MonoRun* m, U2Desc* d) -> bool {
     if (s->cfg.flags & (SIM_FLAG_U2_TWO_PASS | SIM_FLAG_COUNT_INDEX)) return false;
+    if (snaps.size() + 1 >= kSnapMax) return false;   // (the count may be read between the two)
     if (lds_gate(s, ub_out)) return false;
     const size_t j = run_end(i + 1), len = j - (i + 1);
     if (j == n || len > held_most || gates[j].op != SIM_OP_U2) return false;
@@ -1343,16 +1362,6 @@ int apply_impl(sim_t* s, const sim_gate* gates, size_t n, int32_t* outcomes, sim
     *d = u2_desc(gates[j], s->cfg.eps);
     return true;
   };
-  // Gates since the last read of the entry count whose outputs may not fit,
-  // and what the call was like before each.
-  struct Snap {
-    uint32_t seq;
-    size_t i, meas_seen;
-    int cur;
-    uint64_t uni_lo, uni_hi;
-    sim_stats st;
-  };
-  std::vector<Snap> snaps;
   auto may_exceed = [&]() -> uint32_t {
     if (!++s->over_seq) s->over_seq = 1;
     snaps.push_back(Snap{s->over_seq, i, meas_seen, s->cur, s->uni_lo, s->uni_hi, st});
@@ -1375,6 +1384,7 @@ int apply_impl(sim_t* s, const sim_gate* gates, size_t n, int32_t* outcomes, sim
       }
     snaps.clear();
     s->over = 0;
+    *s->h_over = 0;
     s->built = true;   // whatever the launches since then left in the tables
     int rc = drop_built(s);
     if (rc) return rc;
@@ -1388,6 +1398,13 @@ int apply_impl(sim_t* s, const sim_gate* gates, size_t n, int32_t* outcomes, sim
     return fail(SIM_E_CAPACITY, "branching gate would exceed the state capacity");
   };
   for (; i < n; ++i) {
+    if (!snaps.empty() && (__atomic_load_n(s->h_over, __ATOMIC_RELAXED) || (snaps.size() >= kSnapMax && !s->built))) {
+      uint64_t nnz;
+      int rc = read_nnz(s, &nnz);
+      if (rc) return rc;
+      st.host_syncs++;
+      if ((result = settle())) break;
+    }
     const sim_gate& g = gates[i];
     if (g.op == SIM_OP_MONO) {
       flip_uniform(g, s->uni_lo, s->uni_hi);

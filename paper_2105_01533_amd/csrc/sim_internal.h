@@ -242,6 +242,7 @@ struct Ctl {
   // later launches do nothing until the host, which reads these words with nnz,
   // goes back to the state before it.
   uint64_t over, over_n;
+  uint32_t* over_seen;         // host memory: the number again, for the host to see without a wait
   uint64_t updates;            // sum over applied gates of nnz at input
   uint64_t peak;
   uint64_t pruned;

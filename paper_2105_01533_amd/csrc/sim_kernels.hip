@@ -929,6 +929,7 @@ __device__ __forceinline__ void u2_tiles(const Buf& in, const Buf& out, uint64_t
             *nnz_out = 0;
             ctl->over = seq;
             ctl->over_n = n;
+            __hip_atomic_store(ctl->over_seen, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
           }
         }
       }

@@ -48,3 +48,55 @@ def test_outcomes_end_at_the_gate(sim, n, before, after, static):
         assert len(lo) == ENTRIES
     finally:
         s.close()
+
+
+@pytest.mark.parametrize("n", [30, 90])
+@pytest.mark.parametrize("after", [254, 255, 256, 3000])
+def test_launches_end_soon_after_the_gate(sim, n, after):
+    """At most 256 branching gates are launched whose fit is not known."""
+    c = W.Circuit()
+    c.h(n - 1)                                     # does not fit
+    for k in range(after):
+        c.gate(W.K_RX, k % (n - 2), param=0.3)
+        if k % 50 == 49:
+            c.x(1, (2,))
+    s = sim.Simulator(n, CAP, 0.0, tuned=False)
+    try:
+        s.import_state(*_state(n))
+        rc, _, st = s.apply_ops(c.array(), raise_on_error=False)
+        assert rc == sim.SIM_E_CAPACITY and st["gates_applied"] == 0
+        assert sim.sim_kernel_stats(s.h)["u2_write"]["launches"] <= 256
+        lo, hi, amp = s.export(sort=False)
+        for x, y in zip((lo, hi, amp), _state(n)):
+            assert x.tobytes() == np.ascontiguousarray(y, x.dtype).tobytes()
+    finally:
+        s.close()
+
+
+@pytest.mark.parametrize("n", [40, 90])
+@pytest.mark.parametrize("pairs", [127, 128, 300])
+def test_reads_between_gates_that_fit(sim, n, pairs):
+    """Gates at the capacity that do fit run on over the reads of the count
+    between them, as the two-pass form, which reads it at each."""
+    state = W.random_state(62, ENTRIES, n - 2)
+    c = W.Circuit()
+    for k in range(pairs):
+        c.h(k % 11)
+        if k % 7 == 3:
+            c.x(3, (5,))
+            c.x(3, (5,))
+        c.h(k % 11)
+        if k % 16 == 15:
+            c.measure(n - 1, 0.5)                  # 0 everywhere
+    out = []
+    for f in (0, sim.SIM_FLAG_U2_TWO_PASS):
+        s = sim.Simulator(n, 2 * ENTRIES + 100, 1e-20, flags=f, tuned=False)
+        try:
+            s.import_state(*state)
+            rc, outs, st = s.apply_ops(c.array(), raise_on_error=False)
+            out.append((rc, list(outs), [st[k] for k in ("gates_applied", "updates", "u2_applied", "pruned", "peak_nnz")],
+                        [x.tobytes() for x in s.export(sort=False)]))
+        finally:
+            s.close()
+    assert out[0][0] == 0 and out[0][2][2] == 2 * pairs
+    assert out[0] == out[1]
