@@ -1397,6 +1397,22 @@ int apply_impl(sim_t* s, const sim_gate* gates, size_t n, int32_t* outcomes, sim
     held.m = MonoRun{};
     return fail(SIM_E_CAPACITY, "branching gate would exceed the state capacity");
   };
+  // A call left early (an allocation, launch or copy that failed) goes back to
+  // before a gate that did not fit, and leaves neither an index nor a tile
+  // counter in use by a launch that the handle does not know of.
+  struct Leave {
+    std::function<void()> f;
+    ~Leave() {
+      if (f) f();
+    }
+  } leave{[&] {
+    const std::string why = g_last_error;
+    uint64_t nnz;
+    s->built = true;
+    if (read_nnz(s, &nnz) == SIM_OK && settle() == SIM_OK) (void)drop_built(s);
+    launch_u2_tickets(s->stream, s->ctl);
+    g_last_error = why;
+  }};
   for (; i < n; ++i) {
     if (!snaps.empty() && (__atomic_load_n(s->h_over, __ATOMIC_RELAXED) || (snaps.size() >= kSnapMax && !s->built))) {
       uint64_t nnz;
@@ -1506,6 +1522,7 @@ int apply_impl(sim_t* s, const sim_gate* gates, size_t n, int32_t* outcomes, sim
     rc = read_ctl(s);
     if (rc) return rc;
   }
+  leave.f = nullptr;
   // Counters of the last single-pass gate, still staged.
   for (const auto& p : s->h_ctl->fst)
     for (const StageCell& f : p) {

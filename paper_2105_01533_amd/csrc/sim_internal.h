@@ -496,6 +496,8 @@ void launch_u2_fused(hipStream_t st, bool wide, Buf in, Buf out, const uint64_t*
 // Back to the state before a gate that did not fit: its buffer's entry count,
 // and no staged counters, error or mark left.
 void launch_u2_restore(hipStream_t st, Ctl* ctl, int cur);
+// Tile counters as before the first gate.
+void launch_u2_tickets(hipStream_t st, Ctl* ctl);
 // Largest state whose partner index the branching kernels build in LDS.
 constexpr uint32_t kLdsU2Max = 8192;
 // A chain of branching gates on a state of at most kChainMax entries at each,

@@ -1040,6 +1040,10 @@ __global__ void k_u2_restore(Ctl* ctl, int cur) {
     }
 }
 
+__global__ void k_u2_tickets(Ctl* ctl) {
+  for (int p = 0; p < 2; ++p) ctl->ticket[p] = ctl->lds_ticket[p] = 0;
+}
+
 // ---------------------------------------------------------------------------
 // What a thread counted over the gates of a launch; waves add theirs up by
 // shuffles, then one atomic a counter (block sums through LDS were no faster).
@@ -1360,6 +1364,7 @@ __global__ __launch_bounds__(1024) void k_u2_lds_tiles(Buf in, Buf out, const ui
   if (threadIdx.x == 0) sm.tile = ticket;
   __syncthreads();
   const uint32_t b = __builtin_amdgcn_readfirstlane(sm.tile), own = b * 1024 + threadIdx.x;
+  if (b >= blocks) return;   // (uniform; the counter starts from zero, see launch_u2_tickets)
   if (b == 0 && threadIdx.x == 0) ctl->lds_ticket[par ^ 1u] = 0;   // for the next launch
   double2 a = make_double2(0.0, 0.0);
   uint64_t lo = 0, hi = 0;            // of its own entry
@@ -1816,6 +1821,8 @@ void launch_u2_fused(hipStream_t st, bool wide, Buf in, Buf out, const uint64_t*
 void launch_u2_restore(hipStream_t st, Ctl* ctl, int cur) {
   hipLaunchKernelGGL(k_u2_restore, dim3(1), dim3(1), 0, st, ctl, cur);
 }
+
+void launch_u2_tickets(hipStream_t st, Ctl* ctl) { hipLaunchKernelGGL(k_u2_tickets, dim3(1), dim3(1), 0, st, ctl); }
 
 void launch_u2_chain(hipStream_t st, bool wide, Buf in, Buf out, uint64_t* nnz, int cur, const Chain& chain,
                      Ctl* ctl) {
