@@ -1266,6 +1266,7 @@ int apply_impl(sim_t* s, const sim_gate* gates, size_t n, int32_t* outcomes, sim
     ch.ops = nullptr;
     uint64_t ub = s->nnz_known ? s->nnz_exact : s->nnz_ub;
     const int cur = s->cur;
+    int rc = SIM_OK;
     auto add = [&](const MonoRun& m, const sim_gate* g) {
       ChainStep& p = ch.s[ch.n++];
       if (g) p.d = u2_desc(*g, s->cfg.eps);
@@ -1292,8 +1293,8 @@ int apply_impl(sim_t* s, const sim_gate* gates, size_t n, int32_t* outcomes, sim
       if (g ? !small_gate(s, ub) || (g->cap && 2 * ub > g->cap) : len == 0) break;
       MonoRun m;
       if (len) {
-        int rc = need_descs(mono_seen, len);
-        if (rc) return rc;
+        rc = need_descs(mono_seen, len);
+        if (rc) break;   // (what has been taken runs: the state is in the buffer that `cur` says)
         m.g = cb.descs + mono_seen;
         m.ng = (uint32_t)len;
         m.bytes_per_entry = run_cost(mono_seen, len, &m.run_flags);
@@ -1318,7 +1319,7 @@ int apply_impl(sim_t* s, const sim_gate* gates, size_t n, int32_t* outcomes, sim
     HIP_TRY(hipGetLastError());
     s->nnz_known = false;
     s->nnz_ub = ub;
-    return SIM_OK;
+    return rc;
   };
   // Gates since the last read of the entry count whose outputs may not fit,
   // and what the call was like before each.  At kSnapMax of them the count is
