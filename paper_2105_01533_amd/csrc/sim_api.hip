@@ -770,7 +770,8 @@ int import_state(sim_t* s, const uint64_t* lo, const uint64_t* hi, size_t stride
   const uint32_t q = s->cfg.n_qubits;
   const uint64_t out_lo = q < 64 ? ~0ull << q : 0ull, out_hi = q <= 64 ? ~0ull : q < 128 ? ~0ull << (q - 64) : 0ull;
   LabelCell seen;
-  HIP_TRY(copy_state_to_device(lo, hi, stride, amps, n, out_lo, out_hi, b, s->wide, s->stream, &seen));
+  CopyStage stage(s->stream);
+  HIP_TRY(copy_state_to_device(lo, hi, stride, amps, n, out_lo, out_hi, b, s->wide, stage, &seen));
   if ((seen.or_lo & out_lo) || (seen.or_hi & out_hi)) return fail(SIM_E_ARG, "import key has bits above n_qubits");
   const IndexTab t = index_tab(s, s->half);
   auto* found = reinterpret_cast<TabCtl*>(s->h_pinned + 4);
@@ -780,6 +781,7 @@ int import_state(sim_t* s, const uint64_t* lo, const uint64_t* hi, size_t stride
   launch_index_empty(s->stream, t);
   HIP_TRY(hipGetLastError());
   HIP_TRY(timed_sync(s));
+  stage.in_flight = false;
   if (found->dup) {
     found->dup = 0;
     HIP_TRY(hipMemcpyAsync(&t.tc->dup, &found->dup, sizeof found->dup, hipMemcpyHostToDevice, s->stream));

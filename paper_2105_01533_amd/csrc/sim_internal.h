@@ -442,9 +442,21 @@ hipError_t mono_rp_init();
 // pages of the caller's arrays included), where waking the pool takes 10.  (The
 // server's copies, beside its ticks' own use of the pool, take more.)
 constexpr size_t kCopyPart = 1u << 14;
+// A pinned staging buffer borrowed for one copy on stream st; when given back
+// with a copy in flight from it, the stream is waited for.
+struct CopyStage {
+  hipStream_t st;
+  char* p = nullptr;
+  bool in_flight = false;
+  explicit CopyStage(hipStream_t s) : st(s) {}
+  CopyStage(const CopyStage&) = delete;
+  CopyStage& operator=(const CopyStage&) = delete;
+  ~CopyStage();
+  hipError_t take();
+};
 // n entries of a device state (key_lo, key_hi or null for <= 64 qubits, amp)
-// into host key records and amplitudes, through the calling thread's pinned
-// staging buffer; safe to call from several host threads at once.
+// into host key records and amplitudes, through a pinned staging buffer; safe
+// to call from several host threads at once.
 // On stream st, which it waits for.
 hipError_t copy_state_to_host(const uint64_t* lo, const uint64_t* hi, const double2* amp, uint64_t n, sim_key* keys,
                               sim_c64* amps, hipStream_t st);
@@ -457,9 +469,11 @@ hipError_t copy_state_to_host_soa(const uint64_t* lo, const uint64_t* hi, const 
 // into the device arrays b, through the same staging; seen: the AND and OR of
 // the labels.  Returns early, without the rest of the copy,
 // when a label has a bit of out_lo / out_hi (the caller looks at `seen`).
-// The last chunk is left in flight on st.
+// The last chunk is left in flight on the stage's stream (the caller clears
+// in_flight once it has waited for it).
 hipError_t copy_state_to_device(const uint64_t* lo, const uint64_t* hi, size_t stride, const sim_c64* amps, uint64_t n,
-                                uint64_t out_lo, uint64_t out_hi, Buf b, bool wide, hipStream_t st, LabelCell* seen);
+                                uint64_t out_lo, uint64_t out_hi, Buf b, bool wide, CopyStage& stage,
+                                LabelCell* seen);
 // The n entries of `in` into `out`, in ascending order of (hi, lo).  idx: n
 // words of scratch.
 void launch_sort_state(hipStream_t st, bool wide, Buf in, Buf out, uint64_t n, uint32_t* idx);

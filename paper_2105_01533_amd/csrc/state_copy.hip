@@ -3,8 +3,8 @@
 // records to a device state (sim_import_state).
 //
 // A device-to-host copy into pageable memory goes through the runtime's own
-// staging and serialises across host threads; here each calling thread owns a
-// pinned staging buffer, copies a chunk of the state into it at DMA speed and
+// staging and serialises across host threads; here each call borrows a pinned
+// staging buffer, copies a chunk of the state into it at DMA speed and
 // interleaves the chunk into the caller's (lo, hi) key records and amplitudes.
 // Several threads can do this at once (the server copies the states of
 // several finished requests in parallel).
@@ -12,6 +12,8 @@
 
 #include <algorithm>
 #include <cstring>
+#include <mutex>
+#include <vector>
 
 #include "host_pool.h"
 #include "sim_internal.h"
@@ -20,27 +22,53 @@ namespace sparsesim {
 
 namespace {
 
-constexpr size_t kStageBytes = 16u << 20;   // per host thread, kept for the process's lifetime
+constexpr size_t kStageBytes = 16u << 20;
+// Staging buffers kept when no copy uses them (as many as the host pool has
+// threads; beyond, a buffer lasts one call).  An allocation takes longer than
+// most copies.
+constexpr size_t kStagesKept = HostPool::kMaxThreads;
 
-struct Stage {
-  char* p = nullptr;
+struct StagePool {
+  std::mutex mu;
+  std::vector<char*> free;
+  StagePool() { free.reserve(kStagesKept); }
+  static StagePool& get() {
+    static auto* pool = new StagePool;   // (never destroyed: copies may run until the process ends)
+    return *pool;
+  }
 };
 
-// The calling thread's staging buffer (allocated on first use, never freed:
-// host threads of the library live as long as the process).
-hipError_t stage_of_thread(char** out) {
-  static thread_local Stage st;
-  if (!st.p) {
-    void* p = nullptr;
-    const hipError_t e = hipHostMalloc(&p, kStageBytes, hipHostMallocDefault);
-    if (e != hipSuccess) return e;
-    st.p = static_cast<char*>(p);
+}  // namespace
+
+hipError_t CopyStage::take() {
+  StagePool& pool = StagePool::get();
+  {
+    std::lock_guard<std::mutex> lk(pool.mu);
+    if (!pool.free.empty()) {
+      p = pool.free.back();
+      pool.free.pop_back();
+      return hipSuccess;
+    }
   }
-  *out = st.p;
-  return hipSuccess;
+  void* m = nullptr;
+  const hipError_t e = hipHostMalloc(&m, kStageBytes, hipHostMallocDefault);
+  if (e == hipSuccess) p = static_cast<char*>(m);
+  return e;
 }
 
-}  // namespace
+CopyStage::~CopyStage() {
+  if (!p) return;
+  if (in_flight) (void)hipStreamSynchronize(st);
+  StagePool& pool = StagePool::get();
+  {
+    std::lock_guard<std::mutex> lk(pool.mu);
+    if (pool.free.size() < kStagesKept) {
+      pool.free.push_back(p);
+      return;
+    }
+  }
+  (void)hipHostFree(p);
+}
 
 namespace {
 
@@ -50,9 +78,10 @@ template <class Emit>
 hipError_t staged_copy(const uint64_t* lo, const uint64_t* hi, const double2* amp, uint64_t n, hipStream_t st,
                        size_t part, Emit&& emit) {
   if (!n) return hipSuccess;
-  char* stage = nullptr;
-  hipError_t e = stage_of_thread(&stage);
+  CopyStage own(st);
+  hipError_t e = own.take();
   if (e != hipSuccess) return e;
+  char* const stage = own.p;
   const size_t per_entry = hi ? 32 : 24;
   const uint64_t chunk = kStageBytes / per_entry;
   for (uint64_t b = 0; b < n; b += chunk) {
@@ -99,12 +128,13 @@ hipError_t copy_state_to_host_soa(const uint64_t* lo, const uint64_t* hi, const 
 }
 
 hipError_t copy_state_to_device(const uint64_t* lo, const uint64_t* hi, size_t stride, const sim_c64* amps, uint64_t n,
-                                uint64_t out_lo, uint64_t out_hi, Buf b, bool wide, hipStream_t st, LabelCell* seen) {
+                                uint64_t out_lo, uint64_t out_hi, Buf b, bool wide, CopyStage& own, LabelCell* seen) {
   *seen = LabelCell{~0ull, ~0ull, 0, 0};
   if (!n) return hipSuccess;
-  char* stage = nullptr;
-  hipError_t e = stage_of_thread(&stage);
+  hipError_t e = own.take();
   if (e != hipSuccess) return e;
+  char* const stage = own.p;
+  const hipStream_t st = own.st;
   const size_t per_entry = wide ? 32 : 24;
   const uint64_t chunk = kStageBytes / per_entry;
   for (uint64_t c = 0; c < n; c += chunk) {
@@ -135,6 +165,7 @@ hipError_t copy_state_to_device(const uint64_t* lo, const uint64_t* hi, size_t s
       seen->or_hi |= p.or_hi;
     }
     if ((seen->or_lo & out_lo) || (seen->or_hi & out_hi)) return hipSuccess;
+    own.in_flight = true;
     e = hipMemcpyAsync(b.key_lo + c, s_lo, 8 * m, hipMemcpyHostToDevice, st);
     if (e == hipSuccess && wide) e = hipMemcpyAsync(b.key_hi + c, s_hi, 8 * m, hipMemcpyHostToDevice, st);
     if (e == hipSuccess) e = hipMemcpyAsync(b.amp + c, s_amp, 16 * m, hipMemcpyHostToDevice, st);
