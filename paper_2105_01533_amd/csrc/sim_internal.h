@@ -388,7 +388,7 @@ struct BTick {
 // Kernel families of a tick: fused runs on LDS planes, and per entry (kFamEach);
 // branching gates on the global index;
 // branching gates of small states (LDS index); measurements.
-constexpr uint32_t kFamMono = 1, kFamU2 = 2, kFamU2s = 4, kFamMeas = 8, kFamEach = 16;
+constexpr uint32_t kFamMono = 1, kFamU2 = 2, kFamU2s = 4, kFamEach = 8;
 // The kernels of the families in `families`, in tick order.
 void launch_batch_tick(hipStream_t st, const BTick* hdr, const BItem* items, const uint32_t* units, int grid,
                        uint32_t families);
