@@ -376,7 +376,7 @@ int sim_device_state(sim_t* s, uint64_t** key_lo, uint64_t** key_hi, double** am
  * most 8192 entries, index in LDS; a chain of them in one launch counts each).
  * index_fill counts nothing since the gates empty each other's tables; the run
  * before a branching gate may be applied by the class that prepares or runs
- * that gate instead of by mono_pass.
+ * that gate instead of by mono_pass, and is then no launch, byte or update of mono_pass.
  * With profiling on for a class (sim_set_profiling), every launch of it is
  * bracketed by HIP events on the handle's stream and total_ms sums their
  * elapsed times; otherwise total_ms is 0.  alg_bytes is the algorithmic HBM

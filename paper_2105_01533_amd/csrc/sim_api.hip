@@ -1275,7 +1275,6 @@ int apply_impl(sim_t* s, const sim_gate* gates, size_t n, int32_t* outcomes, sim
       if (!ch.n_ops) ch.ops = m.g;   // (the chain's runs follow each other in the descriptor array)
       ch.n_ops += m.ng;
       p.ng = m.ng;
-      p.bytes_per_entry = m.bytes_per_entry;
       p.gate = g != nullptr;
       if (!g) return;
       uint64_t x_lo, x_hi;

@@ -246,8 +246,9 @@ struct Ctl {
   uint64_t updates;            // sum over applied gates of nnz at input
   uint64_t peak;
   uint64_t pruned;
-  uint64_t mono_bytes;         // algorithmic bytes of the fused phase/permutation passes
-  uint64_t mono_updates;       // gate-entry updates of the fused passes
+  // Algorithmic bytes and gate-entry updates of the fused phase/permutation
+  // passes (not of runs that a branching gate's kernels apply on their way).
+  uint64_t mono_bytes, mono_updates;
   // Algorithmic bytes (entries read and written) of the branching count and
   // write passes and of the measurement reduce and write passes.
   uint64_t pass_bytes[5];      // index 4: the one-block (LDS-index) branching kernel
@@ -526,7 +527,7 @@ constexpr uint32_t kLdsRun = 8;
 constexpr uint32_t kChainSteps = 16, kChainOps = 64;
 struct ChainStep {
   U2Desc d;
-  uint32_t ng, bytes_per_entry, gate, pad;
+  uint32_t ng, gate, pad[2];
 };
 struct Chain {
   uint32_t n, n_ops;      // steps; ops of all runs

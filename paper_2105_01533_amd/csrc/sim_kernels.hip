@@ -309,7 +309,7 @@ struct RunLds {
 template <bool WIDE, bool MONO>
 __global__ __launch_bounds__(256) void k_index_build(Buf b, const uint64_t* __restrict__ nnz_p, IndexTab t, U2Desc d,
                                                      unsigned long long* count, const MonoDesc* __restrict__ g,
-                                                     uint32_t ng, uint32_t rf, uint32_t bpe, Ctl* ctl) {
+                                                     uint32_t ng, uint32_t rf, Ctl* ctl) {
   __shared__ RunLds sg;
   const uint64_t n = *nnz_p;
   const Geom gm = index_geom(t, n);
@@ -318,11 +318,7 @@ __global__ __launch_bounds__(256) void k_index_build(Buf b, const uint64_t* __re
     t.tc->mask = gm.mask;
     t.tc->bits = gm.bits;
     t.tc->nopair = 0;
-    if (MONO) {
-      atomicAdd((unsigned long long*)&ctl->updates, (unsigned long long)(n * ng));
-      atomicAdd((unsigned long long*)&ctl->mono_bytes, (unsigned long long)(n * bpe));
-      atomicAdd((unsigned long long*)&ctl->mono_updates, (unsigned long long)(n * ng));
-    }
+    if (MONO) atomicAdd((unsigned long long*)&ctl->updates, (unsigned long long)(n * ng));
   }
   uint32_t inserts = 0, cas = 0;
   for (uint64_t base = (uint64_t)blockIdx.x * blockDim.x; base < n; base += (uint64_t)gridDim.x * blockDim.x) {
@@ -920,11 +916,8 @@ __device__ __forceinline__ void u2_tiles(const Buf& in, const Buf& out, uint64_t
             *nnz_out = total;
             if (total > ctl->peak) ctl->peak = total;
             atomicAdd((unsigned long long*)&ctl->pass_bytes[1], (unsigned long long)((n + total) * eb));
-            if (NEXT && nx.run.ng) {
+            if (NEXT && nx.run.ng)
               atomicAdd((unsigned long long*)&ctl->updates, (unsigned long long)(total * nx.run.ng));
-              atomicAdd((unsigned long long*)&ctl->mono_updates, (unsigned long long)(total * nx.run.ng));
-              atomicAdd((unsigned long long*)&ctl->mono_bytes, (unsigned long long)(total * nx.run.bytes_per_entry));
-            }
           } else {
             *nnz_out = 0;
             ctl->over = seq;
@@ -1257,15 +1250,13 @@ __global__ __launch_bounds__(1024) void k_u2_chain(Buf in, Buf out, uint64_t* nn
   }
   __syncthreads();
   BlockCount cnt;
-  uint64_t updates = 0, mono_updates = 0, mono_bytes = 0, bytes = 0, peak = 0;
+  uint64_t updates = 0, bytes = 0, peak = 0;
   uint32_t op = 0, tail = 0;   // tail: gates of a run after the last branching gate
 #pragma unroll 1
   for (uint32_t k = 0; k < chain.n; ++k) {
     const ChainStep& st = sm.step[k];
     const uint32_t ng = __builtin_amdgcn_readfirstlane(st.ng), gate = __builtin_amdgcn_readfirstlane(st.gate);
     updates += (uint64_t)n * (ng + gate);
-    mono_updates += (uint64_t)n * ng;
-    mono_bytes += (uint64_t)n * st.bytes_per_entry;
     if (!gate) {
       tail = ng;
       break;
@@ -1299,8 +1290,6 @@ __global__ __launch_bounds__(1024) void k_u2_chain(Buf in, Buf out, uint64_t* nn
   if (threadIdx.x == 0) {
     nnz[cur] = n;
     count(&ctl->updates, updates);
-    count(&ctl->mono_updates, mono_updates);
-    count(&ctl->mono_bytes, mono_bytes);
     count(&ctl->pass_bytes[4], bytes);
     if (peak > ctl->peak) ctl->peak = peak;
   }
@@ -1496,8 +1485,6 @@ __global__ __launch_bounds__(1024) void k_u2_lds_tiles(Buf in, Buf out, const ui
     *nnz_out = n_out;
     if (n_out > ctl->peak) ctl->peak = n_out;
     count(&ctl->updates, (uint64_t)n * (m.ng + 1));
-    count(&ctl->mono_updates, (uint64_t)n * m.ng);
-    count(&ctl->mono_bytes, (uint64_t)n * (m.ng ? m.bytes_per_entry : 0u));
     count(&ctl->pass_bytes[4], (n + n_out) * kEntry);
   }
 }
@@ -1746,7 +1733,7 @@ void launch_index_build(hipStream_t st, bool wide, Buf b, const uint64_t* nnz, c
   const int grid = (int)std::max<uint64_t>(1, std::min<uint64_t>((ub + 255) / 256, 4096));
 #define SPARSESIM_BUILD(W, M)                                                                                  \
   hipLaunchKernelGGL((k_index_build<W, M>), dim3(grid), dim3(256), 0, st, b, nnz, t, d, count, m.g, m.ng, \
-                     m.run_flags, m.bytes_per_entry, ctl)
+                     m.run_flags, ctl)
   if (wide) {
     if (m.ng) SPARSESIM_BUILD(true, true);
     else SPARSESIM_BUILD(true, false);
