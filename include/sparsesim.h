@@ -184,7 +184,7 @@ typedef struct sim_config {
 
 /* Count the global index's work (sim_stats index_*): one atomic add per
  * block of the index-build and look-up kernels, so off by default.  The
- * one-block LDS-index kernel always counts (four adds per gate). */
+ * LDS-index kernels always count (four adds per wave and launch). */
 #define SIM_FLAG_COUNT_INDEX 8u
 
 /* The library tracks which qubits are the same in every entry (all, after
@@ -225,7 +225,7 @@ typedef struct sim_stats {
   /* Partner-index work of the branching gates (Sec. 3.1): entries inserted,
    * insert CAS attempts (inserts + collisions), partner look-ups and the index
    * slots they read (probes / look-up is the mean probe length).  Always
-   * counted for the one-block LDS index; for the global index only with
+   * counted for an index in LDS; for the global index only with
    * SIM_FLAG_COUNT_INDEX.  CAS attempts and probes depend on the order in
    * which threads insert, so they vary from run to run; the batched server
    * does not count them (0). */

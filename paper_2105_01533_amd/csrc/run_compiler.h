@@ -67,7 +67,8 @@ struct RunCompiler {
   // Groups of n bit-sliced ops, appended to out.
   void group_range(const BsOp* src, uint32_t n, std::vector<BsGroup>& out) const;
   // Register-plane program of MONO ops [begin, begin+len) (segments of one
-  // shape), appended to out; br as for group().
+  // shape), appended to out; br as for group().  (program()'s scheduling by
+  // itself, for the host checks.)
   void schedule(size_t begin, size_t len, std::vector<RpRec>& out, BsRun* br) const;
   // Segments of n bit-sliced ops, appended to out.
   void schedule_range(const BsOp* src, uint32_t n, std::vector<RpRec>& out) const;

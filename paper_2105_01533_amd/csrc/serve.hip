@@ -939,7 +939,8 @@ int srv_tick(srv_t* s, uint32_t* running, uint32_t* queued) {
     std::vector<BsGroup> grp;
     std::vector<RpBlock> prog;
   };
-  // Register-plane runs of this tick: (request, arena offset, records, run).
+  // Register-plane runs of this tick with a launch of their own: (request, arena
+  // offset, blocks, run).
   struct RpItem {
     Request* r;
     size_t off;

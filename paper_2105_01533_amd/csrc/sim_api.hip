@@ -1540,8 +1540,8 @@ int apply_impl(sim_t* s, const sim_gate* gates, size_t n, int32_t* outcomes, sim
     HIP_TRY(timed_sync(s));
     if (result == SIM_OK)
       result = (err & 2u)   ? fail(SIM_E_HIP, "single-pass branching kernel gave up waiting for a tile")
-               : (err & 4u) ? fail(SIM_E_HIP, "one-block branching kernel launched on a state too large for it")
-                                      : fail(SIM_E_STATE, "measurement of an empty state");
+               : (err & 4u) ? fail(SIM_E_HIP, "LDS-index branching kernel launched on a state too large for it")
+                            : fail(SIM_E_STATE, "measurement of an empty state");
   }
   s->mchain.valid = false;
   st.gates_applied = i;

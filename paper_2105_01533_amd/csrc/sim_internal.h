@@ -251,12 +251,12 @@ struct Ctl {
   uint64_t mono_bytes, mono_updates;
   // Algorithmic bytes (entries read and written) of the branching count and
   // write passes and of the measurement reduce and write passes.
-  uint64_t pass_bytes[5];      // index 4: the one-block (LDS-index) branching kernel
+  uint64_t pass_bytes[5];      // index 4: the LDS-index branching kernels
   // Partner index work of branching gates: entries inserted, CAS attempts
   // (inserts + collisions), partner look-ups, slots the look-ups read.
   uint64_t ix[4];
   uint32_t error;              // bit 0: a measurement had no valid outcome; bit 1: a chained scan gave up
-                               // waiting; bit 2: the one-block branching kernel met a state too large for it
+                               // waiting; bit 2: an LDS-index branching kernel met a state too large for it
   uint32_t ticket[2];          // tile counters of the single-pass branching kernel (launches alternate)
   uint32_t lds_ticket[2];      // those of the LDS-index kernel over several blocks
   TabCtl tab[2];               // the two index tables
