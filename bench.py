@@ -506,8 +506,8 @@ def main():
     # ALU floor (shallow fusion); from the crossover on (ALU floor at least 0.9x
     # the HBM floor) deeper fusion no longer saves bytes and only adds ALU
     # work, so the ALU roof is the one reported.  At c2's depth (F of a few
-    # thousand gates) the two floors are equal within about 1 %; what keeps the
-    # pass far below both is instruction issue (scalar index setup and vector
+    # thousand gates) the ALU floor is a third above the HBM floor; what keeps the
+    # pass far above both is instruction issue (scalar index setup and vector
     # plane operations per gate), measured by the SQ counters and reported as
     # `limiter`.  Both views are in the line (`hbm`, `alu`).
     crossed = alu["floor_ms_per_launch"] >= 0.9 * hbm["floor_ms_per_launch"]
