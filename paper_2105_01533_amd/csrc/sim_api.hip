@@ -1481,7 +1481,16 @@ int apply_impl(sim_t* s, const sim_gate* gates, size_t n, int32_t* outcomes, sim
       if (split) st.u2_split++;
       continue;
     }
-    // measurement
+    // A measurement waits to know that the gates before it fitted: it would take
+    // the empty state of one that did not for the call's own, whose measurement
+    // ends the call.
+    if (!snaps.empty()) {
+      uint64_t nnz;
+      int rc = read_nnz(s, &nnz);
+      if (rc) return rc;
+      st.host_syncs++;
+      if ((result = settle())) break;
+    }
     int rc = flush();
     if (rc) return rc;
     bool bad = false;
@@ -1490,11 +1499,6 @@ int apply_impl(sim_t* s, const sim_gate* gates, size_t n, int32_t* outcomes, sim
     rc = run_measure(s, g.target, g.u, g.forced, cb.recs + meas_seen, cb.outcomes + meas_seen, &bad, q_next);
     if (rc) return rc;
     if (bad) {
-      // (an empty state here may be that of a gate that did not fit)
-      uint64_t nnz;
-      rc = read_nnz(s, &nnz);
-      if (rc) return rc;
-      if ((result = settle())) break;
       result = fail(SIM_E_STATE, "measurement outcome has zero probability");
       break;
     }
@@ -1505,14 +1509,6 @@ int apply_impl(sim_t* s, const sim_gate* gates, size_t n, int32_t* outcomes, sim
   if (result == SIM_OK) {
     int rc = flush();
     if (rc) return rc;
-  }
-  if (outcomes && meas_seen && !snaps.empty()) {
-    // A gate that did not fit takes back the measurements after it, whose
-    // outcomes are not the caller's to see.
-    uint64_t nnz;
-    int rc = read_nnz(s, &nnz);
-    if (rc) return rc;
-    if ((rc = settle())) result = rc;
   }
   if (outcomes && meas_seen)
     HIP_TRY(hipMemcpyAsync(outcomes, cb.outcomes, meas_seen * 4, hipMemcpyDeviceToHost, s->stream));

@@ -100,3 +100,32 @@ def test_reads_between_gates_that_fit(sim, n, pairs):
             s.close()
     assert out[0][0] == 0 and out[0][2][2] == 2 * pairs
     assert out[0] == out[1]
+
+
+@pytest.mark.parametrize("n", [30, 90])
+@pytest.mark.parametrize("flags", ["", "SIM_FLAG_U2_GLOBAL_INDEX", "SIM_FLAG_U2_TWO_PASS"])
+def test_measurement_of_an_emptied_state_ends_the_call(sim, n, flags):
+    """Gates that may not fit but drop everything: the measurement after them
+    ends the call at its place, as in the two-pass form, which reads the count
+    at each of them."""
+    c = W.Circuit()
+    c.h(3)                                         # every |a|^2 is below eps
+    c.x(1, (2,))
+    c.h(4)
+    c.measure(5, 0.5)
+    for k in range(3):
+        c.h(6 + k)
+        c.measure(k, 0.5)
+    gates = sim.sim_gates_from_ops(c.array())
+    outs = np.full(4, 7, np.int32)
+    s = sim.Simulator(n, CAP, 1e-2, tuned=False, flags=getattr(sim, flags) if flags else 0)
+    try:
+        s.import_state(*_state(n))
+        st = sim.sim_stats()
+        rc = sim._lib.sim_apply_gates(s.h, sim._ptr(gates), len(gates), sim._ptr(outs), ctypes.byref(st))
+        assert rc == sim.SIM_E_STATE
+        assert (st.gates_applied, st.u2_applied, st.measures) == (3, 2, 0)
+        assert list(outs) == [7] * 4
+        assert sim.sim_nnz(s.h) == 0
+    finally:
+        s.close()
